@@ -40,6 +40,8 @@ int bwd_conv3_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t
 int bwd_tiled_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in,
                      int64_t C_out, int R, int S, int stride, int pad, int n, int m, int rk, uint64_t seed,
                      hipStream_t stream);
+int bwd_f32_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
+                   int R, int S, int stride, int pad, int n, int m, int rk, uint64_t seed, hipStream_t stream);
 size_t channel_scales_workspace(int64_t rows, int64_t C, int dt, int m);
 int channel_scales_launch(const void* dO, int64_t rows, int64_t C, int dt, int n, int m, float* scale, double* sums,
                           void* partial, hipStream_t stream);
@@ -152,6 +154,10 @@ int bwd_dispatch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, 
         rc = sdgp::bwd_conv3_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, stream);
         if (rc <= 0) return rc;
         rc = sdgp::bwd_tiled_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, stream);
+        if (rc <= 0) return rc;
+    }
+    if (dt == SDGP_F32) {
+        const int rc = sdgp::bwd_f32_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, stream);
         if (rc <= 0) return rc;
     }
     return sdgp::bwd_simple_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m, rk, seed, stream);
