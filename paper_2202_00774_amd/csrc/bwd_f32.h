@@ -6,7 +6,7 @@
 // product of 8192^3), so a wavefront has time for everything else beside it and the kernel needs no LDS: both operands
 // are loaded from global memory straight into the registers the instruction reads.
 //   * Rows: lane l holds row l % 32.  The half h = l / 32 of a step's two reduction positions is free to choose as long
-//     as both operands agree, so half h takes the whole m-group 2g + h: a lane's gradient values are M consecutive
+//     as both operands agree, so half h takes a whole m-group (two of four channels): a lane's gradient values are consecutive
 //     channels of one pixel, four per 16-byte load, and the group is ranked (Sec. III-B) in that lane's registers with
 //     nothing exchanged.
 //   * Columns: lane l of column tile j holds column CN * (l % 32) + j, so the CN tiles of a reduction position come from
@@ -15,10 +15,15 @@
 //   * A wavefront owns 32 rows x 32 CN columns.  WK = 1: the WV wavefronts of a workgroup take consecutive row tiles of
 //     one column block (they read the same W through the L1).  WK > 1 (few tiles): the wavefronts share a tile, split
 //     the reduction and add their sums through LDS in a fixed order.
+// Bound by the matrix pipe's issue: 3x3 128 -> 128 channels at 16x16, batch 128, 2:4 Magnitude 99 us = 98 TFLOP/s (20151
+// us with one thread per element; 195 us while every step waited for its own loads); linear 256 x 128 -> 256 67 -> 10.5
+// us back to back.
 // Strided filters: blockIdx.z is the parity class of the input pixels, whose taps are a sub-grid of the filter.
 // Taps outside the gradient and rows past the end multiply zeros.  Zero times a non-finite weight is NaN where the
 // definition has no term at all, so a result that is NaN is summed again element by element with those taps left out.
 #pragma once
+
+#include <type_traits>
 
 #include "ranker.h"
 
@@ -28,7 +33,13 @@ typedef float f32v2_t __attribute__((ext_vector_type(2)));
 typedef float f32v4_t __attribute__((ext_vector_type(4)));
 typedef float f32v16_t __attribute__((ext_vector_type(16)));
 
+#define SDGP_GLOBAL __attribute__((address_space(1)))
+
 constexpr int kDenseRanker = 3;   // n == m: nothing is ranked
+
+// What a lane reads instead of a gradient group outside the gradient or a weight of a group past the last one: the loads
+// need no branch and no select behind them, either of which would wait for the data in front of the multiplies.
+static __device__ const float kF32Zeros[32] __attribute__((aligned(128))) = {};
 
 struct F32Params {
     const float* dO;
@@ -70,8 +81,10 @@ template <int M, int RK, bool NLE2, int CN, int WV, int WK>
 __global__ void __launch_bounds__(64 * WV) bwd_f32(const F32Params p) {
     static_assert(WK == 1 || WK == WV, "the wavefronts share rows or the reduction");
     static_assert(M % 4 == 0 && (CN == 2 || CN == 4), "16-byte gradient loads, 8- or 16-byte weight loads");
-    constexpr int JS = M / 4;   // reduction sub-steps of 4 channels per half
+    constexpr int CH = M > 8 ? M : 8;   // channels per lane and step: one group, or two of four
+    constexpr int JS = CH / 4;          // sub-steps of 4 channels
     typedef float vcn_t __attribute__((ext_vector_type(CN)));
+    typedef const SDGP_GLOBAL float* gptr_t;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int half = lane >> 5, l32 = lane & 31;
     const int ca = (int)(blockIdx.z / p.stride), cb = (int)(blockIdx.z % p.stride);
@@ -91,12 +104,14 @@ __global__ void __launch_bounds__(64 * WV) bwd_f32(const F32Params p) {
     const int64_t opix = (b * p.H + i * p.stride + ca) * p.Wd + j * p.stride + cb;
 
     const int ntaps = ay.count * ax.count;
-    const int64_t ngroups = p.C_out / M;
-    const int npairs = (int)((ngroups + 1) / 2);
-    const int steps = ntaps * npairs;                                       // one step: a pair of groups of one tap
+    const int npairs = (int)((p.C_out + 2 * CH - 1) / (2 * CH));
+    const int steps = ntaps * npairs;                                       // one step: 2 CH channels of one tap
     const int per = (steps + WK - 1) / WK;
     const int first = WK == 1 ? 0 : wave * per, last = WK == 1 ? steps : (first + per < steps ? first + per : steps);
-    const int64_t kstep = (int64_t)p.R * p.S * p.C_in;                      // elements from one output channel of W to the next
+    const int kstep = p.R * p.S * (int)p.C_in;                              // elements from one output channel of W to the next
+    const int gi = (int)i + ay.shift, gj = (int)j + ax.shift;               // gradient position of the class's first tap
+    const int P = (int)p.P, Q = (int)p.Q, C_out = (int)p.C_out;
+    const int64_t image = b * p.P * p.Q * p.C_out;                          // (an image and the filter are below 2^31 elements)
 
     f32v16_t acc[CN];
 #pragma unroll
@@ -104,90 +119,100 @@ __global__ void __launch_bounds__(64 * WV) bwd_f32(const F32Params p) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[u][e] = 0.0f;
 
-    // position of a step, advanced without divisions
-    struct At {
-        int tap, pair;
-    };
     struct Step {
-        const float* g;       // this lane's gradient group, or null: zeros
-        const float* w;       // W[first channel of the group][tap][cw]
+        gptr_t g[JS];         // this lane's gradient values, four channels each, or zeros
+        gptr_t w[JS];         // W[channel][tap][cw] of the first of the four, or zeros
+        int kstep[JS];        // elements from one channel's weights to the next
         uint64_t e0;
-        bool wok;             // the group exists
     };
+    // where the walk over (tap row, tap column, channels) stands: uniform over the wavefront
+    int tu = 0, tv = 0, pair = 0, step = first;
+    if constexpr (WK > 1) {
+        if (first < last) pair = first % npairs, tv = (first / npairs) % ax.count, tu = first / npairs / ax.count;
+    }
     bool outside = false;     // some tap of this lane's row lies outside the gradient
-    auto locate = [&](const At& a) {
-        const int u = a.tap / ax.count, v = a.tap - u * ax.count;
-        const int64_t pp = i + ay.shift - u, qq = j + ax.shift - v;
-        const bool in = pp >= 0 && pp < p.P && qq >= 0 && qq < p.Q;
-        outside |= !in;
-        const int64_t grp = 2 * (int64_t)a.pair + half;
+    // the step the walk stands at, past the last one nothing but zeros; the walk moves on
+    auto locate = [&]() {
+        const int pp = gi - tu, qq = gj - tv;
+        const bool in = (unsigned)pp < (unsigned)P && (unsigned)qq < (unsigned)Q;
+        const bool within = step < last;
+        outside |= !in && within;
+        const int k0 = (pair * 2 + half) * CH;
+        const int goff = (pp * Q + qq) * C_out + k0;
+        const int woff = k0 * kstep + ((ay.r0 + tu * p.stride) * p.S + ax.r0 + tv * p.stride) * (int)p.C_in + (int)cw;
         Step s;
-        s.wok = grp < ngroups;
-        const int64_t gr = s.wok ? grp : ngroups - 1;
-        s.e0 = (uint64_t)(((b * p.P + pp) * p.Q + qq) * p.C_out + gr * M);
-        s.g = in && live && s.wok ? p.dO + s.e0 : nullptr;
-        s.w = p.W + (gr * M * kstep + ((int64_t)(ay.r0 + u * p.stride) * p.S + ax.r0 + v * p.stride) * p.C_in + cw);
-        return s;
-    };
-    auto advance = [&](At& a) {
-        if (++a.pair == npairs) a.pair = 0, ++a.tap;
-    };
-    auto load_g = [&](const Step& s, uint32_t (&raw)[M]) {
+        s.e0 = (uint64_t)(image + goff);
 #pragma unroll
         for (int q = 0; q < JS; ++q) {
-            f32v4_t v = {0.0f, 0.0f, 0.0f, 0.0f};
-            if (s.g != nullptr) v = *reinterpret_cast<const f32v4_t*>(s.g + 4 * q);
+            const bool exists = within && k0 + 4 * q < C_out;
+            s.g[q] = in && live && exists ? (gptr_t)p.dO + (image + goff + 4 * q) : (gptr_t)kF32Zeros;
+            s.w[q] = exists ? (gptr_t)p.W + (woff + 4 * q * kstep) : (gptr_t)kF32Zeros;
+            s.kstep[q] = exists ? kstep : 0;
+        }
+        ++step;
+        const bool np = ++pair == npairs;
+        pair = np ? 0 : pair;
+        tv += np ? 1 : 0;
+        const bool nt = tv == ax.count;
+        tv = nt ? 0 : tv;
+        tu += nt ? 1 : 0;
+        return s;
+    };
+    auto load_g = [&](const Step& s, uint32_t (&raw)[CH]) {
+#pragma unroll
+        for (int q = 0; q < JS; ++q) {
+            const f32v4_t v = *reinterpret_cast<const SDGP_GLOBAL f32v4_t*>(s.g[q]);
 #pragma unroll
             for (int x = 0; x < 4; ++x) raw[4 * q + x] = float_to_bits(v[x]);
         }
     };
     auto load_w = [&](const Step& s, int q, vcn_t (&w)[4]) {
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            w[x] = *reinterpret_cast<const vcn_t*>(s.w + (4 * q + x) * kstep);
-            if (!s.wok) w[x] = vcn_t(0.0f);
-        }
+        for (int x = 0; x < 4; ++x) w[x] = *reinterpret_cast<const SDGP_GLOBAL vcn_t*>(s.w[q] + x * s.kstep[q]);
     };
 
-    if (first < last) {
-        At at{first / npairs, first % npairs};
-        Step cur = locate(at);
-        uint32_t g[M], gnext[M];
-        vcn_t w[2][4];
-        load_g(cur, g);
-        load_w(cur, 0, w[0]);
-        for (int s = first; s < last; ++s) {
-            advance(at);
-            const bool more = s + 1 < last;
-            const Step next = more ? locate(at) : cur;
-            if (more) load_g(next, gnext);
-            prune_f32<M, RK, NLE2>(g, p.n, p.mix, cur.e0);
+    // The gradient of the next step is in flight during a step, the weights of the two sub-steps after the current one
+    // during a sub-step (4 CN matrix instructions, 64 cycles each): no load is waited for behind its own request.  Two
+    // steps per turn of the loop, so that the register sets change places without copies; an odd last one is followed by
+    // a step of zeros.
+    constexpr int RING = 4;
+    vcn_t w[RING][4];
+    uint32_t ga[CH], gb[CH];
+    Step cur, next;
+    auto body = [&](uint32_t (&g)[CH], uint32_t (&gnext)[CH], auto par) {
+        constexpr int W0 = (decltype(par)::value * JS) % RING;
+        next = locate();
+        load_g(next, gnext);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int q = 0; q < JS; ++q) {
-                // the weights of the next sub-step are in flight while this one is multiplied
-                if constexpr (JS % 2 == 0) {
-                    if (q + 1 < JS) load_w(cur, q + 1, w[(q + 1) & 1]);
-                    else if (more) load_w(next, 0, w[0]);
+        for (int q = 0; q < JS; ++q) {
+            if (q + 2 < JS) load_w(cur, q + 2, w[(W0 + q + 2) % RING]);
+            else load_w(next, q + 2 - JS, w[(W0 + q + 2) % RING]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (q % (M / 4) == 0) {
+                uint32_t grp[M];
 #pragma unroll
-                    for (int x = 0; x < 4; ++x)
+                for (int x = 0; x < M; ++x) grp[x] = g[4 * q + x];
+                prune_f32<M, RK, NLE2>(grp, p.n, p.mix, cur.e0 + (uint64_t)(4 * q));
 #pragma unroll
-                        for (int u = 0; u < CN; ++u)
-                            acc[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(bits_to_float(g[4 * q + x]), w[q & 1][x][u], acc[u], 0, 0, 0);
-                } else {   // one sub-step per step: the two register sets change places by copying
-                    vcn_t wn[4];
-                    if (more) load_w(next, 0, wn);
-#pragma unroll
-                    for (int x = 0; x < 4; ++x)
-#pragma unroll
-                        for (int u = 0; u < CN; ++u)
-                            acc[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(bits_to_float(g[x]), w[0][x][u], acc[u], 0, 0, 0);
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) w[0][x] = wn[x];
-                }
+                for (int x = 0; x < M; ++x) g[4 * q + x] = grp[x];
             }
-            cur = next;
 #pragma unroll
-            for (int x = 0; x < M; ++x) g[x] = gnext[x];
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int u = 0; u < CN; ++u)
+                    acc[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(bits_to_float(g[4 * q + x]), w[(W0 + q) % RING][x][u], acc[u], 0, 0, 0);
+        }
+        cur = next;
+    };
+    if (first < last) {
+        cur = locate();
+        load_g(cur, ga);
+        load_w(cur, 0, w[0]);
+        load_w(cur, 1, w[1]);
+        for (int s = first; s < last; s += 2) {
+            body(ga, gb, std::integral_constant<int, 0>{});
+            body(gb, ga, std::integral_constant<int, 1>{});
         }
     }
 
@@ -240,7 +265,7 @@ __global__ void __launch_bounds__(64 * WV) bwd_f32(const F32Params p) {
                             for (int y = 0; y < M; ++y) raw[y] = float_to_bits(p.dO[e0 + k + y]);
                             prune_f32<M, RK, NLE2>(raw, p.n, p.mix, e0 + (uint64_t)k);
 #pragma unroll
-                            for (int y = 0; y < M; ++y) v += bits_to_float(raw[y]) * *reinterpret_cast<const vcn_t*>(w + (k + y) * kstep);
+                            for (int y = 0; y < M; ++y) v += bits_to_float(raw[y]) * *reinterpret_cast<const vcn_t*>(w + (k + y) * (int64_t)kstep);
                         }
                     }
             }

@@ -16,13 +16,18 @@ int bwd_f32_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H
     const bool dense = n == m;
     if (!dense && m != 4 && m != 8 && m != 16 && m != 32) return 1;
     if (C_out == 0 || C_out % 4 != 0 || C_out > (1 << 24) || C_in == 0 || C_in % 2 != 0 || C_in > (1 << 24)) return 1;
+    // one image of the gradient and the filter are indexed with 32 bits, the zero half of an odd last step included
+    const int64_t P = (H + 2 * pad - R) / stride + 1, Q = (Wd + 2 * pad - S) / stride + 1;
+    const int64_t reach = (int64_t)1 << 30;
+    if (H > (1 << 24) || Wd > (1 << 24) || P * Q > reach / (C_out + 64) || (int64_t)R * S * C_in > reach / (C_out + 64)) return 1;
     if (!is_aligned16(dO) || !is_aligned16(W) || !is_aligned16(dD)) return 1;
     const int64_t rows = B * ((H + stride - 1) / stride) * ((Wd + stride - 1) / stride);   // of the largest parity class
     const int64_t tiles = (rows + 31) / 32;
     if (B == 0 || tiles > (1 << 30)) return 1;
     // One wavefront per SIMD (1024 of them) is the least that fills the matrix units.  Tiles of 128 columns read a
     // gradient row half as often as tiles of 64; with too few of either the eight wavefronts of a workgroup share a tile
-    // and split the reduction.
+    // and split the reduction.  Measured (us, 128 columns / 64 columns / shared): 3x3 128 -> 128 at 16x16, batch 128
+    // 99 / 112 / 120; 64 -> 128 channels at 32x32, batch 64 179 / 112 / 120; batch 32 of the first 96 / 65 / 35.
     const int64_t classes = (int64_t)stride * stride;
     const int64_t wide = tiles * ((C_in + 127) / 128) * classes, slim = tiles * ((C_in + 63) / 64) * classes;
     F32Grid g;
@@ -33,7 +38,7 @@ int bwd_f32_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H
     F32Params p;
     p.dO = static_cast<const float*>(dO), p.W = static_cast<const float*>(W), p.dD = static_cast<float*>(dD);
     p.B = B, p.H = H, p.Wd = Wd, p.C_in = C_in, p.C_out = C_out;
-    p.P = (H + 2 * pad - R) / stride + 1, p.Q = (Wd + 2 * pad - S) / stride + 1;
+    p.P = P, p.Q = Q;
     p.R = R, p.S = S, p.stride = stride, p.pad = pad, p.n = n, p.mix = seed_mix(seed);
     if (dense) return launch_f32_dense(p, g, stream);
     switch (m) {
