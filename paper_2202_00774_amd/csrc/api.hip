@@ -56,9 +56,10 @@ int fwd_narrow_launch(const void* D, const void* W, void* O, int64_t B, int64_t 
                       int R, int S, int stride, int pad, int dt, hipStream_t stream);
 int fwd_simple_launch(const void* D, const void* W, void* O, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
                       int R, int S, int stride, int pad, int dt, hipStream_t stream);
+size_t wgrad_workspace_required(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int dt);
 size_t wgrad_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int dt);
 int wgrad_launch(const void* D, const void* dO, float* dW, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
-                 int R, int S, int stride, int pad, int dt, void* workspace, hipStream_t stream);
+                 int R, int S, int stride, int pad, int dt, bool aligned, void* workspace, size_t workspace_bytes, hipStream_t stream);
 }  // namespace sdgp
 
 // Scratch memory of sdgp_conv_bwd_data_noalloc: lives in the library's device image, one copy per GPU, for the life
@@ -491,13 +492,12 @@ int sdgp_conv_bwd_weight(const void* D, const void* dO, float* dW, int64_t B, in
     if (rc != SDGP_OK) return rc;
     if (g.n_W == 0) return SDGP_OK;
     if (dW == nullptr || (g.n_dD > 0 && D == nullptr) || (g.n_dO > 0 && dO == nullptr)) return SDGP_ERR_NULL;
-    const size_t need = sdgp::wgrad_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dt);
+    const size_t required = sdgp::wgrad_workspace_required(B, H, Wd, C_in, C_out, R, S, stride, pad, dt);
     const bool aligned = sdgp::is_aligned16(D) && sdgp::is_aligned16(dO);  // unaligned tensors take the plain kernel
-    if (need > 0 && aligned &&
-        (workspace == nullptr || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 15u) != 0))
-        return SDGP_ERR_WORKSPACE;
-    return sdgp::wgrad_launch(D, dO, dW, B, H, Wd, C_in, C_out, R, S, stride, pad, dt, (need > 0 && aligned) ? workspace : nullptr,
-                              static_cast<hipStream_t>(hip_stream));
+    const bool usable = workspace != nullptr && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
+    if (required > 0 && aligned && (!usable || workspace_bytes < required)) return SDGP_ERR_WORKSPACE;
+    return sdgp::wgrad_launch(D, dO, dW, B, H, Wd, C_in, C_out, R, S, stride, pad, dt, aligned, aligned && usable ? workspace : nullptr,
+                              workspace_bytes, static_cast<hipStream_t>(hip_stream));
 }
 
 int sdgp_peak_probe(int kind, const void* a, void* b, size_t bytes, int iters, double* work, void* hip_stream) {

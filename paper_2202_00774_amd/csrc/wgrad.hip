@@ -13,8 +13,10 @@
 //   * the next tile travels global -> registers while the current one is multiplied, then registers -> LDS;
 //   * workgroups that share an output block split the tiles between them and write fp32 partial blocks to the
 //     workspace; a second kernel adds the partials in a fixed order, so the result does not depend on timing.
-// Everything else (other filters, strides, channel counts, fp32) goes to a plain reduction kernel.
+// Other filters and strides with channel counts that are multiples of 8 go to wgrad_gather.hip, everything else (fp32, odd
+// channel counts) to a plain reduction kernel.
 #include "common.h"
+#include "wgrad_gather.h"
 
 namespace sdgp {
 
@@ -460,7 +462,8 @@ Plan make_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, in
 
 }  // namespace
 
-size_t wgrad_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int dt) {
+// Bytes of workspace without which the call is refused.
+size_t wgrad_workspace_required(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int dt) {
     const Plan pl = make_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, dt);
     const int64_t nW = C_out * R * S * C_in;
     if (pl.mfma) return (size_t)pl.nsplit * (size_t)nW * sizeof(float);
@@ -470,8 +473,22 @@ size_t wgrad_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C
     return 0;
 }
 
+static size_t gather_bytes(const WgradGatherPlan& g, int64_t nW) {
+    return g.ok && g.nsplit > 1 ? (size_t)g.nsplit * (size_t)nW * sizeof(float) : 0;
+}
+
+// What the query asks for: the required bytes, or room for the partial filters of the gathering kernel, in whose place a
+// call that brings less runs the plain kernel.
+size_t wgrad_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int dt) {
+    const size_t required = wgrad_workspace_required(B, H, Wd, C_in, C_out, R, S, stride, pad, dt);
+    if (required > 0) return required;
+    return gather_bytes(wgrad_gather_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, dt), C_out * R * S * C_in);
+}
+
+// workspace: 16-byte aligned or null; D and dO are 16-byte aligned when it is not null or `aligned` says so.
 int wgrad_launch(const void* D, const void* dO, float* dW, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
-                 int R, int S, int stride, int pad, int dt, void* workspace, hipStream_t stream) {
+                 int R, int S, int stride, int pad, int dt, bool aligned, void* workspace, size_t workspace_bytes,
+                 hipStream_t stream) {
     const int64_t P = (H + 2 * pad - R) / stride + 1, Q = (Wd + 2 * pad - S) / stride + 1;
     const int64_t nW = C_out * R * S * C_in;
     if (nW == 0) return SDGP_OK;
@@ -522,6 +539,16 @@ int wgrad_launch(const void* D, const void* dO, float* dW, int64_t B, int64_t H,
         if (hipGetLastError() != hipSuccess) return SDGP_ERR_HIP;
         wgrad_reduce<<<(unsigned)((nW + 63) / 64), kThreads, 0, stream>>>((const float*)workspace, dW, nW, kNarrowGroups);
         return launch_status();
+    }
+    if (aligned && !pl.mfma) {
+        const WgradGatherPlan g = wgrad_gather_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, dt);
+        const size_t bytes = gather_bytes(g, nW);
+        if (g.ok && (bytes == 0 || (workspace != nullptr && workspace_bytes >= bytes))) {
+            const int rc = wgrad_gather_launch(g, D, dO, bytes > 0 ? (float*)workspace : dW, B, H, Wd, C_in, C_out, R, S, stride, pad, stream);
+            if (rc != SDGP_OK || bytes == 0) return rc;
+            wgrad_reduce<<<(unsigned)((nW + 63) / 64), kThreads, 0, stream>>>((const float*)workspace, dW, nW, (int)g.nsplit);
+            return launch_status();
+        }
     }
     if (workspace != nullptr && !pl.mfma && small_filter(nW, B * P * Q)) {
         if (dt == SDGP_BF16) wgrad_small<SDGP_BF16><<<kSmallGroups, kThreads, 0, stream>>>(a, (float*)workspace, nW);
