@@ -218,28 +218,46 @@ __global__ void __launch_bounds__(kThreads) wgrad_mfma(WgradParams p) {
             }
 }
 
-// dW[e] = sum of the partial filters.  A workgroup takes 64 elements; its four wavefronts each add a quarter of the
-// splits (four loads in flight), then the four sums are added in wavefront order: a fixed order for a given shape.
-__global__ void __launch_bounds__(kThreads) wgrad_reduce(const float* partial, float* dW, int64_t nW, int nsplit) {
-    __shared__ float part[4][64];
+// dW[e] = sum of the partial filters.  A workgroup takes 64 elements; each of its G wavefronts adds a run of the splits
+// (up to eight loads in flight), then the sums are added in wavefront order: a fixed order for a given shape.  Bound by the
+// latency of a wavefront's run, so many splits take many wavefronts: 256 partial filters of 16384 elements (17 MB)
+// 7 us with four wavefronts, 4.1 with sixteen.
+template <int G>
+__global__ void __launch_bounds__(64 * G) wgrad_reduce(const float* partial, float* dW, int64_t nW, int nsplit) {
+    __shared__ float part[G][64];
     const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
     const int64_t e = (int64_t)blockIdx.x * 64 + lane;
-    const int per = (nsplit + 3) / 4;
+    const int per = (nsplit + G - 1) / G;
     const int first = grp * per, last = first + per < nsplit ? first + per : nsplit;
-    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
+    float s[8] = {};
     if (e < nW) {
         int i = first;
-        for (; i + 3 < last; i += 4) {
-            s0 += partial[(int64_t)i * nW + e];
-            s1 += partial[(int64_t)(i + 1) * nW + e];
-            s2 += partial[(int64_t)(i + 2) * nW + e];
-            s3 += partial[(int64_t)(i + 3) * nW + e];
+        for (; i + 7 < last; i += 8) {
+#pragma unroll
+            for (int x = 0; x < 8; ++x) s[x] += partial[(int64_t)(i + x) * nW + e];
         }
-        for (; i < last; ++i) s0 += partial[(int64_t)i * nW + e];
+        for (; i + 3 < last; i += 4) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) s[x] += partial[(int64_t)(i + x) * nW + e];
+        }
+        for (; i < last; ++i) s[0] += partial[(int64_t)i * nW + e];
     }
-    part[grp][lane] = (s0 + s1) + (s2 + s3);
+    part[grp][lane] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
     __syncthreads();
-    if (grp == 0 && e < nW) dW[e] = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+    if (grp == 0 && e < nW) {
+        float sum = part[0][lane];
+#pragma unroll
+        for (int x = 1; x < G; ++x) sum += part[x][lane];
+        dW[e] = sum;
+    }
+}
+
+void launch_reduce(const float* partial, float* dW, int64_t nW, int64_t nsplit, hipStream_t stream) {
+    const unsigned blocks = (unsigned)((nW + 63) / 64);
+    // (from 512 workgroups of four wavefronts on, two rounds' worth per SIMD, more wavefronts are slower: 64 partial filters
+    // of 3x3 128 -> 256 40 us for the call against 37)
+    if (nsplit >= 64 && blocks <= 512) wgrad_reduce<16><<<blocks, 1024, 0, stream>>>(partial, dW, nW, (int)nsplit);
+    else wgrad_reduce<4><<<blocks, 256, 0, stream>>>(partial, dW, nW, (int)nsplit);
 }
 
 struct SimpleArgs {
@@ -512,8 +530,7 @@ int wgrad_launch(const void* D, const void* dO, float* dW, int64_t B, int64_t H,
             wgrad_mfma<3, 3, 1><<<grid, kThreads, pl.lds, stream>>>(p);
         }
         if (hipGetLastError() != hipSuccess) return SDGP_ERR_HIP;
-        const int64_t blocks = (nW + 63) / 64;
-        wgrad_reduce<<<(unsigned)blocks, kThreads, 0, stream>>>((const float*)workspace, dW, nW, pl.nsplit);
+        launch_reduce((const float*)workspace, dW, nW, pl.nsplit, stream);
         return launch_status();
     }
     if (nW > 0x7FFFFFFF) return SDGP_ERR_SHAPE;
@@ -537,7 +554,7 @@ int wgrad_launch(const void* D, const void* dO, float* dW, int64_t B, int64_t H,
             return SDGP_ERR_HIP;
         kernel<<<kNarrowGroups, kThreads, lds, stream>>>(n);
         if (hipGetLastError() != hipSuccess) return SDGP_ERR_HIP;
-        wgrad_reduce<<<(unsigned)((nW + 63) / 64), kThreads, 0, stream>>>((const float*)workspace, dW, nW, kNarrowGroups);
+        launch_reduce((const float*)workspace, dW, nW, kNarrowGroups, stream);
         return launch_status();
     }
     if (aligned && !pl.mfma) {
@@ -546,7 +563,7 @@ int wgrad_launch(const void* D, const void* dO, float* dW, int64_t B, int64_t H,
         if (g.ok && (bytes == 0 || (workspace != nullptr && workspace_bytes >= bytes))) {
             const int rc = wgrad_gather_launch(g, D, dO, bytes > 0 ? (float*)workspace : dW, B, H, Wd, C_in, C_out, R, S, stride, pad, stream);
             if (rc != SDGP_OK || bytes == 0) return rc;
-            wgrad_reduce<<<(unsigned)((nW + 63) / 64), kThreads, 0, stream>>>((const float*)workspace, dW, nW, (int)g.nsplit);
+            launch_reduce((const float*)workspace, dW, nW, g.nsplit, stream);
             return launch_status();
         }
     }
@@ -554,7 +571,7 @@ int wgrad_launch(const void* D, const void* dO, float* dW, int64_t B, int64_t H,
         if (dt == SDGP_BF16) wgrad_small<SDGP_BF16><<<kSmallGroups, kThreads, 0, stream>>>(a, (float*)workspace, nW);
         else wgrad_small<SDGP_F32><<<kSmallGroups, kThreads, 0, stream>>>(a, (float*)workspace, nW);
         if (hipGetLastError() != hipSuccess) return SDGP_ERR_HIP;
-        wgrad_reduce<<<(unsigned)((nW + 63) / 64), kThreads, 0, stream>>>((const float*)workspace, dW, nW, kSmallGroups);
+        launch_reduce((const float*)workspace, dW, nW, kSmallGroups, stream);
         return launch_status();
     }
     if (dt == SDGP_BF16) wgrad_simple<SDGP_BF16><<<(unsigned)nW, kThreads, 0, stream>>>(a);

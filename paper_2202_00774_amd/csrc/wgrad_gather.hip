@@ -7,14 +7,15 @@
 //   * Bound by memory: a 1x1 layer does 2*KB*CB flops per 2*(KB+CB) bytes, so the block shape is the one that reads the
 //     two tensors the fewest times over (64 x 256, 128 x 128, 256 x 64; 64 x 64 where neither side is wider).
 //   * Every byte takes the direct path into LDS (16 bytes per lane, no registers); three buffers, two chunks in flight
-//     while one is multiplied, one barrier per chunk; two to three workgroups per CU.  The 16-byte columns of a row are
+//     while one is multiplied, one barrier per chunk.  The 16-byte columns of a row are
 //     exchanged by row on the way (the copy's source address), so that the four rows of a transposing read lie in four
 //     different quarters of the 64 banks.
 //   * Pixels whose tap falls outside the image, and pixels past the run's end, are zeros on BOTH sides: they add nothing
 //     whatever the other side holds.  Channels past the end repeat the last ones and are not stored.
 //   * The splits' partial filters (fp32) are added in a fixed order by a second kernel: the result is the same from call
 //     to call.
-// 1x1 256 -> 64 at 56x56, batch 64: see the figures at wgrad_gather_plan.
+// 1x1 256 -> 64 at 56x56, batch 64: 29 us with the sum of the splits (25 + 4; 128 MB in 24.4 us = 5.3 TB/s), 105 ms with
+// one workgroup per filter element.
 #include "lds_copy.h"
 #include "wgrad_gather.h"
 
@@ -179,9 +180,9 @@ __global__ void __launch_bounds__(WVK* WVC * 64) wgrad_gather(const GatherParams
 }
 
 struct Shape {
-    int kb, cb, per_cu;   // channels of a block, resident workgroups per compute unit (LDS)
+    int kb, cb, per_cu;   // channels of a block, workgroups per compute unit
 };
-constexpr Shape kShapes[] = {{64, 64, 4}, {64, 256, 2}, {128, 128, 3}, {256, 64, 2}};
+constexpr Shape kShapes[] = {{64, 64, 4}, {64, 256, 1}, {128, 128, 1}, {256, 64, 1}};
 
 void division(uint32_t d, uint32_t* mul, uint32_t* shift) {
     *shift = 0;
@@ -221,9 +222,11 @@ WgradGatherPlan wgrad_gather_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in
     pl.kblocks = (C_out + sh.kb - 1) / sh.kb, pl.cblocks = (C_in + sh.cb - 1) / sh.cb;
     const int64_t blocks = pl.kblocks * pl.cblocks * R * S;
     if (blocks > 65535) return pl;
-    // one round of resident workgroups, none with fewer than eight chunks; the partial filters of a split cost a write
-    // and a read of the whole filter, so no more splits than that
-    int64_t ns = 256 * sh.per_cu / blocks;
+    // one round of workgroups, none with fewer than eight chunks.  Two or three of the large blocks fit a compute unit,
+    // but every split writes and reads a partial filter: 1x1 256 -> 64 at 56x56, batch 64 38 us with two per unit, 31
+    // with one; 1024 -> 256 at 14x14 25.5 against 20.4.  Blocks of 64 x 64 leave a quarter of that and need the
+    // requests of four: 3x3 168 -> 40 at 35x35, batch 32 39 us, 49 with one.
+        int64_t ns = 256 * sh.per_cu / blocks;
     if (ns > (chunks + 7) / 8) ns = (chunks + 7) / 8;
     if (ns < 1) ns = 1;
     pl.per = (chunks + ns - 1) / ns * kPX;
