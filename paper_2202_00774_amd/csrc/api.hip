@@ -54,6 +54,8 @@ int peak_probe_launch(int kind, const void* a, void* b, size_t bytes, int iters,
 int mirror_transpose_filter_launch(const void* W, void* V, int64_t C_out, int64_t C_in, int R, int S, int dt, hipStream_t stream);
 int fwd_narrow_launch(const void* D, const void* W, void* O, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
                       int R, int S, int stride, int pad, int dt, hipStream_t stream);
+int fwd_gather_launch(const void* D, const void* W, void* O, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
+                      int R, int S, int stride, int pad, int dt, hipStream_t stream);
 int fwd_simple_launch(const void* D, const void* W, void* O, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
                       int R, int S, int stride, int pad, int dt, hipStream_t stream);
 size_t wgrad_workspace_required(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int dt);
@@ -466,6 +468,8 @@ int sdgp_conv_fwd(const void* D, const void* W, void* O, int64_t B, int64_t H, i
     if (need == 0) {
         const int rcn = sdgp::fwd_narrow_launch(D, W, O, B, H, Wd, C_in, C_out, R, S, stride, pad, dt, stream);
         if (rcn <= 0) return rcn;
+        const int rcg = sdgp::fwd_gather_launch(D, W, O, B, H, Wd, C_in, C_out, R, S, stride, pad, dt, stream);
+        if (rcg <= 0) return rcg;
         return sdgp::fwd_simple_launch(D, W, O, B, H, Wd, C_in, C_out, R, S, stride, pad, dt, stream);
     }
     if (workspace == nullptr || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 15u) != 0)
