@@ -286,15 +286,19 @@ int sdgp_conv_bwd_data_compact(const void* dO, const void* W, void* dD, int64_t 
  * sdgp_conv_fwd          O[b,p,q,k] = sum_{r,s,c} D[b, p*stride + r - pad, q*stride + s - pad, c] * W[k,r,s,c]
  *                        D [B,H,Wd,C_in], W [C_out,R,S,C_in], O [B,P,Q,C_out], all `dt`; fp32 accumulation, RNE
  *                        on output; taps outside the image contribute nothing.  With stride 1 and R == S the
- *                        dense matrix-core kernels of the backward-data path compute it from a mirrored,
- *                        transposed copy of W that the call builds in the workspace; other layers take a
- *                        plain kernel.  O 16-byte aligned for the matrix-core path.
+ *                        dense matrix-core kernels of the backward-data path compute large layers from a mirrored,
+ *                        transposed copy of W that the call builds in the workspace; other bf16 layers whose
+ *                        channel counts are multiples of 8 take a matrix-core kernel that needs none, the rest a
+ *                        plain kernel.  D, W and O 16-byte aligned for the matrix-core paths.
  * sdgp_conv_bwd_weight   dW[k,r,s,c] = sum_{b,p,q} dO[b,p,q,k] * D[b, p*stride + r - pad, q*stride + s - pad, c]
  *                        D and dO `dt`, dO UNPRUNED; dW [C_out,R,S,C_in] is written in fp32 whatever `dt` is.
  *                        bf16, stride 1, 3x3, C_in and C_out multiples of 64: matrix-core kernel whose workgroups
  *                        split the pixels and leave fp32 partial filters in the workspace, added in a fixed
- *                        order by a second kernel (the result is the same from call to call); other layers
- *                        take a plain reduction kernel.  D and dO 16-byte aligned for the matrix-core path.
+ *                        order by a second kernel (the result is the same from call to call); other bf16 layers
+ *                        whose channel counts are multiples of 8 take a matrix-core kernel of the same kind (its
+ *                        partial filters are what the workspace query asks for; a call that brings less runs the
+ *                        plain kernel), the rest a plain reduction kernel.  D and dO 16-byte aligned for the
+ *                        matrix-core paths.
  *
  * workspace: sdgp_conv_fwd_workspace(...) / sdgp_conv_bwd_weight_workspace(...) bytes (0 for layers that need none),
  * 16-byte aligned, contents undefined afterwards; the queries return (size_t)-1 for invalid arguments.  Geometry
