@@ -219,17 +219,18 @@ __global__ void __launch_bounds__(kThreads) wgrad_mfma(WgradParams p) {
 }
 
 // dW[e] = sum of the partial filters.  A workgroup takes 64 elements; each of its G wavefronts adds a run of the splits
-// (up to eight loads in flight), then the sums are added in wavefront order: a fixed order for a given shape.  Bound by the
+// (up to eight loads in flight), then the sums are added in wavefront order: a fixed order for a given shape, in fp64, so
+// that the partial filters' own rounding is all that their number adds.  Bound by the
 // latency of a wavefront's run, so many splits take many wavefronts: 256 partial filters of 16384 elements (17 MB)
 // 7 us with four wavefronts, 4.1 with sixteen.
 template <int G>
 __global__ void __launch_bounds__(64 * G) wgrad_reduce(const float* partial, float* dW, int64_t nW, int nsplit) {
-    __shared__ float part[G][64];
+    __shared__ double part[G][64];
     const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
     const int64_t e = (int64_t)blockIdx.x * 64 + lane;
     const int per = (nsplit + G - 1) / G;
     const int first = grp * per, last = first + per < nsplit ? first + per : nsplit;
-    float s[8] = {};
+    double s[8] = {};
     if (e < nW) {
         int i = first;
         for (; i + 7 < last; i += 8) {
@@ -245,10 +246,10 @@ __global__ void __launch_bounds__(64 * G) wgrad_reduce(const float* partial, flo
     part[grp][lane] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
     __syncthreads();
     if (grp == 0 && e < nW) {
-        float sum = part[0][lane];
+        double sum = part[0][lane];
 #pragma unroll
         for (int x = 1; x < G; ++x) sum += part[x][lane];
-        dW[e] = sum;
+        dW[e] = (float)sum;
     }
 }
 

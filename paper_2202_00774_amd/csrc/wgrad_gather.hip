@@ -1,11 +1,14 @@
 // Weight gradient on the matrix cores for any filter and stride (Sec. II-A, Fig. 1), bf16, channel counts that are
 // multiples of 8:
 //   dW[k, tap, c] = sum over pixels of dO[pixel][k] * D[the pixel the tap reads][c]
-// One workgroup takes KB output x CB input channels of one tap and a run of gradient pixels (a split), 32 pixels at a
+// One workgroup takes KB output x CB input channels of one tap and a run of gradient pixels (a split), 64 pixels at a
 // time.  The reduction runs over pixels, so both operands of v_mfma_f32_32x32x16_bf16 are read from [pixel][channel] tiles in
 // LDS, the layout they have in memory, with the transposing read ds_read_b64_tr_b16.
 //   * Bound by memory: a 1x1 layer does 2*KB*CB flops per 2*(KB+CB) bytes, so the block shape is the one that reads the
 //     two tensors the fewest times over (64 x 256, 128 x 128, 256 x 64; 64 x 64 where neither side is wider).
+//   * Eight wavefronts (four for 64 x 64), 32 x 64 results each: two per SIMD, so that one's copy addresses, reads and sums
+//     overlap the other's matrix instructions (four wavefronts of 64 x 64 on 32-pixel chunks: 36 us against 29 on 1x1 256 ->
+//     64, 69 against 39 on the gathered 3x3 168 -> 40 at 35x35, batch 32).
 //   * Every byte takes the direct path into LDS (16 bytes per lane, no registers); three buffers, two chunks in flight
 //     while one is multiplied, one barrier per chunk.  The 16-byte columns of a row are
 //     exchanged by row on the way (the copy's source address), so that the four rows of a transposing read lie in four
@@ -14,8 +17,8 @@
 //     whatever the other side holds.  Channels past the end repeat the last ones and are not stored.
 //   * The splits' partial filters (fp32) are added in a fixed order by a second kernel: the result is the same from call
 //     to call.
-// 1x1 256 -> 64 at 56x56, batch 64: 29 us with the sum of the splits (25 + 4; 128 MB in 24.4 us = 5.3 TB/s), 105 ms with
-// one workgroup per filter element.
+// 1x1 256 -> 64 at 56x56, batch 64 (128 MB): 29 us with the sum of the splits, 105 ms with one workgroup per filter
+// element.
 #include "lds_copy.h"
 #include "wgrad_gather.h"
 
@@ -23,8 +26,9 @@ namespace sdgp {
 
 namespace {
 
-constexpr int kPX = 32;      // pixels per chunk
+constexpr int kPX = 64;      // pixels per chunk
 constexpr int kSets = 3;     // LDS buffers
+constexpr int kRun = 2;      // chunks summed on their own, a power of two
 
 __device__ const uint32_t kWgradZeros[4] __attribute__((aligned(16))) = {};
 
@@ -138,6 +142,17 @@ __global__ void __launch_bounds__(WVK* WVC * 64) wgrad_gather(const GatherParams
         return __builtin_bit_cast(bf16x8_t, all);
     };
 
+    // Runs of kRun chunks are summed on their own and added to an fp64 total: a chain of fp32 additions errs by its length.
+    // (Relative error over thirty shapes 5.4e-8 to 7.2e-8; 6.6e-8 to 1.6e-7 as one chain, 5.5e-8 to 1.4e-7 for the plain
+    // kernel's short chains; 2 us of the call below.)
+    double total[TM][TN][16];
+#pragma unroll
+    for (int t = 0; t < TM; ++t)
+#pragma unroll
+        for (int u = 0; u < TN; ++u)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) total[t][u][e] = 0.0;
+
     copy_chunk(0, 0);
     copy_chunk(1, 1);
     int set = 0, next_set = 2;
@@ -160,6 +175,14 @@ __global__ void __launch_bounds__(WVK* WVC * 64) wgrad_gather(const GatherParams
 #pragma unroll
                 for (int u = 0; u < TN; ++u) acc[t][u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t], b[u], acc[t][u], 0, 0, 0);
         }
+        if ((chunk & (kRun - 1)) == kRun - 1) {
+#pragma unroll
+            for (int t = 0; t < TM; ++t)
+#pragma unroll
+                for (int u = 0; u < TN; ++u)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) total[t][u][e] += (double)acc[t][u][e], acc[t][u][e] = 0.0f;
+        }
         set = set == kSets - 1 ? 0 : set + 1;
         next_set = next_set == kSets - 1 ? 0 : next_set + 1;
     }
@@ -175,7 +198,7 @@ __global__ void __launch_bounds__(WVK* WVC * 64) wgrad_gather(const GatherParams
             for (int e = 0; e < 16; ++e) {
                 const int k = kb * KB + (wk * TM + t) * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
                 const int c = cb * CB + (wc * TN + u) * 32 + (lane & 31);
-                if (k < p.C_out && c < p.C_in) out[((int64_t)k * p.ntaps + tap) * p.C_in + c] = acc[t][u][e];
+                if (k < p.C_out && c < p.C_in) out[((int64_t)k * p.ntaps + tap) * p.C_in + c] = (float)(total[t][u][e] + (double)acc[t][u][e]);
             }
 }
 
@@ -222,11 +245,11 @@ WgradGatherPlan wgrad_gather_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in
     pl.kblocks = (C_out + sh.kb - 1) / sh.kb, pl.cblocks = (C_in + sh.cb - 1) / sh.cb;
     const int64_t blocks = pl.kblocks * pl.cblocks * R * S;
     if (blocks > 65535) return pl;
-    // one round of workgroups, none with fewer than eight chunks.  Two or three of the large blocks fit a compute unit,
-    // but every split writes and reads a partial filter: 1x1 256 -> 64 at 56x56, batch 64 38 us with two per unit, 31
-    // with one; 1024 -> 256 at 14x14 25.5 against 20.4.  Blocks of 64 x 64 leave a quarter of that and need the
-    // requests of four: 3x3 168 -> 40 at 35x35, batch 32 39 us, 49 with one.
-        int64_t ns = 256 * sh.per_cu / blocks;
+    // One round of workgroups, none with fewer than eight chunks.  One of the large blocks per compute unit: every split
+    // writes and reads a partial filter (1x1 256 -> 64 at 56x56, batch 64, four-wavefront workgroups: 38 us with two per
+    // unit, 31 with one; 1024 -> 256 at 14x14 25 / 20).  Blocks of 64 x 64 leave a quarter of that and need four for the
+    // requests in flight.
+    int64_t ns = 256 * sh.per_cu / blocks;
     if (ns > (chunks + 7) / 8) ns = (chunks + 7) / 8;
     if (ns < 1) ns = 1;
     pl.per = (chunks + ns - 1) / ns * kPX;
@@ -248,9 +271,9 @@ int wgrad_gather_launch(const WgradGatherPlan& pl, const void* D, const void* dO
     p.plain = R == 1 && S == 1 && stride == 1 && pad == 0;
     switch (pl.shape) {
         case 0: return launch<64, 64, 2, 2>(p, pl, stream);
-        case 1: return launch<64, 256, 1, 4>(p, pl, stream);
+        case 1: return launch<64, 256, 2, 4>(p, pl, stream);
         case 2: return launch<128, 128, 4, 2>(p, pl, stream);
-        default: return launch<256, 64, 4, 1>(p, pl, stream);
+        default: return launch<256, 64, 8, 1>(p, pl, stream);
     }
 }
 
