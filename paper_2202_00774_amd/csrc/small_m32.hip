@@ -1,0 +1,5 @@
+// Instantiates the small-problem backward-data kernel for groups of 32 channels.
+#include "bwd_small_launch.h"
+namespace sdgp {
+int launch_small_m32(const SmallParams& p, int rk, hipStream_t stream) { return launch_small_rk<32>(p, rk, stream); }
+}  // namespace sdgp
