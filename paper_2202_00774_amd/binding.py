@@ -7,6 +7,7 @@ non-zero status.  PyTorch is used for device memory and streams, nothing else.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 import threading
 
@@ -43,6 +44,8 @@ def library_path() -> str:
 def load():
     """Loads libsdgp.so; raises if it has not been built (there is no fallback)."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(_LIB_PATH):
@@ -128,12 +131,20 @@ def _dev(t: torch.Tensor, name: str) -> torch.Tensor:
     return t
 
 
+# The smallest calls are as long as their host side, so pointers and streams go to the library as plain integers
+# (the argument types convert them) and the stream is asked for without building a Stream object around it.
+
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(t: torch.Tensor):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(t: torch.Tensor) -> int:
+    if _raw_stream is not None:
+        return _raw_stream(t.get_device())
+    return torch.cuda.current_stream(t.device).cuda_stream
 
 
 def sdgp_prune(dO: torch.Tensor, n: int, m: int, ranker: int, seed: int = 0, *, pruned: bool = True,
@@ -166,13 +177,19 @@ def sdgp_linear_bwd_data(dO: torch.Tensor, W: torch.Tensor, n: int, m: int, rank
     rows, C_out = dO.shape
     C_in = W.shape[1]
     if out is None:
-        out = torch.empty((rows, C_in), dtype=dO.dtype, device=dO.device)
+        out = dO.new_empty((rows, C_in))
     _dev(out, "out")
     rc = load().sdgp_linear_bwd_data(_ptr(dO), _ptr(W), _ptr(out), rows, C_out, C_in, _dtype_code(dO), n, m, ranker,
                                      seed & (2**64 - 1), _stream(dO))
     if rc != 0:
         raise SdgpError(rc, "sdgp_linear_bwd_data")
     return out
+
+
+@functools.lru_cache(maxsize=1024)
+def _need(query: str, *geometry) -> int:
+    """Workspace bytes of a call: a pure function of its integers, asked of the library once for each layer."""
+    return int(getattr(load(), query)(*geometry))
 
 
 def conv_bwd_data_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dtype_code, n, m) -> int:
@@ -191,10 +208,10 @@ def sdgp_conv_bwd_data(dO: torch.Tensor, W: torch.Tensor, H: int, Wd: int, strid
     if (H + 2 * pad - R) // stride + 1 != P or (Wd + 2 * pad - S) // stride + 1 != Q:
         raise ValueError("dO's spatial size does not match H, Wd, stride, pad")
     if out is None:
-        out = torch.empty((B, H, Wd, C_in), dtype=dO.dtype, device=dO.device)
+        out = dO.new_empty((B, H, Wd, C_in))
     _dev(out, "out")
     dt = _dtype_code(dO)
-    need = conv_bwd_data_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m)
+    need = _need("sdgp_conv_bwd_data_workspace", B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m)
     if need == 2**64 - 1:
         raise SdgpError(-3, "sdgp_conv_bwd_data_workspace")
     if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
@@ -247,7 +264,7 @@ def sdgp_channel_scales(dO: torch.Tensor, n: int, m: int, *, sums: bool = False,
     rows = dO.numel() // C if C else 0
     dt = _dtype_code(dO)
     lib = load()
-    workspace, wbytes = _workspace(int(lib.sdgp_channel_scales_workspace(rows, C, dt, n, m)), workspace, dO.device,
+    workspace, wbytes = _workspace(_need("sdgp_channel_scales_workspace", rows, C, dt, n, m), workspace, dO.device,
                                    "sdgp_channel_scales_workspace")
     scale = torch.empty(C, dtype=torch.float32, device=dO.device)
     both = torch.empty((2, C), dtype=torch.float64, device=dO.device) if sums else None
@@ -316,11 +333,11 @@ def sdgp_conv_bwd_data_channel_rescaled(dO: torch.Tensor, W: torch.Tensor, H: in
     if (H + 2 * pad - R) // stride + 1 != P or (Wd + 2 * pad - S) // stride + 1 != Q:
         raise ValueError("dO's spatial size does not match H, Wd, stride, pad")
     if out is None:
-        out = torch.empty((B, H, Wd, C_in), dtype=dO.dtype, device=dO.device)
+        out = dO.new_empty((B, H, Wd, C_in))
     _dev(out, "out")
     dt = _dtype_code(dO)
     lib = load()
-    need = int(lib.sdgp_conv_bwd_data_channel_rescaled_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m))
+    need = _need("sdgp_conv_bwd_data_channel_rescaled_workspace", B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m)
     workspace, wbytes = _workspace(need, workspace, dO.device, "sdgp_conv_bwd_data_channel_rescaled_workspace")
     rc = lib.sdgp_conv_bwd_data_channel_rescaled(_ptr(dO), _ptr(W), _ptr(out), B, H, Wd, C_in, C_out, R, S, stride, pad,
                                                  dt, n, m, _ptr(workspace), wbytes, _stream(dO))
@@ -350,11 +367,11 @@ def sdgp_conv_bwd_data_compact(dO: torch.Tensor, W: torch.Tensor, H: int, Wd: in
     if (H + 2 * pad - R) // stride + 1 != P or (Wd + 2 * pad - S) // stride + 1 != Q:
         raise ValueError("dO's spatial size does not match H, Wd, stride, pad")
     if out is None:
-        out = torch.empty((B, H, Wd, C_in), dtype=dO.dtype, device=dO.device)
+        out = dO.new_empty((B, H, Wd, C_in))
     _dev(out, "out")
     dt = _dtype_code(dO)
     lib = load()
-    need = int(lib.sdgp_conv_bwd_data_compact_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m))
+    need = _need("sdgp_conv_bwd_data_compact_workspace", B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m)
     workspace, wbytes = _workspace(need, workspace, dO.device, "sdgp_conv_bwd_data_compact_workspace")
     rc = lib.sdgp_conv_bwd_data_compact(_ptr(dO), _ptr(W), _ptr(out), B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m,
                                         ranker, seed & (2**64 - 1), _ptr(workspace), wbytes, _stream(dO))
@@ -376,11 +393,11 @@ def sdgp_conv_bwd_data_grouped(dO: torch.Tensor, W: torch.Tensor, H: int, Wd: in
     if (H + 2 * pad - R) // stride + 1 != P or (Wd + 2 * pad - S) // stride + 1 != Q:
         raise ValueError("dO's spatial size does not match H, Wd, stride, pad")
     if out is None:
-        out = torch.empty((B, H, Wd, C_in), dtype=dO.dtype, device=dO.device)
+        out = dO.new_empty((B, H, Wd, C_in))
     _dev(out, "out")
     dt = _dtype_code(dO)
     lib = load()
-    need = int(lib.sdgp_conv_bwd_data_grouped_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, groups, dt, n, m))
+    need = _need("sdgp_conv_bwd_data_grouped_workspace", B, H, Wd, C_in, C_out, R, S, stride, pad, groups, dt, n, m)
     workspace, wbytes = _workspace(need, workspace, dO.device, "sdgp_conv_bwd_data_grouped_workspace")
     rc = lib.sdgp_conv_bwd_data_grouped(_ptr(dO), _ptr(W), _ptr(out), B, H, Wd, C_in, C_out, R, S, stride, pad, groups, dt,
                                         n, m, ranker, seed & (2**64 - 1), _ptr(workspace), wbytes, _stream(dO))
@@ -405,7 +422,7 @@ def sdgp_conv_fwd(D: torch.Tensor, W: torch.Tensor, stride: int, pad: int, out: 
     _dev(out, "out")
     dt = _dtype_code(D)
     lib = load()
-    need = int(lib.sdgp_conv_fwd_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dt))
+    need = _need("sdgp_conv_fwd_workspace", B, H, Wd, C_in, C_out, R, S, stride, pad, dt)
     workspace, wbytes = _workspace(need, workspace, D.device, "sdgp_conv_fwd_workspace")
     rc = lib.sdgp_conv_fwd(_ptr(D), _ptr(W), _ptr(out), B, H, Wd, C_in, C_out, R, S, stride, pad, dt, _ptr(workspace), wbytes,
                            _stream(D))
@@ -431,7 +448,7 @@ def sdgp_conv_bwd_weight(D: torch.Tensor, dO: torch.Tensor, R: int, S: int, stri
         raise ValueError("out must be float32 [C_out,R,S,C_in]")
     dt = _dtype_code(D)
     lib = load()
-    need = int(lib.sdgp_conv_bwd_weight_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dt))
+    need = _need("sdgp_conv_bwd_weight_workspace", B, H, Wd, C_in, C_out, R, S, stride, pad, dt)
     workspace, wbytes = _workspace(need, workspace, D.device, "sdgp_conv_bwd_weight_workspace")
     rc = lib.sdgp_conv_bwd_weight(_ptr(D), _ptr(dO), _ptr(out), B, H, Wd, C_in, C_out, R, S, stride, pad, dt,
                                   _ptr(workspace), wbytes, _stream(D))
