@@ -15,6 +15,7 @@
 //   * stride 2: the input pixels split into four parity classes (h mod 2, w mod 2) with 1, 2, 2 and 4 taps -- again five
 //     tap pairs.  The tile is 8 x 32 positions (i, j) of the class grid, input pixels (2i + a, 2j + b), all four
 //     classes from one gradient tile of 9 x 33 pixels: tap r of class a reads gradient row i + (a + 1 - r) / 2.
+#include "fastdiv.h"
 #include "lds_copy.h"
 
 namespace sdgp {
@@ -177,8 +178,169 @@ __global__ void __launch_bounds__(256, 2) bwd_group16(const GroupedParams p) {
             }
 }
 
+// The same product for images up to kFlatMaxW grid positions wide, where tiles of 8 x 32 positions leave much of
+// themselves outside the image.  The grid positions of all images lie behind each other in one line, every image row
+// followed by one position of padding and every image by one such row (the padding left of a row is the position behind
+// the row before it): a tap is then a constant distance along that line whatever the row, so a workgroup takes 256
+// consecutive positions, sixteen per matrix instruction, wherever rows and images begin.
+//   * A slab is two groups (64 bytes per pixel, 80-byte pitch: sixteen consecutive pixels read conflict-free), so a layer
+//     of ten groups has no empty ones and five workgroups fit a CU; the slabs of a tile follow each other on one XCD.
+//   * The filter comes straight from W: the slab's 9 KB are copied to LDS as they are, and the transposing read
+//     ds_read_b64_tr_b16 turns four output channels x 16 input channels into a lane's fragment.  No image of the filter,
+//     no second launch.
+// Batch 256, 2:4 Magnitude, tiles above with their filter image / this kernel: 160 channels at 14x14 24.6 / 16.4 us, 384 at
+// 7x7 24.7 / 11.9, 64 at 28x28 24.4 / 20.8, 32 at 112x112 stride 2 77 / 59.  The distance of a tap, and with it the part of a
+// tile that is only read, grows with the width: at 62 positions the two are level (64 channels, batch 64 25.7 / 24.0).
+constexpr int kFlatSlab = 2, kFlatPos = 256, kFlatMaxW = 63;
+constexpr int kFlatPitch = kFlatSlab * kGW * 2 + 16;   // 80 bytes per pixel in LDS
+constexpr int kFlatSlots = kFlatPitch / 16;            // 5 sixteen-byte slots, the last one padding
+constexpr int kFlatFilter = kFlatSlab * kGW * 9 * kGW * 2;   // 9216 bytes
+
+struct FlatParams {
+    const uint16_t* dO;
+    const uint16_t* W;
+    uint16_t* dD;
+    int H, Wd, gh, gw, C, groups;   // input pixels, grid (= gradient) pixels per image
+    int positions, slabs, nblocks;  // grid positions of all images, padding included
+    int npix, units;                // gradient positions of a tile and the 1 KB copies they take
+    FastDiv by_wp, by_hp, by_slabs;
+    int n;
+    uint32_t mix;
+};
+
 template <int STRIDE, int M, int RK, bool PRUNE, bool NLE2>
-int launch_group16(const GroupedParams& p, hipStream_t stream) {
+__global__ void __launch_bounds__(256, 4) bwd_group16_flat(const FlatParams p) {
+    constexpr int kClasses = STRIDE * STRIDE;
+    extern __shared__ __align__(16) unsigned char smem_generic[];
+    SDGP_LDSG unsigned char* smem = (SDGP_LDSG unsigned char*)smem_generic;
+    const uint32_t smem_base = (uint32_t)(uintptr_t)smem;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int logical = ((int)blockIdx.x & 7) * (int)(gridDim.x >> 3) + ((int)blockIdx.x >> 3);
+    if (logical >= p.nblocks) return;
+    const int tile = (int)divide((uint32_t)logical, p.by_slabs), slab = logical - tile * p.slabs;
+    const int wp = p.gw + 1, hp = p.gh + 1, f0 = tile * kFlatPos, g0 = slab * kFlatSlab;
+    const int fstart = STRIDE == 1 ? f0 - wp - 1 : f0;      // the first position a tap reaches
+    const int px = lane & 15, oct = lane >> 4;
+    const uint32_t off_w = (uint32_t)p.units * 1024u;
+
+    // gradient pixel (b * gh + i) * gw + j of a position, or -1 where there is none
+    auto pixel = [&](int f) {
+        if (f < 0 || f >= p.positions) return -1;
+        const int line = (int)divide((uint32_t)f, p.by_wp), j = f - line * wp;
+        const int b = (int)divide((uint32_t)line, p.by_hp), i = line - b * hp;
+        return i < p.gh && j < p.gw ? (b * p.gh + i) * p.gw + j : -1;
+    };
+
+    // ---- copies: the slab's filter as it is, the gradient by slot -> (position, eight channels); what is not there is cleared
+    {
+        const int bytes = (p.groups - g0 < kFlatSlab ? p.groups - g0 : kFlatSlab) * (kFlatFilter / kFlatSlab);
+        const unsigned char* const src = reinterpret_cast<const unsigned char*>(p.W) + (size_t)g0 * (kFlatFilter / kFlatSlab);
+        for (int u = wave; u < kFlatFilter / 1024; u += 4) {
+            const int at = u * 1024 + lane * 16;
+            if (at < bytes) lds_copy16(src + at, smem_base + off_w + (uint32_t)u * 1024u);
+        }
+    }
+    for (int u = wave; u < p.units; u += 4) {
+        const int slot = u * 64 + lane;
+        const int pix = (int)(((uint32_t)slot * 13108u) >> 16);                 // slot / 5 for slot < 16384
+        const int part = slot - kFlatSlots * pix;                               // 0..3 data, 4 padding
+        const int ch = g0 * kGW + part * 8;
+        const int at = part < 4 && ch < p.C && pix < p.npix ? pixel(fstart + pix) : -1;
+        if (at >= 0) lds_copy16(p.dO + ((size_t)at * p.C + ch), smem_base + (uint32_t)u * 1024u);
+        else *(SDGP_LDSG u32x4_t*)(smem + slot * 16) = u32x4_t{0u, 0u, 0u, 0u};
+    }
+    wait_lds_copies<0>();
+    __syncthreads();
+
+    // ---- the filter's fragments: lane (c = px, k-octet = oct) of (group, tap pair)
+    bf16x8_t wf[kFlatSlab][kGPairs];
+#pragma unroll
+    for (int g = 0; g < kFlatSlab; ++g)
+#pragma unroll
+        for (int j = 0; j < kGPairs; ++j) {
+            const int t0 = pair_tap(STRIDE, j, 0), t1 = pair_tap(STRIDE, j, 1);
+            const int tap = (oct >> 1) && t1 >= 0 ? t1 : t0;
+            const uint32_t at = off_w + (uint32_t)(((g * kGW + (oct & 1) * 8 + (px >> 2)) * 9 + tap) * (kGW * 2) + (px & 3) * 8);
+            const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SDGP_LDSG s16x4_t*)(smem + at));
+            const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SDGP_LDSG s16x4_t*)(smem + at + 4 * 9 * kGW * 2));
+            typedef short s16x8_t __attribute__((ext_vector_type(8)));
+            s16x8_t all = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            if (t1 < 0 && (oct >> 1)) all = s16x8_t{0, 0, 0, 0, 0, 0, 0, 0};    // (a pair without a second tap)
+            wf[g][j] = __builtin_bit_cast(bf16x8_t, all);
+        }
+    if constexpr (PRUNE) {
+        for (int it = tid; it < p.npix * kFlatSlab; it += 256) {
+            const int pix = it >> 1, g = it & 1;
+            const int at = g0 + g < p.groups ? pixel(fstart + pix) : -1;
+            if (at >= 0) {
+                SDGP_LDSG u32x4_t* rec = (SDGP_LDSG u32x4_t*)(smem + pix * kFlatPitch + g * 32);
+                u32x4_t v[2] = {rec[0], rec[1]};
+                prune16_dense<M, RK, NLE2>(v, p.n, p.mix, (uint64_t)at * (uint64_t)p.C + (uint64_t)((g0 + g) * kGW));
+                rec[0] = v[0];
+                rec[1] = v[1];
+            }
+        }
+        __syncthreads();
+    }
+
+    // ---- products: wavefront `wave` owns the runs of sixteen positions 4 wave .. 4 wave + 3
+    uint32_t tapoff[kGPairs];
+#pragma unroll
+    for (int j = 0; j < kGPairs; ++j) {
+        const int t0 = pair_tap(STRIDE, j, 0), t1 = pair_tap(STRIDE, j, 1) >= 0 ? pair_tap(STRIDE, j, 1) : t0;
+        const int cls = pair_class(STRIDE, j);
+        const int d0 = tap_shift(STRIDE, cls >> 1, t0 / 3) * wp + tap_shift(STRIDE, cls & 1, t0 % 3);
+        const int d1 = tap_shift(STRIDE, cls >> 1, t1 / 3) * wp + tap_shift(STRIDE, cls & 1, t1 % 3);
+        tapoff[j] = (uint32_t)((((oct >> 1) ? d1 : d0) + wave * 64 + px) * kFlatPitch + (oct & 1) * 16);
+    }
+#pragma unroll
+    for (int run = 0; run < 4; ++run) {
+        const int at = pixel(f0 + wave * 64 + run * 16 + px);   // the grid position has the gradient pixel's index
+        const int line = at >= 0 ? at / p.gw : 0, j2 = at - line * p.gw, b = line / p.gh, i2 = line - b * p.gh;
+#pragma unroll
+        for (int cls = 0; cls < kClasses; ++cls) {
+            const int h = STRIDE * i2 + (cls >> 1), w = STRIDE * j2 + (cls & 1);
+            const bool live = at >= 0 && h < p.H && w < p.Wd;
+            uint16_t* dst = p.dD + ((size_t)(b * p.H + h) * p.Wd + w) * p.C + g0 * kGW + oct * 4;
+#pragma unroll
+            for (int g = 0; g < kFlatSlab; ++g) {
+                f32x4g a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int j = 0; j < kGPairs; ++j) {
+                    if (pair_class(STRIDE, j) != cls) continue;
+                    const uint32_t off = tapoff[j] + (uint32_t)(run * 16 * kFlatPitch + g * 32);
+                    const bf16x8_t gf = __builtin_bit_cast(bf16x8_t, *(SDGP_LDSG u32x4_t*)(smem + off));
+                    a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[g][j], gf, a, 0, 0, 0);
+                }
+                if (live && g0 + g < p.groups) {
+                    typedef uint32_t u32x2g __attribute__((ext_vector_type(2)));
+                    const u32x2g v = {float2_to_bf16x2(a[0], a[1]), float2_to_bf16x2(a[2], a[3])};
+                    *reinterpret_cast<u32x2g*>(dst + g * kGW) = v;
+                }
+            }
+        }
+    }
+}
+
+template <int STRIDE, int M, int RK, bool PRUNE, bool NLE2>
+int launch_flat(const FlatParams& p, hipStream_t stream) {
+    auto kern = bwd_group16_flat<STRIDE, M, RK, PRUNE, NLE2>;
+    const int lds = p.units * 1024 + kFlatFilter;   // at most 41 KB
+    hipLaunchKernelGGL(kern, dim3((unsigned)(p.nblocks + 7) / 8 * 8), dim3(256), lds, stream, p);
+    return launch_status();
+}
+
+struct GroupedLaunch {
+    GroupedParams wide;
+    FlatParams flat;
+    bool is_flat;
+};
+
+template <int STRIDE, int M, int RK, bool PRUNE, bool NLE2>
+int launch_group16(const GroupedLaunch& l, hipStream_t stream) {
+    if (l.is_flat) return launch_flat<STRIDE, M, RK, PRUNE, NLE2>(l.flat, stream);
+    const GroupedParams& p = l.wide;
     auto kern = bwd_group16<STRIDE, M, RK, PRUNE, NLE2>;
     constexpr int lds = GroupedGeom<STRIDE>::kLds;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -188,14 +350,14 @@ int launch_group16(const GroupedParams& p, hipStream_t stream) {
 }
 
 template <int STRIDE, int M, bool NLE2>
-int launch_group16_rk(const GroupedParams& p, int rk, hipStream_t stream) {
+int launch_group16_rk(const GroupedLaunch& p, int rk, hipStream_t stream) {
     if (rk == kRandom) return launch_group16<STRIDE, M, kRandom, true, NLE2>(p, stream);
     if (rk == kGreedy) return launch_group16<STRIDE, M, kGreedy, true, NLE2>(p, stream);
     return launch_group16<STRIDE, M, kAdjusted, true, NLE2>(p, stream);
 }
 
 template <int STRIDE>
-int launch_group16_nm(const GroupedParams& p, int n, int m, int rk, hipStream_t stream) {
+int launch_group16_nm(const GroupedLaunch& p, int n, int m, int rk, hipStream_t stream) {
     if (n == m) return launch_group16<STRIDE, 4, kGreedy, false, true>(p, stream);
     const bool le2 = n <= 2;
     if (m == 4) return le2 ? launch_group16_rk<STRIDE, 4, true>(p, rk, stream) : launch_group16_rk<STRIDE, 4, false>(p, rk, stream);
@@ -229,16 +391,30 @@ int bwd_grouped_launch(const void* dO, const void* W, void* dD, int64_t B, int64
                        hipStream_t stream) {
     if (!group16_fits(B, H, Wd, C_in, C_out, R, S, stride, pad, groups, dt, n, m)) return 1;
     if (workspace == nullptr || !is_aligned16(workspace) || !is_aligned16(dO) || (reinterpret_cast<uintptr_t>(dD) & 7u) != 0) return 1;
-    GroupedParams p{};
-    p.dO = static_cast<const uint16_t*>(dO), p.wimg = static_cast<const unsigned char*>(workspace), p.dD = static_cast<uint16_t*>(dD);
-    p.B = (int)B, p.H = (int)H, p.Wd = (int)Wd, p.C = (int)C_out, p.groups = (int)groups;
-    p.P = (int)((H + 2 - 3) / stride + 1), p.Q = (int)((Wd + 2 - 3) / stride + 1);
     const int64_t gh = (H + stride - 1) / stride, gw = (Wd + stride - 1) / stride;
-    p.tiles_h = (int)((gh + kGTH - 1) / kGTH), p.tiles_w = (int)((gw + kGTW - 1) / kGTW), p.slabs = (int)((groups + kGSlab - 1) / kGSlab);
-    p.n = n, p.mix = seed_mix(seed);
-    hipLaunchKernelGGL(grouped_w_image, dim3((unsigned)(groups * kGPairs)), dim3(256), 0, stream, static_cast<const uint16_t*>(W),
-                       static_cast<uint16_t*>(workspace), stride);
-    return stride == 1 ? launch_group16_nm<1>(p, n, m, rk, stream) : launch_group16_nm<2>(p, n, m, rk, stream);
+    GroupedLaunch l{};
+    const int64_t positions = B * (gh + 1) * (gw + 1), slabs = (groups + kFlatSlab - 1) / kFlatSlab;
+    l.is_flat = gw <= kFlatMaxW && is_aligned16(W) && positions < ((int64_t)1 << 30) && (positions + kFlatPos - 1) / kFlatPos * slabs < ((int64_t)1 << 30);
+    if (l.is_flat) {
+        FlatParams& p = l.flat;
+        p.dO = static_cast<const uint16_t*>(dO), p.W = static_cast<const uint16_t*>(W), p.dD = static_cast<uint16_t*>(dD);
+        p.H = (int)H, p.Wd = (int)Wd, p.gh = (int)gh, p.gw = (int)gw, p.C = (int)C_out, p.groups = (int)groups;
+        p.positions = (int)positions, p.slabs = (int)slabs, p.nblocks = (int)((positions + kFlatPos - 1) / kFlatPos * slabs);
+        p.npix = kFlatPos + (stride == 1 ? 2 : 1) * ((int)gw + 2);
+        p.units = (p.npix * kFlatPitch + 1023) / 1024;
+        p.by_wp = fast_div((uint32_t)gw + 1), p.by_hp = fast_div((uint32_t)gh + 1), p.by_slabs = fast_div((uint32_t)slabs);
+        p.n = n, p.mix = seed_mix(seed);
+    } else {
+        GroupedParams& p = l.wide;
+        p.dO = static_cast<const uint16_t*>(dO), p.wimg = static_cast<const unsigned char*>(workspace), p.dD = static_cast<uint16_t*>(dD);
+        p.B = (int)B, p.H = (int)H, p.Wd = (int)Wd, p.C = (int)C_out, p.groups = (int)groups;
+        p.P = (int)((H + 2 - 3) / stride + 1), p.Q = (int)((Wd + 2 - 3) / stride + 1);
+        p.tiles_h = (int)((gh + kGTH - 1) / kGTH), p.tiles_w = (int)((gw + kGTW - 1) / kGTW), p.slabs = (int)((groups + kGSlab - 1) / kGSlab);
+        p.n = n, p.mix = seed_mix(seed);
+        hipLaunchKernelGGL(grouped_w_image, dim3((unsigned)(groups * kGPairs)), dim3(256), 0, stream, static_cast<const uint16_t*>(W),
+                           static_cast<uint16_t*>(workspace), stride);
+    }
+    return stride == 1 ? launch_group16_nm<1>(l, n, m, rk, stream) : launch_group16_nm<2>(l, n, m, rk, stream);
 }
 
 }  // namespace sdgp

@@ -19,6 +19,7 @@
 //     to call.
 // 1x1 256 -> 64 at 56x56, batch 64 (128 MB): 29 us with the sum of the splits, 105 ms with one workgroup per filter
 // element.
+#include "fastdiv.h"
 #include "lds_copy.h"
 #include "wgrad_gather.h"
 
@@ -40,15 +41,9 @@ struct GatherParams {
     int64_t per;              // pixels per split, a multiple of kPX
     int H, Wd, P, Q, C_in, C_out, S, stride, pad, ntaps;
     int kblocks, cblocks;
-    uint32_t q_mul, q_shift, p_mul, p_shift;   // division by Q and by P (divide())
+    FastDiv by_q, by_p;
     int plain;                // 1x1, stride 1: a gradient pixel reads the image pixel of the same index
 };
-
-// n / d for n < 2^31 by multiplication: mul = ceil(2^(31 + shift) / d) with 2^shift >= d fits 32 bits, and its rounding
-// error of less than one part in 2^31 cannot carry a quotient over.
-__device__ __forceinline__ uint32_t divide(uint32_t n, uint32_t mul, uint32_t shift) {
-    return (uint32_t)(((uint64_t)n * mul) >> (31 + shift));
-}
 
 template <int KB, int CB, int WVK, int WVC>
 __global__ void __launch_bounds__(WVK* WVC * 64) wgrad_gather(const GatherParams p) {
@@ -93,8 +88,8 @@ __global__ void __launch_bounds__(WVK* WVC * 64) wgrad_gather(const GatherParams
     auto source = [&](int64_t pix) -> int64_t {
         if (pix >= pix1) return -1;
         if (p.plain) return pix;
-        const uint32_t n = (uint32_t)pix, row = divide(n, p.q_mul, p.q_shift), q = n - row * (uint32_t)p.Q;
-        const uint32_t b = divide(row, p.p_mul, p.p_shift), pp = row - b * (uint32_t)p.P;
+        const uint32_t n = (uint32_t)pix, row = divide(n, p.by_q), q = n - row * (uint32_t)p.Q;
+        const uint32_t b = divide(row, p.by_p), pp = row - b * (uint32_t)p.P;
         const int h = (int)pp * p.stride + r - p.pad, w = (int)q * p.stride + s - p.pad;
         if ((unsigned)h >= (unsigned)p.H || (unsigned)w >= (unsigned)p.Wd) return -1;
         return ((int64_t)b * p.H + h) * p.Wd + w;
@@ -207,12 +202,6 @@ struct Shape {
 };
 constexpr Shape kShapes[] = {{64, 64, 4}, {64, 256, 1}, {128, 128, 1}, {256, 64, 1}};
 
-void division(uint32_t d, uint32_t* mul, uint32_t* shift) {
-    *shift = 0;
-    while (((uint64_t)1 << *shift) < d) ++*shift;
-    *mul = (uint32_t)((((uint64_t)1 << (31 + *shift)) + d - 1) / d);
-}
-
 template <int KB, int CB, int WVK, int WVC>
 int launch(const GatherParams& p, const WgradGatherPlan& pl, hipStream_t stream) {
     constexpr int lds = kSets * kPX * (KB + CB) * 2;
@@ -266,8 +255,7 @@ int wgrad_gather_launch(const WgradGatherPlan& pl, const void* D, const void* dO
     p.nW = C_out * R * S * C_in, p.npix = B * p.P * p.Q, p.per = pl.per;
     p.C_in = (int)C_in, p.C_out = (int)C_out, p.S = S, p.stride = stride, p.pad = pad, p.ntaps = R * S;
     p.kblocks = (int)pl.kblocks, p.cblocks = (int)pl.cblocks;
-    division((uint32_t)p.Q, &p.q_mul, &p.q_shift);
-    division((uint32_t)p.P, &p.p_mul, &p.p_shift);
+    p.by_q = fast_div((uint32_t)p.Q), p.by_p = fast_div((uint32_t)p.P);
     p.plain = R == 1 && S == 1 && stride == 1 && pad == 0;
     switch (pl.shape) {
         case 0: return launch<64, 64, 2, 2>(p, pl, stream);
