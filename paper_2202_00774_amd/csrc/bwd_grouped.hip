@@ -276,7 +276,7 @@ __global__ void __launch_bounds__(256, 4) bwd_group16_flat(const FlatParams p) {
             if (at >= 0) {
                 SDGP_LDSG u32x4_t* rec = (SDGP_LDSG u32x4_t*)(smem + pix * kFlatPitch + g * 32);
                 u32x4_t v[2] = {rec[0], rec[1]};
-                prune16_dense<M, RK, NLE2>(v, p.n, p.mix, (uint64_t)at * (uint64_t)p.C + (uint64_t)((g0 + g) * kGW));
+                prune16_dense<M, RK, NLE2>(v, p.n, p.mix, (uint64_t)(uint32_t)at * (uint32_t)p.C + (uint32_t)((g0 + g) * kGW));
                 rec[0] = v[0];
                 rec[1] = v[1];
             }

@@ -435,9 +435,12 @@ __global__ void __launch_bounds__(256, 2) bwd_narrow_mm(const NarrowParams p) {
 //     rows 4 rq .. 4 rq + 3: 4 x 2 accumulators of four registers;
 //   * the reduction runs in chunks of 32 channels: the 19 x 35 gradient pixels the tile's windows reach (64 bytes each,
 //     80-byte pitch: sixteen consecutive pixels read conflict-free, and every fragment address is a per-lane base plus
-//     a constant) and V's chunk (16 window positions x 16 columns, built once per call in the workspace) arrive by
-//     direct-to-LDS copies; slots of pixels outside the gradient are cleared once and skipped by the copies; pruning, when asked
-//     for, is done in place;
+//     a constant) arrive by direct-to-LDS copies; slots of pixels outside the gradient are cleared once and skipped by the
+//     copies; pruning, when asked for, is done in place;
+//   * V's chunk (16 window positions x 16 columns, built once per call in the workspace) goes from the L2 straight to the 64
+//     registers that hold its sixteen fragments, in flight while the chunk is ranked: without its 20 KB in LDS three
+//     workgroups fit a CU.  Bound by the ranker's instructions (half of all issue slots): batch 256 at 224 x 224, 2:4
+//     random 217 us (258 with V in LDS and two workgroups per CU), Magnitude 206 (229), 4:8 Rescaled 275 (321);
 //   * a gradient fragment (16 pixels x 32 channels) is read once per (tile row, dq) and feeds up to four matrix
 //     instructions (the output rows whose window holds that gradient row); V's 16 fragments sit in registers.
 constexpr int kFWin = 4;                                  // window positions per dimension
@@ -450,9 +453,7 @@ constexpr int kFPitch = 80;                               // bytes per pixel in 
 constexpr int kFAUnits = (kFPix * kFPitch + 1023) / 1024; // 1 KB copy units
 constexpr int kFABytes = kFAUnits * 1024;
 constexpr int kFWRows = kFWin * kFWin * 16;               // rows of V's chunk: (window position, column)
-constexpr int kFWUnits = kFWRows * kFPitch / 1024;        // 20
 constexpr int kFThreads = 256;
-static_assert(kFWRows * kFPitch % 1024 == 0, "V's chunk is whole copy units");
 
 struct FirstParams {
     const uint16_t* dO;
@@ -504,7 +505,7 @@ __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) 
 
     // this lane's bases: V fragments (row = window position * 16 + column px), gradient fragments (tile row 4 rq,
     // column 32 gp + px, window column 0)
-    SDGP_LDSN unsigned char* const vbase = smem + kFABytes + px * kFPitch + oct * 16;
+    const unsigned char* const vbase = p.vimg + px * kFPitch + oct * 16;
     SDGP_LDSN unsigned char* const abase = smem + ((4 * rq) * kFHaloCols + 32 * gp + px) * kFPitch + oct * 16;
 
     // Where this lane's 16-byte slots of the gradient tile come from: a byte offset inside image b (the same for every
@@ -535,8 +536,11 @@ __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) 
             const int u = wave + 4 * x;
             if (voff[x] != kNothing) lds_copy16(image + (size_t)kc * (kFKC * 2), voff[x], smem_base + (uint32_t)u * 1024u);
         }
-        for (int u = wave; u < kFWUnits; u += 4)
-            lds_copy16(p.vimg + ((size_t)kc * kFWUnits + u) * 1024 + lane * 16, smem_base + (uint32_t)(kFABytes + u * 1024));
+        // V's fragments are in flight while the gradient is ranked
+        bf16x8n vf[kFWin * kFWin];
+#pragma unroll
+        for (int t = 0; t < kFWin * kFWin; ++t)
+            vf[t] = __builtin_bit_cast(bf16x8n, *reinterpret_cast<const u32x4n*>(vbase + (size_t)(kc * kFWRows + t * 16) * kFPitch));
         wait_lds_copies<0>();
         __syncthreads();
         if constexpr (PRUNE) {
@@ -547,17 +551,14 @@ __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) 
                 if (gi >= 0 && gi < p.P && gj >= 0 && gj < p.Q) {
                     SDGP_LDSN u32x4n* g0 = (SDGP_LDSN u32x4n*)(smem + hp * kFPitch + half * 32);
                     u32x4n v[2] = {g0[0], g0[1]};
-                    const size_t gpix = (size_t)(b * p.P + gi) * p.Q + gj;
-                    prune16_dense<M, RK, NLE2>(v, p.n, p.mix, (uint64_t)gpix * (uint64_t)p.C_out + (uint64_t)(kc * kFKC + half * 16));
+                    const uint32_t gpix = (uint32_t)((b * p.P + gi) * p.Q + gj);   // (below 2^31)
+                    prune16_dense<M, RK, NLE2>(v, p.n, p.mix, (uint64_t)gpix * (uint32_t)p.C_out + (uint32_t)(kc * kFKC + half * 16));
                     g0[0] = v[0];
                     g0[1] = v[1];
                 }
             }
             __syncthreads();
         }
-        bf16x8n vf[kFWin * kFWin];
-#pragma unroll
-        for (int t = 0; t < kFWin * kFWin; ++t) vf[t] = __builtin_bit_cast(bf16x8n, *(SDGP_LDSN u32x4n*)(vbase + t * 16 * kFPitch));
 #pragma unroll
         for (int rr = 0; rr < 4 + kFWin - 1; ++rr) {       // gradient rows of this wavefront's four output rows
 #pragma unroll
@@ -608,7 +609,7 @@ size_t first2_image_bytes(int64_t C_out) { return (size_t)(C_out / kFKC) * kFWRo
 template <int M, int RK, bool PRUNE, bool NLE2>
 int launch_first2(const FirstParams& p, hipStream_t stream) {
     auto kern = bwd_first2<M, RK, PRUNE, NLE2>;
-    constexpr int lds = kFABytes + kFWRows * kFPitch;
+    constexpr int lds = kFABytes;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return SDGP_ERR_HIP;
     hipLaunchKernelGGL(kern, dim3((unsigned)(p.B * p.tiles_i * p.tiles_j)), dim3(kFThreads), lds, stream, p);
