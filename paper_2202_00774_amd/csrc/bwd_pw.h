@@ -23,6 +23,7 @@
 
 #include <type_traits>
 
+#include "fastdiv.h"
 #include "lds_copy.h"
 
 namespace sdgp {
@@ -40,6 +41,7 @@ struct PwParams {
     // (i + tap_dp[t], j + tap_dq[t]) -- zeros outside the gradient -- against filter tap tap_w[t] of w_taps
     int gather, ntaps, w_taps, Pc, Qc, oa, ob;
     int tap_dp[4], tap_dq[4], tap_w[4];
+    FastDiv by_image, by_line;   // pixels of an image and of a line of it: the class grid's, or the gradient's (stride > 1)
     int n;
     uint32_t mix;
     int ntiles_n, nblocks;
@@ -360,9 +362,8 @@ __device__ __forceinline__ void bwd_pw_body(const PwParams& p) {
             const long long row = m0 + m;
             int base = -1, ij = 0, opix = -1;
             if (row <= last_row) {
-                const int pq = p.Pc * p.Qc;
-                const int b = (int)(row / pq), rem = (int)(row - (long long)b * pq);
-                const int i = rem / p.Qc, j = rem - i * p.Qc;
+                const int b = (int)divide((uint32_t)row, p.by_image), rem = (int)row - b * p.Pc * p.Qc;
+                const int i = (int)divide((uint32_t)rem, p.by_line), j = rem - i * p.Qc;
                 base = (b * p.P + i) * p.Q + j;
                 if (base < 0) base = 0;
                 ij = i | (j << 16);
@@ -374,20 +375,26 @@ __device__ __forceinline__ void bwd_pw_body(const PwParams& p) {
         auto tap_source = [&](int rl, int t) {
             const int base = rowtab[3 * rl], ij = rowtab[3 * rl + 1];
             const int i = (ij & 0xFFFF) + p.tap_dp[t], j = (ij >> 16) + p.tap_dq[t];
-            const bool ok = t < p.ntaps && base >= 0 && i >= 0 && i < p.P && j >= 0 && j < p.Q;
-            long long src = (long long)base + (long long)p.tap_dp[t] * p.Q + p.tap_dq[t];
-            src = src < 0 ? 0 : (src > last_pix ? last_pix : src);  // (a valid tap is inside anyway)
-            return ok ? (int)src : -1;
+            const bool ok = base >= 0 && (unsigned)i < (unsigned)p.P && (unsigned)j < (unsigned)p.Q;
+            return ok ? base + p.tap_dp[t] * p.Q + p.tap_dq[t] : -1;
         };
+        // (a class without taps t and up reads neither: most classes of a stride-2 filter have one or two of the four)
 #pragma unroll
-        for (int j = 0; j < APW; ++j)
+        for (int t = 0; t < 4; ++t) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) a_src[j][t] = tap_source((wave + j * NW) * 16 + (lane >> 2), t);
-        if constexpr (PRE) {
+            for (int j = 0; j < APW; ++j) a_src[j][t] = -1;
+            if constexpr (PRE) {
 #pragma unroll
-            for (int j = 0; j < MPW; ++j)
+                for (int j = 0; j < MPW; ++j) m_src[j][t] = -1;
+            }
+            if (t < p.ntaps) {
 #pragma unroll
-                for (int t = 0; t < 4; ++t) m_src[j][t] = tap_source((wave + j * NW) * 32 + (lane >> 1), t);
+                for (int j = 0; j < APW; ++j) a_src[j][t] = tap_source((wave + j * NW) * 16 + (lane >> 2), t);
+                if constexpr (PRE) {
+#pragma unroll
+                    for (int j = 0; j < MPW; ++j) m_src[j][t] = tap_source((wave + j * NW) * 32 + (lane >> 1), t);
+                }
+            }
         }
     }
     constexpr int SETS = L::kSets;
@@ -558,9 +565,8 @@ __device__ __forceinline__ void bwd_pw_body(const PwParams& p) {
             const long long row = m0 + m;
             int pix = -1, lim = 0;
             if (row <= last_row) {
-                const int pq = p.P * p.Q;
-                const int b = (int)(row / pq), rem = (int)(row - (long long)b * pq);
-                const int pp = rem / p.Q, qq = rem - pp * p.Q;
+                const int b = (int)divide((uint32_t)row, p.by_image), rem = (int)row - b * p.P * p.Q;
+                const int pp = (int)divide((uint32_t)rem, p.by_line), qq = rem - pp * p.Q;
                 const int h = pp * p.stride, w = qq * p.stride;
                 pix = (b * p.H + h) * p.Wd + w;
                 lim = (min(p.stride, p.H - h) << 8) | min(p.stride, p.Wd - w);
@@ -618,6 +624,8 @@ constexpr int kPwMaxClasses = 16;
 struct PwClasses {
     PwParams c[kPwMaxClasses];
 };
+
+static_assert(sizeof(PwClasses) <= 4096, "kernel arguments");
 
 template <int BN, int MODE, int M, int RK, int ROWS, int NW>
 __global__ void __launch_bounds__(NW * 64) bwd_pw_classes(const PwClasses all) {

@@ -111,6 +111,7 @@ int pw_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R
     p.n = n;
     p.stride = stride, p.P = (int)P, p.Q = (int)Q, p.H = (int)H, p.Wd = (int)Wd;
     p.rows_dO = rows, p.gather = 0, p.ntaps = 1, p.w_taps = 1;
+    if (stride > 1) p.by_image = fast_div((uint32_t)(P * Q)), p.by_line = fast_div((uint32_t)Q);   // (rows below 2^31 then)
 
     int shape = force_shape >= 0 ? force_shape : pw_shape(mode, C_in, C_out);
     const int fused_tiles_n = (int)((C_in + kPwShapes[shape].bn - 1) / kPwShapes[shape].bn);
@@ -293,6 +294,7 @@ int gather_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, i
             }
             if (q.ntaps == 0) return 1;
             q.rows = B * q.Pc * q.Qc;
+            q.by_image = fast_div((uint32_t)(q.Pc * q.Qc)), q.by_line = fast_div((uint32_t)q.Qc);   // (both positive: H, Wd >= stride)
             const int64_t blocks = ((q.rows + rows_per - 1) / rows_per) * q.ntiles_n;
             if (q.rows < 1 || blocks < 64 || blocks >= INT_MAX) return 1;
             q.nblocks = (int)blocks;
