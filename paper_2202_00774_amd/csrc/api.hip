@@ -46,7 +46,7 @@ int bwd_f32_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H
                    int R, int S, int stride, int pad, int n, int m, int rk, uint64_t seed, hipStream_t stream);
 size_t channel_scales_workspace(int64_t rows, int64_t C, int dt, int m);
 int channel_scales_launch(const void* dO, int64_t rows, int64_t C, int dt, int n, int m, float* scale, double* sums,
-                          void* partial, hipStream_t stream);
+                          void* partial, const void* W, void* scaled, int64_t inner, hipStream_t stream);
 int prune_channel_rescaled_launch(const void* dO, int64_t rows, int64_t C, int dt, int n, int m, const float* scale,
                                   void* pruned, hipStream_t stream);
 int scale_rows_launch(const void* W, const float* scale, void* out, int64_t C_out, int64_t inner, int dt, hipStream_t stream);
@@ -353,7 +353,8 @@ int sdgp_channel_scales(const void* dO, int64_t rows, int64_t C, int dt, int n, 
     const size_t need = sdgp::channel_scales_workspace(rows, C, dt, m);
     if (workspace == nullptr || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 7u) != 0)
         return SDGP_ERR_WORKSPACE;
-    return sdgp::channel_scales_launch(dO, rows, C, dt, n, m, scale, sums, workspace, static_cast<hipStream_t>(hip_stream));
+    return sdgp::channel_scales_launch(dO, rows, C, dt, n, m, scale, sums, workspace, nullptr, nullptr, 0,
+                                       static_cast<hipStream_t>(hip_stream));
 }
 
 int sdgp_prune_channel_rescaled(const void* dO, int64_t rows, int64_t C, int dt, int n, int m, const float* scale,
@@ -402,9 +403,7 @@ int sdgp_conv_bwd_data_channel_rescaled(const void* dO, const void* W, void* dD,
     char* base = static_cast<char*>(workspace);
     float* scale = reinterpret_cast<float*>(base + w.off_scale);
     void* filter = base + w.off_filter;
-    rc = sdgp::channel_scales_launch(dO, rows, C_out, dt, n, m, scale, nullptr, base, stream);
-    if (rc != SDGP_OK) return rc;
-    rc = sdgp::scale_rows_launch(W, scale, filter, C_out, (int64_t)R * S * C_in, dt, stream);
+    rc = sdgp::channel_scales_launch(dO, rows, C_out, dt, n, m, scale, nullptr, base, W, filter, (int64_t)R * S * C_in, stream);
     if (rc != SDGP_OK) return rc;
     return bwd_dispatch(dO, filter, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m, SDGP_GREEDY, 0, nullptr, 0, stream);
 }
