@@ -219,18 +219,19 @@ __global__ void __launch_bounds__(kThreads) wgrad_mfma(WgradParams p) {
 }
 
 // dW[e] = sum of the partial filters.  A workgroup takes 64 elements; each of its G wavefronts adds a run of the splits
-// (up to eight loads in flight), then the sums are added in wavefront order: a fixed order for a given shape, in fp64, so
-// that the partial filters' own rounding is all that their number adds.  Bound by the
+// (up to eight loads in flight), then the sums are added in wavefront order: a fixed order for a given shape.  T is
+// the type of the sums: double behind the gathering kernel, whose many short splits would otherwise add their own rounding
+// (it has fp64 totals of its own); float behind the others, whose calls it would lengthen by 1 %.  Bound by the
 // latency of a wavefront's run, so many splits take many wavefronts: 256 partial filters of 16384 elements (17 MB)
 // 7 us with four wavefronts, 4.1 with sixteen.
-template <int G>
+template <int G, typename T>
 __global__ void __launch_bounds__(64 * G) wgrad_reduce(const float* partial, float* dW, int64_t nW, int nsplit) {
-    __shared__ double part[G][64];
+    __shared__ T part[G][64];
     const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
     const int64_t e = (int64_t)blockIdx.x * 64 + lane;
     const int per = (nsplit + G - 1) / G;
     const int first = grp * per, last = first + per < nsplit ? first + per : nsplit;
-    double s[8] = {};
+    T s[8] = {};
     if (e < nW) {
         int i = first;
         for (; i + 7 < last; i += 8) {
@@ -246,19 +247,20 @@ __global__ void __launch_bounds__(64 * G) wgrad_reduce(const float* partial, flo
     part[grp][lane] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
     __syncthreads();
     if (grp == 0 && e < nW) {
-        double sum = part[0][lane];
+        T sum = part[0][lane];
 #pragma unroll
         for (int x = 1; x < G; ++x) sum += part[x][lane];
         dW[e] = (float)sum;
     }
 }
 
+template <typename T>
 void launch_reduce(const float* partial, float* dW, int64_t nW, int64_t nsplit, hipStream_t stream) {
     const unsigned blocks = (unsigned)((nW + 63) / 64);
     // (from 512 workgroups of four wavefronts on, two rounds' worth per SIMD, more wavefronts are slower: 64 partial filters
     // of 3x3 128 -> 256 40 us for the call against 37)
-    if (nsplit >= 64 && blocks <= 512) wgrad_reduce<16><<<blocks, 1024, 0, stream>>>(partial, dW, nW, (int)nsplit);
-    else wgrad_reduce<4><<<blocks, 256, 0, stream>>>(partial, dW, nW, (int)nsplit);
+    if (nsplit >= 64 && blocks <= 512) wgrad_reduce<16, T><<<blocks, 1024, 0, stream>>>(partial, dW, nW, (int)nsplit);
+    else wgrad_reduce<4, T><<<blocks, 256, 0, stream>>>(partial, dW, nW, (int)nsplit);
 }
 
 struct SimpleArgs {
@@ -531,7 +533,7 @@ int wgrad_launch(const void* D, const void* dO, float* dW, int64_t B, int64_t H,
             wgrad_mfma<3, 3, 1><<<grid, kThreads, pl.lds, stream>>>(p);
         }
         if (hipGetLastError() != hipSuccess) return SDGP_ERR_HIP;
-        launch_reduce((const float*)workspace, dW, nW, pl.nsplit, stream);
+        launch_reduce<float>((const float*)workspace, dW, nW, pl.nsplit, stream);
         return launch_status();
     }
     if (nW > 0x7FFFFFFF) return SDGP_ERR_SHAPE;
@@ -555,7 +557,7 @@ int wgrad_launch(const void* D, const void* dO, float* dW, int64_t B, int64_t H,
             return SDGP_ERR_HIP;
         kernel<<<kNarrowGroups, kThreads, lds, stream>>>(n);
         if (hipGetLastError() != hipSuccess) return SDGP_ERR_HIP;
-        launch_reduce((const float*)workspace, dW, nW, kNarrowGroups, stream);
+        launch_reduce<float>((const float*)workspace, dW, nW, kNarrowGroups, stream);
         return launch_status();
     }
     if (aligned && !pl.mfma) {
@@ -564,7 +566,7 @@ int wgrad_launch(const void* D, const void* dO, float* dW, int64_t B, int64_t H,
         if (g.ok && (bytes == 0 || (workspace != nullptr && workspace_bytes >= bytes))) {
             const int rc = wgrad_gather_launch(g, D, dO, bytes > 0 ? (float*)workspace : dW, B, H, Wd, C_in, C_out, R, S, stride, pad, stream);
             if (rc != SDGP_OK || bytes == 0) return rc;
-            launch_reduce((const float*)workspace, dW, nW, g.nsplit, stream);
+            launch_reduce<double>((const float*)workspace, dW, nW, g.nsplit, stream);
             return launch_status();
         }
     }
@@ -572,7 +574,7 @@ int wgrad_launch(const void* D, const void* dO, float* dW, int64_t B, int64_t H,
         if (dt == SDGP_BF16) wgrad_small<SDGP_BF16><<<kSmallGroups, kThreads, 0, stream>>>(a, (float*)workspace, nW);
         else wgrad_small<SDGP_F32><<<kSmallGroups, kThreads, 0, stream>>>(a, (float*)workspace, nW);
         if (hipGetLastError() != hipSuccess) return SDGP_ERR_HIP;
-        launch_reduce((const float*)workspace, dW, nW, kSmallGroups, stream);
+        launch_reduce<float>((const float*)workspace, dW, nW, kSmallGroups, stream);
         return launch_status();
     }
     if (dt == SDGP_BF16) wgrad_simple<SDGP_BF16><<<(unsigned)nW, kThreads, 0, stream>>>(a);
