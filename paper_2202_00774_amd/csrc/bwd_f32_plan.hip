@@ -23,7 +23,7 @@ int bwd_f32_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H
     if (!is_aligned16(dO) || !is_aligned16(W) || !is_aligned16(dD)) return 1;
     const int64_t rows = B * ((H + stride - 1) / stride) * ((Wd + stride - 1) / stride);   // of the largest parity class
     const int64_t tiles = (rows + 31) / 32;
-    if (B == 0 || tiles > (1 << 30)) return 1;
+    if (B == 0 || tiles > (1 << 25)) return 1;   // (a launch holds fewer than 2^32 threads)
     // One wavefront per SIMD (1024 of them) is the least that fills the matrix units.  Tiles of 128 columns read a
     // gradient row half as often as tiles of 64; with too few of either the eight wavefronts of a workgroup share a tile
     // and split the reduction.  Measured (us, 128 columns / 64 columns / shared): 3x3 128 -> 128 at 16x16, batch 128

@@ -394,7 +394,7 @@ int bwd_grouped_launch(const void* dO, const void* W, void* dD, int64_t B, int64
     const int64_t gh = (H + stride - 1) / stride, gw = (Wd + stride - 1) / stride;
     GroupedLaunch l{};
     const int64_t positions = B * (gh + 1) * (gw + 1), slabs = (groups + kFlatSlab - 1) / kFlatSlab;
-    l.is_flat = gw <= kFlatMaxW && is_aligned16(W) && positions < ((int64_t)1 << 30) && (positions + kFlatPos - 1) / kFlatPos * slabs < ((int64_t)1 << 30);
+    l.is_flat = gw <= kFlatMaxW && is_aligned16(W) && positions < ((int64_t)1 << 30) && (positions + kFlatPos - 1) / kFlatPos * slabs < ((int64_t)1 << 23);   // (a launch holds fewer than 2^32 threads)
     if (l.is_flat) {
         FlatParams& p = l.flat;
         p.dO = static_cast<const uint16_t*>(dO), p.W = static_cast<const uint16_t*>(W), p.dD = static_cast<uint16_t*>(dD);

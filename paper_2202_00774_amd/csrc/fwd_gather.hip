@@ -236,7 +236,7 @@ int fwd_gather_launch(const void* D, const void* W, void* O, int64_t B, int64_t 
     const int64_t row_tiles = (p.rows + kRows - 1) / kRows;
     const int bn = C_out > 64 && row_tiles * ((C_out + 127) / 128) >= 256 ? 128 : 64;
     p.col_tiles = (int)((C_out + bn - 1) / bn);
-    if (row_tiles > (1 << 28) / p.col_tiles) return 1;
+    if (row_tiles > (1 << 23) / p.col_tiles) return 1;   // (a launch holds fewer than 2^32 threads)
     const int64_t blocks = row_tiles * p.col_tiles;
     p.nblocks = (int)blocks, p.per_xcd = (int)((blocks + 7) / 8);
     if (blocks <= 512) return bn == 128 ? launch<128, 4>(p, stream) : launch<64, 4>(p, stream);
