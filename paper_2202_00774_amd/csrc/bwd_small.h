@@ -13,7 +13,9 @@
 //   * The wavefronts add their sums through LDS in a fixed order; a result row leaves as 8 bytes per lane, 256 a row.
 // Each XCD takes a run of the tiles in column order, so that its L2 serves one part of W.
 // Strided filters: blockIdx.y is the parity class of the input pixels, whose taps are a sub-grid of the filter.
-// Channels past C_out are zeros on both sides; taps outside the gradient and rows past the end are zero rows.
+// Channels past C_out are zeros on both sides; taps outside the gradient and rows past the end are zero rows.  Zero times a
+// non-finite weight is NaN where the definition has no term at all, so a NaN result of a row with taps outside the gradient
+// is summed again without them.
 #pragma once
 
 #include <type_traits>
@@ -53,6 +55,106 @@ __device__ __forceinline__ SmallAxis small_axis(int size, int filter, int stride
     x.shift = (a + pad - x.r0) / stride;
     x.n = size > a ? (size - a + stride - 1) / stride : 0;
     return x;
+}
+
+// The survivors of the M channels at g (flat element e0): bit j for channel j, by counting the keys ahead of it.
+template <int M, int RK>
+__device__ __forceinline__ uint32_t keep_by_count(const uint16_t* g, int n, uint32_t mix, uint64_t e0) {
+    const uint32_t row = hash_row(mix, (uint32_t)(e0 >> 32));
+    auto key = [&](int j) { return RK == kRandom ? hash_elem(row, (uint32_t)e0 + (uint32_t)j) : (uint32_t)g[j] & 0x7FFFu; };
+    uint32_t mask = 0;
+#pragma nounroll
+    for (int j = 0; j < M; ++j) {
+        const uint32_t kj = key(j);
+        int ahead = 0;
+#pragma nounroll
+        for (int i = 0; i < M; ++i) {
+            const uint32_t ki = key(i);
+            ahead += ki > kj || (ki == kj && i < j);
+        }
+        mask |= (uint32_t)(ahead < n) << j;
+    }
+    return mask;
+}
+
+// The four results of row `row` at channel c0, some of them NaN: those that a weight of a tap outside the gradient can have
+// made NaN are summed again over the taps inside.  Rare, so it is short rather than
+// fast and reads the kernel's arguments again, so that none of it holds a register during the main loop: with
+// the kernel's own ranker and registers every call was 4 % slower (calls of 5 to 70 us; 10 % at 4:32).
+template <int M, int RK>
+__device__ __forceinline__ void sum_inside(int row, int c0, float (&v)[4]) {
+    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+    uint64_t args = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const auto& p = *reinterpret_cast<const __attribute__((address_space(4))) SmallParams*>(args);
+    const SmallAxis ay = small_axis(p.H, p.R, p.stride, p.pad, (int)blockIdx.y / p.stride);
+    const SmallAxis ax = small_axis(p.Wd, p.S, p.stride, p.pad, (int)blockIdx.y % p.stride);
+    const int b = row / (ay.n * ax.n), rem = row - b * (ay.n * ax.n);
+    const int gi = rem / ax.n + ay.shift, gj = rem % ax.n + ax.shift;
+    const int64_t kstep = (int64_t)p.R * p.S * p.C_in;
+    auto weights = [&](int u, int t) { return p.W + ((ay.r0 + u * p.stride) * p.S + ax.r0 + t * p.stride) * p.C_in + c0; };
+    auto inside = [&](int u, int t) { return (unsigned)(gi - u) < (unsigned)p.P && (unsigned)(gj - t) < (unsigned)p.Q; };
+    uint32_t brought = 0;   // columns with a non-finite weight in a tap outside
+#pragma nounroll
+    for (int u = 0; u < ay.count; ++u)
+#pragma nounroll
+        for (int t = 0; t < ax.count; ++t) {
+            if (inside(u, t)) continue;
+            const uint16_t* w = weights(u, t);
+#pragma unroll 4
+            for (int k = 0; k < p.C_out; ++k, w += kstep) {
+                const u32x2_t x = *reinterpret_cast<const u32x2_t*>(w);
+#pragma unroll
+                for (int z = 0; z < 2; ++z)
+                    brought |= ((x[z] & 0x7F80u) == 0x7F80u ? 1u << (2 * z) : 0u) | ((x[z] & 0x7F800000u) == 0x7F800000u ? 2u << (2 * z) : 0u);
+            }
+        }
+    float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    auto settled = [&]() {   // nothing left to find out: not a column of these, or a NaN of its own
+        bool all = true;
+#pragma unroll
+        for (int z = 0; z < 4; ++z) all = all && (v[z] == v[z] || !((brought >> z) & 1u) || sum[z] != sum[z]);
+        return all;
+    };
+#pragma nounroll
+    for (int u = 0; u < ay.count; ++u)
+#pragma nounroll
+        for (int t = 0; t < ax.count; ++t) {
+            if (!inside(u, t)) continue;
+            const int64_t row0 = (int64_t)((b * p.P + gi - u) * p.Q + gj - t) * p.C_out;
+            const uint16_t* w = weights(u, t);
+#pragma nounroll
+            for (int k = 0; k < p.C_out && !settled(); k += M) {
+                const uint16_t* const g = p.dO + row0 + k;
+                const uint32_t mask = RK == kSmallDense ? ~0u : keep_by_count<M, RK>(g, p.n, p.mix, (uint64_t)(row0 + k));
+                float scale = 1.0f;
+                if constexpr (RK == kAdjusted) {
+                    float total = 0.0f, kept = 0.0f;
+#pragma nounroll
+                    for (int j = 0; j < M; ++j) {
+                        const float a = bf16_to_float((uint32_t)g[j] & 0x7FFFu);
+                        total = __fadd_rn(total, a);
+                        if ((mask >> j) & 1u) kept = __fadd_rn(kept, a);
+                    }
+                    if (kept != 0.0f) scale = __fdiv_rn(total, kept);
+                }
+#pragma nounroll
+                for (int j = 0; j < M; ++j, w += kstep) {
+                    float x = (mask >> j) & 1u ? bf16_to_float(g[j]) : 0.0f;
+                    if constexpr (RK == kAdjusted) {
+                        if ((mask >> j) & 1u) x = bf16_to_float(float_to_bf16(__fmul_rn(x, scale)));
+                    }
+                    const u32x2_t y = *reinterpret_cast<const u32x2_t*>(w);
+                    sum[0] = fmaf(x, bf16_to_float(y[0] & 0xFFFFu), sum[0]);
+                    sum[1] = fmaf(x, bf16_to_float(y[0] >> 16), sum[1]);
+                    sum[2] = fmaf(x, bf16_to_float(y[1] & 0xFFFFu), sum[2]);
+                    sum[3] = fmaf(x, bf16_to_float(y[1] >> 16), sum[3]);
+                }
+            }
+        }
+#pragma unroll
+    for (int z = 0; z < 4; ++z)
+        if (v[z] != v[z] && ((brought >> z) & 1u)) v[z] = sum[z];
 }
 
 template <int M, int RK, bool NLE2>
@@ -217,6 +319,7 @@ __global__ void __launch_bounds__(64 * kSmallWaves) bwd_small(const SmallParams 
         const int e = wave * 2 + x;
         const int rr = 8 * (e >> 2) + 4 * half + (e & 3);                   // the row of this result register
         const int pix = __shfl(opix, rr);
+        const bool stored = tile * kSmallRows + rr < rows && c0 < p.C_in;
         float v[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -224,8 +327,11 @@ __global__ void __launch_bounds__(64 * kSmallWaves) bwd_small(const SmallParams 
 #pragma unroll
             for (int k = 0; k < kSmallWaves; ++k) v[u] += part[((k * 4 + u) * 16 + e) * 64 + lane];
         }
+        if (__builtin_expect(stored && (v[0] != v[0] || v[1] != v[1] || v[2] != v[2] || v[3] != v[3]), 0)) {
+            sum_inside<M, RK>(tile * kSmallRows + rr, c0, v);
+        }
         const u32x2_t out = {float2_to_bf16x2(v[0], v[1]), float2_to_bf16x2(v[2], v[3])};
-        if (tile * kSmallRows + rr < rows && c0 < p.C_in) *reinterpret_cast<u32x2_t*>(p.dD + (int64_t)pix * p.C_in + c0) = out;
+        if (stored) *reinterpret_cast<u32x2_t*>(p.dD + (int64_t)pix * p.C_in + c0) = out;
     }
 }
 

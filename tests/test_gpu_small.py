@@ -65,3 +65,39 @@ def test_filters(H, Wd, R, S, stride, pad):
 ])
 def test_neighbours(shape, n, m):
     check(shape, n, m, oracle.RANDOM)
+
+
+@pytest.mark.parametrize("shape,n,m,ranker", [
+    ((1, 9, 9, 8, 24, 3, 3, 3, 1), 4, 4, oracle.GREEDY),        # stride 3: no tap reaches row and column 8
+    ((2, 9, 10, 136, 24, 3, 3, 3, 1), 2, 8, oracle.GREEDY_ADJUSTED),
+    ((2, 13, 9, 24, 40, 7, 7, 4, 3), 2, 4, oracle.GREEDY),
+    ((2, 8, 8, 16, 32, 3, 3, 2, 1), 3, 4, oracle.RANDOM),
+    ((2, 7, 7, 24, 64, 3, 3, 1, 1), 4, 32, oracle.RANDOM),
+    ((1, 9, 9, 8, 16, 9, 9, 1, 4), 2, 16, oracle.GREEDY),       # 81 taps
+])
+def test_non_finite_weights_outside_the_gradient(shape, n, m, ranker):
+    """A tap outside the gradient has no term: a weight there that is infinite or NaN must not reach the pixel.  Every
+    gradient value is positive, so the oracle's NaN and infinities are those of the taps inside."""
+    L = wl.ConvLayer("i", *shape)
+    dO = wl.f32_to_bf16_bits(np.random.default_rng(3).uniform(1, 2, L.dO_shape).astype(np.float32))
+    W = wl.normal(L.W_shape, 0.1, 4, wl.BF16)
+    W[:, 0, 0, 1::2] = 0x7F80               # +inf: meets dropped values (zeros) too, which is a NaN by definition
+    W[:, 0, 0, 4::8] = 0x7FC0               # NaN
+    W[L.C_out // 2, L.R - 1, L.S // 2, 0] = 0xFF80
+    ref, ab = oracle.conv_bwd_data(oracle.prune(dO, n, m, ranker, seed=9)[0], W, L.H, L.Wd, L.stride, L.pad)
+    got = wl.to_f64(to_host(sdgp.sdgp_conv_bwd_data(to_gpu(dO), to_gpu(W), L.H, L.Wd, L.stride, L.pad, n, m, ranker, 9)))
+    fin = np.isfinite(ref)
+    assert fin.any() and not fin.all()
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[~fin & ~np.isnan(ref)], ref[~fin & ~np.isnan(ref)])
+    assert np.all(np.abs(got[fin] - ref[fin]) <= 5e-3 * ab[fin])
+
+
+def test_infinite_weight_outside_the_image_forward():
+    """The forward pass of a 9x9 layer (81 taps) goes through the same kernel with the channels exchanged."""
+    D = torch.ones(1, 12, 12, 32, dtype=torch.bfloat16, device="cuda")
+    W = torch.ones(16, 9, 9, 32, dtype=torch.bfloat16, device="cuda")
+    W[5, 0, 0] = float("inf")               # pad 4: outside for the first four output rows and columns
+    out = sdgp.sdgp_conv_fwd(D, W, 1, 4).float().cpu()
+    inside = torch.isposinf(out[..., 5])
+    assert inside[:, 4:, 4:].all() and torch.isfinite(out[:, :4]).all() and torch.isfinite(out[:, :, :4]).all()
+    assert out[0, 0, 0, 5] == 32 * 25
