@@ -176,6 +176,21 @@ bool pad_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int
 size_t bwd_pw_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n,
                         int m);
 
+// How bwd_pw_launch runs a problem with aligned pointers: -1 not at all, 0 as it is, 1 with the gradient ranked ahead, 2 on
+// padded copies.
+int bwd_pw_way(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n, int m, int rk,
+               const void* workspace, size_t workspace_bytes) {
+    const size_t room = workspace != nullptr && is_aligned16(workspace) ? workspace_bytes : 0;
+    PadPlan padded{};
+    if (pad_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, padded)) return room >= padded.bytes ? 2 : -1;
+    PwPlan plan{};
+    if (pw_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, plan) != 0) return -1;
+    if (!plan.pre) return 0;
+    if (room >= plan.bytes) return 1;
+    const PwShape& shape = kPwShapes[pw_shape(plan.mode, C_in, C_out)];
+    return ((plan.p.rows + shape.rows - 1) / shape.rows) * ((C_in + shape.bn - 1) / shape.bn) < 64 ? -1 : 0;
+}
+
 // SDGP_OK after launching, a positive value when the problem does not fit, or a negative sdgp_status.  With a
 // workspace of at least bwd_pw_workspace(...) bytes the gradient is ranked once, in a pass of its own, where that
 // pays; with less the fused kernel runs.
