@@ -40,7 +40,7 @@ int bwd_conv3_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t
 int bwd_tiled_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in,
                      int64_t C_out, int R, int S, int stride, int pad, int n, int m, int rk, uint64_t seed,
                      hipStream_t stream);
-int bwd_small_launch(bool first, const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
+int bwd_small_launch(int turn, const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
                      int R, int S, int stride, int pad, int n, int m, int rk, uint64_t seed, const void* workspace, size_t workspace_bytes,
                      hipStream_t stream);
 int bwd_f32_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
@@ -151,7 +151,7 @@ int bwd_dispatch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, 
         if (rc <= 0) return rc;
     }
     if (dt == SDGP_BF16 && sdgp::is_aligned16(dD)) {
-        int rc = sdgp::bwd_small_launch(true, dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, workspace, workspace_bytes, stream);
+        int rc = sdgp::bwd_small_launch(0, dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, workspace, workspace_bytes, stream);
         if (rc <= 0) return rc;
         rc = sdgp::bwd_pw_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, workspace, workspace_bytes, stream);
         if (rc <= 0) return rc;
@@ -159,11 +159,13 @@ int bwd_dispatch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, 
         if (rc <= 0) return rc;
         rc = sdgp::bwd_gather_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, workspace, workspace_bytes, stream);
         if (rc <= 0) return rc;
-        rc = sdgp::bwd_small_launch(false, dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, workspace, workspace_bytes, stream);
+        rc = sdgp::bwd_small_launch(1, dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, workspace, workspace_bytes, stream);
         if (rc <= 0) return rc;
         rc = sdgp::bwd_conv3_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, stream);
         if (rc <= 0) return rc;
         rc = sdgp::bwd_tiled_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, stream);
+        if (rc <= 0) return rc;
+        rc = sdgp::bwd_small_launch(2, dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, workspace, workspace_bytes, stream);
         if (rc <= 0) return rc;
     }
     if (dt == SDGP_F32) {

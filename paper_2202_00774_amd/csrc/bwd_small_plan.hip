@@ -77,9 +77,10 @@ int64_t most_strided(bool first, int64_t C_in, int64_t C_out, int taps, int n, i
 
 }  // namespace
 
-// A positive value: the problem does not fit, or is one for the other kernels.  The dispatch asks twice: first of all, and
-// when the kernels for larger problems have declined.
-int bwd_small_launch(bool first, const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
+// A positive value: the problem does not fit, or is one for the other kernels.  The dispatch asks three times: first of all
+// (turn 0), when the kernels for larger problems have declined (1), and when nobody but the plain kernel is left (2: strides of
+// three and four, filters of more than 49 taps), which is slower by more than rounds can make up for.
+int bwd_small_launch(int turn, const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
                      int R, int S, int stride, int pad, int n, int m, int rk, uint64_t seed, const void* workspace, size_t workspace_bytes,
                      hipStream_t stream) {
     const bool dense = n == m;
@@ -93,9 +94,9 @@ int bwd_small_launch(bool first, const void* dO, const void* W, void* dD, int64_
     // pixel indices and offsets within the filter in 32 bits, channels of the step past the last one included
     if (B * (P + 16) * (Q + 16) > (1 << 30) || B * H * Wd > (1 << 30) || (int64_t)R * S * C_in > (1 << 28)) return 1;
     const int64_t tiles = row_tiles * col_tiles * stride * stride;
-    if (tiles > 4 * kRound) return 1;
-    const bool pointwise = R == 1 && S == 1 && stride == 1;
-    const int64_t most = pointwise ? most_pointwise(bwd_pw_way(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, workspace, workspace_bytes),
+    const bool first = turn == 0, pointwise = R == 1 && S == 1 && stride == 1;
+    const int64_t most = turn == 2   ? 4 * kRound
+                         : pointwise ? most_pointwise(bwd_pw_way(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, workspace, workspace_bytes),
                                                     C_out % 32 == 0, C_in, C_out, n, m, rk)
                          : stride == 1 ? most_filter(first, C_in, C_out, R * S, n, m)
                                        : most_strided(first, C_in, C_out, R * S, n, m);

@@ -101,3 +101,21 @@ def test_infinite_weight_outside_the_image_forward():
     inside = torch.isposinf(out[..., 5])
     assert inside[:, 4:, 4:].all() and torch.isfinite(out[:, :4]).all() and torch.isfinite(out[:, :, :4]).all()
     assert out[0, 0, 0, 5] == 32 * 25
+
+
+@pytest.mark.parametrize("shape", [
+    (220, 9, 9, 64, 256, 3, 3, 3, 1),       # stride 3, 558 tiles (a parity class of 62 is too small for the pointwise kernel)
+    (36, 16, 16, 8, 128, 9, 9, 1, 4),       # 81 taps, 288 tiles
+])
+def test_left_by_the_tile_kernels(shape):
+    """Strides beyond two and filters beyond 49 taps, which only the plain kernel takes otherwise."""
+    check(shape, 2, 4, oracle.GREEDY)
+    L = wl.ConvLayer("s", *shape)
+    dO, W = to_gpu(wl.laplace_with_zeros(L.dO_shape, 1e-3, 0.3, 5, wl.BF16)), to_gpu(wl.normal(L.W_shape, 0.1, 6, wl.BF16))
+    begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    begin.record()
+    for _ in range(5):
+        sdgp.sdgp_conv_bwd_data(dO, W, L.H, L.Wd, L.stride, L.pad, 2, 4, sdgp.GREEDY)
+    end.record()
+    end.synchronize()
+    assert begin.elapsed_time(end) / 5 < 0.6   # ms; 0.02 and 0.12 here, 1.3 and 6 on the plain kernel
