@@ -14,8 +14,8 @@
 //     XCDs in runs, so that each one's L2 serves its own part of the image.
 // 3x3 stride 2 128 -> 128 at 56x56, batch 128: 54 us = 545 TFLOP/s and 2.4 TB/s, bound by the latency of the copies between
 // two barriers; one thread per output element took 50.1 ms.
-// Pixels outside the image are zeros.  Zero times a non-finite weight is NaN where the definition has no term, so a
-// result that is NaN is summed again without those taps.
+// Pixels outside the image are zeros.  Zero times a non-finite weight is NaN where the definition has no term, so a NaN
+// of a pixel whose window leaves the image is summed again without those taps.
 #include "lds_copy.h"
 
 namespace sdgp {
@@ -168,40 +168,66 @@ __global__ void __launch_bounds__(256) fwd_gather(const FwdParams p) {
                 *(SDGP_LDS uint16_t*)(smem + (m + 1) * L::kOutPitch + n * 2) = (uint16_t)(pk >> 16);
             }
     __syncthreads();
+    uint32_t nans = 0;   // which of this lane's vectors hold a NaN
 #pragma unroll 4
-    for (int x = tid; x < kRows * (BN / 8); x += 256) {
-        const int m = x / (BN / 8), cc = x % (BN / 8);
+    for (int i = 0; i < kRows * (BN / 8) / 256; ++i) {
+        const int x = tid + 256 * i, m = x / (BN / 8), cc = x % (BN / 8);
         const int64_t row = m0 + m;
         if (row >= p.rows || n0 + cc * 8 >= p.C_out) continue;
-        u32x4_t v = *(SDGP_LDS u32x4_t*)(smem + m * L::kOutPitch + cc * 16);
+        const u32x4_t v = *(SDGP_LDS u32x4_t*)(smem + m * L::kOutPitch + cc * 16);
         if (p.pad > 0) {
             bool nan = false;
 #pragma unroll
             for (int y = 0; y < 4; ++y) nan = nan || (v[y] & 0x7FFFu) > 0x7F80u || (v[y] & 0x7FFF0000u) > 0x7F800000u;
-            if (nan) {
-                const int64_t line = row / p.Q, b = line / p.P;
-                const int h0 = (int)(line - b * p.P) * p.stride - p.pad, w0 = (int)(row - line * p.Q) * p.stride - p.pad;
-                for (int y = 0; y < 8; ++y) {
-                    const uint16_t* w = p.W + (int64_t)(n0 + cc * 8 + y) * p.R * p.S * p.C_in;
-                    float sum = 0.0f;
-                    for (int tr = 0; tr < p.R; ++tr)
-                        for (int ts = 0; ts < p.S; ++ts, w += p.C_in) {
-                            const int h = h0 + tr, ww = w0 + ts;
-                            if (h < 0 || h >= p.H || ww < 0 || ww >= p.Wd) continue;
-                            const uint16_t* d = p.D + ((b * p.H + h) * p.Wd + ww) * p.C_in;
-                            for (int ch = 0; ch < p.C_in; ++ch) sum = fmaf(bf16_to_float(d[ch]), bf16_to_float(w[ch]), sum);
-                        }
-                    const uint32_t bits = float_to_bf16(sum);
-                    const uint32_t old = y < 2 ? v[0] : y < 4 ? v[1] : y < 6 ? v[2] : v[3];
-                    const uint32_t fresh = (y & 1) ? (old & 0xFFFFu) | (bits << 16) : (old & 0xFFFF0000u) | bits;
-                    if (y < 2) v[0] = fresh;
-                    else if (y < 4) v[1] = fresh;
-                    else if (y < 6) v[2] = fresh;
-                    else v[3] = fresh;
-                }
-            }
+            nans |= (uint32_t)nan << i;
         }
         __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(p.O + row * p.C_out + n0 + cc * 8));
+    }
+    if (__builtin_expect(nans != 0, 0)) {
+        uint64_t args = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();   // (read again: nothing below is kept in registers above)
+        asm volatile("" : "+s"(args));
+        const auto& q = *reinterpret_cast<const __attribute__((address_space(4))) FwdParams*>(args);
+#pragma nounroll
+        for (; nans != 0; nans &= nans - 1) {
+            const int x = tid + 256 * (__ffs((int)nans) - 1), m = x / (BN / 8), cc = x % (BN / 8);
+            const int row = (int)m0 + m, line = row / q.Q, b = line / q.P;             // (at most 2^30 rows)
+            const int h0 = (line - b * q.P) * q.stride - q.pad, w0 = (row - line * q.Q) * q.stride - q.pad;
+            if (h0 >= 0 && w0 >= 0 && h0 + q.R <= q.H && w0 + q.S <= q.Wd) continue;   // no tap outside
+            u32x4_t v = *(SDGP_LDS u32x4_t*)(smem + m * L::kOutPitch + cc * 16);
+            const int64_t wstep = (int64_t)q.R * q.S * q.C_in;
+            const uint16_t* wk = q.W + (int64_t)(n0 + cc * 8) * wstep;
+#pragma nounroll
+            for (int y = 0; y < 4; ++y, wk += 2 * wstep) {   // two channels at a time
+                uint32_t pair = v[0];
+                bool lo = (pair & 0x7FFFu) > 0x7F80u, hi = (pair & 0x7FFF0000u) > 0x7F800000u;
+                float s0 = 0.0f, s1 = 0.0f;
+                const uint16_t* w = wk;
+#pragma nounroll
+                for (int t = 0; t < q.R * q.S && (lo || hi); ++t, w += q.C_in) {   // (a NaN of the taps inside stays one)
+                    const int h = h0 + t / q.S, ww = w0 + t % q.S;
+                    if ((unsigned)h >= (unsigned)q.H || (unsigned)ww >= (unsigned)q.Wd) continue;
+                    const uint16_t* d = q.D + (((int64_t)b * q.H + h) * q.Wd + ww) * q.C_in;
+#pragma nounroll
+                    for (int ch = 0; ch < q.C_in && (lo || hi); ch += 4) {
+                        typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+                        const u32x2_t dv = *reinterpret_cast<const u32x2_t*>(d + ch), wa = *reinterpret_cast<const u32x2_t*>(w + ch),
+                                      wb = *reinterpret_cast<const u32x2_t*>(w + wstep + ch);
+#pragma unroll
+                        for (int z = 0; z < 2; ++z) {
+                            s0 = fmaf(bf16_to_float(dv[z] & 0xFFFFu), bf16_to_float(wa[z] & 0xFFFFu), s0);
+                            s0 = fmaf(bf16_to_float(dv[z] >> 16), bf16_to_float(wa[z] >> 16), s0);
+                            s1 = fmaf(bf16_to_float(dv[z] & 0xFFFFu), bf16_to_float(wb[z] & 0xFFFFu), s1);
+                            s1 = fmaf(bf16_to_float(dv[z] >> 16), bf16_to_float(wb[z] >> 16), s1);
+                        }
+                        lo = lo && s0 == s0, hi = hi && s1 == s1;
+                    }
+                }
+                if (lo) pair = (pair & 0xFFFF0000u) | float_to_bf16(s0);
+                if (hi) pair = (pair & 0xFFFFu) | (float_to_bf16(s1) << 16);
+                v = u32x4_t{v[1], v[2], v[3], pair};   // (all four pairs pass the first place)
+            }
+            *reinterpret_cast<u32x4_t*>(q.O + (int64_t)row * q.C_out + n0 + cc * 8) = v;
+        }
     }
 }
 

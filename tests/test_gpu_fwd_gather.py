@@ -47,3 +47,27 @@ def test_infinite_weight_outside_the_image():
     inside = torch.isposinf(out[..., 3])
     assert inside[:, 1:, 1:].all() and not inside[:, 0].any() and not inside[:, :, 0].any()
     assert out[0, 0, 1, 3] == 48 and out[0, 0, 0, 3] == 32 and torch.isfinite(out[..., :3]).all()
+
+
+@pytest.mark.parametrize("B,hw,C_in,C_out,stride", [(64, 56, 128, 128, 2), (64, 16, 128, 128, 1)])
+def test_nan_activations_cost_no_more(B, hw, C_in, C_out, stride):
+    """A diverged step's activations: no weight is non-finite, so nothing has to be summed again."""
+    W = torch.full((C_out, 3, 3, C_in), 0.01, dtype=torch.bfloat16, device="cuda")
+
+    def run(value):
+        D = torch.full((B, hw, hw, C_in), value, dtype=torch.bfloat16, device="cuda")
+        best = 1e9
+        for _ in range(3):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for _ in range(5):
+                out = sdgp.sdgp_conv_fwd(D, W, stride, 1)
+            end.record()
+            end.synchronize()
+            best = min(best, begin.elapsed_time(end))
+        return best, out
+
+    finite, _ = run(1.0)
+    nan, out = run(float("nan"))
+    assert out.isnan().all()
+    assert nan < 3 * finite, (nan, finite)
