@@ -20,7 +20,7 @@
 // us back to back.
 // Strided filters: blockIdx.z is the parity class of the input pixels, whose taps are a sub-grid of the filter.
 // Taps outside the gradient and rows past the end multiply zeros.  Zero times a non-finite weight is NaN where the
-// definition has no term at all, so a result that is NaN is summed again element by element with those taps left out.
+// definition has no term at all, so a NaN result of a row that has such taps is summed again with those taps left out.
 #pragma once
 
 #include <type_traits>
@@ -77,8 +77,53 @@ __device__ __forceinline__ void prune_f32(uint32_t (&raw)[M], int n, uint32_t mi
     }
 }
 
+// The CN stored results of row `row` at channel c0, some of them NaN: where taps of the row lie outside the gradient, the NaNs
+// are summed again over the taps inside.  It reads the kernel's arguments again, so that nothing of it is kept in registers
+// during the main loop.
+template <int M, int RK, bool NLE2, int CN>
+__device__ __forceinline__ void sum_inside_f32(int64_t row, int64_t c0) {
+    typedef float vcn_t __attribute__((ext_vector_type(CN)));
+    uint64_t args = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const auto& p = *reinterpret_cast<const __attribute__((address_space(4))) F32Params*>(args);
+    const int ca = (int)(blockIdx.z / p.stride), cb = (int)(blockIdx.z % p.stride);
+    const F32Axis ay = f32_axis(p.H, p.R, p.stride, p.pad, ca), ax = f32_axis(p.Wd, p.S, p.stride, p.pad, cb);
+    const int64_t b = row / (ay.n * ax.n), rem = row - b * (ay.n * ax.n), i = rem / ax.n, j = rem - i * ax.n;
+    const int64_t gi = i + ay.shift, gj = j + ax.shift;
+    if (gi < p.P && gi - ay.count >= -1 && gj < p.Q && gj - ax.count >= -1) return;   // every tap inside: a NaN of its own
+    float* const at = p.dD + ((b * p.H + i * p.stride + ca) * p.Wd + j * p.stride + cb) * p.C_in + c0;
+    const vcn_t v = *reinterpret_cast<const vcn_t*>(at);
+    vcn_t sum = vcn_t(0.0f);
+    const int64_t kstep = (int64_t)p.R * p.S * p.C_in;
+    bool open = true;   // some NaN result may still turn out not to be one: a NaN of the taps inside stays one
+#pragma nounroll
+    for (int t = 0; t < ay.count * ax.count && open; ++t) {
+        const int u = t / ax.count, s = t - u * ax.count;
+        const int64_t pp = gi - u, qq = gj - s;
+        if (pp < 0 || pp >= p.P || qq < 0 || qq >= p.Q) continue;
+        const uint64_t e0 = (uint64_t)(((b * p.P + pp) * p.Q + qq) * p.C_out);
+        const float* w = p.W + (((int64_t)(ay.r0 + u * p.stride) * p.S + ax.r0 + s * p.stride) * p.C_in + c0);
+#pragma nounroll
+        for (int64_t k = 0; k < p.C_out && open; k += M) {
+            uint32_t raw[M];
+#pragma unroll
+            for (int y = 0; y < M; ++y) raw[y] = float_to_bits(p.dO[e0 + k + y]);
+            prune_f32<M, RK, NLE2>(raw, p.n, p.mix, e0 + (uint64_t)k);
+#pragma unroll
+            for (int y = 0; y < M; ++y) sum += bits_to_float(raw[y]) * *reinterpret_cast<const vcn_t*>(w + (k + y) * kstep);
+            open = false;
+#pragma unroll
+            for (int x = 0; x < CN; ++x) open = open || (v[x] != v[x] && sum[x] == sum[x]);
+        }
+    }
+    vcn_t out;
+#pragma unroll
+    for (int x = 0; x < CN; ++x) out[x] = v[x] != v[x] ? sum[x] : v[x];
+    *reinterpret_cast<vcn_t*>(at) = out;
+}
+
 template <int M, int RK, bool NLE2, int CN, int WV, int WK>
-__global__ void __launch_bounds__(64 * WV) bwd_f32(const F32Params p) {
+__global__ void __launch_bounds__(64 * WV, CN == 2 ? 2 : 1) bwd_f32(const F32Params p) {
     static_assert(WK == 1 || WK == WV, "the wavefronts share rows or the reduction");
     static_assert(M % 4 == 0 && (CN == 2 || CN == 4), "16-byte gradient loads, 8- or 16-byte weight loads");
     constexpr int CH = M > 8 ? M : 8;   // channels per lane and step: one group, or two of four
@@ -130,13 +175,11 @@ __global__ void __launch_bounds__(64 * WV) bwd_f32(const F32Params p) {
     if constexpr (WK > 1) {
         if (first < last) pair = first % npairs, tv = (first / npairs) % ax.count, tu = first / npairs / ax.count;
     }
-    bool outside = false;     // some tap of this lane's row lies outside the gradient
     // the step the walk stands at, past the last one nothing but zeros; the walk moves on
     auto locate = [&]() {
         const int pp = gi - tu, qq = gj - tv;
         const bool in = (unsigned)pp < (unsigned)P && (unsigned)qq < (unsigned)Q;
         const bool within = step < last;
-        outside |= !in && within;
         const int k0 = (pair * 2 + half) * CH;
         const int goff = (pp * Q + qq) * C_out + k0;
         const int woff = k0 * kstep + ((ay.r0 + tu * p.stride) * p.S + ax.r0 + tv * p.stride) * (int)p.C_in + (int)cw;
@@ -236,7 +279,7 @@ __global__ void __launch_bounds__(64 * WV) bwd_f32(const F32Params p) {
             }
     }
 
-    const bool redo_taps = ntaps > 0 && __any(outside) != 0;
+    uint32_t nans = 0;   // which of this lane's results hold a NaN
 #pragma unroll
     for (int x = 0; x < 16 / WK; ++x) {
         const int e = WK == 1 ? x : wave * (16 / WK) + x;
@@ -244,33 +287,17 @@ __global__ void __launch_bounds__(64 * WV) bwd_f32(const F32Params p) {
         const int64_t pix = __shfl(opix, rr);
         if (tile * 32 + rr >= rows || c0 >= p.C_in) continue;
         vcn_t v;
+        bool nan = false;
 #pragma unroll
-        for (int u = 0; u < CN; ++u) v[u] = acc[u][x];
-        if (WK > 1 || redo_taps) {
-            bool nan = false;
-#pragma unroll
-            for (int u = 0; u < CN; ++u) nan = nan || v[u] != v[u];
-            if (nan && (p.R > 1 || p.S > 1)) {
-                const int64_t r2 = tile * 32 + rr, b2 = r2 / (ay.n * ax.n), m2 = r2 % (ay.n * ax.n), i2 = m2 / ax.n, j2 = m2 % ax.n;
-                v = vcn_t(0.0f);
-                for (int u = 0; u < ay.count; ++u)
-                    for (int t = 0; t < ax.count; ++t) {
-                        const int64_t pp = i2 + ay.shift - u, qq = j2 + ax.shift - t;
-                        if (pp < 0 || pp >= p.P || qq < 0 || qq >= p.Q) continue;
-                        const uint64_t e0 = (uint64_t)(((b2 * p.P + pp) * p.Q + qq) * p.C_out);
-                        const float* w = p.W + (((int64_t)(ay.r0 + u * p.stride) * p.S + ax.r0 + t * p.stride) * p.C_in + c0);
-                        for (int64_t k = 0; k < p.C_out; k += M) {
-                            uint32_t raw[M];
-#pragma unroll
-                            for (int y = 0; y < M; ++y) raw[y] = float_to_bits(p.dO[e0 + k + y]);
-                            prune_f32<M, RK, NLE2>(raw, p.n, p.mix, e0 + (uint64_t)k);
-#pragma unroll
-                            for (int y = 0; y < M; ++y) v += bits_to_float(raw[y]) * *reinterpret_cast<const vcn_t*>(w + (k + y) * (int64_t)kstep);
-                        }
-                    }
-            }
-        }
+        for (int u = 0; u < CN; ++u) v[u] = acc[u][x], nan = nan || v[u] != v[u];
+        nans |= (uint32_t)nan << x;
         *reinterpret_cast<vcn_t*>(p.dD + pix * p.C_in + c0) = v;
+    }
+    if (__builtin_expect(nans != 0, 0)) {
+        for (; nans != 0; nans &= nans - 1) {
+            const int e = (WK == 1 ? 0 : wave * (16 / WK)) + __ffs((int)nans) - 1;
+            sum_inside_f32<M, RK, NLE2, CN>(tile * 32 + 8 * (e >> 2) + 4 * half + (e & 3), c0);
+        }
     }
 }
 

@@ -76,3 +76,50 @@ def test_infinite_weight_outside_the_image(B):
     out = to_host(sdgp.sdgp_conv_bwd_data(to_gpu(dO), to_gpu(W), H, H, 1, 1, 8, 8, oracle.GREEDY))
     assert np.all(np.isposinf(out[:, :-1, :-1]))
     assert np.all(out[:, -1, 1:-1] == 8 * 6) and np.all(out[:, 1:-1, -1] == 8 * 6) and np.all(out[:, -1, -1] == 8 * 4)
+
+
+@pytest.mark.parametrize("B", [8, 128])
+def test_nan_gradients_cost_no_more(B):
+    """A diverged step's gradient, on the tiles that share the reduction (batch 8) and on those that do not: no weight is
+    non-finite, so nothing has to be summed again."""
+    W = torch.full((64, 3, 3, 64), 0.01, device="cuda")
+
+    def run(value):
+        dO = torch.full((B, 32, 32, 64), value, device="cuda")
+        best = 1e9
+        for _ in range(3):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for _ in range(5):
+                out = sdgp.sdgp_conv_bwd_data(dO, W, 32, 32, 1, 1, 2, 4, sdgp.GREEDY)
+            end.record()
+            end.synchronize()
+            best = min(best, begin.elapsed_time(end))
+        return best, out
+
+    finite, _ = run(1.0)
+    nan, out = run(float("nan"))
+    assert out.isnan().all()
+    assert nan < 3 * finite, (nan, finite)
+
+
+@pytest.mark.parametrize("shape,n,m,ranker", [
+    ((1, 9, 9, 8, 24, 3, 3, 3, 1), 4, 4, oracle.GREEDY),
+    ((2, 13, 9, 24, 40, 7, 7, 4, 3), 2, 8, oracle.GREEDY_ADJUSTED),
+    ((2, 8, 8, 132, 32, 3, 3, 2, 1), 3, 4, oracle.RANDOM),
+    ((900, 7, 7, 68, 32, 3, 3, 1, 1), 4, 32, oracle.RANDOM),     # one tile per wavefront
+])
+def test_non_finite_weights_outside_the_gradient(shape, n, m, ranker):
+    """Every gradient value is positive, so the oracle's NaN and infinities are those of the taps inside."""
+    L = wl.ConvLayer("i", *shape)
+    dO = np.random.default_rng(3).uniform(1, 2, L.dO_shape).astype(np.float32)
+    W = wl.normal(L.W_shape, 0.1, 4, wl.F32)
+    W[:, 0, 0, 1::2] = np.inf
+    W[:, 0, 0, 4::8] = np.nan
+    W[L.C_out // 2, L.R - 1, L.S // 2, 0] = -np.inf
+    ref, ab = oracle.conv_bwd_data(oracle.prune(dO, n, m, ranker, seed=9)[0], W, L.H, L.Wd, L.stride, L.pad)
+    got = to_host(sdgp.sdgp_conv_bwd_data(to_gpu(dO), to_gpu(W), L.H, L.Wd, L.stride, L.pad, n, m, ranker, 9)).astype(np.float64)
+    fin, nan = np.isfinite(ref), np.isnan(ref)
+    assert fin.any() and not fin.all()
+    assert np.array_equal(np.isnan(got), nan) and np.array_equal(got[~fin & ~nan], ref[~fin & ~nan])
+    assert np.all(np.abs(got[fin] - ref[fin]) <= 1e-5 * ab[fin])
