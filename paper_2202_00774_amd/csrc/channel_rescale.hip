@@ -629,6 +629,8 @@ void prune_dtype(const Plan& p, const void* dO, int64_t rows, int64_t C, int m, 
 
 }  // namespace
 
+int scale_rows_launch(const void* W, const float* scale, void* out, int64_t C_out, int64_t inner, int dt, hipStream_t stream);
+
 // Bytes of partial sums channel_scales_launch writes for these arguments (rows > 0, C > 0, C % m == 0).
 size_t channel_scales_workspace(int64_t rows, int64_t C, int dt, int m) {
     const Plan p = make_plan(rows, C, dt, m, true, kSumsMinRows, sums_max_wgs(m));
@@ -639,10 +641,17 @@ size_t channel_scales_workspace(int64_t rows, int64_t C, int dt, int m) {
     return (size_t)nb * 2u * (size_t)C * sizeof(double);
 }
 
+// Whether the workgroups of channel_finish, two rows each, multiply the filter's rows as well: a launch less, but C / 2
+// workgroups instead of a full grid.  Whole call on two 8x8 images, us, with scale_rows behind it / in one launch, by the
+// steps of 256 vectors (elements where rows are no whole aligned vectors) that a row takes: bf16 C_out 32 one 14.9 / 14.2,
+// three (3x3 512) 15.2 / 15.3, five 15.3 / 16.8, nine 15.6 / 19.8; C_out 512 44.0 / 41.7, 47.2 / 44.0, 50.5 / 47.2 with a
+// workgroup for every compute unit; fp32 C_out 32 five (3x3 128) 16.9 / 16.2, nine 17.0 / 17.4, 72 19.4 / 34.5, C_out 512 69.6 /
+// 69.6 at nine, 73.4 / 77.6 at eighteen.
+static bool finish_scales_filter(int64_t C, int64_t inner, bool vec) { return vec ? inner / 8 <= 3 * kBlock || C >= 512 : inner <= 5 * kBlock; }
+
 // Validated arguments in.  scale [C] floats, sums [2*C] doubles or NULL, partial = the workspace.
-// The factors, and with a filter W [C][inner] its rows multiplied by them (into `scaled`) in the same two launches: 64 ->
-// 128 channels 3x3, batch 512 at 32x32, the whole rescaled call 125.6 us with scale_rows behind the
-// factors, 125.0 with this (batch 64 36.5 / 34.3).
+// The factors, and with a filter W [C][inner] its rows multiplied by them (into `scaled`): 64 -> 128 channels 3x3, batch 512
+// at 32x32, the whole rescaled call 125.6 us with scale_rows behind the factors, 125.0 without that launch (batch 64 36.5 / 34.3).
 int channel_scales_launch(const void* dO, int64_t rows, int64_t C, int dt, int n, int m, float* scale, double* sums,
                           void* partial, const void* W, void* scaled, int64_t inner, hipStream_t stream) {
     const Plan p = make_plan(rows, C, dt, m, is_aligned16(dO), kSumsMinRows, sums_max_wgs(m));
@@ -650,10 +659,12 @@ int channel_scales_launch(const void* dO, int64_t rows, int64_t C, int dt, int n
     if (dt == kBF16) sums_dtype<kBF16>(p, dO, rows, C, m, n, part, stream);
     else sums_dtype<kF32>(p, dO, rows, C, m, n, part, stream);
     const dim3 grid((unsigned)((C + kFinC - 1) / kFinC));
-    const bool vec = inner % 8 == 0 && is_aligned16(W) && is_aligned16(scaled);
-    if (W == nullptr) hipLaunchKernelGGL(channel_finish<-1>, grid, dim3(kBlock), 0, stream, part, p.nb, C, scale, sums, W, scaled, inner, vec);
+    const bool vec = dt == kBF16 && inner % 8 == 0 && is_aligned16(W) && is_aligned16(scaled);
+    const bool apart = W != nullptr && !finish_scales_filter(C, inner, vec);
+    if (W == nullptr || apart) hipLaunchKernelGGL(channel_finish<-1>, grid, dim3(kBlock), 0, stream, part, p.nb, C, scale, sums, W, scaled, inner, vec);
     else if (dt == kBF16) hipLaunchKernelGGL(channel_finish<kBF16>, grid, dim3(kBlock), 0, stream, part, p.nb, C, scale, sums, W, scaled, inner, vec);
     else hipLaunchKernelGGL(channel_finish<kF32>, grid, dim3(kBlock), 0, stream, part, p.nb, C, scale, sums, W, scaled, inner, vec);
+    if (apart && launch_status() == SDGP_OK) return scale_rows_launch(W, scale, scaled, C, inner, dt, stream);
     return launch_status();
 }
 

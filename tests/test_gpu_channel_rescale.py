@@ -150,6 +150,7 @@ LAYERS = [
     ("c3x3_s2", 2, 16, 16, 64, 64, 3, 3, 2, 1),
     ("stem", 2, 12, 12, 3, 64, 3, 3, 1, 1),
     ("odd", 2, 7, 9, 24, 40, 3, 3, 1, 1),
+    ("long_rows", 2, 6, 6, 1040, 32, 3, 3, 1, 1),   # few long filter rows: scaled by a launch of their own
     ("stem5x5", 2, 20, 20, 2, 64, 5, 5, 1, 2),      # first-layer kernel, filter gathered inside the kernel (no filter image here)
     # a wide first-layer filter (five column tiles of (tap, channel) pairs): sdgp_conv_bwd_data would build a transposed
     # image of it in its workspace; this entry point hands the first-layer kernel no workspace, so the kernel gathers
@@ -263,3 +264,28 @@ def test_bench_tensor_at_full_size():
     assert ulp_distance_f32(scale.cpu().numpy(), ref_scale).max() <= 1
     got = sdgp.sdgp_prune_channel_rescaled(d, 2, 4, scale=torch.from_numpy(ref_scale).cuda())
     assert torch.equal(got.view(torch.int16).cpu(), torch.from_numpy(ref_pruned.view(np.int16)).view(got.shape))
+
+
+@pytest.mark.parametrize("dtype,C_in,C_out,R", [(torch.float32, 2048, 32, 7), (torch.bfloat16, 2048, 16, 7), (torch.float32, 1030, 16, 5)])
+def test_long_filter_rows_cost_no_more_than_the_three_steps(dtype, C_in, C_out, R):
+    dO = torch.randn(2, 8, 8, C_out, device="cuda").to(dtype)
+    W = torch.randn(C_out, R, R, C_in, device="cuda").to(dtype)
+
+    def timed(f):
+        best = 1e9
+        for _ in range(4):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for _ in range(10):
+                f()
+            end.record()
+            end.synchronize()
+            best = min(best, begin.elapsed_time(end))
+        return best
+
+    def steps():
+        scaled = sdgp.sdgp_scale_filter(W, sdgp.sdgp_channel_scales(dO, 2, 4))
+        sdgp.sdgp_conv_bwd_data(dO, scaled, 8, 8, 1, R // 2, 2, 4, sdgp.GREEDY)
+
+    one = timed(lambda: sdgp.sdgp_conv_bwd_data_channel_rescaled(dO, W, 8, 8, 1, R // 2, 2, 4))
+    assert one < 1.3 * timed(steps)
