@@ -190,7 +190,7 @@ __global__ void __launch_bounds__(256, 2) bwd_group16(const GroupedParams p) {
 //     no second launch.
 // Batch 256, 2:4 Magnitude, tiles above with their filter image / this kernel: 160 channels at 14x14 24.6 / 16.4 us, 384 at
 // 7x7 24.7 / 11.9, 64 at 28x28 24.4 / 20.8, 32 at 112x112 stride 2 77 / 59.  The distance of a tap, and with it the part of a
-// tile that is only read, grows with the width: at 62 positions the two are level (64 channels, batch 64 25.7 / 24.0).
+// tile that is only read, grows with the width: flat_pays weighs the two.
 constexpr int kFlatSlab = 2, kFlatPos = 256, kFlatMaxW = 63;
 constexpr int kFlatPitch = kFlatSlab * kGW * 2 + 16;   // 80 bytes per pixel in LDS
 constexpr int kFlatSlots = kFlatPitch / 16;            // 5 sixteen-byte slots, the last one padding
@@ -384,6 +384,23 @@ size_t bwd_grouped_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int
     return group16_fits(B, H, Wd, C_in, C_out, R, S, stride, pad, groups, dt, n, m) ? (size_t)groups * kGImageBytes : 0;
 }
 
+// Whether the kernel along the line is the faster one.  `work` is the number of gradient pixels x groups that its
+// workgroups copy and rank over that of the tiles of 8 x 32 positions, padding of rows, tiles and slabs included.  Measured
+// (this kernel's time over the tiles', 4160 calls, grids 7 to 63 wide, 2 to 24 groups): up to 1024 workgroups, which are one
+// round of the chip, 0.36-0.97 whatever the work; up to 4096 0.62-1.05 where the work is no more (0.87-1.13 beyond); above,
+// where neither launch nor fill count, stride 1 0.63-0.99 up to a work of 0.9, 0.81-1.16 at one, 0.91-1.23 beyond; stride 2, whose
+// tiles read the gradient of all four classes once, 0.45-0.93 up to 0.7, 0.83-1.21 beyond.
+static bool flat_pays(int stride, int64_t gh, int64_t gw, int64_t groups, int64_t blocks) {
+    if (blocks <= 1024) return true;
+    const double line = (double)(kFlatPos + (stride == 1 ? 2 : 1) * (gw + 2)) / kFlatPos * (double)((gh + 1) * (gw + 1)) *
+                        (double)((groups + kFlatSlab - 1) / kFlatSlab * kFlatSlab);
+    const double halo = (stride == 1 ? (kGTH + 2.0) * (kGTW + 2) : (kGTH + 1.0) * (kGTW + 1)) / (kGTH * kGTW);
+    const double tiles = halo * (double)((gh + kGTH - 1) / kGTH * kGTH * ((gw + kGTW - 1) / kGTW * kGTW)) *
+                         (double)((groups + kGSlab - 1) / kGSlab * kGSlab);
+    const double work = line / tiles;
+    return work <= (blocks <= 4096 ? 1.0 : stride == 1 ? 0.9 : 0.7);
+}
+
 // SDGP_OK after launching, a positive value when the problem does not fit (or the pointers are not 16-byte aligned),
 // or a negative sdgp_status.  workspace: bwd_grouped_workspace(...) bytes.
 int bwd_grouped_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R,
@@ -394,12 +411,14 @@ int bwd_grouped_launch(const void* dO, const void* W, void* dD, int64_t B, int64
     const int64_t gh = (H + stride - 1) / stride, gw = (Wd + stride - 1) / stride;
     GroupedLaunch l{};
     const int64_t positions = B * (gh + 1) * (gw + 1), slabs = (groups + kFlatSlab - 1) / kFlatSlab;
-    l.is_flat = gw <= kFlatMaxW && is_aligned16(W) && positions < ((int64_t)1 << 30) && (positions + kFlatPos - 1) / kFlatPos * slabs < ((int64_t)1 << 23);   // (a launch holds fewer than 2^32 threads)
+    const int64_t blocks = (positions + kFlatPos - 1) / kFlatPos * slabs;
+    l.is_flat = gw <= kFlatMaxW && is_aligned16(W) && positions < ((int64_t)1 << 30) && blocks < ((int64_t)1 << 23) &&   // (a launch holds fewer than 2^32 threads)
+                flat_pays(stride, gh, gw, groups, blocks);
     if (l.is_flat) {
         FlatParams& p = l.flat;
         p.dO = static_cast<const uint16_t*>(dO), p.W = static_cast<const uint16_t*>(W), p.dD = static_cast<uint16_t*>(dD);
         p.H = (int)H, p.Wd = (int)Wd, p.gh = (int)gh, p.gw = (int)gw, p.C = (int)C_out, p.groups = (int)groups;
-        p.positions = (int)positions, p.slabs = (int)slabs, p.nblocks = (int)((positions + kFlatPos - 1) / kFlatPos * slabs);
+        p.positions = (int)positions, p.slabs = (int)slabs, p.nblocks = (int)blocks;
         p.npix = kFlatPos + (stride == 1 ? 2 : 1) * ((int)gw + 2);
         p.units = (p.npix * kFlatPitch + 1023) / 1024;
         p.by_wp = fast_div((uint32_t)gw + 1), p.by_hp = fast_div((uint32_t)gh + 1), p.by_slabs = fast_div((uint32_t)slabs);

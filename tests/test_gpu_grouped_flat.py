@@ -19,6 +19,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n,m,ranker", [(2, 4, oracle.RANDOM), (4, 8, oracle.GREEDY_ADJUSTED), (4, 4, oracle.GREEDY)])
 @pytest.mark.parametrize("B,H,Wd,groups,stride", [
     (1, 1, 1, 1, 1), (37, 1, 1, 3, 2), (70, 2, 3, 2, 1), (3, 15, 15, 5, 1), (2, 5, 63, 3, 1), (2, 4, 64, 3, 1), (1, 9, 97, 2, 1),
+    (36, 63, 63, 4, 1),   # narrow enough, but enough workgroups for the tiles, which rank fewer pixels of it
     (3, 7, 9, 3, 2), (2, 6, 126, 1, 2), (2, 5, 127, 2, 2), (1, 8, 128, 2, 2),
 ])
 def test_matches_oracle(B, H, Wd, groups, stride, n, m, ranker):
