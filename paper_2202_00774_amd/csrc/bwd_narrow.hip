@@ -438,9 +438,10 @@ __global__ void __launch_bounds__(256, 2) bwd_narrow_mm(const NarrowParams p) {
 //     a constant) arrive by direct-to-LDS copies; slots of pixels outside the gradient are cleared once and skipped by the
 //     copies; pruning, when asked for, is done in place;
 //   * V's chunk (16 window positions x 16 columns, built once per call in the workspace) goes from the L2 straight to the 64
-//     registers that hold its sixteen fragments, in flight while the chunk is ranked: without its 20 KB in LDS three
-//     workgroups fit a CU.  Bound by the ranker's instructions (half of all issue slots): batch 256 at 224 x 224, 2:4
-//     random 217 us (258 with V in LDS and two workgroups per CU), Magnitude 206 (229), 4:8 Rescaled 275 (321);
+//     registers that hold its sixteen fragments, beside the gradient's copies: without its 20 KB in LDS three workgroups
+//     fit a CU.  Bound by the ranker's instructions: batch 256 at 224 x 224, 2:4 random 217 us (258 with V in LDS
+//     and two workgroups per CU), Magnitude 206 (229), 4:8 Rescaled 275 (321).  Through LDS, where one copy serves the four
+//     wavefronts, in some problems of few tiles (launch_first2);
 //   * a gradient fragment (16 pixels x 32 channels) is read once per (tile row, dq) and feeds up to four matrix
 //     instructions (the output rows whose window holds that gradient row); V's 16 fragments sit in registers.
 constexpr int kFWin = 4;                                  // window positions per dimension
@@ -453,7 +454,9 @@ constexpr int kFPitch = 80;                               // bytes per pixel in 
 constexpr int kFAUnits = (kFPix * kFPitch + 1023) / 1024; // 1 KB copy units
 constexpr int kFABytes = kFAUnits * 1024;
 constexpr int kFWRows = kFWin * kFWin * 16;               // rows of V's chunk: (window position, column)
+constexpr int kFWUnits = kFWRows * kFPitch / 1024;        // 20
 constexpr int kFThreads = 256;
+static_assert(kFWRows * kFPitch % 1024 == 0, "V's chunk is whole copy units");
 
 struct FirstParams {
     const uint16_t* dO;
@@ -484,7 +487,8 @@ __global__ void __launch_bounds__(256) first_v_image(const uint16_t* __restrict_
 
 typedef float f32x4f __attribute__((ext_vector_type(4)));
 
-template <int M, int RK, bool PRUNE, bool NLE2>
+// VLDS: V's chunk through LDS, once for the workgroup; otherwise its fragments from the L2, in every wavefront.
+template <int M, int RK, bool PRUNE, bool NLE2, bool VLDS>
 __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) {
     extern __shared__ __align__(16) unsigned char smem_generic[];
     SDGP_LDSN unsigned char* smem = (SDGP_LDSN unsigned char*)smem_generic;
@@ -505,7 +509,7 @@ __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) 
 
     // this lane's bases: V fragments (row = window position * 16 + column px), gradient fragments (tile row 4 rq,
     // column 32 gp + px, window column 0)
-    const unsigned char* const vbase = p.vimg + px * kFPitch + oct * 16;
+    const uint32_t vlane = (uint32_t)(px * kFPitch + oct * 16);
     SDGP_LDSN unsigned char* const abase = smem + ((4 * rq) * kFHaloCols + 32 * gp + px) * kFPitch + oct * 16;
 
     // Where this lane's 16-byte slots of the gradient tile come from: a byte offset inside image b (the same for every
@@ -536,11 +540,15 @@ __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) 
             const int u = wave + 4 * x;
             if (voff[x] != kNothing) lds_copy16(image + (size_t)kc * (kFKC * 2), voff[x], smem_base + (uint32_t)u * 1024u);
         }
-        // V's fragments are in flight while the gradient is ranked
         bf16x8n vf[kFWin * kFWin];
+        if constexpr (!VLDS) {
 #pragma unroll
-        for (int t = 0; t < kFWin * kFWin; ++t)
-            vf[t] = __builtin_bit_cast(bf16x8n, *reinterpret_cast<const u32x4n*>(vbase + (size_t)(kc * kFWRows + t * 16) * kFPitch));
+            for (int t = 0; t < kFWin * kFWin; ++t)
+                vf[t] = __builtin_bit_cast(bf16x8n, *reinterpret_cast<const u32x4n*>(p.vimg + vlane + (size_t)(kc * kFWRows + t * 16) * kFPitch));
+        } else {
+            for (int u = wave; u < kFWUnits; u += 4)
+                lds_copy16(p.vimg + ((size_t)kc * kFWUnits + u) * 1024 + lane * 16, smem_base + (uint32_t)(kFABytes + u * 1024));
+        }
         wait_lds_copies<0>();
         __syncthreads();
         if constexpr (PRUNE) {
@@ -558,6 +566,11 @@ __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) 
                 }
             }
             __syncthreads();
+        }
+        if constexpr (VLDS) {
+#pragma unroll
+            for (int t = 0; t < kFWin * kFWin; ++t)
+                vf[t] = __builtin_bit_cast(bf16x8n, *(SDGP_LDSN u32x4n*)(smem + kFABytes + vlane + t * 16 * kFPitch));
         }
 #pragma unroll
         for (int rr = 0; rr < 4 + kFWin - 1; ++rr) {       // gradient rows of this wavefront's four output rows
@@ -606,14 +619,26 @@ bool first2_fits(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, 
 
 size_t first2_image_bytes(int64_t C_out) { return (size_t)(C_out / kFKC) * kFWRows * kFPitch; }
 
-template <int M, int RK, bool PRUNE, bool NLE2>
-int launch_first2(const FirstParams& p, hipStream_t stream) {
-    auto kern = bwd_first2<M, RK, PRUNE, NLE2>;
-    constexpr int lds = kFABytes;
+template <int M, int RK, bool PRUNE, bool NLE2, bool VLDS>
+int launch_first2_v(const FirstParams& p, hipStream_t stream) {
+    auto kern = bwd_first2<M, RK, PRUNE, NLE2, VLDS>;
+    constexpr int lds = VLDS ? kFABytes + kFWRows * kFPitch : kFABytes;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return SDGP_ERR_HIP;
     hipLaunchKernelGGL(kern, dim3((unsigned)(p.B * p.tiles_i * p.tiles_j)), dim3(kFThreads), lds, stream, p);
     return launch_status();
+}
+
+// V in LDS where one or two rounds of two workgroups per compute unit hold all tiles and the third, for which it makes
+// way, has little to do: dense 128 channels at 224 x 224, batch 8 (224 tiles) 19.3 us in LDS, 21.6 from the L2, batch 32
+// (896) 47.2, 50.6, but 96 channels, batch 256 (7168) 257.9, 248.2; 4:8 Rescaled 128 channels at 96 x 96, batch 32 (192) 32.6,
+// 34.0.  The random ranker 27.7, 26.6 there.
+template <int M, int RK, bool PRUNE, bool NLE2>
+int launch_first2(const FirstParams& p, hipStream_t stream) {
+    if constexpr (!PRUNE || RK == kAdjusted) {
+        if ((int64_t)p.B * p.tiles_i * p.tiles_j <= (PRUNE ? 512 : 1024)) return launch_first2_v<M, RK, PRUNE, NLE2, true>(p, stream);
+    }
+    return launch_first2_v<M, RK, PRUNE, NLE2, false>(p, stream);
 }
 
 template <int M, bool NLE2>

@@ -124,6 +124,17 @@ def test_conv_matches_oracle(layer, ranker, dtype):
         check_conv(layer, dO, W, n, m, ranker, 3, dtype)
 
 
+@pytest.mark.parametrize("n,m,ranker", [(4, 4, oracle.GREEDY), (4, 8, oracle.GREEDY_ADJUSTED), (2, 4, oracle.RANDOM)])
+@pytest.mark.parametrize("B,hw", [(2, 70), (148, 112)])
+def test_stem_of_96_channels(B, hw, n, m, ranker):
+    """The 7x7 stride-2 first layer with the filter's fragments through LDS (few tiles) and from the L2 (1184)."""
+    layer = wl.ConvLayer("c7x7s2_96", B, hw, hw, 3, 96, 7, 7, 2, 3)
+    dO, W = wl.layer_inputs(layer, 1e-3, 0.3, seed=44, dtype=oracle.BF16)
+    hh = hw * hw
+    pixels = np.unique(np.concatenate([np.array([0, hw - 1, hh - 1, B * hh - 1, B * hh - hw]), np.random.default_rng(5).integers(0, B * hh, 3000)]))
+    check_conv(layer, dO, W, n, m, ranker, 3, oracle.BF16, pixels=pixels)
+
+
 def test_conv_2_16_and_dense():
     layer = wl.ConvLayer("c3x3_k64", 2, 8, 8, 32, 64, 3, 3, 1, 1)
     dO, W = wl.layer_inputs(layer, 1e-3, 0.3, seed=43, dtype=oracle.BF16)
