@@ -223,6 +223,13 @@ WgradGatherPlan wgrad_gather_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in
     if (H > (1 << 20) || Wd > (1 << 20) || P <= 0 || Q <= 0 || B <= 0) return pl;
     if (P * Q > limit / B) return pl;
     const int64_t npix = B * P * Q, chunks = (npix + kPX - 1) / kPX;
+    // A filter of a few blocks' results and a few chunks of pixels leave the chip idle here, and the plain kernel's
+    // workgroup per filter element is the faster one.  Measured (this kernel's time over the plain one's): 576 elements 1.3
+    // at 128 pixels, 2.2 at 512, 1.34 at 2048, 1.02 at 3072; 1600 (5x5) 1.06, 1.6, 0.83; 2304 (3x3) 0.90, 1.32, 0.57 and 1.07 at 768;
+    // 1x1 1024 1.06, 1.36, 0.79, 2048 0.86, 0.85, 0.36 (of 256 x 8 channels 1.12, 1.35, 1.02 at 1024); 32 pixels and 512 elements 1.16, 64 pixels
+    // 0.91-1.08 and less from 1600 elements on.
+    const int64_t nW = C_out * R * S * C_in;
+    if (nW <= (R * S > 1 || C_in < 32 || C_out < 32 ? 2304 : 1024) && (npix >= 128 || nW <= 600) && npix < 4096 && nW * npix <= 1800000) return pl;
     // channels read per pixel and tap, over all blocks
     int64_t best = -1;
     for (int i = 0; i < 4; ++i) {

@@ -67,3 +67,15 @@ def test_infinite_gradient_stays_with_its_taps():
     G[0, 0, 0] = float("inf")            # stride 2, pad 1: its taps (0, .) and (., 0) lie outside
     out = sdgp.sdgp_conv_bwd_weight(D, G, 3, 3, 2, 1)
     assert torch.isinf(out[:, 1:, 1:]).all() and torch.isfinite(out[:, 0]).all() and torch.isfinite(out[:, :, 0]).all()
+
+
+@pytest.mark.parametrize("shape,asks", [
+    ((8, 16, 16, 8, 8, 3, 3, 1, 1), False),     # 576 elements, 2048 pixels: the plain kernel, one workgroup an element
+    ((3, 16, 16, 16, 16, 3, 3, 1, 1), False),   # 2304, 768 pixels
+    ((2, 16, 16, 40, 40, 1, 1, 1, 0), False),   # 1600 elements of a 1x1 filter, 512 pixels: one split, no room needed
+    ((8, 16, 16, 40, 40, 1, 1, 1, 0), True),    # the same, 2048 pixels
+])
+def test_few_elements_and_pixels(shape, asks):
+    L = wl.ConvLayer("p", *shape)
+    assert (binding.load().sdgp_conv_bwd_weight_workspace(L.B, L.H, L.Wd, L.C_in, L.C_out, L.R, L.S, L.stride, L.pad, binding.BF16) > 0) == asks
+    test_matches_oracle(shape)
