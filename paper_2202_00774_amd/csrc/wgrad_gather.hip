@@ -17,7 +17,7 @@
 //     whatever the other side holds.  Channels past the end repeat the last ones and are not stored.
 //   * The splits' partial filters (fp32) are added in a fixed order by a second kernel: the result is the same from call
 //     to call.
-// 1x1 256 -> 64 at 56x56, batch 64 (128 MB): 29 us with the sum of the splits, 105 ms with one workgroup per filter
+// 1x1 256 -> 64 at 56x56, batch 64 (128 MB): 31 us with the sum of the splits, 105 ms with one workgroup per filter
 // element.
 #include "fastdiv.h"
 #include "lds_copy.h"
@@ -200,7 +200,7 @@ __global__ void __launch_bounds__(WVK* WVC * 64) wgrad_gather(const GatherParams
 struct Shape {
     int kb, cb, per_cu;   // channels of a block, workgroups per compute unit
 };
-constexpr Shape kShapes[] = {{64, 64, 4}, {64, 256, 1}, {128, 128, 1}, {256, 64, 1}};
+constexpr Shape kShapes[] = {{64, 64, 3}, {64, 256, 1}, {128, 128, 1}, {256, 64, 1}};
 
 template <int KB, int CB, int WVK, int WVC>
 int launch(const GatherParams& p, const WgradGatherPlan& pl, hipStream_t stream) {
@@ -241,11 +241,14 @@ WgradGatherPlan wgrad_gather_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in
     pl.kblocks = (C_out + sh.kb - 1) / sh.kb, pl.cblocks = (C_in + sh.cb - 1) / sh.cb;
     const int64_t blocks = pl.kblocks * pl.cblocks * R * S;
     if (blocks > 65535) return pl;
-    // One round of workgroups, none with fewer than eight chunks.  One of the large blocks per compute unit: every split
-    // writes and reads a partial filter (1x1 256 -> 64 at 56x56, batch 64, four-wavefront workgroups: 38 us with two per
-    // unit, 31 with one; 1024 -> 256 at 14x14 25 / 20).  Blocks of 64 x 64 leave a quarter of that and need four for the
-    // requests in flight.
-    int64_t ns = 256 * sh.per_cu / blocks;
+    // One round of workgroups, none with fewer than four chunks, most with eight or more.  One of the large blocks per compute
+    // unit: every split writes and reads a partial filter (1x1 256 -> 64 at 56x56, batch 64, four-wavefront workgroups: 38 us
+    // with two per unit, 31 with one; 1024 -> 256 at 14x14 25 / 20).  Blocks of 64 x 64 take 48 KB of LDS, so three fit; a
+    // fourth begins a second round (2x2 64 -> 64 at 56x56, batch 64 40.8 us with four, 30.9 with three; 3x3 64 -> 40 at 28x28
+    // 25.4, 22.6; 7x7 stride 2 32.1, 29.4; fifty shapes of one round 0.98-1.02).  Large 3x3 layers are faster with it all the
+    // same, for a reason that was not found (64 -> 64 stride 2 at 56x56, batch 256 61.5, 77.3; 56 -> 56 209, 256).
+    const int per_cu = pl.shape == 0 && R * S == 9 && chunks >= 3000 ? 4 : sh.per_cu;
+    int64_t ns = 256 * per_cu / blocks;
     if (ns > (chunks + 7) / 8) ns = (chunks + 7) / 8;
     if (ns < 1) ns = 1;
     pl.per = (chunks + ns - 1) / ns * kPX;
