@@ -458,14 +458,20 @@ static bool fwd_as_bwd(int64_t C_in, int64_t C_out, int R, int S, int stride) {
 
 // Where both ways can compute a stride-1 layer, the gathering kernel is the faster one while the problem is small: it
 // spreads 128 x 64 tiles over the chip where the backward-data kernels' tiles of 256 and 512 rows leave it idle, and needs
-// no transposed filter.  Measured (us, mirrored / gathered): 3x3 128 -> 128 at 16x16, batch 32 36.7 / 15.9, batch 128 32.4 /
-// 20.2, batch 256 25.6 / 28.7; 64 -> 64 at 56x56, batch 64 40 / 31, batch 128 54.7 / 55.4; 256 -> 64 at 14x14, batch 256
-// 25 / 30.  1x1 1024 -> 256 at 14x14, batch 128 26.3 / 22.5, 2048 -> 512 at 7x7 44 / 29; 64 -> 256 at 56x56, batch 32
-// 16.3 / 14.3, batch 128 44.7 / 49 (a short reduction onto many channels: the pointwise kernel's wider tiles win).
+// no transposed filter.  Its time over the mirrored way's, smallest to largest over 1041 layers (10^9 multiply-adds):
+//   1x1: 128 input channels on 0.22-1.02 up to 26; fewer onto more than 64 0.79-1.03 up to 9 (96 onto 96 1.05-1.09 from 7.4 on); at most 64 onto
+//     at most 64 0.85-1.06 at 1, 0.97-1.15 at 2, 1.04-1.23 beyond.
+//   2x2: 0.11-0.58 up to 9.
+//   3x3, up to 6.4: 0.43-1.06 but for layers that give bwd_row one nearly full round, 128 to 256 workgroups of 256 rows x 64
+//     channels, from 96 input channels onto at most 256: 1.02-1.50 (128 -> 128 at 3.5 1.07-1.12, 512 -> 32 at 6.4 1.37-1.50).
 static bool fwd_gather_pays(const ConvGeom& g, int64_t B, int64_t C_in, int64_t C_out, int R) {
     if (R > 3) return false;
-    const double macs = (double)(B * g.P * g.Q) * (double)g.n_W;
-    return R == 1 ? C_in >= C_out || macs <= 4e9 : macs <= 6.4e9;
+    const int64_t rows = B * g.P * g.Q;
+    const double macs = (double)rows * (double)g.n_W;
+    if (R == 1) return C_in >= 128 || macs <= (C_out <= 64 ? 1.2e9 : C_in > 64 ? 7e9 : 9.5e9);
+    const int64_t row_blocks = (rows + 255) / 256 * ((C_out + 63) / 64);
+    if (R == 3 && C_in >= 96 && C_out <= 256 && row_blocks >= 128 && row_blocks <= 256) return false;
+    return macs <= 6.4e9;
 }
 
 size_t sdgp_conv_fwd_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride,
