@@ -53,6 +53,11 @@ def test_unfit_widths(C_in):
     check(wl.ConvLayer("w", 2, 6, 6, C_in, 8, 3, 3, 1, 1), 2, 4, oracle.GREEDY)
 
 
+@pytest.mark.parametrize("C_out,C_in,n,m", [(4, 2, 2, 4), (8, 2, 3, 4), (4, 6, 4, 4), (8, 4, 2, 8), (4, 8, 2, 4)])
+def test_a_handful_of_channels(C_out, C_in, n, m):
+    check(wl.ConvLayer("h", 3, 9, 9, C_in, C_out, 1, 1, 1, 0), n, m, oracle.GREEDY_ADJUSTED)
+
+
 def test_unaligned_pointers():
     layer = wl.ConvLayer("u", 2, 4, 4, 8, 8, 1, 1, 1, 0)
     dO = wl.laplace_with_zeros(layer.dO_shape, 1.0, 0.3, seed=3, dtype=wl.F32)
