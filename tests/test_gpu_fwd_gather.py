@@ -38,6 +38,24 @@ def test_matches_oracle(shape):
     assert np.max(np.abs(got - ref)[ab > 0] / ab[ab > 0]) <= 4e-3
 
 
+@pytest.mark.parametrize("shape", [
+    (12, 113, 113, 40, 120, 3, 3, 2, 1),    # 305 tiles of 128 channels, four LDS buffers
+    (12, 113, 113, 40, 136, 3, 3, 2, 1),    # 610, two buffers; a second column tile of 8 channels
+    (21, 113, 115, 24, 40, 3, 3, 2, 1),     # 543 tiles of 64 channels, two buffers
+    (12, 113, 113, 72, 200, 1, 1, 2, 0),    # three steps, the last of 8 channels
+])
+def test_larger_grids_match_oracle(shape):
+    """The tile shapes and buffer counts that few tiles do not reach, on sampled pixels."""
+    L = wl.ConvLayer("f", *shape)
+    D, W = wl.normal(L.dD_shape, 1.0, 5, wl.BF16), wl.normal(L.W_shape, 0.1, 6, wl.BF16)
+    total = int(np.prod(L.dO_shape[:3]))
+    pixels = np.unique(np.concatenate([np.arange(130), np.arange(total - 130, total), np.random.default_rng(3).integers(0, total, 4000)]))
+    ref, ab = oracle.conv_fwd(D, W, L.stride, L.pad, pixels=pixels)
+    out = sdgp.sdgp_conv_fwd(to_gpu(D), to_gpu(W), L.stride, L.pad).view(total, L.C_out)
+    got = wl.to_f64(to_host(out[torch.from_numpy(pixels).cuda()]))
+    assert np.max(np.abs(got - ref)[ab > 0] / ab[ab > 0]) <= 4e-3
+
+
 def test_infinite_weight_outside_the_image():
     """A tap outside the image has no term: an infinite weight there must not reach the pixel."""
     D = torch.ones(2, 7, 7, 8, dtype=torch.bfloat16, device="cuda")

@@ -109,18 +109,40 @@ CASES = [
     # pointwise kernel gathering rows per tap: stride-2 3x3 (classes of 1, 2, 2, 4 taps) and 4x4
     (wl.ConvLayer("gather_s2_3x3", 64, 30, 28, 64, 64, 3, 3, 2, 1), True),
     (wl.ConvLayer("gather_s2_4x4", 64, 32, 32, 64, 64, 4, 4, 2, 1), True),
-    # few tiles: the producer/consumer kernel
-    (wl.ConvLayer("conv3_n64", 4, 16, 16, 64, 64, 3, 3, 1, 1), False),
-    (wl.ConvLayer("conv3_n64_spread", 4, 16, 16, 64, 64, 3, 3, 1, 1), True),
-    (wl.ConvLayer("conv3_5x5", 3, 12, 12, 64, 64, 5, 5, 1, 2), True),
-    # channel count not a multiple of 32: the parity-class kernel; stride 2 with few tiles
-    (wl.ConvLayer("tiled_n48", 4, 16, 16, 48, 48, 3, 3, 1, 1), False),
-    (wl.ConvLayer("tiled_n48_spread", 4, 16, 16, 48, 48, 3, 3, 1, 1), True),
-    (wl.ConvLayer("tiled_s2", 2, 14, 14, 32, 32, 3, 3, 2, 1), True),
+    # between the small-problem kernel's 256 tiles of 32 rows and the row kernel's 128 of 256: the producer/consumer kernel
+    (wl.ConvLayer("conv3_n64", 40, 16, 16, 64, 64, 3, 3, 1, 1), False),
+    (wl.ConvLayer("conv3_n64_spread", 40, 16, 16, 64, 64, 3, 3, 1, 1), True),
+    (wl.ConvLayer("conv3_5x5", 72, 12, 12, 64, 64, 5, 5, 1, 2), True),
+    # channel count not a multiple of 32: the parity-class kernel; stride 2 below the pointwise classes' 64 tiles of 128 rows
+    (wl.ConvLayer("tiled_n48", 66, 16, 16, 48, 48, 3, 3, 1, 1), False),
+    (wl.ConvLayer("tiled_n48_spread", 66, 16, 16, 48, 48, 3, 3, 1, 1), True),
+    (wl.ConvLayer("tiled_s2", 90, 14, 14, 32, 32, 3, 3, 2, 1), True),
+    # the small-problem kernel: 3x3, 5x5, stride 2, a channel count that ends inside a reduction step, and 1x1
+    (wl.ConvLayer("small_n64", 4, 16, 16, 64, 64, 3, 3, 1, 1), False),
+    (wl.ConvLayer("small_n64_spread", 4, 16, 16, 64, 64, 3, 3, 1, 1), True),
+    (wl.ConvLayer("small_5x5", 3, 12, 12, 64, 64, 5, 5, 1, 2), True),
+    (wl.ConvLayer("small_n48_spread", 4, 16, 16, 48, 48, 3, 3, 1, 1), True),
+    (wl.ConvLayer("small_s2", 2, 14, 14, 32, 32, 3, 3, 2, 1), True),
+    (wl.ConvLayer("small_1x1_n160", 9, 7, 7, 160, 160, 1, 1, 1, 0), False),
     # first-layer kernel (C_in <= 4): 3x3 on four channels, the 7x7 stride-2 stem on three
     (wl.ConvLayer("narrow_3x3", 2, 19, 21, 4, 32, 3, 3, 1, 1), True),
     (wl.ConvLayer("narrow_7x7s2", 2, 30, 30, 3, 64, 7, 7, 2, 3), True),
 ]
+
+
+# The same on patterns that no structured-sparse instruction takes: the ranked rows are multiplied dense.  32 channels a
+# group, and more than two survivors.
+DENSE_ROWS = [
+    (wl.ConvLayer("tiled_n96", 46, 14, 14, 96, 96, 3, 3, 1, 1), False),        # (no kernel for masked rows before 128 row tiles)
+    (wl.ConvLayer("tiled_s2_n96", 80, 14, 14, 96, 96, 3, 3, 2, 1), False),
+    (wl.ConvLayer("small_n96", 4, 16, 16, 96, 96, 3, 3, 1, 1), False),
+    (wl.ConvLayer("small_s2_n96", 3, 14, 14, 96, 96, 3, 3, 2, 1), False),
+]
+
+
+@pytest.mark.parametrize("layer,spread", DENSE_ROWS, ids=lambda v: v.name if hasattr(v, "name") else "")
+def test_pruned_values_multiplied_dense_equal_the_oracle(layer, spread):
+    check_exact(layer, spread, [(n, m, r) for n, m in ((3, 4), (4, 8), (4, 16), (2, 32), (16, 32)) for r in RANKERS], npix=4000)
 
 
 @pytest.mark.parametrize("layer,spread", CASES, ids=lambda v: v.name if hasattr(v, "name") else "")
@@ -139,11 +161,18 @@ def test_linear_identity_equals_the_oracle():
 def test_padded_reduction_identity_equals_the_oracle():
     """C_out = 40 and 1000 are multiples of 8 but not of the kernel's 32-channel chunk: small 1x1 problems are padded
     into the workspace (zero channels, zero filter rows) and the random ranker keeps indexing rows of C_out elements."""
-    for rows, C in ((9001, 40), (300, 1000)):
+    for rows, C in ((9001, 40), (3100, 1000)):
         layer = wl.ConvLayer("padded_n%d" % C, rows, 1, 1, C, C, 1, 1, 1, 0)
         assert sdgp.conv_bwd_data_workspace(rows, 1, 1, C, C, 1, 1, 1, 0, sdgp.BF16, 2, 4) >= 2 * rows * (-(-C // 32) * 32)
         check_exact(layer, False, [(2, 4, r) for r in RANKERS] + [(2, 8, oracle.RANDOM), (4, 4, oracle.GREEDY), (3, 8, oracle.GREEDY)],
-                    npix=rows)
+                    npix=600)
+
+
+def test_ragged_reduction_identity_on_few_tiles_equals_the_oracle():
+    """The same channel counts on few rows: the small-problem kernel, whose last reduction step ends inside."""
+    for rows, C in ((900, 40), (300, 1000)):
+        check_exact(wl.ConvLayer("small_n%d" % C, rows, 1, 1, C, C, 1, 1, 1, 0), False,
+                    [(2, 4, r) for r in RANKERS] + [(2, 8, oracle.RANDOM), (4, 4, oracle.GREEDY), (3, 8, oracle.GREEDY)], npix=rows)
 
 
 # The gradient ranked and compressed by a pass of its own, then multiplied without ranking (1x1 layers with several

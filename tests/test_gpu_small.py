@@ -54,17 +54,26 @@ def test_filters(H, Wd, R, S, stride, pad):
 
 @pytest.mark.parametrize("n,m", [(2, 4), (4, 4), (5, 8)])
 @pytest.mark.parametrize("shape", [
-    (2100, 4, 4, 264, 40, 1, 1, 1, 0),      # 1x1, ragged C_out, more than 1024 tiles: the padded copies
-    (270, 8, 8, 16, 40, 3, 3, 1, 1),        # ragged C_out, more than 511 tiles: bwd_tiled
+    (2100, 4, 4, 264, 40, 1, 1, 1, 0),      # 1x1, ragged C_out, more than 256 tiles: the padded copies
+    (270, 8, 8, 16, 40, 3, 3, 1, 1),        # ragged C_out, more than 512 tiles: bwd_tiled
     (300, 9, 11, 24, 40, 3, 3, 2, 1),       # the same, strided
-    (64, 16, 16, 72, 32, 5, 5, 1, 2),       # a filter neither three wide nor 1x1: bwd_conv3
-    (65, 16, 16, 72, 32, 2, 2, 1, 1),
-    (70, 16, 16, 64, 64, 3, 3, 1, 1),       # the row kernel
+    (70, 16, 16, 72, 64, 5, 5, 1, 2),       # a filter neither three wide nor 1x1, more than 512 tiles: bwd_conv3
+    (65, 16, 16, 72, 64, 2, 2, 1, 1),
+    (130, 16, 16, 64, 64, 3, 3, 1, 1),      # the row kernel
     (350, 7, 7, 136, 64, 1, 1, 1, 0),       # the pointwise kernel
     (170, 14, 14, 72, 64, 3, 3, 2, 1),      # its parity classes
 ])
 def test_neighbours(shape, n, m):
     check(shape, n, m, oracle.RANDOM)
+
+
+@pytest.mark.parametrize("ranker", RANKERS)
+@pytest.mark.parametrize("n,m", [(1, 4), (2, 16), (7, 16), (4, 32), (16, 32)])
+@pytest.mark.parametrize("shape", [(270, 8, 8, 72, 96, 3, 3, 1, 1), (300, 9, 11, 24, 96, 3, 3, 2, 1)])
+def test_tiled_patterns(shape, n, m, ranker):
+    """bwd_tiled: 540 tiles and 128 row tiles not reached, and a strided layer whose classes have fewer than 64 tiles of 128
+    rows at some patterns."""
+    check(shape, n, m, ranker)
 
 
 @pytest.mark.parametrize("shape,n,m,ranker", [

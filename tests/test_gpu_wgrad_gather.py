@@ -2,8 +2,9 @@
 of its tiles: every block shape, channel counts that end inside a tile, fewer pixels than a chunk, runs that end inside a
 chunk, taps that never meet the image, one split and many.
 
-Tolerance relative to sum |a||b|: the kernel sums N <= 2e4 products in fp32, so errors stay below N * 2^-24 in the worst
-case and near sqrt(N) * 2^-24 = 8e-6 in practice; 1e-4 is asked for.
+Tolerance relative to sum |a||b|: products of bf16 values are exact in fp32, runs of at most 128 of them are summed in fp32
+(128 * 2^-24 = 7.6e-6 of the run's sum |a||b| at the very worst), the runs and the splits in fp64, and the result is rounded
+once to fp32: 8e-6.  (The plain kernel, which takes small filters over few pixels, adds shorter chains.)
 """
 import ctypes
 
@@ -23,7 +24,11 @@ LAYERS = [  # B, H, Wd, C_in, C_out, R, S, stride, pad
     (3, 9, 7, 64, 64, 1, 1, 1, 0),
     (2, 28, 28, 256, 64, 1, 1, 1, 0),       # 64 x 256 blocks, many splits
     (2, 13, 13, 136, 120, 1, 1, 1, 0),      # 128 x 128, ragged on both sides
-    (2, 11, 11, 64, 264, 1, 1, 2, 0),       # 256 x 64, a second block of 8 channels
+    (2, 11, 11, 64, 264, 1, 1, 2, 0),       # 64 x 64, five blocks of output channels, the last of 8
+    (2, 30, 30, 64, 256, 1, 1, 1, 0),       # 256 x 64
+    (2, 30, 30, 56, 248, 2, 2, 1, 1),       # the same, ragged on both sides
+    (12, 56, 56, 64, 256, 1, 1, 1, 0),      # 256 x 64, 74 splits: added by sixteen wavefronts
+    (12, 56, 56, 64, 64, 1, 1, 1, 0),       # 64 x 64, 74 splits
     (1, 1, 1, 8, 8, 1, 1, 1, 0),            # one pixel
     (5, 8, 9, 72, 40, 3, 3, 2, 1),
     (2, 7, 7, 32, 96, 3, 3, 1, 1),          # stride 1 beside the kernel for multiples of 64
@@ -44,7 +49,7 @@ def test_matches_oracle(shape):
     assert torch.equal(out, again)
     got = out.cpu().numpy().astype(np.float64)
     assert np.all(got[ab == 0] == 0)
-    assert np.max(np.abs(got - ref)[ab > 0] / ab[ab > 0]) <= 1e-4
+    assert np.max(np.abs(got - ref)[ab > 0] / ab[ab > 0]) <= 8e-6
 
 
 def test_without_workspace():
