@@ -133,8 +133,8 @@ CASES = [
 # The same on patterns that no structured-sparse instruction takes: the ranked rows are multiplied dense.  32 channels a
 # group, and more than two survivors.
 DENSE_ROWS = [
-    (wl.ConvLayer("tiled_n96", 46, 14, 14, 96, 96, 3, 3, 1, 1), False),        # (no kernel for masked rows before 128 row tiles)
-    (wl.ConvLayer("tiled_s2_n96", 80, 14, 14, 96, 96, 3, 3, 2, 1), False),
+    (wl.ConvLayer("tiled_n64", 70, 16, 16, 64, 64, 3, 3, 1, 1), False),        # between 512 tiles of 32 rows and 128 of 256
+    (wl.ConvLayer("tiled_s2_n96", 400, 9, 9, 96, 96, 3, 3, 2, 1), False),      # classes of 25 to 16 pixels: the last has 50 tiles of 128 rows
     (wl.ConvLayer("small_n96", 4, 16, 16, 96, 96, 3, 3, 1, 1), False),
     (wl.ConvLayer("small_s2_n96", 3, 14, 14, 96, 96, 3, 3, 2, 1), False),
 ]

@@ -69,10 +69,10 @@ def test_neighbours(shape, n, m):
 
 @pytest.mark.parametrize("ranker", RANKERS)
 @pytest.mark.parametrize("n,m", [(1, 4), (2, 16), (7, 16), (4, 32), (16, 32)])
-@pytest.mark.parametrize("shape", [(270, 8, 8, 72, 96, 3, 3, 1, 1), (300, 9, 11, 24, 96, 3, 3, 2, 1)])
+@pytest.mark.parametrize("shape", [(70, 16, 16, 64, 96, 3, 3, 1, 1), (300, 9, 11, 24, 96, 3, 3, 2, 1)])
 def test_tiled_patterns(shape, n, m, ranker):
-    """bwd_tiled: 540 tiles and 128 row tiles not reached, and a strided layer whose classes have fewer than 64 tiles of 128
-    rows at some patterns."""
+    """bwd_tiled on every ranker: more than 512 tiles of 32 rows and fewer than 128 of 256; a strided layer of which a parity
+    class has fewer than 64 tiles of 128."""
     check(shape, n, m, ranker)
 
 
