@@ -8,10 +8,11 @@ pruning with the random ranker seeded by the layer index (Sec. IV; Alg. 1).  One
 over that batch: 54 calls (rank + prune + backward-data product), last layer first.  All inputs are drawn on the
 host by the seeded generators the parity tests use and are resident in HBM before the timed region.
 
-Prints ONE JSON line.  `value` is the effective rate: the FLOPs of the unpruned products divided by the time the
-pruned path took.  Extra fields: per distinct ResNet-50 layer shape the dense and the fused times, the ResNet-9 sweep
-(speedup at 2:4, 2:8, 2:16), the ResNet-50 bottleneck layers, the standalone prune pass's GB/s, roofline objects and
-the CPU oracle timed on a bounded sample.
+Prints ONE JSON line to stdout.  `value` is the effective rate: the FLOPs of the unpruned products divided by the time
+the pruned path took; beside it the roofline objects, the sustained peaks and the CPU oracle timed on a bounded sample.
+The tables go to stderr, one JSON object a line: per distinct ResNet-50 layer shape the dense and the fused times, the
+ResNet-9 sweep (speedup at 2:4, 2:8, 2:16), the ResNet-50 bottleneck layers, the standalone prune pass's GB/s and more (the
+line of all of them is 22 KB long, and whoever keeps the last few KB of the output loses its head).
 
 `--probe` launches a few calls of one kind plus a plain device copy of known size and exits: meant to run under
 rocprofv3 (kernel trace, or one --pmc counter per run; the copy calibrates FETCH_SIZE / WRITE_SIZE).  `--summarize`
@@ -37,6 +38,10 @@ HBM_PEAK_GBS = 8000.0
 MFMA_BF16_PEAK_TFLOPS = 2500.0
 BALANCE_FLOP_PER_BYTE = MFMA_BF16_PEAK_TFLOPS * 1e12 / (HBM_PEAK_GBS * 1e9)   # 312.5
 COPY_BYTES = 256 << 20
+# what the line on stdout holds; the other measurements are tables of their own on stderr
+HEADLINE = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline",
+            "dtype", "data", "config", "paper_context", "roofline", "roofline_dense", "achievable_peaks", "roofline_prune",
+            "cpu_baseline")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_per_launch.md")
 PAPER_CONTEXT = ("the paper reports no measured rate for this path; it estimates a 15-25 % cut of total training time "
                  "assuming 2:4 sparse tensor-core support on an A100 (abstract, Sec. IV-C)")
@@ -196,8 +201,7 @@ def main():
         "config": {"workload": "full ResNet-50 backward-data pass: 53 convolutions + fc, batch %d, 224x224, NHWC bf16, 2:4, "
                                "random ranker seeded per layer (54 sdgp_conv_bwd_data calls per step: one fused kernel each, except that layers "
                                "whose gradient the fused kernel would rank several times over rank and compress it in a pass of their "
-                               "own first, and the classifier layer copies gradient and filter into the workspace with its 1000 "
-                               "channels padded to 1024)" % args.batch,
+                               "own first)" % args.batch,
                    "n": 2, "m": 4, "batch": args.batch, "ranker": "random"},
         "paper_context": PAPER_CONTEXT,
     }
@@ -549,6 +553,10 @@ def main():
             "sample": "the same 54 layers at batch %d, 2:4 random, prune + fp64 product, %.1f s" % (args.cpu_batch, t_cpu),
         }
 
+    tables = [k for k in result if k not in HEADLINE]
+    for k in tables:
+        print(json.dumps({k: result.pop(k)}), file=sys.stderr)
+    sys.stderr.flush()
     print(json.dumps(result))
 
 
