@@ -116,7 +116,9 @@ int sdgp_linear_bwd_data(const void* dO, const void* W, void* dD, int64_t rows, 
  *
  *   dD[b,h,w,c] = sum over taps (r,s) and channels k of
  *                 prune(dO)[b,p,q,k] * W[k,r,s,c],   p = (h + pad - r)/stride, q = (w + pad - s)/stride,
- *   taking only taps for which p and q are integers inside [0,P) x [0,Q).
+ *   taking only taps for which p and q are integers inside [0,P) x [0,Q).  (A weight that is infinite or NaN stays away
+ *   from pixels that its tap does not reach in fp32 and on the plain and the small-problem bf16 kernels; the bf16 tile
+ *   kernels multiply it by a row of zeros there, which is a NaN.)
  *   The forward pass was a cross-correlation with dilation 1 and one group.
  *   Input pixels that no tap reaches receive 0.  Each dO element is pruned once,
  *   with flat element index ((b*P + p)*Q + q)*C_out + k.
@@ -151,9 +153,11 @@ int sdgp_conv_bwd_data(const void* dO, const void* W, void* dD, int64_t B, int64
  *     filter) whose C_out is a multiple of 8 but not of 32 -- a classifier's 1000
  *     outputs -- ask for room for copies of the gradient and the filter with C_out
  *     rounded up to 32 (zeros in the new channels), on which the matrix-core kernel
- *     runs; without the workspace a slower kernel takes the layer.  The result does
+ *     runs; without the workspace another kernel takes the layer.  The result does
  *     not depend on which one ran (the random ranker indexes rows of C_out elements
- *     either way). */
+ *     either way).
+ * The sizes hold for every ranker and alignment, so a call may leave its workspace
+ * unread: problems of few tiles run a kernel that needs none. */
 size_t sdgp_conv_bwd_data_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
                                     int R, int S, int stride, int pad, int dt, int n, int m);
 
@@ -290,7 +294,8 @@ int sdgp_conv_bwd_data_compact(const void* dO, const void* W, void* dD, int64_t 
  *                        dense matrix-core kernels of the backward-data path compute large layers from a mirrored,
  *                        transposed copy of W that the call builds in the workspace; other bf16 layers whose
  *                        channel counts are multiples of 8 take a matrix-core kernel that needs none, the rest a
- *                        plain kernel.  D, W and O 16-byte aligned for the matrix-core paths.
+ *                        plain kernel.  D, W and O 16-byte aligned for the matrix-core paths.  (Infinite or NaN weights
+ *                        of a tap outside the image: as sdgp_conv_bwd_data says, the mirrored way being its kernels.)
  * sdgp_conv_bwd_weight   dW[k,r,s,c] = sum_{b,p,q} dO[b,p,q,k] * D[b, p*stride + r - pad, q*stride + s - pad, c]
  *                        D and dO `dt`, dO UNPRUNED; dW [C_out,R,S,C_in] is written in fp32 whatever `dt` is.
  *                        bf16, stride 1, 3x3, C_in and C_out multiples of 64: matrix-core kernel whose workgroups

@@ -287,7 +287,8 @@ size_t sdgp_conv_bwd_data_grouped_workspace(int64_t B, int64_t H, int64_t Wd, in
     if (check_groups(C_in, C_out, groups, m) != SDGP_OK) return (size_t)-1;
     if (groups == 1) return sdgp_conv_bwd_data_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m);
     if (g.n_dD == 0) return 0;
-    // 16 channels per group, 3x3, stride 1: the matrix-core kernel wants the filter re-indexed
+    // 16 channels per group, 3x3, stride 1 or 2: room for the re-indexed filter of the matrix-core kernel for wide images
+    // (the one for the others reads W as it is, but the size does not say which W and which alignment will come)
     const size_t image = sdgp::bwd_grouped_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, groups, dt, n, m);
     if (image > 0) return image;
     if (n == m) return 0;

@@ -12,8 +12,8 @@
 //   * 16-byte columns of a row are exchanged by row so that the sixteen lanes of a fragment read meet all 64 banks.
 //   * Consecutive tiles share image rows, and the column tiles of one row tile all of them: tiles are dealt to the eight
 //     XCDs in runs, so that each one's L2 serves its own part of the image.
-// 3x3 stride 2 128 -> 128 at 56x56, batch 128: 54 us = 545 TFLOP/s and 2.4 TB/s, bound by the latency of the copies between
-// two barriers; one thread per output element took 50.1 ms.
+// 3x3 stride 2 128 -> 128 at 56x56, batch 128: 60 us a call = 490 TFLOP/s (53 in the kernel; a wavefront waits half of its
+// time, for copies between two barriers); one thread per output element took 50.1 ms.
 // Pixels outside the image are zeros.  Zero times a non-finite weight is NaN where the definition has no term, so a NaN
 // of a pixel whose window leaves the image is summed again without those taps.
 #include "lds_copy.h"
