@@ -25,6 +25,7 @@
 
 #include <type_traits>
 
+#include "parity_axis.h"
 #include "ranker.h"
 
 namespace sdgp {
@@ -50,21 +51,6 @@ struct F32Params {
     uint32_t mix;
 };
 
-// One parity class of input pixels along one axis: pixel i*stride + a meets filter positions r0, r0 + stride, ...
-// (count of them) at gradient positions i + shift, i + shift - 1, ...
-struct F32Axis {
-    int r0, count, shift;
-    int64_t n;
-};
-__device__ __forceinline__ F32Axis f32_axis(int64_t size, int filter, int stride, int pad, int a) {
-    F32Axis x;
-    x.r0 = (a + pad) % stride;
-    x.count = x.r0 < filter ? (filter - x.r0 + stride - 1) / stride : 0;
-    x.shift = (a + pad - x.r0) / stride;
-    x.n = size > a ? (size - a + stride - 1) / stride : 0;
-    return x;
-}
-
 // raw[0..M) of the group that starts at flat element e0 -> the pruned values
 template <int M, int RK, bool NLE2>
 __device__ __forceinline__ void prune_f32(uint32_t (&raw)[M], int n, uint32_t mix, uint64_t e0) {
@@ -87,7 +73,7 @@ __device__ __forceinline__ void sum_inside_f32(int64_t row, int64_t c0) {
     asm volatile("" : "+s"(args));
     const auto& p = *reinterpret_cast<const __attribute__((address_space(4))) F32Params*>(args);
     const int ca = (int)(blockIdx.z / p.stride), cb = (int)(blockIdx.z % p.stride);
-    const F32Axis ay = f32_axis(p.H, p.R, p.stride, p.pad, ca), ax = f32_axis(p.Wd, p.S, p.stride, p.pad, cb);
+    const ParityAxis<int64_t> ay = parity_axis<int64_t>(p.H, p.R, p.stride, p.pad, ca), ax = parity_axis<int64_t>(p.Wd, p.S, p.stride, p.pad, cb);
     const int64_t b = row / (ay.n * ax.n), rem = row - b * (ay.n * ax.n), i = rem / ax.n, j = rem - i * ax.n;
     const int64_t gi = i + ay.shift, gj = j + ax.shift;
     if (gi < p.P && gi - ay.count >= -1 && gj < p.Q && gj - ax.count >= -1) return;   // every tap inside: a NaN of its own
@@ -133,7 +119,7 @@ __global__ void __launch_bounds__(64 * WV, CN == 2 ? 2 : 1) bwd_f32(const F32Par
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int half = lane >> 5, l32 = lane & 31;
     const int ca = (int)(blockIdx.z / p.stride), cb = (int)(blockIdx.z % p.stride);
-    const F32Axis ay = f32_axis(p.H, p.R, p.stride, p.pad, ca), ax = f32_axis(p.Wd, p.S, p.stride, p.pad, cb);
+    const ParityAxis<int64_t> ay = parity_axis<int64_t>(p.H, p.R, p.stride, p.pad, ca), ax = parity_axis<int64_t>(p.Wd, p.S, p.stride, p.pad, cb);
     const int64_t rows = p.B * ay.n * ax.n;
     const int64_t tile = (int64_t)blockIdx.x * (WK == 1 ? WV : 1) + (WK == 1 ? wave : 0);
     if (tile * 32 >= rows) return;   // (with WK > 1 the whole workgroup leaves: no barrier is missed)

@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "lds_copy.h"
+#include "parity_axis.h"
 
 namespace sdgp {
 
@@ -42,20 +43,6 @@ struct SmallParams {
     int col_tiles, row_tiles;   // row tiles of the largest parity class
     uint32_t mix;
 };
-
-// One parity class of input pixels along one axis: pixel i*stride + a meets filter positions r0, r0 + stride, ...
-// (count of them) at gradient positions i + shift, i + shift - 1, ...
-struct SmallAxis {
-    int r0, count, shift, n;
-};
-__device__ __forceinline__ SmallAxis small_axis(int size, int filter, int stride, int pad, int a) {
-    SmallAxis x;
-    x.r0 = (a + pad) % stride;
-    x.count = x.r0 < filter ? (filter - x.r0 + stride - 1) / stride : 0;
-    x.shift = (a + pad - x.r0) / stride;
-    x.n = size > a ? (size - a + stride - 1) / stride : 0;
-    return x;
-}
 
 // The survivors of the M channels at g (flat element e0): bit j for channel j, by counting the keys ahead of it.
 template <int M, int RK>
@@ -87,8 +74,8 @@ __device__ __forceinline__ void sum_inside(int row, int c0, float (&v)[4]) {
     uint64_t args = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(args));
     const auto& p = *reinterpret_cast<const __attribute__((address_space(4))) SmallParams*>(args);
-    const SmallAxis ay = small_axis(p.H, p.R, p.stride, p.pad, (int)blockIdx.y / p.stride);
-    const SmallAxis ax = small_axis(p.Wd, p.S, p.stride, p.pad, (int)blockIdx.y % p.stride);
+    const ParityAxis<int> ay = parity_axis<int>(p.H, p.R, p.stride, p.pad, (int)blockIdx.y / p.stride);
+    const ParityAxis<int> ax = parity_axis<int>(p.Wd, p.S, p.stride, p.pad, (int)blockIdx.y % p.stride);
     const int b = row / (ay.n * ax.n), rem = row - b * (ay.n * ax.n);
     const int gi = rem / ax.n + ay.shift, gj = rem % ax.n + ax.shift;
     const int64_t kstep = (int64_t)p.R * p.S * p.C_in;
@@ -166,7 +153,7 @@ __global__ void __launch_bounds__(64 * kSmallWaves) bwd_small(const SmallParams 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int half = lane >> 5, l32 = lane & 31;
     const int ca = (int)blockIdx.y / p.stride, cb = (int)blockIdx.y % p.stride;
-    const SmallAxis ay = small_axis(p.H, p.R, p.stride, p.pad, ca), ax = small_axis(p.Wd, p.S, p.stride, p.pad, cb);
+    const ParityAxis<int> ay = parity_axis<int>(p.H, p.R, p.stride, p.pad, ca), ax = parity_axis<int>(p.Wd, p.S, p.stride, p.pad, cb);
     const int rows = (int)p.B * ay.n * ax.n;
     // workgroups go to the XCDs in turn: each takes a run of the tiles, which are in column order
     const int per_xcd = (int)gridDim.x >> 3, logical = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
