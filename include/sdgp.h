@@ -301,9 +301,9 @@ int sdgp_conv_bwd_data_compact(const void* dO, const void* W, void* dD, int64_t 
  *                        bf16, stride 1, 3x3, C_in and C_out multiples of 64: matrix-core kernel whose workgroups
  *                        split the pixels and leave fp32 partial filters in the workspace, added in a fixed
  *                        order by a second kernel (the result is the same from call to call); other bf16 layers
- *                        whose channel counts are multiples of 8 take a matrix-core kernel of the same kind (its
- *                        partial filters are what the workspace query asks for; a call that brings less runs the
- *                        plain kernel), the rest a plain reduction kernel.  D and dO 16-byte aligned for the
+ *                        whose channel counts are multiples of 8, but for small filters over few pixels, take a
+ *                        matrix-core kernel of the same kind (its partial filters are what the workspace query asks
+ *                        for; a call that brings less runs the plain kernel), the rest a plain reduction kernel.  D and dO 16-byte aligned for the
  *                        matrix-core paths.
  *
  * workspace: sdgp_conv_fwd_workspace(...) / sdgp_conv_bwd_weight_workspace(...) bytes (0 for layers that need none),

@@ -35,8 +35,8 @@ namespace {
 //   bwd_row, which takes them from about 480 tiles on: 1.0-1.9 (groups of 32 0.33-0.99, at C_in 96 1.02-1.14).
 //   bwd_conv3 (C_out a multiple of 64, dense or n <= 2), two rounds: dense and C_in > 64 0.69-0.91, n <= 2 and C_in > 64 0.81-1.0 where
 //     C_out >= 256 and 0.93-1.14 below; C_in <= 64 1.0-1.46, half of every tile being columns that do not exist.
-//   bwd_tiled, two rounds: C_in > 64 0.38-0.98; C_in <= 64 and nine taps 0.62-0.92 (C_out 64, n > 2 1.12-1.28), more taps up
-//     to 1.52; C_out 40 and 48 at 25 and 49 taps 0.97-1.12; groups of 32 0.20-0.92 (49 taps at C_in 24 1.23).
+//   bwd_tiled, two rounds: C_in > 64 0.38-0.98; C_in <= 64 and nine taps 0.62-0.92 (C_out 48 and 56 1.08-1.22, 64, n > 2
+//     1.12-1.28), more taps up to 1.52; C_out 40 and 48 at 25 and 49 taps 0.97-1.12; groups of 32 0.20-0.92 (49 taps at C_in 24 1.23).
 // Strided filters (the parity classes of the pointwise kernel take them from about 900 tiles on, 0.79-2.77), bwd_tiled:
 //   1x1: C_in > 64 0.11-0.80 up to four rounds; C_in <= 64 three 0.19-0.98, four 0.21-1.25.
 //   wider: C_in > 64 two rounds 0.17-0.81, three 0.22-0.99 where C_out >= 128 or the filter has at most nine taps and
@@ -63,7 +63,7 @@ int64_t most_filter(bool first, int64_t C_in, int64_t C_out, int taps, int n, in
     if (!dense && m == 32 && (first ? C_in >= 128 : C_in > 64 || taps <= 25)) return 2 * kRound;
     if (first || (taps > 9 && (C_in <= 64 || C_out < 64))) return kRound;
     if (C_out % 64 == 0 && taps >= 4 && taps <= 49 && (dense || sparse)) return C_in > 64 && (dense || C_out >= 256) ? 2 * kRound : kRound;
-    return C_in > 64 || C_out < 64 || C_out >= 256 ? 2 * kRound : kRound;
+    return C_in > 64 || C_out <= 40 || C_out >= 256 ? 2 * kRound : kRound;
 }
 
 int64_t most_strided(bool first, int64_t C_in, int64_t C_out, int taps, int n, int m) {
