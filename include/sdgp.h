@@ -125,7 +125,7 @@ int sdgp_linear_bwd_data(const void* dO, const void* W, void* dD, int64_t rows, 
  *
  *   workspace / workspace_bytes: scratch memory of at least
  *   sdgp_conv_bwd_data_workspace(...) bytes (16-byte aligned); may be NULL when the
- *   query returns 0.  Its contents are undefined afterwards.  Calls that share a
+ *   query returns 0, and in fp32.  Its contents are undefined afterwards.  Calls that share a
  *   workspace must be ordered on one stream.
  *
  * Requires 1 <= R,S <= 11, 1 <= stride <= 4, 0 <= pad < R and pad < S,
@@ -156,6 +156,10 @@ int sdgp_conv_bwd_data(const void* dO, const void* W, void* dD, int64_t B, int64
  *     runs; without the workspace another kernel takes the layer.  The result does
  *     not depend on which one ran (the random ranker indexes rows of C_out elements
  *     either way).
+ *   - fp32 layers large enough to gain by it ask for room for both operands as three bf16
+ *     parts of every value (up to 1.5 times the gradient and the filter), which the bf16
+ *     matrix instructions multiply; an fp32 call with a smaller workspace, or none, runs
+ *     the kernel that needs none (same kept values, same result up to summation order).
  * The sizes hold for every ranker and alignment, so a call may leave its workspace
  * unread: problems of few tiles run a kernel that needs none. */
 size_t sdgp_conv_bwd_data_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,

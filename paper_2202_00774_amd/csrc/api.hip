@@ -45,6 +45,11 @@ int bwd_small_launch(int turn, const void* dO, const void* W, void* dD, int64_t 
                      hipStream_t stream);
 int bwd_f32_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
                    int R, int S, int stride, int pad, int n, int m, int rk, uint64_t seed, hipStream_t stream);
+int bwd_f32_split_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
+                         int R, int S, int stride, int pad, int n, int m, int rk, uint64_t seed, void* workspace,
+                         size_t workspace_bytes, hipStream_t stream);
+size_t bwd_f32_split_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad,
+                               int n, int m);
 size_t channel_scales_workspace(int64_t rows, int64_t C, int dt, int m);
 int channel_scales_launch(const void* dO, int64_t rows, int64_t C, int dt, int n, int m, float* scale, double* sums,
                           void* partial, const void* W, void* scaled, int64_t inner, hipStream_t stream);
@@ -169,7 +174,10 @@ int bwd_dispatch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, 
         if (rc <= 0) return rc;
     }
     if (dt == SDGP_F32) {
-        const int rc = sdgp::bwd_f32_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, stream);
+        int rc = sdgp::bwd_f32_split_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, workspace,
+                                            workspace_bytes, stream);
+        if (rc <= 0) return rc;
+        rc = sdgp::bwd_f32_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, stream);
         if (rc <= 0) return rc;
     }
     return sdgp::bwd_simple_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m, rk, seed, stream);
@@ -233,7 +241,8 @@ int sdgp_conv_bwd_data(const void* dO, const void* W, void* dD, int64_t B, int64
     if (g.n_dD == 0) return SDGP_OK;
     if (dD == nullptr || (g.n_dO > 0 && dO == nullptr) || (g.n_W > 0 && W == nullptr)) return SDGP_ERR_NULL;
     const size_t need = sdgp_conv_bwd_data_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m);
-    if (need > 0 && (workspace == nullptr || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 15u) != 0))
+    // (an fp32 call runs without one too, on the kernel that needs none)
+    if (dt != SDGP_F32 && need > 0 && (workspace == nullptr || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 15u) != 0))
         return SDGP_ERR_WORKSPACE;
     return bwd_dispatch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m, rk, seed, need > 0 ? workspace : nullptr,
                         need > 0 ? workspace_bytes : 0, static_cast<hipStream_t>(hip_stream));
@@ -254,7 +263,7 @@ int sdgp_conv_bwd_data_noalloc(const void* dO, const void* W, void* dD, int64_t 
     if (must > (size_t)SDGP_NOALLOC_SCRATCH_BYTES) return SDGP_ERR_WORKSPACE;  // more scratch than the library holds
     const size_t need = sdgp_conv_bwd_data_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m);
     void* ws = nullptr;
-    if (need > 0 && need <= (size_t)SDGP_NOALLOC_SCRATCH_BYTES) {
+    if (dt != SDGP_F32 && need > 0 && need <= (size_t)SDGP_NOALLOC_SCRATCH_BYTES) {
         ws = scratch_on_current_device();
         if (ws == nullptr) return SDGP_ERR_HIP;
     }
@@ -269,6 +278,7 @@ size_t sdgp_conv_bwd_data_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_
     const size_t first = first_layer_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m, g);
     if (first > 0) return first;
     // 1x1 layers many column tiles wide and strided filters: room for the gradient ranked and compressed once
+    if (dt == SDGP_F32 && g.n_dD > 0 && g.n_dO > 0) return sdgp::bwd_f32_split_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m);
     if (dt == SDGP_BF16 && C_in > 4 && g.n_dD > 0 && g.n_dO > 0) return sdgp::bwd_pw_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m);
     return 0;
 }

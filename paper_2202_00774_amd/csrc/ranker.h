@@ -641,12 +641,15 @@ __host__ __device__ __forceinline__ void prune_compress16_random(const uint32_t 
 // survivor may point at any dropped position.
 __device__ __forceinline__ void compress_quad(const bool (&k)[4], const uint32_t (&o)[4], uint32_t& v0, uint32_t& v1,
                                               uint32_t& pos) {
-    const uint32_t p0 = k[0] ? 0u : (k[1] ? 1u : (k[2] ? 2u : 0u));
-    v0 = k[0] ? o[0] : (k[1] ? o[1] : (k[2] ? o[2] : o[0]));
-    const bool two_low = k[2] && (k[0] || k[1]);
-    const bool both01 = k[1] && k[0];
-    const uint32_t p1 = k[3] ? 3u : (two_low ? 2u : (both01 ? 1u : 3u));
-    v1 = k[3] ? o[3] : (two_low ? o[2] : (both01 ? o[1] : o[3]));
+    // (by value: a choice between elements of the arrays would be a choice of addresses, and keep them in memory)
+    const bool k0 = k[0], k1 = k[1], k2 = k[2], k3 = k[3];
+    const uint32_t o0 = o[0], o1 = o[1], o2 = o[2], o3 = o[3];
+    const uint32_t p0 = k0 ? 0u : (k1 ? 1u : (k2 ? 2u : 0u));
+    v0 = k0 ? o0 : (k1 ? o1 : (k2 ? o2 : o0));
+    const bool two_low = k2 && (k0 || k1);
+    const bool both01 = k1 && k0;
+    const uint32_t p1 = k3 ? 3u : (two_low ? 2u : (both01 ? 1u : 3u));
+    v1 = k3 ? o3 : (two_low ? o2 : (both01 ? o1 : o3));
     pos = p0 | (p1 << 2);
 }
 

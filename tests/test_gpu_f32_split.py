@@ -1,0 +1,100 @@
+"""fp32 backward-data products as sums of bf16 ones, on problems large enough to take that path, against the CPU oracle:
+every shape of its tiles, widths and channel counts that fill none of them, classes without a tap, images laid together
+in a tile, non-finite operands, and the same call without a workspace.
+
+Tolerance: a product of two values of three bf16 parts each, the three smallest of its nine terms left out, errs by at most
+2^-23.4 of itself = 9e-8; K terms in fp32 add like the other fp32 tests, whose bound of 1e-5 of sum |a||w| is used.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2202_00774_amd as sdgp
+from paper_2202_00774_amd import workloads as wl
+from util import rel_error, to_gpu, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+def takes(layer, n, m):
+    return sdgp.conv_bwd_data_workspace(layer.B, layer.H, layer.Wd, layer.C_in, layer.C_out, layer.R, layer.S, layer.stride, layer.pad,
+                                        sdgp.F32, n, m) > 0
+
+
+def run(layer, dO, W, n, m, ranker, seed):
+    return to_host(sdgp.sdgp_conv_bwd_data(to_gpu(dO), to_gpu(W), layer.H, layer.Wd, layer.stride, layer.pad, n, m, ranker, seed))
+
+
+SHAPES = [
+    (128, 16, 16, 64, 64, 3, 3, 1, 1),     # 256 rows, 384 positions
+    (30, 21, 19, 72, 36, 3, 3, 1, 1),      # ragged tiles, columns and channels
+    (400, 9, 9, 136, 100, 3, 3, 1, 1),      # several images to a tile
+    (24, 30, 30, 96, 64, 5, 5, 1, 2),      # 512 positions
+    (40, 24, 24, 33, 64, 3, 3, 2, 1),      # classes of one, two and four taps, an odd width
+    (120, 17, 17, 448, 128, 1, 1, 1, 0),   # one tap: one stage to a chunk
+    (62, 29, 29, 33, 128, 1, 1, 2, 0),     # classes without a tap
+    (30, 16, 16, 256, 64, 3, 3, 1, 1),     # 128 rows
+]
+
+
+@pytest.mark.parametrize("n,m,ranker", [(2, 4, oracle.GREEDY), (1, 4, oracle.RANDOM), (2, 4, oracle.GREEDY_ADJUSTED), (4, 4, oracle.GREEDY)])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_shapes(shape, n, m, ranker):
+    layer = wl.ConvLayer("s", *shape)
+    assert takes(layer, 2, 4)
+    dO = wl.laplace_with_zeros(layer.dO_shape, 1e-3, 0.3, seed=5, dtype=wl.F32)
+    W = wl.normal(layer.W_shape, 0.1, 6, wl.F32)
+    ref, ab = oracle.conv_bwd_data(oracle.prune(dO, n, m, ranker, seed=7)[0], W, layer.H, layer.Wd, layer.stride, layer.pad)
+    out = run(layer, dO, W, n, m, ranker, 7)
+    assert rel_error(out, ref, ab) <= 1e-5
+    assert np.all(out[ab == 0] == 0)
+
+
+@pytest.mark.parametrize("ranker", (oracle.RANDOM, oracle.GREEDY, oracle.GREEDY_ADJUSTED))
+@pytest.mark.parametrize("n,m", [(3, 4), (2, 8), (5, 8), (1, 16), (7, 16), (2, 32), (16, 32)])
+def test_groups(n, m, ranker):
+    layer = wl.ConvLayer("g", 64, 16, 16, 128, 96, 3, 3, 1, 1)
+    assert takes(layer, n, m)
+    dO = wl.laplace_with_zeros(layer.dO_shape, 1e-3, 0.3, seed=8, dtype=wl.F32)
+    W = wl.normal(layer.W_shape, 0.1, 9, wl.F32)
+    ref, ab = oracle.conv_bwd_data(oracle.prune(dO, n, m, ranker, seed=10)[0], W, 16, 16, 1, 1)
+    assert rel_error(run(layer, dO, W, n, m, ranker, 10), ref, ab) <= 1e-5
+
+
+@pytest.mark.parametrize("n,m", [(2, 4), (4, 8)])
+def test_non_finite(n, m):
+    """An infinite gradient value times a weight with few bits, dropped channels under an infinite weight, NaN."""
+    layer = wl.ConvLayer("i", 64, 16, 16, 128, 96, 3, 3, 1, 1)
+    assert takes(layer, n, m)
+    rng = np.random.default_rng(3)
+    dO = rng.uniform(1, 2, layer.dO_shape).astype(np.float32)
+    W = (rng.integers(1, 4, layer.W_shape) * 0.25).astype(np.float32)
+    dO[3, 5, 7, 11] = np.inf
+    dO[4, 0, 0, 2] = -np.inf
+    dO[5, 1, 1, :4] = np.nan
+    W[:, 0, 0, 5] = np.inf
+    W[9, 2, 2, 40] = np.nan
+    ref, ab = oracle.conv_bwd_data(oracle.prune(dO, n, m, oracle.GREEDY)[0], W, 16, 16, 1, 1)
+    got = run(layer, dO, W, n, m, oracle.GREEDY, 0).astype(np.float64)
+    fin, nan = np.isfinite(ref), np.isnan(ref)
+    assert fin.any() and nan.any() and (~fin & ~nan).any()
+    assert np.array_equal(np.isnan(got), nan) and np.array_equal(got[~fin & ~nan], ref[~fin & ~nan])
+    assert np.all(np.abs(got[fin] - ref[fin]) <= 1e-5 * ab[fin])
+
+
+def test_without_a_workspace():
+    """The library's own entry point takes an fp32 problem without, with too small and with a misaligned workspace."""
+    layer = wl.ConvLayer("w", 64, 16, 16, 128, 96, 3, 3, 1, 1)
+    dO = to_gpu(wl.laplace_with_zeros(layer.dO_shape, 1e-3, 0.3, seed=1, dtype=wl.F32))
+    W = to_gpu(wl.normal(layer.W_shape, 0.1, 2, wl.F32))
+    need = sdgp.conv_bwd_data_workspace(64, 16, 16, 128, 96, 3, 3, 1, 1, sdgp.F32, 2, 4)
+    want = sdgp.sdgp_conv_bwd_data(dO, W, 16, 16, 1, 1, 2, 4, sdgp.GREEDY)
+    room = torch.empty(need + 16, dtype=torch.uint8, device="cuda")
+    lib = sdgp.binding.load()
+    for ptr, size in ((None, 0), (room.data_ptr(), need - 1), (room.data_ptr() + 4, need), (room.data_ptr(), need)):
+        out = torch.empty(64, 16, 16, 128, device="cuda")
+        rc = lib.sdgp_conv_bwd_data(dO.data_ptr(), W.data_ptr(), out.data_ptr(), 64, 16, 16, 128, 96, 3, 3, 1, 1, sdgp.F32, 2, 4, sdgp.GREEDY, 0,
+                                    ptr, size, torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        assert (out - want).norm() <= 1e-6 * want.norm()
