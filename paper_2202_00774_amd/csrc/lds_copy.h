@@ -55,6 +55,16 @@ __device__ __forceinline__ void prune16_dense(u32x4_t (&v)[2], int n, uint32_t m
         v[0] = u32x4_t{o[0], o[1], o[2], o[3]}, v[1] = u32x4_t{o[4], o[5], o[6], o[7]};
         return;
     }
+    if constexpr (M == 4 && NLE2 && RK != kRandom) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t d01 = v[q >> 1][2 * (q & 1)], d23 = v[q >> 1][2 * (q & 1) + 1];
+            uint32_t o01, o23;
+            prune_of4_magnitude<RK>(d01, d23, n >= 2, o01, o23);
+            v[q >> 1][2 * (q & 1)] = o01, v[q >> 1][2 * (q & 1) + 1] = o23;
+        }
+        return;
+    }
     uint32_t raw[16], out[16];
 #pragma unroll
     for (int i = 0; i < 2; ++i)

@@ -5,6 +5,7 @@
 //   * prune_compress16_random against a rank count by (H(seed, e), -position) with H written out from its definition
 //     (28-bit keys: the kernel's word "key | position code" must order exactly like the pair).
 //   * keep_mask_packed (Magnitude on 16 or 32 channels, any n, packed 16-bit arithmetic) against the same rank count.
+//   * the rankers of quads by comparison, in place and as positions, on magnitudes that tie.
 //   * select_by_sort_ties (the random ranker's selection in groups of 32) against the rank count, ties included.
 // Prints one line per configuration and returns the number of mismatches.  Test infrastructure, not product code.
 #include <hip/hip_runtime.h>
@@ -239,8 +240,37 @@ static int run_sort_ties(int iters, unsigned seed) {
     printf("M=%d sort with ties: %d mismatches\n", M, bad);
     return bad;
 }
+// The rankers of single quads by comparison, in place and as positions, on magnitudes that tie in every way.
+static int run_quads(int iters, unsigned sd) {
+    int bad = 0;
+    srand(sd);
+    for (int it = 0; it < iters; ++it) {
+        uint16_t x[4];
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t r = (uint32_t)rand();
+            x[i] = (uint16_t)(it % 4 == 0 ? r : (r & 0x8000) | (it % 4 == 1 ? 0x7F7F + (r >> 3) % 3 : it % 4 == 2 ? (r >> 3) % 3 : 0x7FFD + (r >> 3) % 3));
+        }
+        const uint32_t d01 = x[0] | ((uint32_t)x[1] << 16), d23 = x[2] | ((uint32_t)x[3] << 16);
+        for (int n = 1; n <= 2; ++n) {
+            uint32_t m01, m23, want[2] = {0, 0}, pos[2], found = 0;
+            keep_of4_magnitude(d01, d23, n == 2, m01, m23);
+            for (uint32_t j = 0; j < 4; ++j) {
+                int rank = 0;
+                for (uint32_t i = 0; i < 4; ++i) rank += (x[i] & 0x7FFF) > (x[j] & 0x7FFF) || ((x[i] & 0x7FFF) == (x[j] & 0x7FFF) && i < j);
+                if (rank < n) want[j >> 1] |= 0xFFFFu << (16 * (j & 1));
+                if (rank < 2) pos[found++] = j;
+            }
+            const uint32_t code = rank_2of4_magnitude(d01, d23);
+            if ((m01 != want[0] || m23 != want[1] || code != (pos[0] | ((pos[1] - 1) << 16))) && bad++ < 5)
+                printf("MISMATCH quad n=%d x=%08x %08x: %08x %08x code %08x\n", n, d01, d23, m01, m23, code);
+        }
+    }
+    printf("quads: %d mismatches\n", bad);
+    return bad;
+}
 int main() {
     int bad = 0;
+    bad += run_quads(1000000, 11);
     bad += run_sort_ties<32>(40000, 9); bad += run_sort_ties<8>(40000, 10);
     bad += run_mag<4, kGreedy>(100000, 1); bad += run_mag<8, kGreedy>(100000, 2); bad += run_mag<16, kGreedy>(100000, 3);
     bad += run_mag<4, kAdjusted>(100000, 4); bad += run_mag<8, kAdjusted>(100000, 5); bad += run_mag<16, kAdjusted>(100000, 6);
