@@ -439,8 +439,8 @@ __global__ void __launch_bounds__(256, 2) bwd_narrow_mm(const NarrowParams p) {
 //     copies; pruning, when asked for, is done in place;
 //   * V's chunk (16 window positions x 16 columns, built once per call in the workspace) goes from the L2 straight to the 64
 //     registers that hold its sixteen fragments, beside the gradient's copies: without its 20 KB in LDS three workgroups
-//     fit a CU.  Bound by the ranker's instructions: batch 256 at 224 x 224, 2:4 random 217 us (258 with V in LDS
-//     and two workgroups per CU), Magnitude 206 (229), 4:8 Rescaled 275 (321).  Through LDS, where one copy serves the four
+//     fit a CU.  Bound by the ranker's instructions: batch 256 at 224 x 224, 2:4 random 212 us (217 with tiles in launch order,
+//     whose halos the XCDs fetched one by one: 928 MB instead of 623; 258 with V in LDS and two workgroups per CU).  Through LDS, where one copy serves the four
 //     wavefronts, in some problems of few tiles (launch_first2);
 //   * a gradient fragment (16 pixels x 32 channels) is read once per (tile row, dq) and feeds up to four matrix
 //     instructions (the output rows whose window holds that gradient row); V's 16 fragments sit in registers.
@@ -496,7 +496,11 @@ __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rq = wave, gp = 0;
-    const int tile = blockIdx.x;
+    int tile = blockIdx.x;
+    {   // consecutive tiles on one XCD (workgroups are dealt round-robin over 8): a tile's halo is then in its L2
+        const int per = (int)gridDim.x >> 3;
+        if (tile < (per << 3)) tile = (tile & 7) * per + (tile >> 3);
+    }
     const int tj = tile % p.tiles_j, ti = (tile / p.tiles_j) % p.tiles_i, b = tile / (p.tiles_j * p.tiles_i);
     const int i0 = ti * kFRows, j0 = tj * kFCols;
     const int px = lane & 15, oct = lane >> 4;
