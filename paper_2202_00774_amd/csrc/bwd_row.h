@@ -264,7 +264,8 @@ __global__ void __launch_bounds__(512) bwd_row(const RowParams p) {
     };
 
     // rank / prune / compress 64 items (pixel, 16-channel half) of a raw share into a halo buffer (Sec. III-B)
-    auto prune_items = [&](int item0, int nitems, int u0, uint32_t raw, uint32_t abuf, uint32_t mbuf, uint32_t chan0) {
+    // (inlined by force: as a function it would take everything it uses by address, the kernel's arguments included)
+    auto prune_items = [&](int item0, int nitems, int u0, uint32_t raw, uint32_t abuf, uint32_t mbuf, uint32_t chan0) __attribute__((always_inline)) {
         if constexpr (PRUNES && !SPARSE) {
             // any n of m (m up to 32): the pruned pixels are stored dense, zeros in the dropped positions, in the
             // layout the dense matrix instruction reads.  A 32-group is the whole chunk of a pixel: the lane of its
@@ -516,7 +517,8 @@ __global__ void __launch_bounds__(512) bwd_row(const RowParams p) {
                 }
             }
         };
-        if (wave < 4) prune_share();
+        constexpr bool kOneSite = M > 16;   // (the 32-key ranker is too long to be there twice)
+        if (kOneSite || wave < 4) prune_share();
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
@@ -528,7 +530,7 @@ __global__ void __launch_bounds__(512) bwd_row(const RowParams p) {
             const bool entries_now = has_next && ks == 0 && tap + 1 < TS && NKS > 1;   // read the next tap's entries early
             const bool new_tap = has_next && ntap != tap;
             if (q == 1) {
-                if (wave >= 4) prune_share();
+                if (!kOneSite && wave >= 4) prune_share();
                 __builtin_amdgcn_sched_barrier(0);
             }
             // pieces: 0 table entries; 1..APIECES A fragments (two row tiles each); then TN B fragments;
