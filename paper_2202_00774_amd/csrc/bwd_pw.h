@@ -84,7 +84,7 @@ struct PwLayout {
 // what a tap outside the gradient copies (one 64-byte chunk row)
 __device__ __align__(64) const uint32_t kPwZeros[16] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 
-template <int BN, int MODE, int M, int RK, int ROWS, int NW, bool GATHER>
+template <int BN, int MODE, int M, int RK, int ROWS, int NW, bool GATHER, bool TAIL>
 __device__ __forceinline__ void bwd_pw_body(const PwParams& p) {
     using L = PwLayout<BN, MODE, ROWS>;
     static_assert(L::total() <= 160 * 1024, "LDS budget");
@@ -129,7 +129,12 @@ __device__ __forceinline__ void bwd_pw_body(const PwParams& p) {
     const int ntile = lid % p.ntiles_n;
     const long long m0 = (long long)(lid / p.ntiles_n) * ROWS;
     const int n0 = ntile * BN;
-    const int nchunks = p.C_out / KC;
+    // TAIL: C_out is a multiple of 8 but not of the chunk; the last chunk's missing channels and W rows are copied from zeros.
+    // One test per chunk picks the copies that look for them.  (In the kernel for whole chunks that test cost 1 to 7 percent.)
+    static_assert(!(TAIL && PRE), "the compressed gradient comes in whole chunks");
+    const int nchunks = TAIL ? (p.C_out + KC - 1) / KC : p.C_out / KC;
+    const int tail = TAIL ? p.C_out % KC : 0;
+    auto is_short = [&](int chunk) { return TAIL && chunk == nchunks - 1; };
     const int nstages = GATHER ? nchunks * p.ntaps : nchunks;   // reduction steps: (tap, chunk), the chunks of a tap in a row
     const long long last_row = p.rows - 1;
     const long long last_pix = (long long)p.rows_dO - 1;
@@ -175,19 +180,24 @@ __device__ __forceinline__ void bwd_pw_body(const PwParams& p) {
         w_base = gWb + ((size_t)row * wrowB + (size_t)col * 2u);
     }
     // unit wave + j * NW of reduction step `st` into the buffer that starts at `dst`
-    auto copy_a_j = [&](int j, int st, uint32_t dst) {
+    auto copy_a_j = [&](int j, int st, uint32_t dst, auto short_chunk) {
+        constexpr bool kShort = decltype(short_chunk)::value;
         const int u = wave + j * NW;
         if constexpr (!GATHER) {
-            lds_copy16(a_base[j] + (size_t)st * 64u, dst + (uint32_t)u * 1024u);
+            const unsigned char* a = a_base[j] + (size_t)st * 64u;
+            if (kShort && (int)c16_a >= tail * 2) a = reinterpret_cast<const unsigned char*>(kPwZeros);
+            lds_copy16(a, dst + (uint32_t)u * 1024u);
         } else {
             const int t = tap_of(st), chunk = st - t * nchunks;
             const int src = t == 0 ? a_src[j][0] : t == 1 ? a_src[j][1] : t == 2 ? a_src[j][2] : a_src[j][3];
             const unsigned char* a = src >= 0 ? gdO + ((size_t)src * rowB + (size_t)chunk * 64u + c16_a)
                                               : reinterpret_cast<const unsigned char*>(kPwZeros) + c16_a;
+            if (kShort && (int)c16_a >= tail * 2) a = reinterpret_cast<const unsigned char*>(kPwZeros);
             lds_copy16(a, dst + (uint32_t)u * 1024u);
         }
     };
-    auto w_src_j = [&](int j, int st) {
+    auto w_src_j = [&](int j, int st, auto short_chunk) {
+        if (decltype(short_chunk)::value && wave * RPU + lane / CPR + j * (NW * RPU) >= tail) return reinterpret_cast<const unsigned char*>(kPwZeros);
         if constexpr (!GATHER) {
             return w_base + ((size_t)j * w_unit_step + (size_t)st * w_chunk_step);
         } else {
@@ -202,8 +212,13 @@ __device__ __forceinline__ void bwd_pw_body(const PwParams& p) {
     constexpr int WPW = WU / NW;   // W units per wavefront and chunk
     u32x4_t wreg[WPW];
     auto fetch_w = [&](int st) {
+        if (is_short(st - tap_of(st) * nchunks)) {
 #pragma unroll
-        for (int j = 0; j < WPW; ++j) wreg[j] = *reinterpret_cast<const u32x4_t*>(w_src_j(j, st));
+            for (int j = 0; j < WPW; ++j) wreg[j] = *reinterpret_cast<const u32x4_t*>(w_src_j(j, st, std::true_type{}));
+        } else {
+#pragma unroll
+            for (int j = 0; j < WPW; ++j) wreg[j] = *reinterpret_cast<const u32x4_t*>(w_src_j(j, st, std::false_type{}));
+        }
     };
     auto store_w = [&](int set) {
 #pragma unroll
@@ -222,11 +237,29 @@ __device__ __forceinline__ void bwd_pw_body(const PwParams& p) {
             m_base[j] = p.meta + ((size_t)row * 8u + (uint32_t)(lane & 1) * 4u);
         }
     }
+    auto copy_a_chunk = [&](int st, uint32_t dst) {
+        if (is_short(st - tap_of(st) * nchunks)) {
+#pragma unroll
+            for (int j = 0; j < APW; ++j) copy_a_j(j, st, dst, std::true_type{});
+        } else {
+#pragma unroll
+            for (int j = 0; j < APW; ++j) copy_a_j(j, st, dst, std::false_type{});
+        }
+    };
+    auto copy_w_chunk = [&](int chunk, int set) {
+        const uint32_t dst = smem_base + L::off_w() + set * L::kWSlab + (uint32_t)wave * 1024u;
+        if (is_short(chunk - tap_of(chunk) * nchunks)) {
+#pragma unroll
+            for (int j = 0; j < WPW; ++j) lds_copy16(w_src_j(j, chunk, std::true_type{}), dst + (uint32_t)(j * NW) * 1024u);
+        } else {
+#pragma unroll
+            for (int j = 0; j < WPW; ++j) lds_copy16(w_src_j(j, chunk, std::false_type{}), dst + (uint32_t)(j * NW) * 1024u);
+        }
+    };
     // everything chunk `chunk` needs, into buffer set `set` (pruning: the gradient goes to raw slot `set`)
     auto copy_chunk = [&](int chunk, int set, bool with_w) {
         const uint32_t a_dst = smem_base + (PRUNES ? L::off_raw() + set * L::kRawBytes : L::off_a() + set * L::kABytes);
-#pragma unroll
-        for (int j = 0; j < APW; ++j) copy_a_j(j, chunk, a_dst);
+        copy_a_chunk(chunk, a_dst);
         if constexpr (PRE) {
             static_assert((ROWS / 32) % NW == 0, "every wavefront copies the same number of position units");
 #pragma unroll
@@ -245,16 +278,7 @@ __device__ __forceinline__ void bwd_pw_body(const PwParams& p) {
                 }
             }
         }
-        if (with_w) {
-#pragma unroll
-            for (int j = 0; j < WPW; ++j)
-                lds_copy16(w_src_j(j, chunk), smem_base + L::off_w() + set * L::kWSlab + (uint32_t)(wave + j * NW) * 1024u);
-        }
-    };
-    auto copy_w_chunk = [&](int chunk, int set) {
-#pragma unroll
-        for (int j = 0; j < WPW; ++j)
-            lds_copy16(w_src_j(j, chunk), smem_base + L::off_w() + set * L::kWSlab + (uint32_t)(wave + j * NW) * 1024u);
+        if (with_w) copy_w_chunk(chunk, set);
     };
 
     // rank / prune / compress raw slot `set` (chunk `chunk`) into gradient buffer `set`: ROWS * 2 items of 16 channels
@@ -503,9 +527,7 @@ __device__ __forceinline__ void bwd_pw_body(const PwParams& p) {
         if constexpr (PRUNES) {
             if (s + 1 < nstages) copy_w_chunk(s + 1, set ^ 1);
             if (s + 2 < nstages) {
-                const uint32_t a_dst = smem_base + L::off_raw() + set * L::kRawBytes;
-#pragma unroll
-                for (int j = 0; j < APW; ++j) copy_a_j(j, s + 2, a_dst);
+                copy_a_chunk(s + 2, smem_base + L::off_raw() + set * L::kRawBytes);
             }
         } else {
             if (s + SETS - 1 < nstages) {
@@ -612,9 +634,9 @@ __device__ __forceinline__ void bwd_pw_body(const PwParams& p) {
 }
 
 // One problem per launch.
-template <int BN, int MODE, int M, int RK, int ROWS, int NW, bool GATHER>
+template <int BN, int MODE, int M, int RK, int ROWS, int NW, bool GATHER, bool TAIL>
 __global__ void __launch_bounds__(NW * 64) bwd_pw(const PwParams p) {
-    bwd_pw_body<BN, MODE, M, RK, ROWS, NW, GATHER>(p);
+    bwd_pw_body<BN, MODE, M, RK, ROWS, NW, GATHER, TAIL>(p);
 }
 
 // The parity classes of one strided filter in one launch: blockIdx.y is the class, blockIdx.x the tile of that class
@@ -627,11 +649,11 @@ struct PwClasses {
 
 static_assert(sizeof(PwClasses) <= 4096, "kernel arguments");
 
-template <int BN, int MODE, int M, int RK, int ROWS, int NW>
+template <int BN, int MODE, int M, int RK, int ROWS, int NW, bool TAIL>
 __global__ void __launch_bounds__(NW * 64) bwd_pw_classes(const PwClasses all) {
     const PwParams& p = all.c[blockIdx.y];
     if ((int)blockIdx.x >= p.nblocks) return;
-    bwd_pw_body<BN, MODE, M, RK, ROWS, NW, true>(p);
+    bwd_pw_body<BN, MODE, M, RK, ROWS, NW, true, TAIL>(p);
 }
 
 }  // namespace sdgp

@@ -1,5 +1,5 @@
 // Host side of the pointwise kernel: 1x1 convolutions without padding (any stride) and linear layers whose channel
-// counts fit (C_out a multiple of 32, C_in a multiple of 8); chooses the tile shape and launches.
+// counts fit (both multiples of 8); chooses the tile shape and launches.
 #include <climits>
 
 #include "bwd_pw_launch.h"
@@ -71,12 +71,12 @@ int launch_pw_classes_any(const PwClasses& all, int ncls, int mode, int m, int s
 // gradient row is ranked once per 256 columns; dense: 128 x 128 tiles measured fastest (column tiles of one row tile
 // run side by side on one XCD and find the gradient rows in its L2).
 int pw_shape(int mode, int64_t C_in, int64_t C_out) {
-    if (C_in <= 64) return 3;   // 128 x 64: 256-row tiles measured the same or slower (fewer workgroups, a longer last round)
+    if (C_in <= 64) return 2;   // 128 x 64: 256-row tiles measured the same or slower (fewer workgroups, a longer last round)
     if (mode != 0 && C_in > 128 && C_out > 64) return 0;   // (64 channels to rank: ranking them per 128 columns costs less than the third workgroup per CU gains)
     return 1;
 }
 // Tile shape when the gradient arrives compressed (nothing is ranked in the kernel): the dense kernel's.
-int pw_pre_shape(int64_t C_in) { return C_in <= 64 ? 3 : 1; }
+int pw_pre_shape(int64_t C_in) { return C_in <= 64 ? 2 : 1; }
 
 // Whether a pass that ranks and compresses the gradient first (csrc/compress.hip) pays: the fused kernel would rank
 // every gradient element `times` times, the pass reads it once and writes half of it, and the product that follows
@@ -99,12 +99,15 @@ int pw_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R
             int rk, PwPlan& out, int force_shape = -1) {
     const int mode = pw_mode(n, m);
     if (mode < 0) return 1;
-    if (R != 1 || S != 1 || stride < 1 || stride > 255 || pad != 0 || (C_out % kPwKC) != 0 || (C_in % 8) != 0) return 1;
+    if (R != 1 || S != 1 || stride < 1 || stride > 255 || pad != 0 || (C_out % 8) != 0 || (C_in % 8) != 0) return 1;
     if (mode != 0 && (C_out % m) != 0) return 1;
     const int64_t P = (H - 1) / stride + 1, Q = (Wd - 1) / stride + 1;  // gradient image
     const int64_t rows = B * P * Q;
     if (stride > 1 && (B * H * Wd >= INT_MAX || H < 1 || Wd < 1)) return 1;
-    if (rows < 1 || C_out < kPwKC || C_in < 8 || C_out >= (1 << 24) || C_in >= (1 << 24)) return 1;
+    if (rows < 1 || C_out < 8 || C_in < 8 || C_out >= (1 << 24) || C_in >= (1 << 24)) return 1;
+
+    // (the random ranker's sixteen channels of a short chunk must not straddle a carry into the index's high word)
+    if (rk == kRandom && mode != 0 && C_out % 16 != 0 && rows > (int64_t)0xFFFFFFFFu / C_out) return 1;
 
     PwParams p{};
     p.rows = rows, p.C_out = (int)C_out, p.C_in = (int)C_in, p.idx_pitch = (int)C_out;
@@ -199,10 +202,10 @@ int bwd_pw_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H,
                   hipStream_t stream) {
     if (!is_aligned16(dO) || !is_aligned16(W) || !is_aligned16(dD)) return 1;
     PadPlan padded{};
-    if (pad_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, padded)) {
-        if (workspace == nullptr || workspace_bytes < padded.bytes || !is_aligned16(workspace)) return 1;  // another kernel takes it
+    if (pad_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, padded) && workspace != nullptr && workspace_bytes >= padded.bytes &&
+        is_aligned16(workspace)) {
         PwPlan plan{};
-        const int shape = 3;   // 128 x 64 tiles, the most workgroups: these problems are small
+        const int shape = 2;   // 128 x 64 tiles, the most workgroups: these problems are small
         if (pw_plan(1, 1, padded.rows, C_in, padded.Kp, 1, 1, 1, 0, n, m, rk, plan, shape) != 0) return 1;
         PwParams& p = plan.p;
         p.idx_pitch = (int)C_out;
@@ -267,13 +270,16 @@ int gather_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, i
     const int mode = pw_mode(n, m);
     if (mode < 0) return 1;
     if (stride < 2 || stride > 4 || R < stride || S < stride || R > 2 * stride || S > 2 * stride || pad < 0) return 1;
-    if (C_out < kPwKC || (C_out % kPwKC) != 0 || C_in < 8 || (C_in % 8) != 0) return 1;
+    if (C_out < 8 || (C_out % 8) != 0 || C_in < 8 || (C_in % 8) != 0) return 1;
     if (mode != 0 && (C_out % m) != 0) return 1;
     if (H + 2 * pad < R || Wd + 2 * pad < S || H < stride || Wd < stride) return 1;
     const int64_t P = (H + 2 * pad - R) / stride + 1, Q = (Wd + 2 * pad - S) / stride + 1;
     if (B < 1 || P < 1 || Q < 1 || P >= 65536 || Q >= 32768 || H >= 65536 || Wd >= 32768 || B * (P + 8) * (Q + 8) >= (1 << 30) || B * H * Wd >= INT_MAX ||
         C_out >= (1 << 20) || (int64_t)R * S * C_in >= (1 << 20))
         return 1;
+
+    // (the random ranker's sixteen channels of a short chunk must not straddle a carry into the index's high word)
+    if (mode != 0 && C_out % 16 != 0 && B * P * Q > (int64_t)0xFFFFFFFFu / C_out) return 1;
 
     PwParams base{};
     base.C_out = (int)C_out, base.C_in = (int)C_in, base.idx_pitch = (int)C_out;

@@ -52,6 +52,8 @@ struct RowParams {
     int ntiles_n, nblocks;
 };
 
+__device__ __align__(16) const uint32_t kRowZeros[4] = {0, 0, 0, 0};   // what a short last chunk lacks
+
 constexpr int kRowKC = 32;         // reduction channels per chunk
 constexpr int kRowTaps = 3;        // taps per stage (filter width)
 constexpr int kRowMaxRows = 3;
@@ -94,7 +96,7 @@ struct RowLayout {
     }
 };
 
-template <int BN, int MODE, int M, int RK, int ROWS>
+template <int BN, int MODE, int M, int RK, int ROWS, bool TAIL>
 __global__ void __launch_bounds__(512) bwd_row(const RowParams p) {
     using L = RowLayout<BN, MODE, ROWS>;
     static_assert(ROWS == 512 || ROWS == 256, "rows of a workgroup tile");
@@ -150,7 +152,11 @@ __global__ void __launch_bounds__(512) bwd_row(const RowParams p) {
     const int halo_hw = HTH * HTW;
     const int nhalo = p.TB * halo_hw;
     const int nunits = (nhalo + 15) >> 4;
-    const int nchunks = p.C_out / KC;
+    // TAIL: C_out is a multiple of 8 but not of the chunk; the last chunk's missing channels and W rows are copied from zeros.
+    // (3x3 208 -> 256 channels at 24x24, batch 94, 2:4 Magnitude: 128 us on bwd_tiled, 48 here.  The test for the last chunk in the
+    // kernel for whole chunks cost 1 to 7 percent.)
+    const int nchunks = TAIL ? (p.C_out + KC - 1) / KC : p.C_out / KC;
+    const int tail = TAIL ? p.C_out % KC : 0;
     const int nstages = R * nchunks;
     // every workgroup walks the chunks and the filter rows in its own rotation: the sum does not care, and the
     // workgroups of an XCD then ask its L2 for different W slabs at a given moment
@@ -243,24 +249,29 @@ __global__ void __launch_bounds__(512) bwd_row(const RowParams p) {
     const uint32_t chunkB = (uint32_t)KC * (uint32_t)p.w_row * 2u;  // ... of consecutive chunks
     // the three slabs of (physical chunk pc, physical filter row pr) into ring set `set`
     auto copy_w_set = [&](int pc, int pr, int set) {
+        const bool short_chunk = TAIL && pc == nchunks - 1;
         for (int i = wave; i < TS * WU; i += 8) {
             const int j = i / WU;
-            lds_copy16(gWb + ((size_t)pc * chunkB + (size_t)(pr * TS + j) * tapB), w_voff,
-                        smem_base + L::off_w() + (uint32_t)set * L::kWSet + (uint32_t)j * L::kWSlab + (uint32_t)(wave % WU) * 1024u);
+            const unsigned char* const src = gWb + ((size_t)pc * chunkB + (size_t)(pr * TS + j) * tapB);
+            const uint32_t dst = smem_base + L::off_w() + (uint32_t)set * L::kWSet + (uint32_t)j * L::kWSlab + (uint32_t)(wave % WU) * 1024u;
+            if (short_chunk) lds_copy16((wave % WU) * RPU + lane / CPR < tail ? src + w_voff : reinterpret_cast<const unsigned char*>(kRowZeros), dst);
+            else lds_copy16(src, w_voff, dst);
         }
     };
     // 16-byte column a lane copies: LDS position (lane & 3) of pixel (lane >> 2) holds the swizzled source column
     const uint32_t c16_halo = PRUNES ? (uint32_t)(((lane & 3) ^ ((lane >> 4) & 1)) * 16)
                                      : (uint32_t)(((lane & 3) ^ ((lane >> 4) & 3)) * 16);
     const uint32_t haloaddr_lane = (uint32_t)L::off_haloaddr() + (uint32_t)(lane >> 2) * 8u;
-    // unit u of the halo, channels at byte offset src_off of every pixel, to LDS address dst
-    auto copy_halo = [&](int u, uint32_t src_off, uint32_t dst) {
-        const u64_t a = *(SDGP_LDS u64_t*)(smem + haloaddr_lane + (uint32_t)u * 128u);
-        lds_copy16(reinterpret_cast<const void*>((uintptr_t)(a + (u64_t)(c16_halo + src_off))), dst);
-    };
-    // up to two units per wavefront of the share [u0, u0 + cnt) of a chunk's halo; unit u0 + i lands at dst0 + i KB
+    // up to two units per wavefront of the share [u0, u0 + cnt) of chunk pc's halo; unit u0 + i lands at dst0 + i KB
     auto copy_halo_share = [&](int u0, int cnt, int pc, uint32_t dst0) {
-        for (int i = wave; i < cnt; i += 8) copy_halo(u0 + i, (uint32_t)pc * (KC * 2), dst0 + (uint32_t)i * 1024u);
+        const bool short_chunk = TAIL && pc == nchunks - 1;
+        const uint32_t src_off = c16_halo + (uint32_t)pc * (KC * 2);
+        for (int i = wave; i < cnt; i += 8) {
+            const u64_t a = *(SDGP_LDS u64_t*)(smem + haloaddr_lane + (uint32_t)(u0 + i) * 128u);
+            const void* src = reinterpret_cast<const void*>((uintptr_t)(a + (u64_t)src_off));
+            if (short_chunk) src = (int)c16_halo < tail * 2 ? src : reinterpret_cast<const void*>(kRowZeros);
+            lds_copy16(src, dst0 + (uint32_t)i * 1024u);
+        }
     };
 
     // rank / prune / compress 64 items (pixel, 16-channel half) of a raw share into a halo buffer (Sec. III-B)
@@ -362,7 +373,7 @@ __global__ void __launch_bounds__(512) bwd_row(const RowParams p) {
     const int pc1 = c_rot + 1 == nchunks ? 0 : c_rot + 1;  // physical chunk of logical chunk 1
     copy_w_set(c_rot, r_rot, 0);
     if constexpr (!PRUNES) {
-        for (int u = wave; u < nunits; u += 8) copy_halo(u, (uint32_t)c_rot * (KC * 2), smem_base + off_a + u * 1024);
+        copy_halo_share(0, nunits, c_rot, smem_base + off_a);
         build_row_tables();
     } else {
         // rounds of 16 units through the two raw slots: round r + 1 is in flight while round r is ranked

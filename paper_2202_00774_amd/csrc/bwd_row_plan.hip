@@ -64,12 +64,14 @@ int bwd_row_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H
     else if (n <= 2 && (m == 4 || m == 8 || m == 16)) mode = 2;
     else if (m == 4 || m == 8 || m == 16 || m == 32) mode = 1;
     else return 1;
-    if (stride != 1 || S != kRowTaps || R < 1 || R > kRowMaxRows || (C_out % kRowKC) != 0 || (C_in % 8) != 0) return 1;
+    if (stride != 1 || S != kRowTaps || R < 1 || R > kRowMaxRows || C_out < 8 || (C_out % 8) != 0 || (C_in % 8) != 0) return 1;
     if (mode != 0 && (C_out % m) != 0) return 1;
     if (!is_aligned16(dO) || !is_aligned16(W) || !is_aligned16(dD)) return 1;
     const int ntaps = R * S;
     const int64_t P = H + 2 * pad - R + 1, Q = Wd + 2 * pad - S + 1;
     if (P < 1 || Q < 1 || pad < 0) return 1;
+    // (the random ranker's sixteen channels of a short chunk must not straddle a carry into the index's high word)
+    if (rk == kRandom && mode != 0 && C_out % 16 != 0 && B * P * Q > (int64_t)(0xFFFFFFFFu) / C_out) return 1;
     if (B * P * Q >= INT_MAX || B * H * Wd >= INT_MAX || (int64_t)ntaps * C_in >= (1 << 24) ||
         C_out * (int64_t)ntaps * C_in >= (1 << 30) || C_out >= INT_MAX / 2)
         return 1;

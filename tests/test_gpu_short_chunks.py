@@ -1,0 +1,70 @@
+"""bf16 backward data on C_out that is a multiple of 8 but not of the 32-channel chunk, on problems large enough for the
+row, pointwise and parity-class kernels: every remainder, every kind of ranker, and NaN next to the channels that are missing.
+
+Tolerance: the tests of the other bf16 kernels, 1e-2 of sum |a||w| (one rounding to bf16 shows 2^-9)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2202_00774_amd as sdgp
+from paper_2202_00774_amd import workloads as wl
+from util import rel_error, to_gpu, to_host
+
+pytestmark = pytest.mark.gpu
+
+KINDS = {  # B, H, Wd, C_in and R, S, stride, pad: enough tiles for the kernel named
+    "row_256": ((150, 16, 16, 72), (3, 3, 1, 1)),
+    "row_64": ((300, 9, 9, 40), (3, 3, 1, 1)),
+    "pointwise": ((1100, 13, 13, 136), (1, 1, 1, 0)),       # (past the limit of the padded copies)
+    "pointwise_strided": ((300, 20, 20, 64), (1, 1, 2, 0)),
+    "classes": ((60, 28, 28, 136), (3, 3, 2, 1)),
+}
+PATTERNS = [(2, 4, oracle.RANDOM), (1, 4, oracle.GREEDY_ADJUSTED), (2, 8, oracle.GREEDY), (4, 8, oracle.RANDOM), (3, 4, oracle.GREEDY),
+            (8, 8, oracle.GREEDY)]
+
+
+def run(kind, C_out, n, m, ranker, dO=None, seed=21):
+    at, rest = KINDS[kind]
+    layer = wl.ConvLayer("t", *at, C_out, *rest)
+    if dO is None:
+        dO = wl.laplace_with_zeros(layer.dO_shape, 1e-3, 0.3, seed=seed, dtype=wl.BF16)
+    W = wl.normal(layer.W_shape, 0.1, seed + 1, wl.BF16)
+    pixels = np.random.default_rng(2).choice(layer.B * layer.H * layer.Wd, 3000, replace=False)
+    pixels.sort()
+    pruned = oracle.prune(dO, n, m, ranker, seed=seed)[0]
+    ref, ab = oracle.conv_bwd_data(pruned, W, layer.H, layer.Wd, layer.stride, layer.pad, pixels=pixels)
+    out = sdgp.sdgp_conv_bwd_data(to_gpu(dO), to_gpu(W), layer.H, layer.Wd, layer.stride, layer.pad, n, m, ranker, seed)
+    return layer, wl.to_f64(to_host(out.reshape(-1, layer.C_in)[torch.from_numpy(pixels).to(out.device)])), ref, ab
+
+
+@pytest.mark.parametrize("n,m,ranker", PATTERNS)
+@pytest.mark.parametrize("C_out", [40, 56, 72, 8])
+@pytest.mark.parametrize("kind", sorted(KINDS))
+def test_remainders(kind, C_out, n, m, ranker):
+    _, got, ref, ab = run(kind, C_out, n, m, ranker)
+    assert rel_error(got, ref, ab) <= 1e-2
+    assert np.all(got[ab == 0] == 0)
+
+
+@pytest.mark.parametrize("n", [2, 5])
+@pytest.mark.parametrize("kind", sorted(KINDS))
+def test_half_a_chunk(kind, n):
+    """Groups of 16: the last chunk is one group."""
+    _, got, ref, ab = run(kind, 80, n, 16, oracle.GREEDY)
+    assert rel_error(got, ref, ab) <= 1e-2
+
+
+@pytest.mark.parametrize("n,m", [(8, 8), (2, 4)])
+@pytest.mark.parametrize("kind", sorted(KINDS))
+def test_nan_behind_the_last_channel(kind, n, m):
+    """What follows a pixel's last channel in memory is the next pixel's first one: a NaN there must stay there."""
+    at, rest = KINDS[kind]
+    layer = wl.ConvLayer("t", *at, 40, *rest)
+    dO = wl.laplace_with_zeros(layer.dO_shape, 1e-3, 0.0, seed=4, dtype=wl.BF16)
+    dO[1::2, :, :, 0] = 0x7FC0        # every second image; the images between them stay clean
+    _, got, ref, ab = run(kind, 40, n, m, oracle.GREEDY, dO)
+    clean = np.isfinite(ref)
+    assert clean.any() and not clean.all()
+    assert np.array_equal(np.isfinite(got), clean)
+    assert np.all(np.abs(got[clean] - ref[clean]) <= 1e-2 * ab[clean])
