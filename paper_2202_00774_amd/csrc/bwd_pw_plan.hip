@@ -67,13 +67,26 @@ int launch_pw_classes_any(const PwClasses& all, int ncls, int mode, int m, int s
 }
 
 // Tile shape of the fused and dense kernels.  Workgroups of four wavefronts, two or more to a CU, so that one's loads
-// and stores overlap the other's arithmetic.  Pruning: all of C_in (up to 256 columns) in one workgroup, so every
-// gradient row is ranked once per 256 columns; dense: 128 x 128 tiles measured fastest (column tiles of one row tile
-// run side by side on one XCD and find the gradient rows in its L2).
-int pw_shape(int mode, int64_t C_in, int64_t C_out) {
+// and stores overlap the other's arithmetic.  Dense: 128 x 128 tiles measured fastest (column tiles of one row tile run side
+// by side on one XCD and find the gradient rows in its L2).  Pruning: 256 columns, so that a gradient row is ranked once
+// per 256, or 128, of which two workgroups more fit a CU.  Time with 128 columns over that with 256, 1x1 layers:
+//   general n of m up to 16: 0.59-0.96 (424 and 960 columns 1.04, 1.08), whose kernel with 256 leaves one workgroup to a CU;
+//     Rescaled, up to 256 columns and C_out 1152 1.23;
+//   n <= 2: columns rounded up to 128 fewer than to 256 0.75-0.97, fewer than 128 tiles of 256 0.65-0.79; otherwise 0.89-1.32;
+//   groups of 32: 1.09-1.51, fewer than 64 tiles (which went elsewhere) 0.66.
+// Parity classes rank an element once per tap and column tile: 1.04-1.52, where fewer than 64 tiles went elsewhere 0.48-0.68.
+int pw_shape(int mode, int64_t C_in, int64_t C_out, int m, int rk, int64_t row_tiles, bool classes) {
     if (C_in <= 64) return 2;   // 128 x 64: 256-row tiles measured the same or slower (fewer workgroups, a longer last round)
-    if (mode != 0 && C_in > 128 && C_out > 64) return 0;   // (64 channels to rank: ranking them per 128 columns costs less than the third workgroup per CU gains)
-    return 1;
+    if (mode == 0 || C_in <= 128 || C_out <= 64) return 1;   // (64 channels to rank: ranking them per 128 columns costs less than the third workgroup per CU gains)
+    const int64_t wide = (C_in + 255) / 256;
+    if (row_tiles * wide < 64) return 1;
+    if (classes || m == 32 || (mode == 1 && rk == kAdjusted && wide == 1 && C_out > 512)) return 0;
+    return mode == 1 || (C_in + 127) / 128 < 2 * wide || row_tiles * wide < 128 ? 1 : 0;
+}
+// How many column tiles of the fused kernel would rank a gradient element, as the choice below counts them.
+int pw_times_ranked(int mode, int64_t C_in, int64_t C_out) {
+    const int bn = C_in <= 64 ? 64 : mode != 0 && C_in > 128 && C_out > 64 ? 256 : 128;
+    return (int)((C_in + bn - 1) / bn);
 }
 // Tile shape when the gradient arrives compressed (nothing is ranked in the kernel): the dense kernel's.
 int pw_pre_shape(int64_t C_in) { return C_in <= 64 ? 2 : 1; }
@@ -116,9 +129,8 @@ int pw_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R
     p.rows_dO = rows, p.gather = 0, p.ntaps = 1, p.w_taps = 1;
     if (stride > 1) p.by_image = fast_div((uint32_t)(P * Q)), p.by_line = fast_div((uint32_t)Q);   // (rows below 2^31 then)
 
-    int shape = force_shape >= 0 ? force_shape : pw_shape(mode, C_in, C_out);
-    const int fused_tiles_n = (int)((C_in + kPwShapes[shape].bn - 1) / kPwShapes[shape].bn);
-    out.pre = force_shape < 0 && pre_pays(mode, C_out, rows, fused_tiles_n, rk);
+    int shape = force_shape >= 0 ? force_shape : pw_shape(mode, C_in, C_out, m, rk, (rows + 127) / 128, false);
+    out.pre = force_shape < 0 && pre_pays(mode, C_out, rows, pw_times_ranked(mode, C_in, C_out), rk);
     if (out.pre) shape = pw_pre_shape(C_in);
     const int bn = kPwShapes[shape].bn, rows_per = kPwShapes[shape].rows;
     const int64_t blocks = ((rows + rows_per - 1) / rows_per) * ((C_in + bn - 1) / bn);
@@ -190,7 +202,7 @@ int bwd_pw_way(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, in
     if (pw_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, plan) != 0) return -1;
     if (!plan.pre) return 0;
     if (room >= plan.bytes) return 1;
-    const PwShape& shape = kPwShapes[pw_shape(plan.mode, C_in, C_out)];
+    const PwShape& shape = kPwShapes[pw_shape(plan.mode, C_in, C_out, m, rk, (plan.p.rows + 127) / 128, false)];
     return ((plan.p.rows + shape.rows - 1) / shape.rows) * ((C_in + shape.bn - 1) / shape.bn) < 64 ? -1 : 0;
 }
 
@@ -227,7 +239,7 @@ int bwd_pw_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H,
     if (pw_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, plan) != 0) return 1;
     if (plan.pre && (workspace == nullptr || workspace_bytes < plan.bytes || !is_aligned16(workspace))) {
         // no room for the compressed gradient: the fused kernel
-        const int shape = pw_shape(plan.mode, C_in, C_out);
+        const int shape = pw_shape(plan.mode, C_in, C_out, m, rk, (plan.p.rows + 127) / 128, false);
         const int bn = kPwShapes[shape].bn, rows_per = kPwShapes[shape].rows;
         const int64_t blocks = ((plan.p.rows + rows_per - 1) / rows_per) * ((C_in + bn - 1) / bn);
         if (blocks < 64 || blocks >= INT_MAX) return 1;
@@ -289,7 +301,8 @@ int gather_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, i
 
     // every tap of every class ranks the rows it reads: R * S times per gradient element and column tile
     out.pre = want_pre && pre_pays(mode, C_out, base.rows_dO, R * S, kRandom);
-    const int shape = out.pre ? pw_pre_shape(C_in) : pw_shape(mode, C_in, C_out);
+    const int64_t least_rows = B * (H / stride) * (Wd / stride);   // of the smallest class
+    const int shape = out.pre ? pw_pre_shape(C_in) : pw_shape(mode, C_in, C_out, m, kRandom, (least_rows + 127) / 128, true);
     const int bn = kPwShapes[shape].bn, rows_per = kPwShapes[shape].rows;
     base.ntiles_n = (int)((C_in + bn - 1) / bn);
 
