@@ -240,20 +240,38 @@ __device__ __forceinline__ void narrow_item_in_place(const NarrowParams& p, int 
     const int pp = pmin + hrow, qq = qmin + (hp - hrow * p.HQ);
     const int k = kc0 + part * 16;
     const int sw = (hp >> 1) & 7;
-    SDGP_LDSN u32x4n* g0 = (SDGP_LDSN u32x4n*)(lds_a + hp * kMmRowB + (((2 * part) ^ sw) << 4));
-    SDGP_LDSN u32x4n* g1 = (SDGP_LDSN u32x4n*)(lds_a + hp * kMmRowB + (((2 * part + 1) ^ sw) << 4));
-    const u32x4n zero = {0u, 0u, 0u, 0u};
-    if (!(pp < p.P && qq < p.Q) || k >= p.C_out) {
-        *g0 = zero;
-        *g1 = zero;
-    } else if (PRUNE || k + 8 >= p.C_out) {
-        u32x4n v[2] = {*g0, k + 8 < p.C_out ? *g1 : zero};
-        if constexpr (PRUNE) {
+    if constexpr (PRUNE && M == 32) {   // one group is two items: the lane of the first takes both (C_out is a multiple of 32)
+        if (part & 1) return;
+        u32x4n v[4];
+        SDGP_LDSN u32x4n* g[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) g[i] = (SDGP_LDSN u32x4n*)(lds_a + hp * kMmRowB + (((2 * part + i) ^ sw) << 4)), v[i] = *g[i];
+        if (!(pp < p.P && qq < p.Q) || k >= p.C_out) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = u32x4n{0u, 0u, 0u, 0u};
+        } else {
             const size_t gp = (size_t)(b * p.P + pp) * p.Q + qq;
-            prune16_dense<M, RK, NLE2>(v, p.n, p.mix, (uint64_t)gp * (uint64_t)p.C_out + (uint64_t)k);
+            prune32_dense<RK, NLE2>(v, p.n, p.mix, (uint64_t)gp * (uint64_t)p.C_out + (uint64_t)k);
         }
-        *g0 = v[0];
-        *g1 = v[1];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *g[i] = v[i];
+        return;
+    } else {
+        SDGP_LDSN u32x4n* g0 = (SDGP_LDSN u32x4n*)(lds_a + hp * kMmRowB + (((2 * part) ^ sw) << 4));
+        SDGP_LDSN u32x4n* g1 = (SDGP_LDSN u32x4n*)(lds_a + hp * kMmRowB + (((2 * part + 1) ^ sw) << 4));
+        const u32x4n zero = {0u, 0u, 0u, 0u};
+        if (!(pp < p.P && qq < p.Q) || k >= p.C_out) {
+            *g0 = zero;
+            *g1 = zero;
+        } else if (PRUNE || k + 8 >= p.C_out) {
+            u32x4n v[2] = {*g0, k + 8 < p.C_out ? *g1 : zero};
+            if constexpr (PRUNE) {
+                const size_t gp = (size_t)(b * p.P + pp) * p.Q + qq;
+                prune16_dense<M, RK, NLE2>(v, p.n, p.mix, (uint64_t)gp * (uint64_t)p.C_out + (uint64_t)k);
+            }
+            *g0 = v[0];
+            *g1 = v[1];
+        }
     }
 }
 
@@ -556,17 +574,26 @@ __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) 
         wait_lds_copies<0>();
         __syncthreads();
         if constexpr (PRUNE) {
-            for (int it = tid; it < kFPix * 2; it += kFThreads) {
-                const int hp = it >> 1, half = it & 1;
+            constexpr int kHalves = M == 32 ? 1 : 2;   // items of a pixel: 16 channels, or its chunk's group of 32
+            for (int it = tid; it < kFPix * kHalves; it += kFThreads) {
+                const int hp = it / kHalves, half = it % kHalves;
                 const int hr = (int)(((uint32_t)hp * kFColMagic) >> 16);
                 const int gi = i0 - 1 + hr, gj = j0 - 1 + (hp - hr * kFHaloCols);
                 if (gi >= 0 && gi < p.P && gj >= 0 && gj < p.Q) {
                     SDGP_LDSN u32x4n* g0 = (SDGP_LDSN u32x4n*)(smem + hp * kFPitch + half * 32);
-                    u32x4n v[2] = {g0[0], g0[1]};
                     const uint32_t gpix = (uint32_t)((b * p.P + gi) * p.Q + gj);   // (below 2^31)
-                    prune16_dense<M, RK, NLE2>(v, p.n, p.mix, (uint64_t)gpix * (uint32_t)p.C_out + (uint32_t)(kc * kFKC + half * 16));
-                    g0[0] = v[0];
-                    g0[1] = v[1];
+                    const uint64_t e0 = (uint64_t)gpix * (uint32_t)p.C_out + (uint32_t)(kc * kFKC + half * 16);
+                    if constexpr (M == 32) {
+                        u32x4n v[4] = {g0[0], g0[1], g0[2], g0[3]};
+                        prune32_dense<RK, NLE2>(v, p.n, p.mix, e0);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) g0[i] = v[i];
+                    } else {
+                        u32x4n v[2] = {g0[0], g0[1]};
+                        prune16_dense<M, RK, NLE2>(v, p.n, p.mix, e0);
+                        g0[0] = v[0];
+                        g0[1] = v[1];
+                    }
                 }
             }
             __syncthreads();
@@ -615,7 +642,7 @@ __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) 
 bool first2_fits(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n, int m) {
     if (R != 7 || S != 7 || stride != 2 || pad != 3 || C_in < 1 || C_in > 4 || C_out < kFKC || C_out % kFKC != 0) return false;
     if ((H & 1) || (Wd & 1) || H < 2 || Wd < 2) return false;
-    if (n != m && !(m == 4 || m == 8 || m == 16)) return false;
+    if (n != m && !(m == 4 || m == 8 || m == 16 || m == 32)) return false;
     const int64_t P = H / 2, Q = Wd / 2;   // (H + 6 - 7) / 2 + 1 for even H
     const int64_t tiles = B * ((P + kFRows - 1) / kFRows) * ((Q + kFCols - 1) / kFCols);
     return tiles > 0 && tiles < INT32_MAX && B * H * Wd < INT32_MAX && P * Q * C_out < ((int64_t)1 << 30);
@@ -1119,6 +1146,9 @@ int launch_narrow_rk(const NarrowParams& p, int rk, int nt, int grid, int lds, h
         if (rk == kGreedy) return launch_narrow_mm<M, kGreedy, true, NLE2>(p, grid, stream);
         return launch_narrow_mm<M, kAdjusted, true, NLE2>(p, grid, stream);
     }
+    if constexpr (M == 32) {
+        return SDGP_ERR_SHAPE;   // (the planner does not send them here)
+    } else {
 #define SDGP_NARROW(RKV)                                                                                              \
     {                                                                                                                 \
         auto kern = bwd_narrow<M, RKV, true, NLE2>;                                                                   \
@@ -1132,6 +1162,7 @@ int launch_narrow_rk(const NarrowParams& p, int rk, int nt, int grid, int lds, h
     else SDGP_NARROW(kAdjusted)
 #undef SDGP_NARROW
     return launch_status();
+    }
 }
 
 }  // namespace
@@ -1143,7 +1174,8 @@ namespace {
 int narrow_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n, int m,
                 NarrowParams& p, int64_t& grid, int& lds) {
     if (C_in < 1 || C_in > 4 || (C_out % 8) != 0) return 1;
-    if (n != m && !(m == 4 || m == 8 || m == 16)) return 1;
+    if (n != m && !(m == 4 || m == 8 || m == 16 || m == 32)) return 1;
+    if (m == 32 && C_out % 32 != 0) return 1;
     const int64_t P = (H + 2 * pad - R) / stride + 1, Q = (Wd + 2 * pad - S) / stride + 1;
     if (B * P * Q >= INT32_MAX || B * H * Wd >= INT32_MAX) return 1;
     p.B = (int)B, p.H = (int)H, p.Wd = (int)Wd, p.P = (int)P, p.Q = (int)Q, p.C_in = (int)C_in, p.C_out = (int)C_out;
@@ -1164,7 +1196,7 @@ int narrow_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, i
     p.nt = nt;
     p.nt_magic = nt > 0 ? (uint32_t)(65536 / nt + 1) : 0u;
     lds = ((npix * kAPitchN + 15) & ~15) + kNarrowKC * R * S * 16;
-    if (nt == 0 && lds > 160 * 1024) return 1;
+    if (nt == 0 && (lds > 160 * 1024 || (m == 32 && n != m))) return 1;   // (groups of 32: the matrix-core variant only)
     return SDGP_OK;
 }
 
@@ -1247,6 +1279,7 @@ int bwd_narrow_launch(const void* dO, const void* W, void* dD, int64_t B, int64_
         const bool le2 = n <= 2;
         if (m == 4) return le2 ? launch_first2_rk<4, true>(f, rk, stream) : launch_first2_rk<4, false>(f, rk, stream);
         if (m == 8) return le2 ? launch_first2_rk<8, true>(f, rk, stream) : launch_first2_rk<8, false>(f, rk, stream);
+        if (m == 32) return le2 ? launch_first2_rk<32, true>(f, rk, stream) : launch_first2_rk<32, false>(f, rk, stream);
         return le2 ? launch_first2_rk<16, true>(f, rk, stream) : launch_first2_rk<16, false>(f, rk, stream);
     }
     NarrowParams p{};
@@ -1278,6 +1311,7 @@ int bwd_narrow_launch(const void* dO, const void* W, void* dD, int64_t B, int64_
     const bool nle2 = n <= 2;
     if (m == 4) return nle2 ? launch_narrow_rk<4, true>(p, rk, nt, (int)grid, lds, stream) : launch_narrow_rk<4, false>(p, rk, nt, (int)grid, lds, stream);
     if (m == 8) return nle2 ? launch_narrow_rk<8, true>(p, rk, nt, (int)grid, lds, stream) : launch_narrow_rk<8, false>(p, rk, nt, (int)grid, lds, stream);
+    if (m == 32) return nle2 ? launch_narrow_rk<32, true>(p, rk, nt, (int)grid, lds, stream) : launch_narrow_rk<32, false>(p, rk, nt, (int)grid, lds, stream);
     return nle2 ? launch_narrow_rk<16, true>(p, rk, nt, (int)grid, lds, stream) : launch_narrow_rk<16, false>(p, rk, nt, (int)grid, lds, stream);
 }
 

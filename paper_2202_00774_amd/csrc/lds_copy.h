@@ -90,4 +90,25 @@ __device__ __forceinline__ void prune16_dense(u32x4_t (&v)[2], int n, uint32_t m
         for (int x = 0; x < 4; ++x) v[i][x] = out[i * 8 + 2 * x] | (out[i * 8 + 2 * x + 1] << 16);
 }
 
+// Thirty-two channels of one gradient pixel that form one group, likewise.
+template <int RK, bool NLE2>
+__device__ __forceinline__ void prune32_dense(u32x4_t (&v)[4], int n, uint32_t mix, uint64_t e0) {
+    if constexpr (RK != kRandom) {
+        uint32_t w[16], o[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) w[i] = v[i >> 2][i & 3];
+        prune_packed<32, RK>(w, n, o);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = u32x4_t{o[4 * i], o[4 * i + 1], o[4 * i + 2], o[4 * i + 3]};
+    } else {
+        uint32_t raw[32], out[32];
+        bool keep[32];
+#pragma unroll
+        for (int i = 0; i < 32; ++i) raw[i] = (i & 1) ? v[i >> 3][(i >> 1) & 3] >> 16 : v[i >> 3][(i >> 1) & 3] & 0xFFFFu;
+        prune_group<kBF16, 32, RK, NLE2>(raw, n, hash_row(mix, (uint32_t)(e0 >> 32)), (uint32_t)e0, keep, out);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i >> 2][i & 3] = out[2 * i] | (out[2 * i + 1] << 16);
+    }
+}
+
 }  // namespace sdgp

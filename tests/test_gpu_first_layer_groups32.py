@@ -1,0 +1,43 @@
+"""First layers (up to four input channels) pruned in groups of 32, on the matrix-core kernels, against the CPU oracle: the
+7x7 stem, sizes and filters it does not fit, every ranker, with and without the workspace, which these calls can do without.
+
+Tolerance: the tests of the other bf16 kernels, 1e-2 of sum |a||w|."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2202_00774_amd as sdgp
+from paper_2202_00774_amd import workloads as wl
+from util import rel_error, to_gpu, to_host
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(2, 36, 68, 3, 64, 7, 7, 2, 3), (2, 35, 33, 3, 64, 7, 7, 2, 3), (3, 20, 18, 3, 64, 3, 3, 1, 1), (3, 17, 21, 4, 96, 3, 3, 1, 1),
+          (2, 12, 12, 1, 32, 5, 5, 1, 2)]
+
+
+@pytest.mark.parametrize("ranker", (oracle.RANDOM, oracle.GREEDY, oracle.GREEDY_ADJUSTED))
+@pytest.mark.parametrize("n", [1, 2, 4, 16, 31])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_matches_oracle(shape, n, ranker):
+    L = wl.ConvLayer("f", *shape)
+    dO = wl.laplace_with_zeros(L.dO_shape, 1e-3, 0.3, seed=3 + n, dtype=wl.BF16)
+    W = wl.normal(L.W_shape, 0.1, 4, wl.BF16)
+    ref, ab = oracle.conv_bwd_data(oracle.prune(dO, n, 32, ranker, seed=11)[0], W, L.H, L.Wd, L.stride, L.pad)
+    g, w = to_gpu(dO), to_gpu(W)
+    out = sdgp.sdgp_conv_bwd_data(g, w, L.H, L.Wd, L.stride, L.pad, n, 32, ranker, 11)
+    got = wl.to_f64(to_host(out))
+    assert rel_error(got, ref, ab) <= 1e-2
+    assert np.all(got[ab == 0] == 0)
+    # none, and one too small to be written to
+    small = torch.full((64,), 7, dtype=torch.uint8, device="cuda")
+    for ptr, size in ((None, 0), (small.data_ptr(), 16)):
+        bare = torch.empty_like(out)
+        rc = sdgp.binding.load().sdgp_conv_bwd_data(g.data_ptr(), w.data_ptr(), bare.data_ptr(), L.B, L.H, L.Wd, L.C_in, L.C_out, L.R, L.S, L.stride,
+                                                    L.pad, sdgp.BF16, n, 32, ranker, 11, ptr, size, torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        assert rel_error(wl.to_f64(to_host(bare)), ref, ab) <= 1e-2
+    assert torch.all(small == 7)
+    sdgp.sdgp_conv_bwd_data_noalloc(g, w, L.H, L.Wd, L.stride, L.pad, n, 32, ranker, 11, bare)
+    assert rel_error(wl.to_f64(to_host(bare)), ref, ab) <= 1e-2
