@@ -142,7 +142,8 @@ int sdgp_conv_bwd_data(const void* dO, const void* W, void* dD, int64_t B, int64
  *     pairs) asks for room for a re-indexed copy of the filter that one small kernel
  *     builds before the fused one: 20 KB per 32 output channels for a 7x7 stride-2
  *     filter with padding 3 on an image of even size, 23 KB per 64 output channels
- *     for other 7x7 layers on three channels.
+ *     for other 7x7 layers on three channels.  (Pruned with m = 32 it also runs
+ *     without, on a slower kernel.)
  *   - bf16 layers with n <= 2, m in {4, 8, 16} and C_out a multiple of 64 in which the
  *     fused kernel would rank a gradient element several times -- 1x1 filters with
  *     more than 256 input channels, strided filters up to 2*stride taps wide -- ask

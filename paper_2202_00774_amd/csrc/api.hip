@@ -20,7 +20,7 @@ int bwd_grouped_launch(const void* dO, const void* W, void* dD, int64_t B, int64
                        hipStream_t stream);
 int bwd_narrow_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in,
                       int64_t C_out, int R, int S, int stride, int pad, int n, int m, int rk, uint64_t seed,
-                      void* workspace, hipStream_t stream);
+                      void* workspace, size_t workspace_bytes, hipStream_t stream);
 size_t bwd_narrow_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride,
                             int pad, int n, int m);
 int bwd_pw_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
@@ -152,7 +152,7 @@ int bwd_dispatch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, 
     if (C_out == 0) return sdgp::bwd_simple_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m, rk, seed, stream);
     if (dt == SDGP_BF16 && C_in <= 4) {
         const int rc = sdgp::bwd_narrow_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, workspace,
-                                               stream);
+                                               workspace_bytes, stream);
         if (rc <= 0) return rc;
     }
     if (dt == SDGP_BF16 && sdgp::is_aligned16(dD)) {

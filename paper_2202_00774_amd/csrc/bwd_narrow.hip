@@ -4,7 +4,7 @@
 // (Sec. III-B; stored dense with zeros).  Four kernels (Fig. 3 left; bf16 storage, fp32 accumulation):
 //   * bwd_first_stream (further down), for 3x3 stride-1 padding-1 filters with 64 output channels on even images: the
 //     16-column product below, one wavefront streaming a strip of the image through a ring of gradient rows.
-//   * bwd_first2 (further down), for 7x7 stride-2 padding-3 filters on even images: a 2 x 2 block of input pixels and
+//   * bwd_first2 (further down), for 7x7 stride-2 padding-3 filters: a 2 x 2 block of input pixels and
 //     their channels are the 16 columns of one small product over a 4 x 4 window of gradient pixels.
 //   * bwd_narrow_mm, when the tile's (row tile, column tile) pairs and LDS fit (up to 7x7 filters on RGB): with so few columns per tap the product is turned around.  The matrix
 //     cores compute T[gradient pixel][tap, c] = sum_k prune(dL/dO)[pixel][k] W[k][tap][c] -- a plain GEMM with
@@ -439,7 +439,7 @@ __global__ void __launch_bounds__(256, 2) bwd_narrow_mm(const NarrowParams p) {
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// 7x7, stride 2, padding 3 on C_in <= 4 (the first layer of an ImageNet ResNet), even image sizes.
+// 7x7, stride 2, padding 3 on C_in <= 4 (the first layer of an ImageNet ResNet).
 //
 // An input pixel (2i + a, 2j + b) is reached by the taps r = a + 3 - 2 dp, s = b + 3 - 2 dq of the gradient pixels
 // (i + dp, j + dq), dp, dq in [-1, 2].  So the four pixels of a 2 x 2 block and their channels (padded to four) are the
@@ -478,9 +478,11 @@ static_assert(kFWRows * kFPitch % 1024 == 0, "V's chunk is whole copy units");
 
 struct FirstParams {
     const uint16_t* dO;
-    const unsigned char* vimg;   // [C_out / 32][kFWRows][kFPitch bytes]
+    const uint16_t* W;
+    const unsigned char* vimg;   // V through LDS: [C_out / 32][kFWRows][kFPitch bytes], else [C_out / 32][49][C_in][32 channels]
+    size_t room;                 // bytes behind vimg
     uint16_t* dD;
-    int B, P, Q, C_in, C_out;
+    int B, H, Wd, P, Q, C_in, C_out;
     int tiles_i, tiles_j;
     int n;
     uint32_t mix;
@@ -501,6 +503,15 @@ __global__ void __launch_bounds__(256) first_v_image(const uint16_t* __restrict_
             v = W[(((size_t)(kc * kFKC + kk) * 7 + r) * 7 + s2) * C_in + c];
         dst[e] = v;
     }
+}
+
+// The same filter for fragments that come from the L2: [chunk][tap][c][32 channels], V's zeros left out -- a fragment's
+// lanes know them -- which is half of V's bytes.
+__global__ void __launch_bounds__(256) first_v_taps(const uint16_t* __restrict__ W, uint16_t* __restrict__ img, int columns, int total) {
+    const int e = (int)blockIdx.x * 256 + (int)threadIdx.x;   // columns = 49 C_in
+    if (e >= total) return;
+    const int k = e / columns, col = e - k * columns;          // (reads in order)
+    img[((size_t)(k / kFKC) * columns + col) * kFKC + k % kFKC] = W[e];
 }
 
 typedef float f32x4f __attribute__((ext_vector_type(4)));
@@ -564,9 +575,27 @@ __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) 
         }
         bf16x8n vf[kFWin * kFWin];
         if constexpr (!VLDS) {
+            // column px = (a, b, c) of window (dp, dq) is tap (a + 3 - 2 dp, b + 3 - 2 dq) of channel c, or zero
 #pragma unroll
-            for (int t = 0; t < kFWin * kFWin; ++t)
-                vf[t] = __builtin_bit_cast(bf16x8n, *reinterpret_cast<const u32x4n*>(p.vimg + vlane + (size_t)(kc * kFWRows + t * 16) * kFPitch));
+            for (int t = 0; t < kFWin * kFWin; ++t) vf[t] = __builtin_bit_cast(bf16x8n, u32x4n{0u, 0u, 0u, 0u});
+            const int va = px >> 3, vb = (px >> 2) & 1, vc = px & 3;
+            const unsigned char* const at = p.vimg + ((size_t)(kc * 49 + (va + 3) * 7 + vb + 3) * p.C_in + vc) * (kFKC * 2) + oct * 16;
+            auto take = [&](int dpi, int dqi) {
+                vf[dpi * kFWin + dqi] = __builtin_bit_cast(bf16x8n, *reinterpret_cast<const u32x4n*>(at - (2 * (dpi - 1) * 7 + 2 * (dqi - 1)) * p.C_in * (kFKC * 2)));
+            };
+            if (vc < p.C_in) {
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) take(i, j);
+                if (va)
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) take(3, j);
+                if (vb)
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) take(i, 3);
+                if (va && vb) take(3, 3);
+            }
         } else {
             for (int u = wave; u < kFWUnits; u += 4)
                 lds_copy16(p.vimg + ((size_t)kc * kFWUnits + u) * 1024 + lane * 16, smem_base + (uint32_t)(kFABytes + u * 1024));
@@ -626,9 +655,9 @@ __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) 
     for (int ri = 0; ri < 4; ++ri)
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
-            const int i = i0 + 4 * rq + ri, j = j0 + 32 * gp + 16 * g + px;
-            if (i < p.P && j < p.Q) {
-                uint16_t* dst = p.dD + ((size_t)(b * 2 * p.P + 2 * i + a) * (2 * p.Q) + 2 * j + bb) * p.C_in;
+            const int h = 2 * (i0 + 4 * rq + ri) + a, w = 2 * (j0 + 32 * gp + 16 * g + px) + bb;
+            if (h < p.H && w < p.Wd) {   // (an odd size ends on half a block)
+                uint16_t* dst = p.dD + ((size_t)(b * p.H + h) * p.Wd + w) * p.C_in;
                 const uint32_t c01 = float2_to_bf16x2(acc[ri][g][0], acc[ri][g][1]), c23 = float2_to_bf16x2(acc[ri][g][2], acc[ri][g][3]);
                 dst[0] = (uint16_t)c01;
                 if (p.C_in > 1) dst[1] = (uint16_t)(c01 >> 16);
@@ -641,14 +670,15 @@ __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) 
 // Whether bwd_first2 takes the problem (everything but the workspace).
 bool first2_fits(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n, int m) {
     if (R != 7 || S != 7 || stride != 2 || pad != 3 || C_in < 1 || C_in > 4 || C_out < kFKC || C_out % kFKC != 0) return false;
-    if ((H & 1) || (Wd & 1) || H < 2 || Wd < 2) return false;
+    if (H < 2 || Wd < 2) return false;
     if (n != m && !(m == 4 || m == 8 || m == 16 || m == 32)) return false;
-    const int64_t P = H / 2, Q = Wd / 2;   // (H + 6 - 7) / 2 + 1 for even H
+    const int64_t P = (H + 1) / 2, Q = (Wd + 1) / 2;   // (H + 6 - 7) / 2 + 1
     const int64_t tiles = B * ((P + kFRows - 1) / kFRows) * ((Q + kFCols - 1) / kFCols);
     return tiles > 0 && tiles < INT32_MAX && B * H * Wd < INT32_MAX && P * Q * C_out < ((int64_t)1 << 30);
 }
 
 size_t first2_image_bytes(int64_t C_out) { return (size_t)(C_out / kFKC) * kFWRows * kFPitch; }
+size_t first2_taps_bytes(int64_t C_in, int64_t C_out) { return (size_t)C_out * 49 * (size_t)C_in * 2; }
 
 template <int M, int RK, bool PRUNE, bool NLE2, bool VLDS>
 int launch_first2_v(const FirstParams& p, hipStream_t stream) {
@@ -656,6 +686,10 @@ int launch_first2_v(const FirstParams& p, hipStream_t stream) {
     constexpr int lds = VLDS ? kFABytes + kFWRows * kFPitch : kFABytes;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return SDGP_ERR_HIP;
+    uint16_t* const img = reinterpret_cast<uint16_t*>(const_cast<unsigned char*>(p.vimg));
+    const int taps = 49 * p.C_in * p.C_out;
+    if (VLDS) hipLaunchKernelGGL(first_v_image, dim3((unsigned)(p.C_out / kFKC * 16)), dim3(256), 0, stream, p.W, img, p.C_in);
+    else hipLaunchKernelGGL(first_v_taps, dim3((unsigned)((taps + 255) / 256)), dim3(256), 0, stream, p.W, img, 49 * p.C_in, taps);
     hipLaunchKernelGGL(kern, dim3((unsigned)(p.B * p.tiles_i * p.tiles_j)), dim3(kFThreads), lds, stream, p);
     return launch_status();
 }
@@ -667,7 +701,7 @@ int launch_first2_v(const FirstParams& p, hipStream_t stream) {
 template <int M, int RK, bool PRUNE, bool NLE2>
 int launch_first2(const FirstParams& p, hipStream_t stream) {
     if constexpr (!PRUNE || RK == kAdjusted) {
-        if ((int64_t)p.B * p.tiles_i * p.tiles_j <= (PRUNE ? 512 : 1024)) return launch_first2_v<M, RK, PRUNE, NLE2, true>(p, stream);
+        if (p.room >= first2_image_bytes(p.C_out) && (int64_t)p.B * p.tiles_i * p.tiles_j <= (PRUNE ? 512 : 1024)) return launch_first2_v<M, RK, PRUNE, NLE2, true>(p, stream);
     }
     return launch_first2_v<M, RK, PRUNE, NLE2, false>(p, stream);
 }
@@ -1210,7 +1244,8 @@ size_t narrow_image_bytes(const NarrowParams& p) {
 
 }  // namespace
 
-// Workspace bytes bwd_narrow_launch wants for these arguments (0: none, also when another kernel takes the problem).
+// Workspace bytes bwd_narrow_launch wants for these arguments (0: none, also when another kernel takes the problem).  The
+// stem on odd sizes makes do with the other kernels' image size.
 size_t bwd_narrow_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride,
                             int pad, int n, int m) {
     NarrowParams p{};
@@ -1218,16 +1253,18 @@ size_t bwd_narrow_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int6
     int lds = 0;
     if (narrow_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, p, grid, lds) != SDGP_OK || grid == 0) return 0;
     const size_t image = narrow_image_bytes(p);
-    if (first2_fits(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m) && first2_image_bytes(C_out) > image) return first2_image_bytes(C_out);
+    if (((H | Wd) & 1) == 0 && first2_fits(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m) && first2_image_bytes(C_out) > image)
+        return first2_image_bytes(C_out);
     return image;
 }
 
-// SDGP_OK after launching, a positive value when the problem does not fit, or a negative sdgp_status.  workspace:
-// bwd_narrow_workspace(...) bytes, 16-byte aligned, or null (the kernel then gathers the filter itself).
+// SDGP_OK after launching, a positive value when the problem does not fit, or a negative sdgp_status.  workspace: room for
+// bwd_narrow_workspace(...) bytes, 16-byte aligned; with less another kernel, or one that gathers the filter itself.
 int bwd_narrow_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in,
                       int64_t C_out, int R, int S, int stride, int pad, int n, int m, int rk, uint64_t seed,
-                      void* workspace, hipStream_t stream) {
+                      void* workspace, size_t workspace_bytes, hipStream_t stream) {
     if (!is_aligned16(dO)) return 1;
+    const size_t room = workspace != nullptr && is_aligned16(workspace) ? workspace_bytes : 0;
     if (stream_fits(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m)) {
         StreamParams f{};
         f.dO = static_cast<const uint16_t*>(dO), f.W = static_cast<const uint16_t*>(W), f.dD = static_cast<uint16_t*>(dD);
@@ -1267,14 +1304,14 @@ int bwd_narrow_launch(const void* dO, const void* W, void* dD, int64_t B, int64_
         f.n = n, f.mix = seed_mix(seed);
         return launch_stem_stream<4, kGreedy, false, true>(f, stream);
     }
-    if (workspace != nullptr && is_aligned16(workspace) && B * H * Wd > 0 && first2_fits(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m)) {
+    if (B * H * Wd > 0 && room >= first2_taps_bytes(C_in, C_out) && first2_fits(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m)) {
         FirstParams f{};
         f.dO = static_cast<const uint16_t*>(dO), f.vimg = static_cast<const unsigned char*>(workspace), f.dD = static_cast<uint16_t*>(dD);
-        f.B = (int)B, f.P = (int)(H / 2), f.Q = (int)(Wd / 2), f.C_in = (int)C_in, f.C_out = (int)C_out;
+        f.B = (int)B, f.H = (int)H, f.Wd = (int)Wd, f.P = (int)((H + 1) / 2), f.Q = (int)((Wd + 1) / 2);
+        f.C_in = (int)C_in, f.C_out = (int)C_out;
         f.tiles_i = (f.P + kFRows - 1) / kFRows, f.tiles_j = (f.Q + kFCols - 1) / kFCols;
         f.n = n, f.mix = seed_mix(seed);
-        hipLaunchKernelGGL(first_v_image, dim3((unsigned)(C_out / kFKC * 16)), dim3(256), 0, stream, static_cast<const uint16_t*>(W),
-                           static_cast<uint16_t*>(workspace), (int)C_in);
+        f.W = static_cast<const uint16_t*>(W), f.room = room;
         if (n == m) return launch_first2<4, kGreedy, false, true>(f, stream);
         const bool le2 = n <= 2;
         if (m == 4) return le2 ? launch_first2_rk<4, true>(f, rk, stream) : launch_first2_rk<4, false>(f, rk, stream);
@@ -1292,7 +1329,7 @@ int bwd_narrow_launch(const void* dO, const void* W, void* dD, int64_t B, int64_
     const bool dense = n == m;
     const int nt = p.nt;
     const size_t image = narrow_image_bytes(p);
-    if (image > 0 && workspace != nullptr && is_aligned16(workspace)) {
+    if (image > 0 && room >= image) {
         p.wimg = static_cast<const unsigned char*>(workspace);
         p.wimg_units = narrow_image_units(nt);
         const int slices = (p.C_out + kNarrowKC - 1) / kNarrowKC;

@@ -1,5 +1,5 @@
-"""First layers (up to four input channels) pruned in groups of 32, on the matrix-core kernels, against the CPU oracle: the
-7x7 stem, sizes and filters it does not fit, every ranker, with and without the workspace, which these calls can do without.
+"""First layers (up to four input channels) against the CPU oracle: pruned in groups of 32, on the 7x7 stem and on sizes and
+filters it does not fit, with and without the workspace, which these calls can do without; the stem on odd image sizes.
 
 Tolerance: the tests of the other bf16 kernels, 1e-2 of sum |a||w|."""
 import numpy as np
@@ -41,3 +41,17 @@ def test_matches_oracle(shape, n, ranker):
     assert torch.all(small == 7)
     sdgp.sdgp_conv_bwd_data_noalloc(g, w, L.H, L.Wd, L.stride, L.pad, n, 32, ranker, 11, bare)
     assert rel_error(wl.to_f64(to_host(bare)), ref, ab) <= 1e-2
+
+
+@pytest.mark.parametrize("n,m,ranker", [(4, 4, oracle.GREEDY), (2, 4, oracle.RANDOM), (4, 8, oracle.GREEDY_ADJUSTED)])
+@pytest.mark.parametrize("H,Wd", [(35, 33), (36, 65), (31, 66), (34, 36), (7, 9), (3, 2)])
+@pytest.mark.parametrize("C_in", [1, 2, 3, 4])
+def test_stem_on_odd_sizes(C_in, H, Wd, n, m, ranker):
+    L = wl.ConvLayer("s", 2, H, Wd, C_in, 64, 7, 7, 2, 3)
+    dO = wl.laplace_with_zeros(L.dO_shape, 1e-3, 0.3, seed=3 + n, dtype=wl.BF16)
+    W = wl.normal(L.W_shape, 0.1, 4, wl.BF16)
+    ref, ab = oracle.conv_bwd_data(oracle.prune(dO, n, m, ranker, seed=11)[0], W, H, Wd, 2, 3)
+    g, w = to_gpu(dO), to_gpu(W)
+    out = torch.full((2, H, Wd, C_in), float("nan"), dtype=torch.bfloat16, device="cuda")
+    sdgp.sdgp_conv_bwd_data(g, w, H, Wd, 2, 3, n, m, ranker, 11, out=out)
+    assert rel_error(wl.to_f64(to_host(out)), ref, ab) <= 1e-2
