@@ -95,6 +95,11 @@ bool plan(SplitPlan& s, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t 
     const int ny = (R + stride - 1) / stride, nx = (S + stride - 1) / stride;
     const int64_t h = (H + stride - 1) / stride, w = (Wd + stride - 1) / stride;
     const int64_t classes = (int64_t)stride * stride;
+    // most small problems go by without the search for tiles, a microsecond or more of host time: the estimate is lowest with
+    // whole tiles of 256 rows, the cheaper step of 128 and the larger group of taps
+    s.rows = 128, s.np = 384;
+    const Estimates least = estimate(s, (B * h * w + 255) / 256, m);
+    if (least.split > 0.9 * least.plain) return false;
     // 384 positions leave room for two taps of compressed planes per stage, 512 for one
     int64_t tiles = plan_tiles(s, 256, 384, B, h, w, ny, nx);
     SplitPlan other = s;
