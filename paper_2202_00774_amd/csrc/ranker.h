@@ -560,13 +560,15 @@ __host__ __device__ __forceinline__ void prune_compress16_bf16(const uint32_t (&
     // position code is an inline constant and a key costs two instructions
     constexpr uint32_t kMark = (RK == kAdjusted) ? 0x200u : 0u;
     const bool two = n >= 2;
-    if constexpr (M == 4) {
+    // (one of four without the rescale is cheaper with the keys below, which then lose one survivor: 512 -> 96 channels at 49x49,
+    // batch 57, 44.0 us against 44.7 by the signs; with it, the signs' 42.6 against 43.3)
+    if (M == 4 && (RK == kAdjusted || two)) {   // (n is uniform over the wavefront)
         uint32_t code[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) code[q] = rank_2of4_magnitude(w[2 * q], w[2 * q + 1]);
         take_2of4(w, code, packed, meta);
         uint32_t mask[4] = {~0u, ~0u, ~0u, ~0u};
-        if (!two) {   // (n is uniform over the wavefront) the larger of a quad's two stays
+        if (RK == kAdjusted && !two) {   // the larger of a quad's two stays
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const uint32_t a = packed[q] & 0x7FFFu, b = (packed[q] >> 16) & 0x7FFFu;
@@ -604,8 +606,12 @@ __host__ __device__ __forceinline__ void prune_compress16_bf16(const uint32_t (&
         s[q] = sdgp_umax(sdgp_umax(sdgp_umin(hi, hi2), lo), lo2);
     }
     // drop what is below the group's threshold
+    if constexpr (M == 4) {
 #pragma unroll
-    for (int g = 0; g < 16 / M; ++g) {
+        for (int q = 0; q < 4; ++q) s[q] &= kCodeMask;
+    }
+#pragma unroll
+    for (int g = 0; M > 4 && g < 16 / M; ++g) {
         constexpr int QG = M / 4;  // quads per group
         uint32_t v1 = f[g * QG], v2 = s[g * QG];
 #pragma unroll
