@@ -70,18 +70,23 @@ int launch_pw_classes_any(const PwClasses& all, int ncls, int mode, int m, int s
 // and stores overlap the other's arithmetic.  Dense: 128 x 128 tiles measured fastest (column tiles of one row tile run side
 // by side on one XCD and find the gradient rows in its L2).  Pruning: 256 columns, so that a gradient row is ranked once
 // per 256, or 128, of which two workgroups more fit a CU.  Time with 128 columns over that with 256, 1x1 layers:
-//   general n of m up to 16: 0.59-0.96 (424 and 960 columns 1.04, 1.08), whose kernel with 256 leaves one workgroup to a CU;
+//   general n of m up to 16: 0.57-0.97 (424 and 960 columns 1.04, 1.08), whose kernel with 256 leaves one workgroup to a CU;
 //     Rescaled, up to 256 columns and C_out 1152 1.23;
-//   n <= 2: columns rounded up to 128 fewer than to 256 0.75-0.97, fewer than 128 tiles of 256 0.65-0.79; otherwise 0.89-1.32;
+//   n <= 2: columns rounded up to 128 fewer than to 256 0.75-0.97 up to 512 of them, from there on 0.74-0.94 in groups of 4
+//     with the magnitude rankers and 0.98-1.12 otherwise; fewer than 128 tiles of 256 0.65-0.84; otherwise 0.89-1.32;
 //   groups of 32: 1.09-1.51, fewer than 64 tiles (which went elsewhere) 0.66.
+// 129 to 256 tiles of 256 columns are one workgroup on a CU; where that makes more than 256 tiles of 128, some CUs get two and the
+// rest wait for them: 1.05-1.29 (C_out up to 192 0.96-1.01), 0.70-0.85 where it makes 256 or fewer.
 // Parity classes rank an element once per tap and column tile: 1.04-1.52, where fewer than 64 tiles went elsewhere 0.48-0.68.
 int pw_shape(int mode, int64_t C_in, int64_t C_out, int m, int rk, int64_t row_tiles, bool classes) {
     if (C_in <= 64) return 2;   // 128 x 64: 256-row tiles measured the same or slower (fewer workgroups, a longer last round)
     if (mode == 0 || C_in <= 128 || C_out <= 64) return 1;   // (64 channels to rank: ranking them per 128 columns costs less than the third workgroup per CU gains)
-    const int64_t wide = (C_in + 255) / 256;
-    if (row_tiles * wide < 64) return 1;
+    const int64_t wide = (C_in + 255) / 256, narrow = (C_in + 127) / 128, tiles = row_tiles * wide;
+    if (tiles < 64) return 1;
     if (classes || m == 32 || (mode == 1 && rk == kAdjusted && wide == 1 && C_out > 512)) return 0;
-    return mode == 1 || (C_in + 127) / 128 < 2 * wide || row_tiles * wide < 128 ? 1 : 0;
+    if (tiles < 128) return 1;
+    if (tiles <= 256) return row_tiles * narrow > 256 ? 0 : 1;
+    return mode == 1 || (narrow < 2 * wide && (wide <= 2 || (m == 4 && rk != kRandom))) ? 1 : 0;
 }
 // How many column tiles of the fused kernel would rank a gradient element, as the choice below counts them.
 int pw_times_ranked(int mode, int64_t C_in, int64_t C_out) {
