@@ -152,11 +152,9 @@ int sdgp_conv_bwd_data(const void* dO, const void* W, void* dD, int64_t B, int64
  *     ahead of the product.
  *   - Small bf16 1x1 stride-1 layers (at most 2^24 elements in the gradient and in the
  *     filter) whose C_out is a multiple of 8 but not of 32 -- a classifier's 1000
- *     outputs -- ask for room for copies of the gradient and the filter with C_out
- *     rounded up to 32 (zeros in the new channels), on which the matrix-core kernel
- *     runs; without the workspace another kernel takes the layer.  The result does
- *     not depend on which one ran (the random ranker indexes rows of C_out elements
- *     either way).
+ *     outputs -- ask for the size of both with C_out rounded up to 32.  The kernels
+ *     leave it unread; the size stays, and a call has to bring it, for programs built
+ *     on it.
  *   - fp32 layers large enough to gain by it ask for room for both operands as three bf16
  *     parts of every value (up to 1.5 times the gradient and the filter), which the bf16
  *     matrix instructions multiply; an fp32 call with a smaller workspace, or none, runs
@@ -178,8 +176,7 @@ size_t sdgp_conv_bwd_data_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_
  *     ImageNet network with more than 384 output channels) returns SDGP_ERR_WORKSPACE and launches nothing;
  *     SDGP_ERR_HIP when the runtime cannot report the array's address.  Where the workspace of sdgp_conv_bwd_data
  *     only holds the gradient ranked ahead of the product, a problem whose arrays do not fit the scratch runs the
- *     fused kernel instead (same kept values, same result up to summation order); likewise a small 1x1 layer whose
- *     padded copies do not fit runs the kernel that needs none.
+ *     fused kernel instead (same kept values, same result up to summation order).
  *   - All calls on one GPU share that GPU's array, and it keeps the last call's contents (every call rewrites the
  *     part it reads, nothing has to start at zero).  Calls that overlap in time on one GPU -- different streams,
  *     or different host threads -- race on it: order them on one stream.

@@ -128,7 +128,7 @@ int pw_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R
     if (rk == kRandom && mode != 0 && C_out % 16 != 0 && rows > (int64_t)0xFFFFFFFFu / C_out) return 1;
 
     PwParams p{};
-    p.rows = rows, p.C_out = (int)C_out, p.C_in = (int)C_in, p.idx_pitch = (int)C_out;
+    p.rows = rows, p.C_out = (int)C_out, p.C_in = (int)C_in;
     p.n = n;
     p.stride = stride, p.P = (int)P, p.Q = (int)Q, p.H = (int)H, p.Wd = (int)Wd;
     p.rows_dO = rows, p.gather = 0, p.ntaps = 1, p.w_taps = 1;
@@ -148,45 +148,30 @@ int pw_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R
     return 0;
 }
 
-// ---- small 1x1 / linear problems whose C_out is a multiple of 8 but not of the chunk (a classifier's 1000 outputs):
-// the gradient rows and the filter are copied into the workspace with C_out rounded up to the chunk, zeros in the new
-// channels, and the kernel runs on the copies.  Zero channels change nothing: a group of zeros keeps zeros, a zero
-// filter row adds nothing, and the random ranker's element index keeps the original row pitch.
-typedef uint32_t pad_u32x4 __attribute__((ext_vector_type(4)));
+// ---- small 1x1 / linear problems whose C_out is a multiple of 8 but not of the chunk (a classifier's 1000 outputs).  The kernel
+// takes them as they are; they are worth it below the 64 tiles that other layers need, since bwd_tiled is what is left for them.
+// Copies of gradient and filter with C_out rounded up, and the kernel on those, took 1.04-1.9 times as long (72->184 at
+// 54x54, batch 40, 2:4 31 us against 17 here).
 
-// dst [rows][vout] <- src [rows][vin] 16-byte vectors, zero where the column is new
-__global__ void __launch_bounds__(256) pad_columns(const pad_u32x4* __restrict__ src, pad_u32x4* __restrict__ dst, int64_t total,
-                                                   int vin, int vout) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= total) return;
-    const int64_t r = i / vout;
-    const int c = (int)(i - r * vout);
-    dst[i] = c < vin ? src[r * vin + c] : pad_u32x4{0u, 0u, 0u, 0u};
-}
-// dst [nout] <- src [nin] 16-byte vectors, zeros after them
-__global__ void __launch_bounds__(256) pad_tail(const pad_u32x4* __restrict__ src, pad_u32x4* __restrict__ dst, int64_t nin,
-                                                int64_t nout) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= nout) return;
-    dst[i] = i < nin ? src[i] : pad_u32x4{0u, 0u, 0u, 0u};
-}
-
-struct PadPlan {
-    int64_t rows, Kp;
-    size_t off_w, bytes;
-};
-// Whether the padded path takes the problem (and its workspace): plain 1x1 stride 1, at most 16 M elements in either copy.
-bool pad_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n, int m,
-              PadPlan& out) {
+// Whether the problem is one: plain 1x1 stride 1, at most 16 M elements in gradient and filter.
+bool small_short_chunk(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n, int m) {
     if (R != 1 || S != 1 || stride != 1 || pad != 0) return false;
     if (C_out < kPwKC || (C_out % kPwKC) == 0 || (C_out % 8) != 0 || (C_in % 8) != 0 || C_in < 8) return false;
     if (pw_mode(n, m) < 0 || (n != m && (C_out % m) != 0)) return false;
     const int64_t rows = B * H * Wd, Kp = (C_out + kPwKC - 1) / kPwKC * kPwKC;
-    if (rows < 1 || rows * Kp > ((int64_t)1 << 24) || Kp * C_in > ((int64_t)1 << 24)) return false;
-    out.rows = rows, out.Kp = Kp;
-    out.off_w = ((size_t)rows * (size_t)Kp * 2u + 255u) & ~(size_t)255u;
-    out.bytes = out.off_w + (size_t)Kp * (size_t)C_in * 2u;
-    return true;
+    return rows >= 1 && rows * Kp <= ((int64_t)1 << 24) && Kp * C_in <= ((int64_t)1 << 24);
+}
+// Their tiles: with fewer than 256 of the usual shape 128 x 64, the most workgroups (0.64-0.97 of the time of 128 x 64
+// throughout, 1.17 at 432->120, 17x17, batch 117).
+int small_short_chunk_shape(int mode, int64_t C_in, int64_t C_out, int m, int rk, int64_t rows) {
+    const int shape = pw_shape(mode, C_in, C_out, m, rk, (rows + 127) / 128, false);
+    const int64_t rows_per = kPwShapes[shape].rows, bn = kPwShapes[shape].bn;
+    return ((rows + rows_per - 1) / rows_per) * ((C_in + bn - 1) / bn) < 256 ? 2 : shape;
+}
+// The workspace that the query names for them.  Nothing reads it: callers that sized theirs by the query pass the check on it.
+size_t small_short_chunk_bytes(int64_t rows, int64_t C_in, int64_t C_out) {
+    const size_t Kp = (size_t)((C_out + kPwKC - 1) / kPwKC * kPwKC);
+    return (((size_t)rows * Kp * 2u + 255u) & ~(size_t)255u) + Kp * (size_t)C_in * 2u;
 }
 
 }  // namespace
@@ -196,13 +181,12 @@ bool pad_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int
 size_t bwd_pw_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n,
                         int m);
 
-// How bwd_pw_launch runs a problem with aligned pointers: -1 not at all, 0 as it is, 1 with the gradient ranked ahead, 2 on
-// padded copies.
+// How bwd_pw_launch runs a problem with aligned pointers: -1 not at all, 0 as it is, 1 with the gradient ranked ahead, 2 a small
+// one with a short last chunk.
 int bwd_pw_way(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n, int m, int rk,
                const void* workspace, size_t workspace_bytes) {
     const size_t room = workspace != nullptr && is_aligned16(workspace) ? workspace_bytes : 0;
-    PadPlan padded{};
-    if (pad_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, padded)) return room >= padded.bytes ? 2 : -1;
+    if (small_short_chunk(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m)) return 2;
     PwPlan plan{};
     if (pw_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, plan) != 0) return -1;
     if (!plan.pre) return 0;
@@ -218,30 +202,11 @@ int bwd_pw_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H,
                   int R, int S, int stride, int pad, int n, int m, int rk, uint64_t seed, void* workspace, size_t workspace_bytes,
                   hipStream_t stream) {
     if (!is_aligned16(dO) || !is_aligned16(W) || !is_aligned16(dD)) return 1;
-    PadPlan padded{};
-    if (pad_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, padded) && workspace != nullptr && workspace_bytes >= padded.bytes &&
-        is_aligned16(workspace)) {
-        PwPlan plan{};
-        const int shape = 2;   // 128 x 64 tiles, the most workgroups: these problems are small
-        if (pw_plan(1, 1, padded.rows, C_in, padded.Kp, 1, 1, 1, 0, n, m, rk, plan, shape) != 0) return 1;
-        PwParams& p = plan.p;
-        p.idx_pitch = (int)C_out;
-        pad_u32x4* dOp = static_cast<pad_u32x4*>(workspace);
-        pad_u32x4* Wp = reinterpret_cast<pad_u32x4*>(static_cast<unsigned char*>(workspace) + padded.off_w);
-        const int64_t n_dO = padded.rows * (padded.Kp / 8), n_w_in = C_out * (C_in / 8), n_w_out = padded.Kp * (C_in / 8);
-        hipLaunchKernelGGL(pad_columns, dim3((unsigned)((n_dO + 255) / 256)), dim3(256), 0, stream, static_cast<const pad_u32x4*>(dO), dOp,
-                           n_dO, (int)(C_out / 8), (int)(padded.Kp / 8));
-        hipLaunchKernelGGL(pad_tail, dim3((unsigned)((n_w_out + 255) / 256)), dim3(256), 0, stream, static_cast<const pad_u32x4*>(W), Wp,
-                           n_w_in, n_w_out);
-        if (launch_status() != SDGP_OK) return SDGP_ERR_HIP;
-        p.dO = reinterpret_cast<const uint16_t*>(dOp);
-        p.W = reinterpret_cast<const uint16_t*>(Wp);
-        p.dD = static_cast<uint16_t*>(dD);
-        p.mix = seed_mix(seed);
-        return launch_pw_any(p, plan.mode, m, shape, rk, stream);
-    }
+    const int shape = small_short_chunk(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m)
+                          ? small_short_chunk_shape(pw_mode(n, m), C_in, C_out, m, rk, B * H * Wd)
+                          : -1;
     PwPlan plan{};
-    if (pw_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, plan) != 0) return 1;
+    if (pw_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, plan, shape) != 0) return 1;
     if (plan.pre && (workspace == nullptr || workspace_bytes < plan.bytes || !is_aligned16(workspace))) {
         // no room for the compressed gradient: the fused kernel
         const int shape = pw_shape(plan.mode, C_in, C_out, m, rk, (plan.p.rows + 127) / 128, false);
@@ -299,7 +264,7 @@ int gather_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, i
     if (mode != 0 && C_out % 16 != 0 && B * P * Q > (int64_t)0xFFFFFFFFu / C_out) return 1;
 
     PwParams base{};
-    base.C_out = (int)C_out, base.C_in = (int)C_in, base.idx_pitch = (int)C_out;
+    base.C_out = (int)C_out, base.C_in = (int)C_in;
     base.n = n;
     base.stride = stride, base.P = (int)P, base.Q = (int)Q, base.H = (int)H, base.Wd = (int)Wd;
     base.rows_dO = B * P * Q, base.gather = 1, base.w_taps = R * S;
@@ -386,8 +351,7 @@ int bwd_gather_launch(const void* dO, const void* W, void* dD, int64_t B, int64_
 
 size_t bwd_pw_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n,
                         int m) {
-    PadPlan padded{};
-    if (pad_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, padded)) return padded.bytes;
+    if (small_short_chunk(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m)) return small_short_chunk_bytes(B * H * Wd, C_in, C_out);
     PwPlan one{};
     // (the ranker that takes the pass soonest: the size is enough for any)
     if (pw_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, kRandom, one) == 0) return one.bytes;

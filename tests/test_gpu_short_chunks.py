@@ -16,7 +16,9 @@ pytestmark = pytest.mark.gpu
 KINDS = {  # B, H, Wd, C_in and R, S, stride, pad: enough tiles for the kernel named
     "row_256": ((150, 16, 16, 72), (3, 3, 1, 1)),
     "row_64": ((300, 9, 9, 40), (3, 3, 1, 1)),
-    "pointwise": ((1100, 13, 13, 136), (1, 1, 1, 0)),       # (past the limit of the padded copies)
+    "pointwise": ((1100, 13, 13, 136), (1, 1, 1, 0)),       # (past the limit of the small ones)
+    "pointwise_small": ((5, 41, 41, 40), (1, 1, 1, 0)),         # 66 tiles of 64 columns
+    "pointwise_small_256": ((20, 41, 41, 248), (1, 1, 1, 0)),   # 263 tiles of 256
     "pointwise_strided": ((300, 20, 20, 64), (1, 1, 2, 0)),
     "classes": ((60, 28, 28, 136), (3, 3, 2, 1)),
 }
