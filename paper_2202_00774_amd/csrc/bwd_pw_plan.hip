@@ -150,8 +150,8 @@ int pw_plan(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R
 
 // ---- small 1x1 / linear problems whose C_out is a multiple of 8 but not of the chunk (a classifier's 1000 outputs).  The kernel
 // takes them as they are; they are worth it below the 64 tiles that other layers need, since bwd_tiled is what is left for them.
-// Copies of gradient and filter with C_out rounded up, and the kernel on those, took 1.04-1.9 times as long (72->184 at
-// 54x54, batch 40, 2:4 31 us against 17 here).
+// Copies of gradient and filter with C_out rounded up, and the kernel on those, took 1.3-2.6 times as long (136->144 at
+// 25x25, batch 92, 2:4 Rescaled 32.8 us against 12.9, 1536->392 at 25x25, batch 20, 1:4 74.9 against 35.9).
 
 // Whether the problem is one: plain 1x1 stride 1, at most 16 M elements in gradient and filter.
 bool small_short_chunk(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n, int m) {
@@ -161,8 +161,8 @@ bool small_short_chunk(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C
     const int64_t rows = B * H * Wd, Kp = (C_out + kPwKC - 1) / kPwKC * kPwKC;
     return rows >= 1 && rows * Kp <= ((int64_t)1 << 24) && Kp * C_in <= ((int64_t)1 << 24);
 }
-// Their tiles: with fewer than 256 of the usual shape 128 x 64, the most workgroups (0.64-0.97 of the time of 128 x 64
-// throughout, 1.17 at 432->120, 17x17, batch 117).
+// Their tiles: with fewer than 256 of the usual shape 128 x 64, the most workgroups; with more the usual one took 0.64-0.97
+// of the time of 128 x 64 (1.17 at 432->120, 17x17, batch 117).
 int small_short_chunk_shape(int mode, int64_t C_in, int64_t C_out, int m, int rk, int64_t rows) {
     const int shape = pw_shape(mode, C_in, C_out, m, rk, (rows + 127) / 128, false);
     const int64_t rows_per = kPwShapes[shape].rows, bn = kPwShapes[shape].bn;

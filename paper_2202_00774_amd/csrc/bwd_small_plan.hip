@@ -27,7 +27,7 @@ namespace {
 //     and C_out 2048 0.59-0.99, 1024 0.67-0.99 (Magnitude 0.79-1.13).
 //   ranked in the kernel, others: one round and C_out 128 on 0.18-1.02 (160 at C_in 64 1.08-1.13), else 0.98-1.73; two and
 //     C_out 1024 on 0.33-0.81.
-//   C_out no multiple of its chunk, measured against padded copies, which took 1.04-1.9 times the kernel's time on the layer as
+//   C_out no multiple of its chunk, measured against padded copies, which took 1.3-2.6 times the kernel's time on the layer as
 //     it is: one round 0.31-0.75; two and C_out 1000 on 0.20-0.83, 200 0.92-1.24; three and C_out 1000 on 0.30-1.07; four 0.39-1.33.
 //   the same where its elements are too many for that (bwd_tiled): two rounds 0.20-0.84; three 0.31-0.89 (1.17 at C_in 64);
 //     four and C_out 1000 on 0.38-0.70, 200 0.97-1.45.
