@@ -57,6 +57,15 @@ def test_half_a_chunk(kind, n):
     assert rel_error(got, ref, ab) <= 1e-2
 
 
+@pytest.mark.parametrize("n,m,ranker", PATTERNS + [(1, 4, oracle.GREEDY), (3, 16, oracle.GREEDY_ADJUSTED), (5, 8, oracle.GREEDY)])
+def test_one_round_of_wide_tiles(n, m, ranker, monkeypatch):
+    """134 tiles of 256 columns, which would be 268 of 128: pruned patterns on the wide ones (whole chunks)."""
+    monkeypatch.setitem(KINDS, "wide", ((101, 13, 13, 248), (1, 1, 1, 0)))
+    _, got, ref, ab = run("wide", 96, n, m, ranker)
+    assert rel_error(got, ref, ab) <= 1e-2
+    assert np.all(got[ab == 0] == 0)
+
+
 @pytest.mark.parametrize("n,m", [(8, 8), (2, 4)])
 @pytest.mark.parametrize("kind", sorted(KINDS))
 def test_nan_behind_the_last_channel(kind, n, m):
