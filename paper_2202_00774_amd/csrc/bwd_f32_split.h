@@ -47,8 +47,26 @@ struct SplitParams {
     uint32_t mix;
     int nflags, wblocks, nchunks, nc32;
     int TB, TH, TW, tiles_h, tiles_w, ntiles_n, nblocks;
-    int slot0[16];           // first slot of the class whose taps begin at filter position (i / stride, i % stride)
+    int slot0[16];           // class_slots
 };
+
+// W's slots hold the taps of one parity class after another, so that a stage's slabs lie behind each other: class i has the taps
+// that begin at filter position (i / stride, i % stride), row by row, from slot0[i] on.  A filter narrower than the stride
+// leaves classes without taps, which begin where the next class does.
+__host__ __device__ __forceinline__ void class_slots(int R, int S, int stride, int (&slot0)[16]) {
+    for (int i = 0, at = 0; i < stride * stride; ++i) {
+        slot0[i] = at;
+        const int r0 = i / stride, s0 = i % stride;
+        at += (r0 < R ? (R - r0 + stride - 1) / stride : 0) * (s0 < S ? (S - s0 + stride - 1) / stride : 0);
+    }
+}
+// The tap (r, s) of a slot: of the last class with taps that begins at or before it.
+__host__ __device__ __forceinline__ void slot_tap(const int (&slot0)[16], int R, int S, int stride, int slot, int& r, int& s) {
+    int cl = 0;   // (always has taps)
+    for (int i = 1; i < stride * stride; ++i) cl = i / stride < R && i % stride < S && slot0[i] <= slot ? i : cl;
+    const int nx = (S - cl % stride + stride - 1) / stride;
+    r = cl / stride + (slot - slot0[cl]) / nx * stride, s = cl % stride + (slot - slot0[cl]) % nx * stride;
+}
 
 constexpr int kSlab = 6 * 1024;       // W for one tap, 16 channels and 64 columns: 2 column tiles x 3 planes
 
@@ -102,11 +120,8 @@ __global__ void __launch_bounds__(256) split_operands(const SplitParams p) {
         const int unit = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (slab, column tile)
         if (unit >= p.ntiles_n * p.nc32 * 2 * taps * 2) return;
         const int slab = unit >> 1, slot = slab % taps, part = slab / taps & 1, c32 = slab / taps / 2 % p.nc32, nt = slab / taps / 2 / p.nc32;
-        // the tap of a slot: the last class that begins at or before it (classes without taps begin where the next one does)
-        int cl = 0;
-        for (int i = 1; i < p.stride * p.stride; ++i) cl = p.slot0[i] <= slot && p.slot0[i] > p.slot0[cl] ? i : cl;
-        const int r0 = cl / p.stride, s0 = cl % p.stride, nx = (p.S - s0 + p.stride - 1) / p.stride;
-        const int r = r0 + (slot - p.slot0[cl]) / nx * p.stride, q = s0 + (slot - p.slot0[cl]) % nx * p.stride;
+        int r, q;
+        slot_tap(p.slot0, p.R, p.S, p.stride, slot, r, q);
         const int col = nt * 64 + (unit & 1) * 32 + (lane & 31), k0 = c32 * 32 + part * 16 + (lane >> 5) * 8;
         uint32_t x[8];
         bool bad = false;

@@ -114,11 +114,7 @@ bool plan(SplitPlan& s, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t 
     if (tiles == 0 || blocks > (1 << 22)) return false;
     const Estimates e = estimate(s, tiles, m);
     if (e.split > 0.9 * e.plain) return false;
-    for (int i = 0, at = 0; i < stride * stride; ++i) {
-        p.slot0[i] = at;
-        const int r0 = i / stride, s0 = i % stride;
-        at += (r0 < R ? (R - r0 + stride - 1) / stride : 0) * (s0 < S ? (S - s0 + stride - 1) / stride : 0);
-    }
+    class_slots(R, S, stride, p.slot0);
     s.p.nblocks = (int)blocks;
     const int64_t units = (int64_t)R * S * p.nc32 * p.ntiles_n * 4;
     if (units > (1 << 22)) return false;

@@ -1,0 +1,45 @@
+// Host build of what the planner of the fp32 products on the bf16 matrix instructions and its first pass share
+// (csrc/bwd_f32_split.h).
+//   * class_slots, slot_tap: every slot of every filter up to 11 x 11 at strides 1 to 4 is the tap that the product, walking a
+//     class's taps row by row from the class's first slot on, takes it for (Fig. 3: dD's pixels of one parity class meet the
+//     taps r0, r0 + stride, ... of each axis), every tap has one slot, and no slot lies outside the filter.
+// Prints one line per check and returns the number of mismatches.  Test infrastructure, not product code.
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <cstring>
+
+#include "bwd_f32_split.h"
+
+using namespace sdgp;
+
+static int check_slots() {
+    int bad = 0;
+    for (int R = 1; R <= 11; ++R)
+        for (int S = 1; S <= 11; ++S)
+            for (int stride = 1; stride <= 4; ++stride) {
+                int slot0[16] = {}, seen[121] = {}, slots = 0;
+                class_slots(R, S, stride, slot0);
+                for (int r0 = 0; r0 < stride; ++r0)
+                    for (int s0 = 0; s0 < stride; ++s0) {
+                        int slot = slot0[r0 * stride + s0];
+                        for (int r = r0; r < R; r += stride)
+                            for (int s = s0; s < S; s += stride, ++slot, ++slots) {
+                                int gr = -1, gs = -1;
+                                slot_tap(slot0, R, S, stride, slot, gr, gs);
+                                if (slot < 0 || slot >= R * S || gr != r || gs != s) ++bad;
+                                else ++seen[slot];
+                            }
+                    }
+                if (slots != R * S) ++bad;
+                for (int i = 0; i < R * S; ++i) bad += seen[i] != 1;
+            }
+    printf("slots: mismatches %d\n", bad);
+    return bad;
+}
+
+int main() {
+    const int total = check_slots();
+    printf("total mismatches %d\n", total);
+    return total != 0;
+}

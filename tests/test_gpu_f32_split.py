@@ -98,3 +98,19 @@ def test_without_a_workspace():
                                     ptr, size, torch.cuda.current_stream().cuda_stream)
         assert rc == 0
         assert (out - want).norm() <= 1e-6 * want.norm()
+
+
+@pytest.mark.parametrize("n,m,ranker", [(2, 4, oracle.GREEDY_ADJUSTED), (3, 4, oracle.RANDOM), (4, 4, oracle.GREEDY)])
+@pytest.mark.parametrize("shape", [
+    (32, 24, 25, 67, 64, 3, 1, 2, 0), (32, 24, 25, 33, 64, 2, 1, 2, 0), (32, 24, 25, 67, 64, 1, 3, 2, 0), (32, 24, 25, 33, 64, 2, 2, 3, 0),
+    (32, 24, 24, 67, 96, 3, 3, 4, 1), (32, 24, 25, 33, 64, 2, 3, 4, 1), (32, 25, 24, 33, 64, 3, 2, 3, 1), (64, 25, 24, 33, 64, 1, 1, 3, 0)])
+def test_classes_without_taps(shape, n, m, ranker):
+    """Filters narrower than the stride along one axis or both: classes without taps lie between those that have some."""
+    layer = wl.ConvLayer("c", *shape)
+    assert takes(layer, n, m)
+    dO = wl.laplace_with_zeros(layer.dO_shape, 1e-3, 0.3, seed=15, dtype=wl.F32)
+    W = wl.normal(layer.W_shape, 0.1, 16, wl.F32)
+    ref, ab = oracle.conv_bwd_data(oracle.prune(dO, n, m, ranker, seed=17)[0], W, layer.H, layer.Wd, layer.stride, layer.pad)
+    out = run(layer, dO, W, n, m, ranker, 17)
+    assert rel_error(out, ref, ab) <= 1e-6
+    assert np.all(out[ab == 0] == 0)
