@@ -117,8 +117,10 @@ int sdgp_linear_bwd_data(const void* dO, const void* W, void* dD, int64_t rows, 
  *   dD[b,h,w,c] = sum over taps (r,s) and channels k of
  *                 prune(dO)[b,p,q,k] * W[k,r,s,c],   p = (h + pad - r)/stride, q = (w + pad - s)/stride,
  *   taking only taps for which p and q are integers inside [0,P) x [0,Q).  (A weight that is infinite or NaN stays away
- *   from pixels that its tap does not reach in fp32 and on the plain and the small-problem bf16 kernels; the bf16 tile
- *   kernels multiply it by a row of zeros there, which is a NaN.)
+ *   from pixels that its tap does not reach in fp32, in first layers (C_in <= 4) and on the plain and the small-problem
+ *   bf16 kernels; the bf16 tile kernels multiply it by a row of zeros there, which is a NaN.  An infinite or NaN gradient
+ *   value stays with the pixels that its taps reach.  One kernel does neither: the unpruned 7x7 stride-2 padding-3 layer
+ *   of up to three channels onto 64 on images of even size multiplies all of a 4x4 window of the gradient.)
  *   The forward pass was a cross-correlation with dilation 1 and one group.
  *   Input pixels that no tap reaches receive 0.  Each dO element is pruned once,
  *   with flat element index ((b*P + p)*Q + q)*C_out + k.

@@ -516,6 +516,72 @@ __global__ void __launch_bounds__(256) first_v_taps(const uint16_t* __restrict__
 
 typedef float f32x4f __attribute__((ext_vector_type(4)));
 
+constexpr int kFirstDense = 3;   // n == m: nothing is ranked
+
+// The kernel's arguments, read again: what uses them keeps nothing in registers before.
+template <typename Params>
+__device__ __forceinline__ const __attribute__((address_space(4))) Params& first_params_again() {
+    uint64_t args = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    return *reinterpret_cast<const __attribute__((address_space(4))) Params*>(args);
+}
+
+// The stored channels of input pixel (b, h, w), some of them NaN: those are summed again over the pixel's own taps, term by term.
+// The window products above and below also multiply gradient pixels that no tap joins to the pixel, by a zero of V, and weights
+// whose gradient pixel does not exist, by a zero, which is a NaN where the other factor is infinite or NaN.  Rare, so it is short
+// rather than fast; looking for NaN results costs up to 1 percent (3 -> 64 channels at 224 x 224, batch 256, 4:8 Rescaled 280.4 -> 284.2 us).
+template <int M, int RK, typename Params>
+__device__ __forceinline__ void first_sum_again(const Params& p, int side, int stride, int P, int Q, int C_out, uint16_t* dst, int b, int h, int w) {
+    const int hp = h + side / 2, wp = w + side / 2;   // (padding: half the filter)
+    uint32_t wrong = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) wrong |= c < p.C_in && (dst[c] & 0x7FFFu) > 0x7F80u ? 1u << c : 0u;
+    if (wrong == 0) return;
+    float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    uint32_t open = wrong;   // may still turn out not to be NaN
+#pragma nounroll
+    for (int r = hp % stride; r < side && r <= hp; r += stride)
+#pragma nounroll
+        for (int s = wp % stride; s < side && s <= wp; s += stride) {
+            const int pp = (hp - r) / stride, qq = (wp - s) / stride;
+            if (pp >= P || qq >= Q) continue;
+            const int64_t e0 = (((int64_t)b * P + pp) * Q + qq) * C_out;
+            const int64_t kstep = (int64_t)side * side * p.C_in;
+            const uint16_t* wk = p.W + (r * side + s) * p.C_in;
+#pragma nounroll
+            for (int k = 0; k < C_out && open != 0; k += M) {
+                const uint16_t* const g = p.dO + e0 + k;
+                const uint32_t mask = RK == kFirstDense ? ~0u : keep_by_count<M, RK>(g, p.n, p.mix, (uint64_t)(e0 + k));
+                float scale = 1.0f;
+                if constexpr (RK == kAdjusted) {
+                    float total = 0.0f, kept = 0.0f;
+#pragma nounroll
+                    for (int j = 0; j < M; ++j) {
+                        const float a = bf16_to_float((uint32_t)g[j] & 0x7FFFu);
+                        total = __fadd_rn(total, a);
+                        if ((mask >> j) & 1u) kept = __fadd_rn(kept, a);
+                    }
+                    if (kept != 0.0f) scale = __fdiv_rn(total, kept);
+                }
+#pragma nounroll
+                for (int j = 0; j < M; ++j, wk += kstep) {
+                    float x = (mask >> j) & 1u ? bf16_to_float(g[j]) : 0.0f;
+                    if constexpr (RK == kAdjusted) {
+                        if ((mask >> j) & 1u) x = bf16_to_float(float_to_bf16(__fmul_rn(x, scale)));
+                    }
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if (c < p.C_in) sum[c] = fmaf(x, bf16_to_float(wk[c]), sum[c]);
+                }
+#pragma unroll
+                for (int c = 0; c < 4; ++c) open &= sum[c] == sum[c] ? ~0u : ~(1u << c);
+            }
+        }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        if ((wrong >> c) & 1u) dst[c] = (uint16_t)float_to_bf16(sum[c]);
+}
+
 // VLDS: V's chunk through LDS, once for the workgroup; otherwise its fragments from the L2, in every wavefront.
 template <int M, int RK, bool PRUNE, bool NLE2, bool VLDS>
 __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) {
@@ -651,10 +717,12 @@ __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) 
     }
     // result register c of lane (px, oct = 2 a + b): channel c of input pixel (2 i + a, 2 j + b)
     const int a = oct >> 1, bb = oct & 1;
+    uint32_t nans = 0;
 #pragma unroll
     for (int ri = 0; ri < 4; ++ri)
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
+            nans |= __builtin_isunordered(acc[ri][g][0], acc[ri][g][1]) || __builtin_isunordered(acc[ri][g][2], acc[ri][g][3]) ? 1u << (ri * 2 + g) : 0u;
             const int h = 2 * (i0 + 4 * rq + ri) + a, w = 2 * (j0 + 32 * gp + 16 * g + px) + bb;
             if (h < p.H && w < p.Wd) {   // (an odd size ends on half a block)
                 uint16_t* dst = p.dD + ((size_t)(b * p.H + h) * p.Wd + w) * p.C_in;
@@ -665,6 +733,15 @@ __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) 
                 if (p.C_in > 3) dst[3] = (uint16_t)(c23 >> 16);
             }
         }
+    if (__builtin_expect(nans != 0, 0)) {
+        const auto& q = first_params_again<FirstParams>();
+#pragma nounroll
+        for (; nans != 0; nans &= nans - 1) {
+            const int x = __ffs((int)nans) - 1, h = 2 * (i0 + 4 * rq + (x >> 1)) + a, w = 2 * (j0 + 16 * (x & 1) + px) + bb;
+            if (h < q.H && w < q.Wd)
+                first_sum_again<M, PRUNE ? RK : kFirstDense>(q, 7, 2, q.P, q.Q, q.C_out, q.dD + ((size_t)(b * q.H + h) * q.Wd + w) * q.C_in, b, h, w);
+        }
+    }
 }
 
 // Whether bwd_first2 takes the problem (everything but the workspace).
@@ -843,6 +920,7 @@ __global__ void __launch_bounds__(256, 1) bwd_first_stream(const StreamParams p)
         }
 
     const int a = oct >> 1, bb = oct & 1;
+    bool nan = false;                                         // in a result of this lane's
     for (int i = i_begin; i < i_end; ++i) {
         // the rows of block rows i + 1 and i + 2 (ten copies each) may still be in flight.  (The stores of earlier block
         // rows are in the same counter; not counting them only makes the wait stricter.)
@@ -913,12 +991,20 @@ __global__ void __launch_bounds__(256, 1) bwd_first_stream(const StreamParams p)
             if (p.C_in > 1) dst[1] = (uint16_t)(c01 >> 16);
             if (p.C_in > 2) dst[2] = (uint16_t)c23;
             if (p.C_in > 3) dst[3] = (uint16_t)(c23 >> 16);
+            nan = nan || __builtin_isunordered(acc[0], acc[1]) || __builtin_isunordered(acc[2], acc[3]);
         }
         // rows 2i - 1 and 2i are done with: their ring slots take the rows of block row i + 3
         if (i + 3 < i_end) {
             __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this block row's fragment reads have returned
             issue_step(i + 3, false);
         }
+    }
+    if (__builtin_expect(nan, 0)) {
+        const auto& q = first_params_again<StreamParams>();
+        const int w = 2 * (j0 + px) + bb;
+#pragma nounroll
+        for (int h = 2 * i_begin + a; h < 2 * i_end; h += 2)
+            first_sum_again<M, PRUNE ? RK : kFirstDense>(q, 3, 1, q.H, q.Wd, 64, q.dD + (((size_t)b * q.H + h) * q.Wd + w) * q.C_in, b, h, w);
     }
 }
 
@@ -953,6 +1039,7 @@ int launch_stream_rk(const StreamParams& p, int rk, hipStream_t stream) {
 // seven rows of 2560 bytes ([half][20 records of 64 bytes], parts permuted by bits 2..3 of the record number): four in
 // use, three in flight.  Eight wavefronts per workgroup, one workgroup per CU (two wavefronts per SIMD); the filter is
 // copied transposed into LDS ([tap, c][k], 128 bytes per row) and a fragment is one 16-byte read.
+// (Infinite and NaN values reach the whole window here: looking for NaN results cost 2 to 5 percent at batch 256, 224 x 224.)
 constexpr int kTRowBytes = 2560;
 constexpr int kTRing = 7;
 constexpr int kTRingBytes = kTRing * kTRowBytes;

@@ -44,26 +44,6 @@ struct SmallParams {
     uint32_t mix;
 };
 
-// The survivors of the M channels at g (flat element e0): bit j for channel j, by counting the keys ahead of it.
-template <int M, int RK>
-__device__ __forceinline__ uint32_t keep_by_count(const uint16_t* g, int n, uint32_t mix, uint64_t e0) {
-    const uint32_t row = hash_row(mix, (uint32_t)(e0 >> 32));
-    auto key = [&](int j) { return RK == kRandom ? hash_elem(row, (uint32_t)e0 + (uint32_t)j) : (uint32_t)g[j] & 0x7FFFu; };
-    uint32_t mask = 0;
-#pragma nounroll
-    for (int j = 0; j < M; ++j) {
-        const uint32_t kj = key(j);
-        int ahead = 0;
-#pragma nounroll
-        for (int i = 0; i < M; ++i) {
-            const uint32_t ki = key(i);
-            ahead += ki > kj || (ki == kj && i < j);
-        }
-        mask |= (uint32_t)(ahead < n) << j;
-    }
-    return mask;
-}
-
 // The four results of row `row` at channel c0, some of them NaN: those that a weight of a tap outside the gradient can have
 // made NaN are summed again over the taps inside.  Rare, so it is short rather than fast and reads the kernel's arguments
 // again, so that none of it holds a register during the main loop: with the kernel's own ranker and registers every call

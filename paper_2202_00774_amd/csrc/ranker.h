@@ -787,4 +787,25 @@ __device__ __forceinline__ void prune_compress16(const uint32_t (&w)[8], int n, 
     }
 }
 
+// The survivors of the M bf16 channels at g (flat element e0): bit j for channel j, by counting the keys ahead of it.  Short
+// rather than fast, for results that are summed again.
+template <int M, int RK>
+__device__ __forceinline__ uint32_t keep_by_count(const uint16_t* g, int n, uint32_t mix, uint64_t e0) {
+    const uint32_t row = hash_row(mix, (uint32_t)(e0 >> 32));
+    auto key = [&](int j) { return RK == kRandom ? hash_elem(row, (uint32_t)e0 + (uint32_t)j) : (uint32_t)g[j] & 0x7FFFu; };
+    uint32_t mask = 0;
+#pragma nounroll
+    for (int j = 0; j < M; ++j) {
+        const uint32_t kj = key(j);
+        int ahead = 0;
+#pragma nounroll
+        for (int i = 0; i < M; ++i) {
+            const uint32_t ki = key(i);
+            ahead += ki > kj || (ki == kj && i < j);
+        }
+        mask |= (uint32_t)(ahead < n) << j;
+    }
+    return mask;
+}
+
 }  // namespace sdgp

@@ -55,3 +55,30 @@ def test_stem_on_odd_sizes(C_in, H, Wd, n, m, ranker):
     out = torch.full((2, H, Wd, C_in), float("nan"), dtype=torch.bfloat16, device="cuda")
     sdgp.sdgp_conv_bwd_data(g, w, H, Wd, 2, 3, n, m, ranker, 11, out=out)
     assert rel_error(wl.to_f64(to_host(out)), ref, ab) <= 1e-2
+
+
+@pytest.mark.parametrize("n,m,ranker", [(4, 4, oracle.GREEDY), (2, 4, oracle.GREEDY), (1, 4, oracle.RANDOM), (3, 8, oracle.GREEDY),
+                                        (2, 32, oracle.RANDOM), (5, 32, oracle.GREEDY)])
+@pytest.mark.parametrize("shape", [(2, 35, 33, 3, 64, 7, 7, 2, 3), (2, 36, 68, 3, 96, 7, 7, 2, 3), (2, 37, 36, 4, 96, 7, 7, 2, 3), (2, 24, 36, 3, 64, 3, 3, 1, 1),
+                                   (2, 17, 21, 4, 96, 3, 3, 1, 1)])
+def test_non_finite_stay_with_their_taps(shape, n, m, ranker):
+    """An infinite or NaN gradient value reaches the pixels that a tap joins to it, a weight those whose tap lies inside the
+    gradient, and no others.  Every other value is positive, so the oracle's NaN and infinities are those of these terms."""
+    L = wl.ConvLayer("n", *shape)
+    rng = np.random.default_rng(5)
+    dO = wl.f32_to_bf16_bits(rng.uniform(1, 2, L.dO_shape).astype(np.float32))
+    W = wl.f32_to_bf16_bits(rng.uniform(0.5, 1, L.W_shape).astype(np.float32))
+    P, Q = L.dO_shape[1:3]
+    dO[0, P // 2, Q // 2, 1] = 0x7F80
+    dO[0, 1, 2, 40:44] = 0x7FC0
+    dO[0, P - 1, Q - 2, 3] = 0xFF80
+    dO[0, 0, Q - 1, 5] = 0x7F80
+    W[7, 0, 1, 0] = 0x7F80         # meets dropped values (zeros) too, which is a NaN by definition
+    W[2, L.R - 1, 0, L.C_in - 1] = 0x7FC0
+    ref, ab = oracle.conv_bwd_data(oracle.prune(dO, n, m, ranker, seed=11)[0], W, L.H, L.Wd, L.stride, L.pad)
+    fin, nan = np.isfinite(ref), np.isnan(ref)
+    assert fin.any() and nan.any() and (~fin & ~nan).any()
+    g, w = to_gpu(dO), to_gpu(W)
+    got = wl.to_f64(to_host(sdgp.sdgp_conv_bwd_data(g, w, L.H, L.Wd, L.stride, L.pad, n, m, ranker, 11)))
+    assert np.array_equal(np.isnan(got), nan) and np.array_equal(got[~fin & ~nan], ref[~fin & ~nan])
+    assert np.all(np.abs(got[fin] - ref[fin]) <= 1e-2 * ab[fin])
