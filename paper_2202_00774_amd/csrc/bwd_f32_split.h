@@ -68,6 +68,10 @@ __host__ __device__ __forceinline__ void slot_tap(const int (&slot0)[16], int R,
     r = cl / stride + (slot - slot0[cl]) / nx * stride, s = cl % stride + (slot - slot0[cl]) % nx * stride;
 }
 
+// Grid positions along one side of a tile of `side` pixels whose class has `count` taps on that axis.  (A class without taps
+// copies none; a side of at least one position keeps the divisions by it defined.)
+__host__ __device__ __forceinline__ int grid_side(int side, int count) { return count > 0 ? side + count - 1 : side; }
+
 constexpr int kSlab = 6 * 1024;       // W for one tap, 16 channels and 64 columns: 2 column tiles x 3 planes
 
 // Tile of ROWS rows on a grid of at most NP positions (64 per wavefront: one copy unit each); W: three sets of kGroup taps.
@@ -275,7 +279,7 @@ __global__ void __launch_bounds__(ROWS * 4) f32_split(const SplitParams p) {
     const int b0 = mtile / (p.tiles_w * p.tiles_h) * p.TB, i0 = mtile / p.tiles_w % p.tiles_h * p.TH, j0 = mtile % p.tiles_w * p.TW;
     if (i0 >= ay.n || j0 >= ax.n) return;           // (the other classes have a row or column more; the whole workgroup leaves)
     const int ny = ay.count, nx = ax.count, ntaps = ny * nx;
-    const int GH = p.TH + ny - 1, GW = p.TW + nx - 1, npad = p.TB * GH * GW;
+    const int GH = grid_side(p.TH, ny), GW = grid_side(p.TW, nx), npad = p.TB * GH * GW;
 
     SDGP_LDS int* rowpix = (SDGP_LDS int*)smem;                          // input pixel of a tile row, -1: none
     SDGP_LDS uint32_t* notes = (SDGP_LDS uint32_t*)(smem + ROWS * 4);    // [0] infinite gradient, [1..2] columns

@@ -3,6 +3,7 @@
 //   * class_slots, slot_tap: every slot of every filter up to 11 x 11 at strides 1 to 4 is the tap that the product, walking a
 //     class's taps row by row from the class's first slot on, takes it for (Fig. 3: dD's pixels of one parity class meet the
 //     taps r0, r0 + stride, ... of each axis), every tap has one slot, and no slot lies outside the filter.
+//   * grid_side: never below one, and no position fewer than the taps reach.
 // Prints one line per check and returns the number of mismatches.  Test infrastructure, not product code.
 #include <hip/hip_runtime.h>
 
@@ -38,8 +39,16 @@ static int check_slots() {
     return bad;
 }
 
+static int check_sides() {
+    int bad = 0;
+    for (int side = 1; side <= 256; ++side)
+        for (int count = 0; count <= 11; ++count) bad += grid_side(side, count) < 1 || grid_side(side, count) < side + count - 1;
+    printf("sides: mismatches %d\n", bad);
+    return bad;
+}
+
 int main() {
-    const int total = check_slots();
+    const int total = check_slots() + check_sides();
     printf("total mismatches %d\n", total);
     return total != 0;
 }

@@ -103,7 +103,8 @@ def test_without_a_workspace():
 @pytest.mark.parametrize("n,m,ranker", [(2, 4, oracle.GREEDY_ADJUSTED), (3, 4, oracle.RANDOM), (4, 4, oracle.GREEDY)])
 @pytest.mark.parametrize("shape", [
     (32, 24, 25, 67, 64, 3, 1, 2, 0), (32, 24, 25, 33, 64, 2, 1, 2, 0), (32, 24, 25, 67, 64, 1, 3, 2, 0), (32, 24, 25, 33, 64, 2, 2, 3, 0),
-    (32, 24, 24, 67, 96, 3, 3, 4, 1), (32, 24, 25, 33, 64, 2, 3, 4, 1), (32, 25, 24, 33, 64, 3, 2, 3, 1), (64, 25, 24, 33, 64, 1, 1, 3, 0)])
+    (32, 24, 24, 67, 96, 3, 3, 4, 1), (32, 24, 25, 33, 64, 2, 3, 4, 1), (32, 25, 24, 33, 64, 3, 2, 3, 1), (64, 25, 24, 33, 64, 1, 1, 3, 0),
+    (64, 2, 97, 33, 64, 1, 2, 2, 0)])   # tiles of one row
 def test_classes_without_taps(shape, n, m, ranker):
     """Filters narrower than the stride along one axis or both: classes without taps lie between those that have some."""
     layer = wl.ConvLayer("c", *shape)
