@@ -1,16 +1,17 @@
 // Host build of what the planner of the fp32 products on the bf16 matrix instructions and its first pass share
-// (csrc/bwd_f32_split.h).
+// (csrc/bwd_f32_split.h, csrc/bwd_f32_split_tiles.h).
 //   * class_slots, slot_tap: every slot of every filter up to 11 x 11 at strides 1 to 4 is the tap that the product, walking a
 //     class's taps row by row from the class's first slot on, takes it for (Fig. 3: dD's pixels of one parity class meet the
 //     taps r0, r0 + stride, ... of each axis), every tap has one slot, and no slot lies outside the filter.
 //   * grid_side: never below one, and no position fewer than the taps reach.
+//   * the planner declines launches of 2^32 threads and more.
 // Prints one line per check and returns the number of mismatches.  Test infrastructure, not product code.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
 #include <cstring>
 
-#include "bwd_f32_split.h"
+#include "bwd_f32_split_tiles.h"
 
 using namespace sdgp;
 
@@ -47,8 +48,19 @@ static int check_sides() {
     return bad;
 }
 
+static int check_limits() {
+    SplitPlan s;
+    int bad = 0;
+    for (int64_t B = (1 << 22) - 2; B <= 1 << 22; ++B) {   // one tile of 256 rows an image, 1024 threads each
+        const bool takes = split_plan(s, B, 16, 16, 33, 16, 1, 1, 1, 0, 4, 4);
+        bad += takes != (B < 1 << 22) || (takes && (s.rows != 256 || s.p.nblocks != B));
+    }
+    printf("limits: mismatches %d\n", bad);
+    return bad;
+}
+
 int main() {
-    const int total = check_slots() + check_sides();
+    const int total = check_slots() + check_sides() + check_limits();
     printf("total mismatches %d\n", total);
     return total != 0;
 }
