@@ -160,7 +160,9 @@ int sdgp_conv_bwd_data(const void* dO, const void* W, void* dD, int64_t B, int64
  *   - fp32 layers large enough to gain by it ask for room for both operands as three bf16
  *     parts of every value (up to 1.5 times the gradient and the filter), which the bf16
  *     matrix instructions multiply; an fp32 call with a smaller workspace, or none, runs
- *     the kernel that needs none (same kept values, same result up to summation order).
+ *     the kernel that needs none.  Both keep the same values and are fp32 sums: without the
+ *     workspace every product is exact, with it within 2^-24 of itself, over the whole range
+ *     of fp32; the sums are rounded less often then, and the error against 64 bits is smaller.
  * The sizes hold for every ranker and alignment, so a call may leave its workspace
  * unread: problems of few tiles run a kernel that needs none. */
 size_t sdgp_conv_bwd_data_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,

@@ -1,12 +1,15 @@
 // fp32 backward-data products on the bf16 matrix instructions (Fig. 2, Fig. 3; Sec. II-A), for problems large enough to
 // pay for a pass over the operands.
 //
-// An fp32 value is the sum of three bf16 values: its upper eight significant bits, the next eight and the last eight, by
-// truncation and two exact subtractions.  A product of two such sums is nine bf16 products, each exact in fp32; the three
-// smallest are below 2^-24 of the whole and are left out (together at most 2^-23.4, on average 2^-25).  So six bf16
-// instructions replace the fp32 one, which takes 16 times as long for the same work, and every sum stays fp32, in fewer
-// steps: error against 64 bits of 3x3 128 -> 128 at 16x16, batch 128, 2:4 Magnitude 3.6e-7, on the fp32 instruction 4.1e-7.
-// (Values below 2^-110 lose the parts that no bf16 holds.)
+// An fp32 value is the sum of three bf16 values: the nearest one, the one nearest to what is left, which is at most 2^-8 of the
+// whole, and the rest, at most 2^-17 and exact.  A product of two such sums is nine bf16 products, each exact in fp32; the
+// three smallest are together at most 2^-24 of the whole, of either sign, and are left out.  So six bf16 instructions replace
+// the fp32 one, which takes 16 times as long for the same work, and every sum stays fp32, in fewer steps.  Operands are scaled by
+// 2^24 on the way in and results by 2^-48 on the way out, so that parts of the smallest values are normal numbers too.
+// The products of the first parts and the five smaller ones have sums of their own, so that a sum that counts is rounded once per
+// chunk and tap.  Error against 64 bits over that of the fp32 instruction, 762 products of 4 to 4608 terms, three distributions:
+// 0.05 to 0.81 (3x3 128 -> 128 at 16x16, batch 128, 2:4 Magnitude 1.3e-7 against 4.1e-7; parts by truncation, whose loss is
+// towards zero, and one sum: 3.6e-7 there, up to 12 times the fp32 instruction's on same-sign data).
 //   1. split_operands ranks the gradient (Sec. III-B) and writes its three planes -- kept values only, with their
 //      positions, where at most two of four channels stay -- and W's, in the order in which the product reads its fragments.
 //      Bound by latency and memory: 6.3 us there.
@@ -19,9 +22,11 @@
 //      Bound by fragment reads and matrix instructions, which take equal time and overlap by half: 7 us per 32 channels
 //      and nine taps, 10 us of prologue, first copies and stores.
 // 3x3 128 -> 128 at 16x16, batch 128, 2:4 Magnitude: 96.6 us on the fp32 instruction, 42.9 here.
-// Infinite and NaN inputs: an infinite value times a zero plane is a NaN the definition does not have, and a dropped
-// channel meets no weight at all here where the definition multiplies it by zero.  split_operands notes columns of W with
-// a non-finite weight and whether an infinite gradient value is kept; results they can reach are summed again term by term.
+// Values that scaling takes out of the range, infinite and NaN ones have parts that make NaN of every result they reach
+// (split3), and sums may leave the range on the way: where split_operands notes an operand that can have done so, results that are
+// not finite are summed again term by term.  (A NaN gradient alone costs nothing: its NaN is the result.)  A dropped channel meets
+// no weight here, where the definition multiplies it by zero: the columns of W with a non-finite weight are noted too, and
+// summed again.
 #pragma once
 
 #include "bwd_f32.h"
@@ -40,12 +45,13 @@ struct SplitParams {
     uint16_t* idx;           // [chunk][pixel][half] 2-bit positions (compressed planes)
     unsigned char* wimg;     // [64 columns][32 channels][part][slot][32 columns][plane][lane] 16 bytes; slot: the filter's taps
                              // class by class, so that a stage's slabs lie behind each other
-    uint32_t* wmask;         // [64 columns][32 channels][part][slot][32 columns]: bit c set, column c has a non-finite weight there
-    uint32_t* flags;         // one word per workgroup of the first pass: an infinite gradient value is kept
+    uint32_t* wnotes;        // [64 columns][32 channels][part][slot][32 columns] two words: bit c set, column c has a non-finite
+                             // weight there; not zero, a weight is large
+    uint32_t* gnotes;        // one word per workgroup of the first pass that has gradient: a large value is kept
     int64_t npix;
     int B, H, Wd, P, Q, C_in, C_out, R, S, stride, pad, n;
     uint32_t mix;
-    int nflags, wblocks, nchunks, nc32;
+    int gblocks, wblocks, nchunks, nc32;
     int TB, TH, TW, tiles_h, tiles_w, ntiles_n, nblocks;
     int slot0[16];           // class_slots
 };
@@ -88,20 +94,32 @@ struct SplitLayout {
     static_assert(kTotal <= 160 * 1024 && NP <= 512, "fits the LDS, and eight wavefronts copy it");
 };
 
+// An operand's scale: parts of the smallest fp32 value are then normal numbers of bf16, whatever the instructions do with others.
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
+
 struct Split3 {
-    uint32_t h, m, l;   // fp32 patterns whose lower halves are zero
+    uint32_t h, m, l;   // fp32 patterns whose lower halves are zero: x 2^24 = h + m + l
 };
-__device__ __forceinline__ Split3 split3(uint32_t x) {
+// A value that bf16 cannot hold then (infinite, NaN, from 2^104 on) has a NaN for h, which makes NaN of every result it reaches,
+// and its own two halves for m and l (split_join).
+__host__ __device__ __forceinline__ Split3 split3(uint32_t x) {
+    auto nearest = [](uint32_t u) { return (u + 0x7FFFu + ((u >> 16) & 1u)) & 0xFFFF0000u; };
+    const float v = bits_to_float(x) * kSplitScale;
     Split3 s;
-    s.h = x & 0xFFFF0000u;
-    const float rest = bits_to_float(x) - bits_to_float(s.h);
-    s.m = float_to_bits(rest) & 0xFFFF0000u;
-    s.l = float_to_bits(rest - bits_to_float(s.m));
-    if ((x & 0x7F800000u) == 0x7F800000u) {
-        if (x & 0x007FFFFFu) s.h |= 0x00400000u;   // a NaN stays one
-        s.m = s.l = 0u;
-    }
+    s.h = nearest(float_to_bits(v));
+    const float rest = v - bits_to_float(s.h);
+    s.m = nearest(float_to_bits(rest));
+    s.l = float_to_bits(rest - bits_to_float(s.m));   // (at most seven bits are left)
+    if ((s.h & 0x7F800000u) == 0x7F800000u || (x & 0x7F800000u) == 0x7F800000u) s.h = 0x7FC00000u, s.m = x & 0xFFFF0000u, s.l = x << 16;
     return s;
+}
+// From 2^24 on, and infinite.  Without such operands no sum leaves the range: products are below 2^48, and a filter has fewer than
+// 2^27 taps and channels, which makes less than 2^75, scaled 2^123.
+__host__ __device__ __forceinline__ bool is_large(uint32_t x) { return (x & 0x7FFFFFFFu) - 0x4B800000u <= 0x7F800000u - 0x4B800000u; }
+// The value of three parts given as bf16.
+__host__ __device__ __forceinline__ float split_join(uint32_t h, uint32_t m, uint32_t l) {
+    if (h == 0x7FC0u) return bits_to_float(m << 16 | l);
+    return (bits_to_float(l << 16) + bits_to_float(m << 16) + bits_to_float(h << 16)) * (1.0f / kSplitScale);
 }
 // eight values -> eight bf16 of each plane
 __device__ __forceinline__ void split8(const uint32_t (&x)[8], u32x4_t (&out)[3]) {
@@ -128,28 +146,28 @@ __global__ void __launch_bounds__(256) split_operands(const SplitParams p) {
         slot_tap(p.slot0, p.R, p.S, p.stride, slot, r, q);
         const int col = nt * 64 + (unit & 1) * 32 + (lane & 31), k0 = c32 * 32 + part * 16 + (lane >> 5) * 8;
         uint32_t x[8];
-        bool bad = false;
+        bool bad = false, large = false;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             x[j] = 0u;
             if (k0 + j < p.C_out && col < p.C_in) x[j] = float_to_bits(p.W[((size_t)(k0 + j) * taps + r * p.S + q) * p.C_in + col]);
         }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) bad = bad || (x[j] & 0x7F800000u) == 0x7F800000u;
+        for (int j = 0; j < 8; ++j) bad = bad || (x[j] & 0x7F800000u) == 0x7F800000u, large = large || is_large(x[j]);
         u32x4_t out[3];
         split8(x, out);
 #pragma unroll
         for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u32x4_t*>(p.wimg + ((size_t)unit * 3 + pl) * 1024 + lane * 16) = out[pl];
-        const uint64_t cols = __ballot(bad);
-        if (lane == 0) p.wmask[unit] = (uint32_t)cols | (uint32_t)(cols >> 32);
+        const uint64_t cols = __ballot(bad), larges = __ballot(large);
+        if (lane == 0) p.wnotes[2 * unit] = (uint32_t)cols | (uint32_t)(cols >> 32), p.wnotes[2 * unit + 1] = larges != 0;
         return;
     }
     constexpr int IC = M > 16 ? M : 16;               // channels per thread
     constexpr int TPP = 64 / IC, PX = 256 / TPP;      // threads per pixel, pixels at a time
     const int wg = (int)blockIdx.x - p.wblocks;
     const uint32_t cblocks = (uint32_t)(p.C_out + 63) / 64u, tiles = (uint32_t)((p.npix + PX - 1) / PX) * cblocks;   // (below 2^31)
-    bool inf = false;
-    for (uint32_t t = (uint32_t)wg; t < tiles; t += (uint32_t)p.nflags) {
+    bool large = false;
+    for (uint32_t t = (uint32_t)wg; t < tiles; t += (uint32_t)p.gblocks) {
         const int64_t pix = (int64_t)(t / cblocks) * PX + threadIdx.x / TPP;
         const int ch = (int)(t % cblocks) * 64 + (int)(threadIdx.x % TPP) * IC;
         if (pix >= p.npix || ch >= p.nchunks * (SPARSE ? 32 : 16)) continue;
@@ -176,10 +194,7 @@ __global__ void __launch_bounds__(256) split_operands(const SplitParams p) {
                 for (int j = 0; j < M; ++j) in[j] = out[j];
             }
 #pragma unroll
-            for (int j = 0; j < M; ++j) {
-                raw[g * M + j] = in[j], keep |= (k[j] ? 1u : 0u) << (g * M + j);
-                inf = inf || (in[j] & 0x7FFFFFFFu) == 0x7F800000u;
-            }
+            for (int j = 0; j < M; ++j) raw[g * M + j] = in[j], keep |= (k[j] ? 1u : 0u) << (g * M + j), large = large || is_large(in[j]);
         }
         const size_t plane = (size_t)p.npix * 16;
         if constexpr (SPARSE) {
@@ -216,8 +231,8 @@ __global__ void __launch_bounds__(256) split_operands(const SplitParams p) {
             }
         }
     }
-    const int any = __syncthreads_or(inf);
-    if (threadIdx.x == 0) p.flags[wg] = any ? 1u : 0u;
+    const int any = __syncthreads_or(large);
+    if (threadIdx.x == 0) p.gnotes[wg] = any ? 1u : 0u;
 }
 
 // Result (input pixel `pix`, column `col`) as the definition has it, term by term, from the planes (whose sums are the
@@ -242,11 +257,9 @@ __device__ __attribute__((noinline)) float split_sum_again(const SDGP_CONSTANT S
                 }
                 float v = 0.0f;
                 if (e >= 0) {
-#pragma unroll
-                    for (int pl = 2; pl >= 0; --pl) {
-                        const size_t at = (((size_t)chunk * 6 + pl * 2 + half) * (size_t)p.npix + g) * 8 + (size_t)e;
-                        v += bf16_to_float(reinterpret_cast<const uint16_t*>(p.planes)[at]);
-                    }
+                    const uint16_t* const at = reinterpret_cast<const uint16_t*>(p.planes) + (((size_t)chunk * 6 + half) * (size_t)p.npix + g) * 8 + (size_t)e;
+                    const size_t plane = (size_t)p.npix * 16;   // (two half chunks of eight)
+                    v = split_join(at[0], at[plane], at[2 * plane]);
                 }
                 sum += v * p.W[((size_t)k * (p.R * p.S) + r * p.S + s) * p.C_in + col];
             }
@@ -282,7 +295,7 @@ __global__ void __launch_bounds__(ROWS * 4) f32_split(const SplitParams p) {
     const int GH = grid_side(p.TH, ny), GW = grid_side(p.TW, nx), npad = p.TB * GH * GW;
 
     SDGP_LDS int* rowpix = (SDGP_LDS int*)smem;                          // input pixel of a tile row, -1: none
-    SDGP_LDS uint32_t* notes = (SDGP_LDS uint32_t*)(smem + ROWS * 4);    // [0] infinite gradient, [1..2] columns
+    SDGP_LDS uint32_t* notes = (SDGP_LDS uint32_t*)(smem + ROWS * 4);    // columns with a non-finite weight
 
     // the gradient pixel of the grid position this lane copies; positions outside the gradient copy zeros
     const unsigned char* src_plane = reinterpret_cast<const unsigned char*>(kF32Zeros);
@@ -344,7 +357,7 @@ __global__ void __launch_bounds__(ROWS * 4) f32_split(const SplitParams p) {
     if (chunks > 0) copy_a(L::kOffA);
     copy_w();
     copy_w();
-    if (tid < 3) notes[tid] = 0u;
+    if (tid < 2) notes[tid] = 0u;
     uint32_t lane_a, lane_i;   // this lane's row: grid position of the last tap of both axes
     {
         const int m = tid;
@@ -363,21 +376,17 @@ __global__ void __launch_bounds__(ROWS * 4) f32_split(const SplitParams p) {
         }
     }
     __syncthreads();
-    // what the first pass noted about the operands
     {
-        uint32_t inf = 0;
-        for (int i = tid; i < p.nflags; i += THREADS) inf |= p.flags[i];
-        if (inf) atomicOr((uint32_t*)(smem_generic + ROWS * 4), 1u);
         const int n = p.nc32 * 2 * taps * 2;
         for (int i = tid; i < n; i += THREADS) {
-            const uint32_t cols = p.wmask[(size_t)ntile * n + i];
-            if (cols) atomicOr((uint32_t*)(smem_generic + ROWS * 4 + 4 + 4 * (i & 1)), cols);
+            const uint32_t cols = p.wnotes[2 * ((size_t)ntile * n + i)];
+            if (cols) atomicOr((uint32_t*)(smem_generic + ROWS * 4 + 4 * (i & 1)), cols);
         }
     }
 
-    f32x16_t acc;
+    f32x16_t acc, low;   // the products of the first parts, the five smaller ones
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+    for (int e = 0; e < 16; ++e) acc[e] = low[e] = 0.0f;
 
     struct Frags {
         u32x4_t a[3];
@@ -403,11 +412,12 @@ __global__ void __launch_bounds__(ROWS * 4) f32_split(const SplitParams p) {
 #pragma unroll
         for (int q = 0; q < 6; ++q) {
             const bf16x8_t a = __builtin_bit_cast(bf16x8_t, f.a[PA[q]]);
+            f32x16_t& sum = q < 5 ? low : acc;
             if constexpr (SPARSE) {
                 struct { u32x4_t lo, hi; } both = {f.b[PB[q]][0], f.b[PB[q]][PARTS - 1]};
-                acc = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(a, __builtin_bit_cast(bf16x16_t, both), acc, f.idx, 0, 0);
+                sum = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(a, __builtin_bit_cast(bf16x16_t, both), sum, f.idx, 0, 0);
             } else {
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8_t, f.b[PB[q]][0]), acc, 0, 0, 0);
+                sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8_t, f.b[PB[q]][0]), sum, 0, 0, 0);
             }
         }
     };
@@ -451,8 +461,19 @@ __global__ void __launch_bounds__(ROWS * 4) f32_split(const SplitParams p) {
         if (more && !early) load(f, abuf, wbuf, first_at, 0);
     }
 
+    float check = 0.0f;   // NaN: a result is not finite
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] += low[e], check = fmaf(acc[e], 0.0f, check);
+    const bool unusual = check != check;
+    bool large = false;   // what the first pass noted about the operands
+    if (__builtin_expect(__any(unusual), 0)) {
+        const int n = p.nc32 * 2 * taps * 2;
+        for (int i = lane; i < p.gblocks; i += 64) large = large || p.gnotes[i] != 0;
+        for (int i = lane; i < n; i += 64) large = large || p.wnotes[2 * ((size_t)ntile * n + i) + 1] != 0;
+        large = __any(large);
+    }
     const int col = ntile * 64 + wn * 32 + (lane & 31);
-    const bool inf = notes[0] != 0, bad_col = ((notes[1 + wn] >> (lane & 31)) & 1u) != 0;
+    const bool bad_col = ((notes[wn] >> (lane & 31)) & 1u) != 0;
     if (col >= p.C_in) return;
     typedef int i32x4_t __attribute__((ext_vector_type(4)));
     i32x4_t pixels[4];
@@ -461,14 +482,14 @@ __global__ void __launch_bounds__(ROWS * 4) f32_split(const SplitParams p) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
         const int pix = pixels[e >> 2][e & 3];
-        if (pix >= 0) p.dD[(size_t)pix * p.C_in + col] = acc[e];
+        if (pix >= 0) p.dD[(size_t)pix * p.C_in + col] = acc[e] * kSplitUnscale;
     }
-    if (__builtin_expect(inf || bad_col, 0)) {
+    if (__builtin_expect((large && unusual) || bad_col, 0)) {
         for (int e = 0; e < 16; ++e) {
             const int pix = rowpix[wm * 32 + 8 * (e >> 2) + 4 * half + (e & 3)];
             if (pix < 0) continue;
             float* const at = p.dD + (size_t)pix * p.C_in + col;
-            if (bad_col || *at != *at)
+            if (bad_col || (float_to_bits(*at) & 0x7F800000u) == 0x7F800000u)   // (with no large operand a NaN is the gradient's own)
                 *at = split_sum_again<SPARSE>(reinterpret_cast<const SDGP_CONSTANT SplitParams*>((uint64_t)__builtin_amdgcn_kernarg_segment_ptr()), pix, col);
         }
     }

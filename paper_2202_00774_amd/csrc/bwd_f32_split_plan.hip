@@ -7,7 +7,7 @@ namespace {
 
 template <int M, int RK, bool NLE2, bool SPARSE>
 int first_pass(const SplitParams& p, hipStream_t stream) {
-    hipLaunchKernelGGL((split_operands<M, RK, NLE2, SPARSE>), dim3((unsigned)(p.wblocks + p.nflags)), dim3(256), 0, stream, p);
+    hipLaunchKernelGGL((split_operands<M, RK, NLE2, SPARSE>), dim3((unsigned)(p.wblocks + p.gblocks)), dim3(256), 0, stream, p);
     return launch_status();
 }
 template <int M, bool NLE2, bool SPARSE>
@@ -51,7 +51,7 @@ int bwd_f32_split_launch(const void* dO, const void* W, void* dD, int64_t B, int
     p.dO = static_cast<const float*>(dO), p.W = static_cast<const float*>(W), p.dD = static_cast<float*>(dD);
     unsigned char* const ws = static_cast<unsigned char*>(workspace);
     p.planes = ws, p.idx = reinterpret_cast<uint16_t*>(ws + s.off_idx), p.wimg = ws + s.off_wimg;
-    p.wmask = reinterpret_cast<uint32_t*>(ws + s.off_wmask), p.flags = reinterpret_cast<uint32_t*>(ws + s.off_flags);
+    p.wnotes = reinterpret_cast<uint32_t*>(ws + s.off_wnotes), p.gnotes = reinterpret_cast<uint32_t*>(ws + s.off_gnotes);
     p.mix = seed_mix(seed);
     int rc;
     if (n == m) rc = first_pass<4, kDenseRanker, false, false>(p, stream);

@@ -13,7 +13,7 @@ struct SplitPlan {
     bool sparse;
     int rows, np;   // of the product's tile; np: grid positions the kernel variant holds
     size_t bytes;   // workspace
-    size_t off_idx, off_wimg, off_wmask, off_flags;
+    size_t off_idx, off_wimg, off_wnotes, off_gnotes;
 };
 
 inline size_t split_align(size_t x) { return (x + 255u) & ~(size_t)255u; }
@@ -120,12 +120,12 @@ inline bool split_plan(SplitPlan& s, int64_t B, int64_t H, int64_t Wd, int64_t C
     if (units > (1 << 22)) return false;
     s.p.wblocks = (int)((units + 3) / 4);
     const int ic = m > 16 && !dense ? 32 : 16, px = 256 / (64 / ic);
-    s.p.nflags = (int)std::min<int64_t>(2048, (p.npix + px - 1) / px * ((C_out + 63) / 64));
+    s.p.gblocks = (int)std::min<int64_t>(2048, (p.npix + px - 1) / px * ((C_out + 63) / 64));
     s.off_idx = split_align((size_t)p.nchunks * 96 * (size_t)p.npix);
     s.off_wimg = s.off_idx + (s.sparse ? split_align((size_t)p.nchunks * 4 * (size_t)p.npix) : 0);
-    s.off_wmask = s.off_wimg + (size_t)units * 3 * 1024;
-    s.off_flags = s.off_wmask + split_align((size_t)units * 4);
-    s.bytes = s.off_flags + split_align((size_t)s.p.nflags * 4);
+    s.off_wnotes = s.off_wimg + (size_t)units * 3 * 1024;
+    s.off_gnotes = s.off_wnotes + split_align((size_t)units * 8);
+    s.bytes = s.off_gnotes + split_align((size_t)s.p.gblocks * 4);
     return true;
 }
 

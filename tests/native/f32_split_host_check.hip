@@ -4,6 +4,8 @@
 //     class's taps row by row from the class's first slot on, takes it for (Fig. 3: dD's pixels of one parity class meet the
 //     taps r0, r0 + stride, ... of each axis), every tap has one slot, and no slot lies outside the filter.
 //   * grid_side: never below one, and no position fewer than the taps reach.
+//   * split3, split_join: three bf16 parts that add up to 2^24 x exactly, the second at most 2^-8 of it and the third 2^-17, no
+//     subnormal among them, so that the products left out are at most 2^-24 (1 + 2^-9) of the whole; and back to x's own bits.
 //   * the planner declines launches of 2^32 threads and more.
 // Prints one line per check and returns the number of mismatches.  Test infrastructure, not product code.
 #include <hip/hip_runtime.h>
@@ -48,6 +50,42 @@ static int check_sides() {
     return bad;
 }
 
+static bool bf16_part(uint32_t u) { return (u & 0xFFFFu) == 0u && ((u & 0x7F800000u) != 0u || (u & 0x7FFFFFFFu) == 0u); }
+
+static int check_split() {
+    int bad = 0;
+    uint64_t state = 88172645463325252ull;
+    double most = 0.0, other = 0.0;
+    for (int64_t i = 0; i < 20000000; ++i) {
+        state ^= state << 13, state ^= state >> 7, state ^= state << 17;
+        uint32_t x = (uint32_t)state, kind = (uint32_t)(state >> 40) & 7u;
+        if (kind == 0) x = (x & 0x80000000u) | (0x3F800000u + (x & 0xFFFFu) * 0x81u);       // runs of ones
+        if (kind == 1) x &= 0x807FFFFFu;                                                     // subnormal
+        if (kind == 2) x = (x & 0x80FFFFFFu) | 0x73000000u;                                  // about 2^104
+        if (kind == 3) x |= 0x7F800000u;                                                     // infinite, NaN
+        if (kind == 4) x |= 0xFFFFu << (x >> 27 & 7u);
+        if (i < 4) x = (i & 1 ? 0x80000000u : 0u) | (i & 2 ? 0x7F800000u : 0u);
+        const Split3 s = split3(x);
+        const float back = split_join(s.h >> 16, s.m >> 16, s.l >> 16);
+        if (float_to_bits(back) != x && !(back == 0.0f && (x << 1) == 0u)) ++bad;
+        if (s.h == 0x7FC00000u) {
+            if ((x & 0x7FFFFFFFu) < 0x737F8000u) ++bad;   // (rounds to 2^104 and beyond)
+            continue;
+        }
+        const double v = (double)bits_to_float(x) * 0x1p24, m = bits_to_float(s.m), l = bits_to_float(s.l);
+        if (!bf16_part(s.h) || !bf16_part(s.m) || !bf16_part(s.l) || (double)bits_to_float(s.h) + m + l != v) ++bad;
+        if (v < 0 ? m < v * 0x1p-8 || m > -v * 0x1p-8 || l < v * 0x1p-17 || l > -v * 0x1p-17 : m > v * 0x1p-8 || m < -v * 0x1p-8 || l > v * 0x1p-17 || l < -v * 0x1p-17) ++bad;
+        if (v != 0) {   // the products left out, of this value and the one before
+            static double pm = 0, pl = 0;
+            const double dm = m / v, dl = l / v, out = dm * pl + dl * pm + dl * pl;
+            most = out > most ? out : most, other = out < other ? out : other, pm = dm, pl = dl;
+        }
+    }
+    bad += most > 0x1p-24 * (1 + 0x1p-9) || -other > 0x1p-24 * (1 + 0x1p-9);
+    printf("split: left out at most %.3g and %.3g, mismatches %d\n", most, other, bad);
+    return bad;
+}
+
 static int check_limits() {
     SplitPlan s;
     int bad = 0;
@@ -60,7 +98,7 @@ static int check_limits() {
 }
 
 int main() {
-    const int total = check_slots() + check_sides() + check_limits();
+    const int total = check_slots() + check_sides() + check_split() + check_limits();
     printf("total mismatches %d\n", total);
     return total != 0;
 }

@@ -115,3 +115,36 @@ def test_classes_without_taps(shape, n, m, ranker):
     out = run(layer, dO, W, n, m, ranker, 17)
     assert rel_error(out, ref, ab) <= 1e-6
     assert np.all(out[ab == 0] == 0)
+
+
+@pytest.mark.parametrize("n,m", [(2, 4), (3, 4), (4, 4)])
+def test_every_product_counts(n, m):
+    """One term to a result: an error of 2^-24 for the products left out, as much for each of the two sums and the result.  The
+    smallest products that count are 2^-17 of the whole, and every result has its own."""
+    layer = wl.ConvLayer("p", 128, 32, 32, 33, 32, 1, 1, 1, 0)
+    assert takes(layer, n, m)
+    rng = np.random.default_rng(31)
+    dO = np.zeros(layer.dO_shape, np.float32).reshape(-1, 32)
+    pixels = np.arange(dO.shape[0])
+    dO[pixels, rng.integers(0, 32, pixels.size)] = rng.choice([-1, 1], pixels.size) * rng.uniform(1, 2, pixels.size)
+    dO[::7, 3] += 2.0 ** -9 - 2.0 ** -23           # (some pixels have two terms)
+    W = (rng.choice([-1, 1], layer.W_shape) * rng.uniform(1, 2, layer.W_shape)).astype(np.float32)
+    W[:, 0, 0, ::3] = np.float32(1 + 2.0 ** -7 - 2.0 ** -23) * np.sign(W[:, 0, 0, ::3])   # the most that truncation loses
+    dO = dO.reshape(layer.dO_shape)
+    ref, ab = oracle.conv_bwd_data(oracle.prune(dO, n, m, oracle.GREEDY)[0], W, 32, 32, 1, 0)
+    assert rel_error(run(layer, dO, W, n, m, oracle.GREEDY, 0), ref, ab) <= 4 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("n,m", [(2, 4), (4, 4)])
+@pytest.mark.parametrize("grad,weight", [(1e-38, 1.0), (1e-36, 1e3), (1.0, 1e-38), (1e-30, 1e-7), (1e34, 1e-20), (1e-20, 1e34), (1e13, 1e13)])
+def test_whole_range(grad, weight, n, m):
+    """Operands and results next to both ends of fp32's range, subnormal ones among them, have the error of any others (and half
+    the smallest step, of the result and of the terms of a sum)."""
+    layer = wl.ConvLayer("r", 32, 24, 24, 33, 64, 3, 3, 1, 1)
+    assert takes(layer, n, m)
+    rng = np.random.default_rng(33)
+    dO = (wl.laplace_with_zeros(layer.dO_shape, 1.0, 0.3, seed=33, dtype=wl.F32).astype(np.float64) * grad).astype(np.float32)
+    W = (rng.normal(size=layer.W_shape) * weight).astype(np.float32)
+    ref, ab = oracle.conv_bwd_data(oracle.prune(dO, n, m, oracle.GREEDY)[0], W, 24, 24, 1, 1)
+    got = run(layer, dO, W, n, m, oracle.GREEDY, 0).astype(np.float64)
+    assert np.all(np.isfinite(ref)) and np.all(np.abs(got - ref) <= 1e-6 * ab + 2.0 ** -149 * (1 + 9 * 64))
