@@ -213,9 +213,9 @@ size_t first_layer_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int
     return 0;
 }
 
-// Problems that run without a workspace too, whatever the query says: fp32, on the kernel that needs none, and pruned first
-// layers in groups of 32, whose kernel then gathers the filter itself.
-bool workspace_is_optional(int64_t C_in, int dt, int n, int m) { return dt == SDGP_F32 || (C_in <= 4 && m == 32 && n != m); }
+// bf16 problems that run without a workspace too, whatever the query says: pruned first layers in groups of 32, whose kernel then
+// gathers the filter itself.
+bool workspace_is_optional(int64_t C_in, int n, int m) { return C_in <= 4 && m == 32 && n != m; }
 
 }  // namespace
 
@@ -244,9 +244,13 @@ int sdgp_conv_bwd_data(const void* dO, const void* W, void* dD, int64_t B, int64
     if (!valid_ranker(rk)) return SDGP_ERR_RANKER;
     if (g.n_dD == 0) return SDGP_OK;
     if (dD == nullptr || (g.n_dO > 0 && dO == nullptr) || (g.n_W > 0 && W == nullptr)) return SDGP_ERR_NULL;
+    // (in fp32 the kernel that uses a workspace looks at its size itself: asking here would plan every call twice)
+    if (dt == SDGP_F32)
+        return bwd_dispatch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m, rk, seed, workspace, workspace_bytes,
+                            static_cast<hipStream_t>(hip_stream));
     const size_t need = sdgp_conv_bwd_data_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m);
     const bool room = need > 0 && workspace != nullptr && workspace_bytes >= need && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
-    if (need > 0 && !room && !workspace_is_optional(C_in, dt, n, m)) return SDGP_ERR_WORKSPACE;
+    if (need > 0 && !room && !workspace_is_optional(C_in, n, m)) return SDGP_ERR_WORKSPACE;
     return bwd_dispatch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m, rk, seed, room ? workspace : nullptr,
                         room ? workspace_bytes : 0, static_cast<hipStream_t>(hip_stream));
 }
@@ -262,11 +266,11 @@ int sdgp_conv_bwd_data_noalloc(const void* dO, const void* W, void* dD, int64_t 
     if (dD == nullptr || (g.n_dO > 0 && dO == nullptr) || (g.n_W > 0 && W == nullptr)) return SDGP_ERR_NULL;
     // what the call cannot do without (a first layer's filter image); a pass that ranks the gradient ahead of the
     // product is only an option, taken when its arrays fit the scratch
-    const size_t must = workspace_is_optional(C_in, dt, n, m) ? 0 : first_layer_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m, g);
+    const size_t must = workspace_is_optional(C_in, n, m) ? 0 : first_layer_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m, g);
     if (must > (size_t)SDGP_NOALLOC_SCRATCH_BYTES) return SDGP_ERR_WORKSPACE;  // more scratch than the library holds
-    const size_t need = sdgp_conv_bwd_data_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m);
+    const size_t need = dt == SDGP_F32 ? 0 : sdgp_conv_bwd_data_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m);
     void* ws = nullptr;
-    if (dt != SDGP_F32 && need > 0 && need <= (size_t)SDGP_NOALLOC_SCRATCH_BYTES) {
+    if (need > 0 && need <= (size_t)SDGP_NOALLOC_SCRATCH_BYTES) {
         ws = scratch_on_current_device();
         if (ws == nullptr) return SDGP_ERR_HIP;
     }

@@ -18,24 +18,43 @@ struct SplitPlan {
 
 inline size_t split_align(size_t x) { return (x + 255u) & ~(size_t)255u; }
 
-// Fewest tiles, then fewest grid positions, for tiles of `rows` rows on grids of at most `np` positions.  0: nothing fits.
-inline int64_t split_tiles(SplitPlan& s, int rows, int np, int64_t B, int64_t h, int64_t w, int ny, int nx) {
+// Tile sides worth a look on an axis of n pixels, longest first: the shortest for every number of tiles.  Beside a short other
+// axis all of them: a longer side makes another count of images to halve, there sometimes a better one.
+struct SplitSides {
+    int count;
+    int side[256], tiles[256];
+};
+inline void split_sides(SplitSides& s, int64_t n, int64_t other) {
+    s.count = 0;
+    for (int side = (int)std::min<int64_t>(n, 256); side >= 1; --side) {
+        const int tiles = (int)((n + side - 1) / side);
+        if (other > 8) side = (int)((n + tiles - 1) / tiles);
+        s.side[s.count] = side, s.tiles[s.count++] = tiles;
+    }
+}
+
+// The tiles of `rows` rows on grids of at most `np` positions that take the fewest steps: rows times taps and grid positions,
+// of all tiles.  Their number, 0 when nothing fits.  (On the host, in every call: trying every side took 10 to 40 us.)
+inline int64_t split_tiles(SplitPlan& s, int rows, int np, int64_t B, const SplitSides& hs, const SplitSides& ws, int ny, int nx) {
     SplitParams& p = s.p;
     double best = 1e300;
     int64_t tiles = 0;
-    for (int TH = 1; TH <= std::min<int64_t>(h, rows); ++TH)
-        for (int TW = 1; TW <= std::min<int64_t>(w, rows / TH); ++TW)
-            for (int TB = std::max(1, (int)std::min<int64_t>(B, rows / (TH * TW))); TB >= 1; TB /= 2) {
-                const int npad = TB * (TH + ny - 1) * (TW + nx - 1);
-                if (npad > np) continue;
-                const int64_t tb = (B + TB - 1) / TB, th = (h + TH - 1) / TH, tw = (w + TW - 1) / TW;
-                const double cost = (double)tb * th * tw * (rows * (double)(ny * nx) + npad);
-                if (cost < best || (cost == best && TW > p.TW)) {
-                    best = cost, tiles = tb * th * tw;
-                    p.TB = TB, p.TH = TH, p.TW = TW, p.tiles_h = (int)th, p.tiles_w = (int)tw;
-                    s.rows = rows, s.np = np;
-                }
+    for (int j = 0; j < ws.count; ++j)
+        for (int i = 0; i < hs.count; ++i) {
+            const int area = hs.side[i] * ws.side[j], grid = (hs.side[i] + ny - 1) * (ws.side[j] + nx - 1);
+            if (area > rows || grid > np) continue;
+            const double each = (double)hs.tiles[i] * ws.tiles[j];
+            if ((double)B * each * (area * (double)(ny * nx) + grid) >= best) continue;   // with full tiles
+            int TB = (int)std::min<int64_t>(B, rows / area);
+            while (TB * grid > np) TB /= 2;
+            const int64_t tb = (B + TB - 1) / TB;
+            const double cost = (double)tb * each * (rows * (double)(ny * nx) + (double)(TB * grid));
+            if (cost < best) {
+                best = cost, tiles = tb * hs.tiles[i] * ws.tiles[j];
+                p.TB = TB, p.TH = hs.side[i], p.TW = ws.side[j], p.tiles_h = hs.tiles[i], p.tiles_w = ws.tiles[j];
+                s.rows = rows, s.np = np;
             }
+        }
     return tiles;
 }
 
@@ -95,19 +114,24 @@ inline bool split_plan(SplitPlan& s, int64_t B, int64_t H, int64_t Wd, int64_t C
     const int ny = (R + stride - 1) / stride, nx = (S + stride - 1) / stride;
     const int64_t h = (H + stride - 1) / stride, w = (Wd + stride - 1) / stride;
     const int64_t classes = (int64_t)stride * stride;
-    // most small problems go by without the search for tiles, a microsecond or more of host time: the estimate is lowest with
-    // whole tiles of 256 rows, the cheaper step of 128 and the larger group of taps
+    // most small problems go by without the search for tiles: the estimate is lowest with whole tiles of 256 rows, the cheaper step
+    // of 128 and the larger group of taps
+    const int64_t whole = (B * h * w + 255) / 256;
     s.rows = 128, s.np = 384;
-    const SplitEstimates least = split_estimate(s, (B * h * w + 255) / 256, m);
+    const SplitEstimates least = split_estimate(s, whole, m);
     if (least.split > 0.9 * least.plain) return false;
+    SplitSides hs, ws;
+    split_sides(hs, h, w), split_sides(ws, w, h);
     // 384 positions leave room for two taps of compressed planes per stage, 512 for one
-    int64_t tiles = split_tiles(s, 256, 384, B, h, w, ny, nx);
-    SplitPlan other = s;
-    int64_t t = split_tiles(other, 256, 512, B, h, w, ny, nx);
-    if (t > 0 && (tiles == 0 || t < tiles)) s = other, tiles = t;
+    int64_t tiles = split_tiles(s, 256, 384, B, hs, ws, ny, nx);
+    if (tiles == 0 || tiles > whole) {
+        SplitPlan other = s;
+        const int64_t t = split_tiles(other, 256, 512, B, hs, ws, ny, nx);
+        if (t > 0 && (tiles == 0 || t < tiles)) s = other, tiles = t;
+    }
     if (tiles * p.ntiles_n * classes < 192) {
-        other = s;
-        t = split_tiles(other, 128, 256, B, h, w, ny, nx);
+        SplitPlan other = s;
+        const int64_t t = split_tiles(other, 128, 256, B, hs, ws, ny, nx);
         if (t > 0) s = other, tiles = t;
     }
     const int64_t blocks = tiles * p.ntiles_n;

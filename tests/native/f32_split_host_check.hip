@@ -6,10 +6,12 @@
 //   * grid_side: never below one, and no position fewer than the taps reach.
 //   * split3, split_join: three bf16 parts that add up to 2^24 x exactly, the second at most 2^-8 of it and the third 2^-17, no
 //     subnormal among them, so that the products left out are at most 2^-24 (1 + 2^-9) of the whole; and back to x's own bits.
+//   * split_tiles against every tile side, and the time a plan takes.
 //   * the planner declines launches of 2^32 threads and more.
 // Prints one line per check and returns the number of mismatches.  Test infrastructure, not product code.
 #include <hip/hip_runtime.h>
 
+#include <chrono>
 #include <cstdio>
 #include <cstring>
 
@@ -86,6 +88,58 @@ static int check_split() {
     return bad;
 }
 
+// Rows times taps and grid positions of all tiles.
+static double tile_cost(int rows, int taps, int64_t tb, int64_t th, int64_t tw, int grid) { return (double)tb * th * tw * (rows * (double)taps + grid); }
+
+static int check_tiles() {
+    int bad = 0;
+    double worst = 1.0;
+    uint64_t state = 88172645463325252ull;
+    auto draw = [&](int lo, int hi) { state ^= state << 13, state ^= state >> 7, state ^= state << 17; return lo + (int)(state % (uint64_t)(hi - lo + 1)); };
+    for (int i = 0; i < 2000; ++i) {
+        const int64_t B = draw(1, 300);
+        const int h = draw(1, 80), w = draw(1, 80), ny = draw(1, 5), nx = draw(1, 5), rows = draw(0, 1) ? 256 : 128;
+        const int np = rows == 128 ? 256 : draw(0, 1) ? 384 : 512;
+        double best = 1e300;
+        for (int TH = 1; TH <= std::min(h, rows); ++TH)
+            for (int TW = 1; TW <= std::min(w, rows / TH); ++TW)
+                for (int TB = (int)std::min<int64_t>(B, rows / (TH * TW)); TB >= 1; TB /= 2) {
+                    const int grid = TB * (TH + ny - 1) * (TW + nx - 1);
+                    if (grid <= np) best = std::min(best, tile_cost(rows, ny * nx, (B + TB - 1) / TB, (h + TH - 1) / TH, (w + TW - 1) / TW, grid));
+                }
+        SplitPlan s;
+        SplitSides hs, ws;
+        split_sides(hs, h, w), split_sides(ws, w, h);
+        const int64_t tiles = split_tiles(s, rows, np, B, hs, ws, ny, nx);
+        const SplitParams& p = s.p;
+        if (tiles == 0) {
+            bad += best < 1e300;
+            continue;
+        }
+        const int grid = p.TB * (p.TH + ny - 1) * (p.TW + nx - 1);
+        const int64_t tb = (B + p.TB - 1) / p.TB;
+        bad += grid > np || p.TB * p.TH * p.TW > rows || p.tiles_h * p.TH < h || p.tiles_w * p.TW < w || tiles != tb * p.tiles_h * p.tiles_w;
+        worst = std::max(worst, tile_cost(rows, ny * nx, tb, p.tiles_h, p.tiles_w, grid) / best);
+    }
+    bad += worst > 1.05;
+    double slowest = 0.0;
+    for (int hw = 16; hw <= 224; ++hw) {
+        double best = 1e9;
+        for (int k = 0; k < 10; ++k) {
+            const auto begin = std::chrono::steady_clock::now();
+            for (int x = 0; x < 8; ++x) {
+                SplitPlan s;
+                bad += split_plan(s, 16, hw, hw, 64, 64, 3, 3, 1, 1, 2, 4) && s.p.nblocks < 1;
+            }
+            best = std::min(best, std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - begin).count() / 8);
+        }
+        slowest = std::max(slowest, best);
+    }
+    bad += slowest > 8.0;   // 2.5 us; the walk over every side 33
+    printf("tiles: worst %.3f of the best, plans take up to %.2f us, mismatches %d\n", worst, slowest, bad);
+    return bad;
+}
+
 static int check_limits() {
     SplitPlan s;
     int bad = 0;
@@ -98,7 +152,7 @@ static int check_limits() {
 }
 
 int main() {
-    const int total = check_slots() + check_sides() + check_split() + check_limits();
+    const int total = check_slots() + check_sides() + check_split() + check_tiles() + check_limits();
     printf("total mismatches %d\n", total);
     return total != 0;
 }

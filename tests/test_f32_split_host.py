@@ -14,7 +14,7 @@ HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
 def test_host_check(tmp_path):
     exe = str(tmp_path / "f32_split_host_check")
     src = os.path.join(ROOT, "tests", "native", "f32_split_host_check.hip")
-    cmd = [HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    cmd = [HIPCC, "-O2", "-std=c++17", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
            "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(ROOT, "paper_2202_00774_amd", "csrc"), "-o", exe, src]
     subprocess.run(cmd, check=True, capture_output=True, timeout=300)
     run = subprocess.run([exe], capture_output=True, text=True, timeout=300)
