@@ -215,7 +215,12 @@ def sdgp_conv_bwd_data(dO: torch.Tensor, W: torch.Tensor, H: int, Wd: int, strid
     if need == 2**64 - 1:
         raise SdgpError(-3, "sdgp_conv_bwd_data_workspace")
     if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
-        workspace = torch.empty(need, dtype=torch.uint8, device=dO.device)
+        try:
+            workspace = torch.empty(need, dtype=torch.uint8, device=dO.device)
+        except torch.OutOfMemoryError:
+            if dt != F32:
+                raise
+            workspace = None    # (fp32 runs without, on another kernel)
     wbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     rc = load().sdgp_conv_bwd_data(_ptr(dO), _ptr(W), _ptr(out), B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m,
                                    ranker, seed & (2**64 - 1), _ptr(workspace), wbytes, _stream(dO))

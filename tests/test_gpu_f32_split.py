@@ -148,3 +148,23 @@ def test_whole_range(grad, weight, n, m):
     ref, ab = oracle.conv_bwd_data(oracle.prune(dO, n, m, oracle.GREEDY)[0], W, 24, 24, 1, 1)
     got = run(layer, dO, W, n, m, oracle.GREEDY, 0).astype(np.float64)
     assert np.all(np.isfinite(ref)) and np.all(np.abs(got - ref) <= 1e-6 * ab + 2.0 ** -149 * (1 + 9 * 64))
+
+
+def test_without_room_for_a_workspace():
+    """Where the device has no room for the operands' parts the binding makes the call without them, as before there were any."""
+    layer = wl.ConvLayer("m", 512, 16, 16, 128, 96, 3, 3, 1, 1)   # 42 MB
+    assert takes(layer, 2, 4)
+    dO = to_gpu(wl.laplace_with_zeros(layer.dO_shape, 1e-3, 0.3, seed=1, dtype=wl.F32))
+    W = to_gpu(wl.normal(layer.W_shape, 0.1, 2, wl.F32))
+    want = sdgp.sdgp_conv_bwd_data(dO, W, 16, 16, 1, 1, 2, 4, sdgp.GREEDY)
+    out = torch.zeros_like(want)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    torch.cuda.set_per_process_memory_fraction(1e-9)
+    try:
+        with pytest.raises(torch.OutOfMemoryError):
+            torch.empty(1 << 26, dtype=torch.uint8, device="cuda")
+        sdgp.sdgp_conv_bwd_data(dO, W, 16, 16, 1, 1, 2, 4, sdgp.GREEDY, out=out)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert (out - want).norm() <= 1e-6 * want.norm()
