@@ -155,8 +155,8 @@ int sdgp_conv_bwd_data(const void* dO, const void* W, void* dD, int64_t B, int64
  *   - Small bf16 1x1 stride-1 layers (at most 2^24 elements in the gradient and in the
  *     filter) whose C_out is a multiple of 8 but not of 32 -- a classifier's 1000
  *     outputs -- ask for the size of both with C_out rounded up to 32.  The kernels
- *     leave it unread; the size stays, and a call has to bring it, for programs built
- *     on it.
+ *     leave it unread, and a call may come without it; the size stays for programs that
+ *     know it.
  *   - fp32 layers large enough to gain by it ask for room for both operands as three bf16
  *     parts of every value (up to 1.5 times the gradient and the filter), which the bf16
  *     matrix instructions multiply; an fp32 call with a smaller workspace, or none, runs

@@ -214,6 +214,8 @@ def sdgp_conv_bwd_data(dO: torch.Tensor, W: torch.Tensor, H: int, Wd: int, strid
     need = _need("sdgp_conv_bwd_data_workspace", B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m)
     if need == 2**64 - 1:
         raise SdgpError(-3, "sdgp_conv_bwd_data_workspace")
+    if dt == BF16 and R == S == stride == 1 and C_out % 32:
+        need = 0    # (whatever the query says: no kernel for these reads a workspace)
     if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
         try:
             workspace = torch.empty(need, dtype=torch.uint8, device=dO.device)

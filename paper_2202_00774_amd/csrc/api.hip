@@ -29,6 +29,7 @@ int bwd_pw_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H,
 int bwd_gather_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
                       int R, int S, int stride, int pad, int n, int m, int rk, uint64_t seed, void* workspace, size_t workspace_bytes,
                       hipStream_t stream);
+bool bwd_pw_workspace_unread(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n, int m);
 size_t bwd_pw_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n,
                         int m);
 int bwd_row_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in,
@@ -250,7 +251,9 @@ int sdgp_conv_bwd_data(const void* dO, const void* W, void* dD, int64_t B, int64
                             static_cast<hipStream_t>(hip_stream));
     const size_t need = sdgp_conv_bwd_data_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m);
     const bool room = need > 0 && workspace != nullptr && workspace_bytes >= need && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
-    if (need > 0 && !room && !workspace_is_optional(C_in, n, m)) return SDGP_ERR_WORKSPACE;
+    if (need > 0 && !room && !workspace_is_optional(C_in, n, m) &&
+        !sdgp::bwd_pw_workspace_unread(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m))
+        return SDGP_ERR_WORKSPACE;
     return bwd_dispatch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m, rk, seed, room ? workspace : nullptr,
                         room ? workspace_bytes : 0, static_cast<hipStream_t>(hip_stream));
 }

@@ -168,7 +168,7 @@ int small_short_chunk_shape(int mode, int64_t C_in, int64_t C_out, int m, int rk
     const int64_t rows_per = kPwShapes[shape].rows, bn = kPwShapes[shape].bn;
     return ((rows + rows_per - 1) / rows_per) * ((C_in + bn - 1) / bn) < 256 ? 2 : shape;
 }
-// The workspace that the query names for them.  Nothing reads it: callers that sized theirs by the query pass the check on it.
+// The workspace that the query names for them.  Nothing reads it, and a call may leave it out; the size stays as programs know it.
 size_t small_short_chunk_bytes(int64_t rows, int64_t C_in, int64_t C_out) {
     const size_t Kp = (size_t)((C_out + kPwKC - 1) / kPwKC * kPwKC);
     return (((size_t)rows * Kp * 2u + 255u) & ~(size_t)255u) + Kp * (size_t)C_in * 2u;
@@ -180,6 +180,11 @@ size_t small_short_chunk_bytes(int64_t rows, int64_t C_in, int64_t C_out) {
 // fused kernel is used, or neither takes the problem).
 size_t bwd_pw_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n,
                         int m);
+
+// Whether no kernel reads the workspace that the query names for a bf16 problem.
+bool bwd_pw_workspace_unread(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n, int m) {
+    return small_short_chunk(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m);
+}
 
 // How bwd_pw_launch runs a problem with aligned pointers: -1 not at all, 0 as it is, 1 with the gradient ranked ahead, 2 a small
 // one with a short last chunk.

@@ -79,3 +79,30 @@ def test_nan_behind_the_last_channel(kind, n, m):
     assert clean.any() and not clean.all()
     assert np.array_equal(np.isfinite(got), clean)
     assert np.all(np.abs(got[clean] - ref[clean]) <= 1e-2 * ab[clean])
+
+
+def test_small_ones_need_no_workspace():
+    """The query names one for small 1x1 layers with a short last chunk, and nothing reads it: a call without it, with one that is too
+    small and through the binding, which allocates none, gives the same bits."""
+    layer = wl.ConvLayer("w", 5, 41, 41, 248, 1000, 1, 1, 1, 0)
+    dO, W = to_gpu(wl.laplace_with_zeros(layer.dO_shape, 1e-3, 0.3, seed=1, dtype=wl.BF16)), to_gpu(wl.normal(layer.W_shape, 0.1, 2, wl.BF16))
+    geometry = (layer.B, layer.H, layer.Wd, layer.C_in, layer.C_out, 1, 1, 1, 0, sdgp.BF16, 2, 4)
+    need = sdgp.conv_bwd_data_workspace(*geometry)
+    assert need > 1 << 20
+    room = torch.full((need,), 7, dtype=torch.uint8, device="cuda")
+    outs = []
+    for ptr, size in ((room.data_ptr(), need), (None, 0), (room.data_ptr(), 16)):
+        out = torch.empty(layer.dD_shape, dtype=torch.bfloat16, device="cuda")
+        rc = sdgp.binding.load().sdgp_conv_bwd_data(dO.data_ptr(), W.data_ptr(), out.data_ptr(), *geometry, sdgp.GREEDY, 0, ptr, size,
+                                                    torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        outs.append(out)
+    torch.cuda.synchronize()
+    assert torch.all(room == 7)
+    out = torch.empty_like(out)
+    torch.cuda.reset_peak_memory_stats()
+    before = torch.cuda.memory_allocated()
+    sdgp.sdgp_conv_bwd_data(dO, W, layer.H, layer.Wd, 1, 0, 2, 4, sdgp.GREEDY, 0, out=out)
+    assert torch.cuda.max_memory_allocated() == before
+    for other in outs:
+        assert torch.equal(other.view(torch.int16), out.view(torch.int16))
