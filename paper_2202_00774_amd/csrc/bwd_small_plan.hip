@@ -27,10 +27,18 @@ namespace {
 //     and C_out 2048 0.59-0.99, 1024 0.67-0.99 (Magnitude 0.79-1.13).
 //   ranked in the kernel, others: one round and C_out 128 on 0.18-1.02 (160 at C_in 64 1.08-1.13), else 0.98-1.73; two and
 //     C_out 1024 on 0.33-0.81.
-//   C_out no multiple of its chunk, measured against padded copies, which took 1.3-2.6 times the kernel's time on the layer as
-//     it is: one round 0.31-0.75; two and C_out 1000 on 0.20-0.83, 200 0.92-1.24; three and C_out 1000 on 0.30-1.07; four 0.39-1.33.
-//   the same where its elements are too many for that (bwd_tiled): two rounds 0.20-0.84; three 0.31-0.89 (1.17 at C_in 64);
-//     four and C_out 1000 on 0.38-0.70, 200 0.97-1.45.
+//   C_out no multiple of its chunk (6955 calls, hardly a difference between C_in of 64 to 2048):
+//     dense: one round and C_out 40 to 250 1.19-1.40, 256 to 520 0.90-1.14, 650 on 0.35-1.02; two and 2000 on 0.68-1.40 (from C_in 1024
+//       on 0.81-0.98), 1496 and C_in 2048 0.81-0.84, else 1.0-2.3; three 1.07-3.3.
+//     n <= 2, Magnitude: one and 40 to 200 1.01-1.27, 200 to 256 0.95-1.12, from there on 0.35-0.90; two and 1300 on 0.75-1.06, else
+//       0.92-2.0; three 0.96-2.6.
+//     n <= 2, Random and Rescaled: one and 40 to 160 0.94-1.29, 200 0.83-1.08, on 0.26-0.85; two and 800 on 0.44-1.03, else 0.84-2.0;
+//       three and 1300 on 0.65-1.24, else 0.83-2.6.
+//     general n: one and 40 to 160 0.90-1.22, 200 0.81-1.02, on 0.26-0.80; two and 800 on 0.55-0.97 (Rescaled 650 0.85-0.98), else
+//       0.79-1.9; three and 1000 on 0.55-1.13, else 0.82-2.5.
+//     more than 2^24 elements (the pointwise kernel on its usual tiles), two rounds: dense and Magnitude 1000 on 0.67-0.99.
+//     four rounds: 0.77-4.05, below 1 for few.
+//   the same where fewer than 64 tiles of more elements are left to bwd_tiled: four rounds 0.38-0.70.
 // Other filters, stride 1: one round 0.16-0.86 whatever takes them.
 //   bwd_row, which takes them from about 480 tiles on: 1.0-1.9 (groups of 32 0.33-0.99, at C_in 96 1.02-1.14).
 //   bwd_conv3 (C_out a multiple of 64, dense or n <= 2), two rounds: dense and C_in > 64 0.69-0.91, n <= 2 and C_in > 64 0.81-1.0 where
@@ -47,8 +55,13 @@ constexpr int64_t kRound = 256;
 int64_t most_pointwise(int way, bool whole_chunks, int64_t C_in, int64_t C_out, int n, int m, int rk) {
     const bool sparse = n <= 2 && m <= 16;
     if (!whole_chunks) {
-        if (way < 0) return C_out >= 512 ? 4 * kRound : C_in > 64 ? 3 * kRound : 2 * kRound;
-        return C_out >= 512 ? 3 * kRound : kRound;
+        if (way < 0) return 4 * kRound;
+        if (n == m) {
+            const bool two = C_out >= (way == 0 ? 1000 : C_in >= 2048 ? 1400 : 2000) && (way == 0 || C_in >= 1024);
+            return two ? 2 * kRound : C_out >= 320 ? kRound : 0;
+        }
+        if (sparse && rk == kGreedy) return C_out >= (way == 0 ? 1000 : 1300) ? 2 * kRound : C_out >= 200 ? kRound : 0;
+        return C_out >= (sparse ? 1300 : 1000) ? 3 * kRound : C_out >= (!sparse && rk == kAdjusted ? 650 : 800) ? 2 * kRound : C_out >= 160 ? kRound : 0;
     }
     if (way < 0) return 2 * kRound;
     if (n == m) return C_out >= 2048 && C_in >= 1024 ? 2 * kRound : C_out >= 1024 || (C_out >= 512 && C_in > 64) ? kRound : 0;
