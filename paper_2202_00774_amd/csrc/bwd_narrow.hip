@@ -748,6 +748,7 @@ __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) 
 bool first2_fits(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n, int m) {
     if (R != 7 || S != 7 || stride != 2 || pad != 3 || C_in < 1 || C_in > 4 || C_out < kFKC || C_out % kFKC != 0) return false;
     if (H < 2 || Wd < 2) return false;
+    if (C_out > INT32_MAX / (49 * C_in)) return false;   // (first_v_taps counts the filter's elements in 32 bits)
     if (n != m && !(m == 4 || m == 8 || m == 16 || m == 32)) return false;
     const int64_t P = (H + 1) / 2, Q = (Wd + 1) / 2;   // (H + 6 - 7) / 2 + 1
     const int64_t tiles = B * ((P + kFRows - 1) / kFRows) * ((Q + kFCols - 1) / kFCols);

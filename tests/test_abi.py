@@ -124,6 +124,13 @@ def test_first_layer_workspace_query(lib):
     assert lib.sdgp_conv_bwd_data_workspace(512, 32, 32, 64, 128, 3, 3, 1, 1, 1, 2, 4) == 0
 
 
+def test_first_layers_with_more_weights_than_32_bits_count(lib):
+    # the stem's kernel on even images counts its filter's elements in 32 bits; the other kernel's image is smaller
+    most = (2**31 - 1) // 147 // 32 * 32
+    assert lib.sdgp_conv_bwd_data_workspace(1, 2, 2, 3, most, 7, 7, 2, 3, 1, 2, 4) == most // 32 * 20 * 1024
+    assert lib.sdgp_conv_bwd_data_workspace(1, 2, 2, 3, most + 32, 7, 7, 2, 3, 1, 2, 4) == (most + 32 + 63) // 64 * 23 * 1024
+
+
 def test_workspace_too_small_is_rejected(lib):
     # wherever the library asks for workspace, passing none or too little is an error before any launch
     shapes = [(512, 32, 32, 64, 128, 3, 3, 1, 1), (128, 56, 56, 256, 64, 1, 1, 1, 0), (256, 56, 56, 128, 128, 3, 3, 2, 1),
