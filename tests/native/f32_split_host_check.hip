@@ -8,12 +8,14 @@
 //     subnormal among them, so that the products left out are at most 2^-24 (1 + 2^-9) of the whole; and back to x's own bits.
 //   * split_tiles against every tile side, and the time a plan takes.
 //   * the planner declines launches of 2^32 threads and more.
-// Prints one line per check and returns the number of mismatches.  Test infrastructure, not product code.
+// Prints one line per check and returns the number of mismatches; with the eleven numbers of a layer and a pattern as arguments
+// prints the tile (rows, grid positions of the kernel, images, height, width) the planner gives it, or "none".  Test
+// infrastructure, not product code.
 #include <hip/hip_runtime.h>
 
 #include <chrono>
 #include <cstdio>
-#include <cstring>
+#include <cstdlib>
 
 #include "bwd_f32_split_tiles.h"
 
@@ -151,7 +153,15 @@ static int check_limits() {
     return bad;
 }
 
-int main() {
+int main(int argc, char** argv) {
+    if (argc == 12) {
+        int v[11];
+        for (int i = 0; i < 11; ++i) v[i] = std::atoi(argv[i + 1]);
+        SplitPlan s;
+        if (!split_plan(s, v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], v[9], v[10])) printf("none\n");
+        else printf("%d %d %d %d %d\n", s.rows, s.np, s.p.TB, s.p.TH, s.p.TW);
+        return 0;
+    }
     const int total = check_slots() + check_sides() + check_split() + check_tiles() + check_limits();
     printf("total mismatches %d\n", total);
     return total != 0;

@@ -1,9 +1,11 @@
 """fp32 backward-data products as sums of bf16 ones, on problems large enough to take that path, against the CPU oracle:
-every shape of its tiles, widths and channel counts that fill none of them, classes without a tap, images laid together
-in a tile, non-finite operands, and the same call without a workspace.
+every shape of its tiles (tests/test_f32_split_host.py asks the planner that the layers here reach them), widths and channel
+counts that fill none of them, classes without a tap, images laid together in a tile, every product of parts on its own, both
+ends of fp32's range, non-finite operands, and the same call without a workspace.
 
-Tolerance: a product of two values of three bf16 parts each, the three smallest of its nine terms left out, errs by at most
-2^-23.4 of itself = 9e-8; K terms in fp32 add like the other fp32 tests, whose bound of 1e-5 of sum |a||w| is used.
+Tolerance, of sum |a||w|: the products left out are within 2^-24 of a term; a sum of S steps (taps times chunks of channels) is
+rounded S times by at most 2^-24 of itself, which add like their square root, at most 11 in the layers here; the sum of the
+smaller products and the result add one each: 1e-6.
 """
 import numpy as np
 import pytest
@@ -26,46 +28,64 @@ def run(layer, dO, W, n, m, ranker, seed):
     return to_host(sdgp.sdgp_conv_bwd_data(to_gpu(dO), to_gpu(W), layer.H, layer.Wd, layer.stride, layer.pad, n, m, ranker, seed))
 
 
+# the layer, rows and grid positions of its tiles
 SHAPES = [
-    (128, 16, 16, 64, 64, 3, 3, 1, 1),     # 256 rows, 384 positions
-    (30, 21, 19, 72, 36, 3, 3, 1, 1),      # ragged tiles, columns and channels
-    (400, 9, 9, 136, 100, 3, 3, 1, 1),      # several images to a tile
-    (24, 30, 30, 96, 64, 5, 5, 1, 2),      # 512 positions
-    (40, 24, 24, 33, 64, 3, 3, 2, 1),      # classes of one, two and four taps, an odd width
-    (120, 17, 17, 448, 128, 1, 1, 1, 0),   # one tap: one stage to a chunk
-    (62, 29, 29, 33, 128, 1, 1, 2, 0),     # classes without a tap
-    (30, 16, 16, 256, 64, 3, 3, 1, 1),     # 128 rows
+    ((128, 16, 16, 64, 64, 3, 3, 1, 1), (128, 256)),
+    ((30, 21, 19, 72, 36, 3, 3, 1, 1), (128, 256)),       # ragged tiles, columns and channels
+    ((30, 16, 16, 256, 64, 3, 3, 1, 1), (128, 256)),
+    ((40, 24, 24, 33, 64, 3, 3, 2, 1), (128, 256)),       # classes of one, two and four taps, an odd width
+    ((400, 9, 9, 136, 100, 3, 3, 1, 1), (256, 384)),      # three images to a tile
+    ((130, 16, 16, 136, 32, 3, 3, 1, 1), (256, 384)),
+    ((24, 30, 30, 96, 64, 5, 5, 1, 2), (256, 384)),
+    ((62, 29, 29, 33, 128, 1, 1, 2, 0), (256, 384)),      # classes without a tap, one tap: one stage to a chunk
+    ((128, 16, 16, 160, 32, 5, 5, 1, 2), (256, 512)),     # compressed: one tap to a stage
+    ((240, 8, 8, 200, 36, 3, 3, 1, 1), (256, 512)),       # four images to a tile
 ]
+PATTERNS = [(2, 4, oracle.GREEDY), (1, 4, oracle.RANDOM), (2, 4, oracle.GREEDY_ADJUSTED), (4, 4, oracle.GREEDY), (3, 4, oracle.RANDOM)]
 
 
-@pytest.mark.parametrize("n,m,ranker", [(2, 4, oracle.GREEDY), (1, 4, oracle.RANDOM), (2, 4, oracle.GREEDY_ADJUSTED), (4, 4, oracle.GREEDY)])
-@pytest.mark.parametrize("shape", SHAPES)
-def test_shapes(shape, n, m, ranker):
-    layer = wl.ConvLayer("s", *shape)
-    assert takes(layer, 2, 4)
+def compare(layer, n, m, ranker, pixels=None):
+    """The largest error of the layer's results, of some pixels where the oracle would take long."""
+    assert takes(layer, n, m)
     dO = wl.laplace_with_zeros(layer.dO_shape, 1e-3, 0.3, seed=5, dtype=wl.F32)
     W = wl.normal(layer.W_shape, 0.1, 6, wl.F32)
-    ref, ab = oracle.conv_bwd_data(oracle.prune(dO, n, m, ranker, seed=7)[0], W, layer.H, layer.Wd, layer.stride, layer.pad)
-    out = run(layer, dO, W, n, m, ranker, 7)
-    assert rel_error(out, ref, ab) <= 1e-5
+    count = layer.B * layer.H * layer.Wd
+    at = np.arange(count) if pixels is None else np.sort(np.random.default_rng(2).choice(count, pixels, replace=False))
+    ref, ab = oracle.conv_bwd_data(oracle.prune(dO, n, m, ranker, seed=7)[0], W, layer.H, layer.Wd, layer.stride, layer.pad, pixels=at)
+    out = run(layer, dO, W, n, m, ranker, 7).reshape(count, layer.C_in)[at]
+    ref, ab = ref.reshape(out.shape), ab.reshape(out.shape)
     assert np.all(out[ab == 0] == 0)
+    return rel_error(out, ref, ab)
+
+
+@pytest.mark.parametrize("n,m,ranker", PATTERNS)
+@pytest.mark.parametrize("shape", [s for s, _ in SHAPES])
+def test_shapes(shape, n, m, ranker):
+    assert compare(wl.ConvLayer("s", *shape), n, m, ranker) <= 1e-6
+
+
+@pytest.mark.parametrize("n,ranker", [(2, oracle.GREEDY), (1, oracle.RANDOM)])
+def test_one_tap(n, ranker):
+    """1x1 on several chunks: a grid lands as late as its only stage."""
+    assert compare(wl.ConvLayer("o", 120, 17, 17, 448, 128, 1, 1, 1, 0), n, 4, ranker, pixels=6000) <= 1e-6
+
+
+GROUP_LAYERS = [((64, 16, 16, 128, 96, 3, 3, 1, 1), (128, 256)), ((128, 16, 16, 128, 96, 3, 3, 1, 1), (256, 384)), ((240, 8, 8, 200, 96, 3, 3, 1, 1), (256, 512))]
+GROUPS = [(3, 4), (2, 8), (5, 8), (1, 16), (7, 16), (2, 32), (16, 32)]
 
 
 @pytest.mark.parametrize("ranker", (oracle.RANDOM, oracle.GREEDY, oracle.GREEDY_ADJUSTED))
-@pytest.mark.parametrize("n,m", [(3, 4), (2, 8), (5, 8), (1, 16), (7, 16), (2, 32), (16, 32)])
-def test_groups(n, m, ranker):
-    layer = wl.ConvLayer("g", 64, 16, 16, 128, 96, 3, 3, 1, 1)
-    assert takes(layer, n, m)
-    dO = wl.laplace_with_zeros(layer.dO_shape, 1e-3, 0.3, seed=8, dtype=wl.F32)
-    W = wl.normal(layer.W_shape, 0.1, 9, wl.F32)
-    ref, ab = oracle.conv_bwd_data(oracle.prune(dO, n, m, ranker, seed=10)[0], W, 16, 16, 1, 1)
-    assert rel_error(run(layer, dO, W, n, m, ranker, 10), ref, ab) <= 1e-5
+@pytest.mark.parametrize("n,m", GROUPS)
+@pytest.mark.parametrize("shape", [s for s, _ in GROUP_LAYERS])
+def test_groups(shape, n, m, ranker):
+    assert compare(wl.ConvLayer("g", *shape), n, m, ranker, pixels=4000) <= 1e-6
 
 
 @pytest.mark.parametrize("n,m", [(2, 4), (4, 8)])
-def test_non_finite(n, m):
+@pytest.mark.parametrize("shape", [s for s, _ in GROUP_LAYERS])
+def test_non_finite(shape, n, m):
     """An infinite gradient value times a weight with few bits, dropped channels under an infinite weight, NaN."""
-    layer = wl.ConvLayer("i", 64, 16, 16, 128, 96, 3, 3, 1, 1)
+    layer = wl.ConvLayer("i", *shape)
     assert takes(layer, n, m)
     rng = np.random.default_rng(3)
     dO = rng.uniform(1, 2, layer.dO_shape).astype(np.float32)
@@ -75,12 +95,14 @@ def test_non_finite(n, m):
     dO[5, 1, 1, :4] = np.nan
     W[:, 0, 0, 5] = np.inf
     W[9, 2, 2, 40] = np.nan
-    ref, ab = oracle.conv_bwd_data(oracle.prune(dO, n, m, oracle.GREEDY)[0], W, 16, 16, 1, 1)
-    got = run(layer, dO, W, n, m, oracle.GREEDY, 0).astype(np.float64)
+    images = 8 * layer.H * layer.Wd
+    ref, ab = oracle.conv_bwd_data(oracle.prune(dO, n, m, oracle.GREEDY)[0], W, layer.H, layer.Wd, 1, 1, pixels=np.arange(images))
+    got = run(layer, dO, W, n, m, oracle.GREEDY, 0).astype(np.float64).reshape(-1, layer.C_in)[:images]
+    ref, ab = ref.reshape(got.shape), ab.reshape(got.shape)
     fin, nan = np.isfinite(ref), np.isnan(ref)
     assert fin.any() and nan.any() and (~fin & ~nan).any()
     assert np.array_equal(np.isnan(got), nan) and np.array_equal(got[~fin & ~nan], ref[~fin & ~nan])
-    assert np.all(np.abs(got[fin] - ref[fin]) <= 1e-5 * ab[fin])
+    assert np.all(np.abs(got[fin] - ref[fin]) <= 1e-6 * ab[fin])
 
 
 def test_without_a_workspace():

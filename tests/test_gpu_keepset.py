@@ -159,8 +159,9 @@ def test_linear_identity_equals_the_oracle():
 
 
 def test_padded_reduction_identity_equals_the_oracle():
-    """C_out = 40 and 1000 are multiples of 8 but not of the kernel's 32-channel chunk: small 1x1 problems are padded
-    into the workspace (zero channels, zero filter rows) and the random ranker keeps indexing rows of C_out elements."""
+    """C_out = 40 and 1000 are multiples of 8 but not of the kernel's 32-channel chunk: the last chunk's missing channels and
+    filter rows are zeros, and the random ranker keeps indexing rows of C_out elements.  (The query still names the size of
+    padded copies.)"""
     for rows, C in ((9001, 40), (3100, 1000)):
         layer = wl.ConvLayer("padded_n%d" % C, rows, 1, 1, C, C, 1, 1, 1, 0)
         assert sdgp.conv_bwd_data_workspace(rows, 1, 1, C, C, 1, 1, 1, 0, sdgp.BF16, 2, 4) >= 2 * rows * (-(-C // 32) * 32)

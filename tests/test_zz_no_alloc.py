@@ -74,8 +74,8 @@ def test_noalloc_ranks_ahead_of_the_product_when_the_arrays_fit_the_scratch():
 
 
 def test_noalloc_pads_a_ragged_reduction_into_the_scratch():
-    """A small 1x1 layer with 40 output channels (a multiple of 8, not of the kernel's 32-channel chunk): the padded
-    copies of gradient and filter (49 KB here) go into the scratch array; a second, smaller call follows."""
+    """A small 1x1 layer with 40 output channels (a multiple of 8, not of the kernel's 32-channel chunk), whose query names the
+    size of padded copies (49 KB here) that the kernels no longer make; a second, smaller call follows."""
     big = wl.ConvLayer("padded_n40", 3, 11, 11, 96, 40, 1, 1, 1, 0)
     small = wl.ConvLayer("padded_n40_small", 1, 5, 7, 64, 40, 1, 1, 1, 0)
     need = sdgp.conv_bwd_data_workspace(3, 11, 11, 96, 40, 1, 1, 1, 0, sdgp.BF16, 2, 4)
