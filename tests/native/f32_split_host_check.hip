@@ -6,7 +6,7 @@
 //   * grid_side: never below one, and no position fewer than the taps reach.
 //   * split3, split_join: three bf16 parts that add up to 2^24 x exactly, the second at most 2^-8 of it and the third 2^-17, no
 //     subnormal among them, so that the products left out are at most 2^-24 (1 + 2^-9) of the whole; and back to x's own bits.
-//   * split_tiles against every tile side, and the time a plan takes.
+//   * split_tiles against every tile side, and how many it looks at.
 //   * the planner declines launches of 2^32 threads and more.
 // Prints one line per check and returns the number of mismatches; with the eleven numbers of a layer and a pattern as arguments
 // prints the tile (rows, grid positions of the kernel, images, height, width) the planner gives it, or "none".  Test
@@ -124,21 +124,26 @@ static int check_tiles() {
         worst = std::max(worst, tile_cost(rows, ny * nx, tb, p.tiles_h, p.tiles_w, grid) / best);
     }
     bad += worst > 1.05;
-    double slowest = 0.0;
+    int most = 0;   // pairs of sides that a plan looks at (all of them: up to 1400)
     for (int hw = 16; hw <= 224; ++hw) {
-        double best = 1e9;
-        for (int k = 0; k < 10; ++k) {
-            const auto begin = std::chrono::steady_clock::now();
-            for (int x = 0; x < 8; ++x) {
-                SplitPlan s;
-                bad += split_plan(s, 16, hw, hw, 64, 64, 3, 3, 1, 1, 2, 4) && s.p.nblocks < 1;
-            }
-            best = std::min(best, std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - begin).count() / 8);
-        }
-        slowest = std::max(slowest, best);
+        SplitSides sides;
+        split_sides(sides, hw, hw);
+        int pairs = 0;
+        for (int i = 0; i < sides.count; ++i)
+            for (int j = 0; j < sides.count; ++j) pairs += sides.side[i] * sides.side[j] <= 256;
+        most = std::max(most, pairs);
     }
-    bad += slowest > 8.0;   // 2.5 us; the walk over every side 33
-    printf("tiles: worst %.3f of the best, plans take up to %.2f us, mismatches %d\n", worst, slowest, bad);
+    bad += most > 500;
+    double best_us = 1e9;
+    for (int k = 0; k < 20; ++k) {
+        const auto begin = std::chrono::steady_clock::now();
+        for (int x = 0; x < 20; ++x) {
+            SplitPlan s;
+            bad += !split_plan(s, 16, 112, 112, 64, 64, 3, 3, 1, 1, 2, 4);
+        }
+        best_us = std::min(best_us, std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - begin).count() / 20);
+    }
+    printf("tiles: worst %.3f of the best, up to %d pairs of sides, a plan at 112x112 takes %.2f us, mismatches %d\n", worst, most, best_us, bad);
     return bad;
 }
 
