@@ -196,6 +196,14 @@ def conv_bwd_data_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dtype_code
     return int(load().sdgp_conv_bwd_data_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dtype_code, n, m))
 
 
+@functools.lru_cache(maxsize=1024)
+def _conv_need(B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m) -> int:
+    """What sdgp_conv_bwd_data is given: nothing for the layers whose workspace no kernel reads, whatever the query says."""
+    need = conv_bwd_data_workspace(B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m)
+    unread = dt == BF16 and R == S == stride == 1 and C_out % 32 != 0
+    return 0 if unread and need != 2**64 - 1 else need
+
+
 def sdgp_conv_bwd_data(dO: torch.Tensor, W: torch.Tensor, H: int, Wd: int, stride: int, pad: int, n: int, m: int,
                        ranker: int, seed: int = 0, out: torch.Tensor | None = None,
                        workspace: torch.Tensor | None = None) -> torch.Tensor:
@@ -211,11 +219,9 @@ def sdgp_conv_bwd_data(dO: torch.Tensor, W: torch.Tensor, H: int, Wd: int, strid
         out = dO.new_empty((B, H, Wd, C_in))
     _dev(out, "out")
     dt = _dtype_code(dO)
-    need = _need("sdgp_conv_bwd_data_workspace", B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m)
+    need = _conv_need(B, H, Wd, C_in, C_out, R, S, stride, pad, dt, n, m)
     if need == 2**64 - 1:
         raise SdgpError(-3, "sdgp_conv_bwd_data_workspace")
-    if dt == BF16 and R == S == stride == 1 and C_out % 32:
-        need = 0    # (whatever the query says: no kernel for these reads a workspace)
     if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
         try:
             workspace = torch.empty(need, dtype=torch.uint8, device=dO.device)
