@@ -21,7 +21,7 @@
 //      fewest bytes per multiplication that still give 256 workgroups to ResNet-9's 3x3 layers at batch 128.
 //      Bound by fragment reads and matrix instructions, which take equal time and overlap by half: 7 us per 32 channels
 //      and nine taps, 10 us of prologue, first copies and stores.
-// 3x3 128 -> 128 at 16x16, batch 128, 2:4 Magnitude: 96.6 us on the fp32 instruction, 42.9 here.
+// 3x3 128 -> 128 at 16x16, batch 128, 2:4 Magnitude: 96.6 us on the fp32 instruction, 43.4 here.
 // Values that scaling takes out of the range, infinite and NaN ones have parts that make NaN of every result they reach
 // (split3), and sums may leave the range on the way: where split_operands notes an operand that can have done so, results that are
 // not finite are summed again term by term.  (A NaN gradient alone costs nothing: its NaN is the result.)  A dropped channel meets

@@ -529,7 +529,7 @@ __device__ __forceinline__ const __attribute__((address_space(4))) Params& first
 // The stored channels of input pixel (b, h, w), some of them NaN: those are summed again over the pixel's own taps, term by term.
 // The window products above and below also multiply gradient pixels that no tap joins to the pixel, by a zero of V, and weights
 // whose gradient pixel does not exist, by a zero, which is a NaN where the other factor is infinite or NaN.  Rare, so it is short
-// rather than fast; looking for NaN results costs up to 1 percent (3 -> 64 channels at 224 x 224, batch 256, 4:8 Rescaled 280.4 -> 284.2 us).
+// rather than fast, but for a kept NaN under the pixel's own taps, a diverged step's gradient, after which nothing is summed; looking for NaN results costs up to 1 percent (3 -> 64 channels at 224 x 224, batch 256, 4:8 Rescaled 280.4 -> 284.2 us).
 template <int M, int RK, typename Params>
 __device__ __forceinline__ void first_sum_again(const Params& p, int side, int stride, int P, int Q, int C_out, uint16_t* dst, int b, int h, int w) {
     const int hp = h + side / 2, wp = w + side / 2;   // (padding: half the filter)
@@ -537,46 +537,70 @@ __device__ __forceinline__ void first_sum_again(const Params& p, int side, int s
 #pragma unroll
     for (int c = 0; c < 4; ++c) wrong |= c < p.C_in && (dst[c] & 0x7FFFu) > 0x7F80u ? 1u << c : 0u;
     if (wrong == 0) return;
-    float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    uint32_t open = wrong;   // may still turn out not to be NaN
+    auto own_taps = [&](auto&& visit) {   // (tap, flat index of its gradient pixel's first channel) until one says it is enough
 #pragma nounroll
-    for (int r = hp % stride; r < side && r <= hp; r += stride)
+        for (int r = hp % stride; r < side && r <= hp; r += stride)
 #pragma nounroll
-        for (int s = wp % stride; s < side && s <= wp; s += stride) {
-            const int pp = (hp - r) / stride, qq = (wp - s) / stride;
-            if (pp >= P || qq >= Q) continue;
-            const int64_t e0 = (((int64_t)b * P + pp) * Q + qq) * C_out;
-            const int64_t kstep = (int64_t)side * side * p.C_in;
-            const uint16_t* wk = p.W + (r * side + s) * p.C_in;
+            for (int s = wp % stride; s < side && s <= wp; s += stride) {
+                const int pp = (hp - r) / stride, qq = (wp - s) / stride;
+                if (pp < P && qq < Q && visit(r * side + s, (((int64_t)b * P + pp) * Q + qq) * C_out)) return;
+            }
+    };
+    bool own = false;
+    own_taps([&](int, int64_t e0) {
 #pragma nounroll
-            for (int k = 0; k < C_out && open != 0; k += M) {
-                const uint16_t* const g = p.dO + e0 + k;
-                const uint32_t mask = RK == kFirstDense ? ~0u : keep_by_count<M, RK>(g, p.n, p.mix, (uint64_t)(e0 + k));
-                float scale = 1.0f;
-                if constexpr (RK == kAdjusted) {
-                    float total = 0.0f, kept = 0.0f;
+        for (int k = 0; k < C_out && !own; k += M) {
+            const uint16_t* const g = p.dO + e0 + k;
+            // by magnitude one of a group's NaNs is its first; at random one stays when there are more than are dropped
+            const int enough = RK == kRandom ? M - p.n + 1 : 1;
+            int nans = 0;
 #pragma nounroll
-                    for (int j = 0; j < M; ++j) {
-                        const float a = bf16_to_float((uint32_t)g[j] & 0x7FFFu);
-                        total = __fadd_rn(total, a);
-                        if ((mask >> j) & 1u) kept = __fadd_rn(kept, a);
-                    }
-                    if (kept != 0.0f) scale = __fdiv_rn(total, kept);
-                }
+            for (int j = 0; j < M && nans < enough; ++j) nans += (g[j] & 0x7FFFu) > 0x7F80u;
+            own = nans >= enough;
+            if (RK == kRandom && nans > 0 && !own) {
+                const uint32_t mask = keep_by_count<M, RK>(g, p.n, p.mix, (uint64_t)(e0 + k));
 #pragma nounroll
-                for (int j = 0; j < M; ++j, wk += kstep) {
-                    float x = (mask >> j) & 1u ? bf16_to_float(g[j]) : 0.0f;
-                    if constexpr (RK == kAdjusted) {
-                        if ((mask >> j) & 1u) x = bf16_to_float(float_to_bf16(__fmul_rn(x, scale)));
-                    }
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        if (c < p.C_in) sum[c] = fmaf(x, bf16_to_float(wk[c]), sum[c]);
-                }
-#pragma unroll
-                for (int c = 0; c < 4; ++c) open &= sum[c] == sum[c] ? ~0u : ~(1u << c);
+                for (int j = 0; j < M; ++j) own = own || (((mask >> j) & 1u) != 0 && (g[j] & 0x7FFFu) > 0x7F80u);
             }
         }
+        return own;
+    });
+    if (own) return;
+    float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    uint32_t open = wrong;   // may still turn out not to be NaN
+    own_taps([&](int tap, int64_t e0) {
+        const int64_t kstep = (int64_t)side * side * p.C_in;
+        const uint16_t* wk = p.W + tap * p.C_in;
+#pragma nounroll
+        for (int k = 0; k < C_out && open != 0; k += M) {
+            const uint16_t* const g = p.dO + e0 + k;
+            const uint32_t mask = RK == kFirstDense ? ~0u : keep_by_count<M, RK>(g, p.n, p.mix, (uint64_t)(e0 + k));
+            float scale = 1.0f;
+            if constexpr (RK == kAdjusted) {
+                float total = 0.0f, kept = 0.0f;
+#pragma nounroll
+                for (int j = 0; j < M; ++j) {
+                    const float a = bf16_to_float((uint32_t)g[j] & 0x7FFFu);
+                    total = __fadd_rn(total, a);
+                    if ((mask >> j) & 1u) kept = __fadd_rn(kept, a);
+                }
+                if (kept != 0.0f) scale = __fdiv_rn(total, kept);
+            }
+#pragma nounroll
+            for (int j = 0; j < M; ++j, wk += kstep) {
+                float x = (mask >> j) & 1u ? bf16_to_float(g[j]) : 0.0f;
+                if constexpr (RK == kAdjusted) {
+                    if ((mask >> j) & 1u) x = bf16_to_float(float_to_bf16(__fmul_rn(x, scale)));
+                }
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (c < p.C_in) sum[c] = fmaf(x, bf16_to_float(wk[c]), sum[c]);
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) open &= sum[c] == sum[c] ? ~0u : ~(1u << c);
+        }
+        return open == 0;
+    });
 #pragma unroll
     for (int c = 0; c < 4; ++c)
         if ((wrong >> c) & 1u) dst[c] = (uint16_t)float_to_bf16(sum[c]);

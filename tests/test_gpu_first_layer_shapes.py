@@ -82,3 +82,29 @@ def test_non_finite_stay_with_their_taps(shape, n, m, ranker):
     got = wl.to_f64(to_host(sdgp.sdgp_conv_bwd_data(g, w, L.H, L.Wd, L.stride, L.pad, n, m, ranker, 11)))
     assert np.array_equal(np.isnan(got), nan) and np.array_equal(got[~fin & ~nan], ref[~fin & ~nan])
     assert np.all(np.abs(got[fin] - ref[fin]) <= 1e-2 * ab[fin])
+
+
+@pytest.mark.parametrize("n,m,ranker", [(4, 4, sdgp.GREEDY), (2, 4, sdgp.RANDOM), (2, 4, sdgp.GREEDY_ADJUSTED), (4, 32, sdgp.RANDOM), (4, 32, sdgp.GREEDY)])
+@pytest.mark.parametrize("shape", [(32, 111, 111, 3, 64, 7, 7, 2, 3), (64, 64, 64, 3, 64, 3, 3, 1, 1)])
+def test_nan_gradients_cost_no_more(shape, n, m, ranker):
+    """A diverged step's gradient: a NaN under a pixel's own taps leaves nothing to sum again."""
+    L = wl.ConvLayer("d", *shape)
+    W = torch.full(L.W_shape, 0.01, dtype=torch.bfloat16, device="cuda")
+
+    def run(value):
+        dO = torch.full(L.dO_shape, value, dtype=torch.bfloat16, device="cuda")
+        best = 1e9
+        for _ in range(3):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for _ in range(5):
+                out = sdgp.sdgp_conv_bwd_data(dO, W, L.H, L.Wd, L.stride, L.pad, n, m, ranker)
+            end.record()
+            end.synchronize()
+            best = min(best, begin.elapsed_time(end))
+        return best, out
+
+    finite, _ = run(1.0)
+    nan, out = run(float("nan"))
+    assert out.isnan().all()
+    assert nan < 3 * finite, (nan, finite)
