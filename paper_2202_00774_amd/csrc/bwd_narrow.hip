@@ -741,12 +741,12 @@ __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) 
     }
     // result register c of lane (px, oct = 2 a + b): channel c of input pixel (2 i + a, 2 j + b)
     const int a = oct >> 1, bb = oct & 1;
-    uint32_t nans = 0;
+    float check = 0.0f;   // NaN: some result is, or is infinite
 #pragma unroll
     for (int ri = 0; ri < 4; ++ri)
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
-            nans |= __builtin_isunordered(acc[ri][g][0], acc[ri][g][1]) || __builtin_isunordered(acc[ri][g][2], acc[ri][g][3]) ? 1u << (ri * 2 + g) : 0u;
+            check = fmaf((acc[ri][g][0] + acc[ri][g][1]) + (acc[ri][g][2] + acc[ri][g][3]), 0.0f, check);
             const int h = 2 * (i0 + 4 * rq + ri) + a, w = 2 * (j0 + 32 * gp + 16 * g + px) + bb;
             if (h < p.H && w < p.Wd) {   // (an odd size ends on half a block)
                 uint16_t* dst = p.dD + ((size_t)(b * p.H + h) * p.Wd + w) * p.C_in;
@@ -757,11 +757,11 @@ __global__ void __launch_bounds__(kFThreads, 2) bwd_first2(const FirstParams p) 
                 if (p.C_in > 3) dst[3] = (uint16_t)(c23 >> 16);
             }
         }
-    if (__builtin_expect(nans != 0, 0)) {
+    if (__builtin_expect(check != check, 0)) {
         const auto& q = first_params_again<FirstParams>();
 #pragma nounroll
-        for (; nans != 0; nans &= nans - 1) {
-            const int x = __ffs((int)nans) - 1, h = 2 * (i0 + 4 * rq + (x >> 1)) + a, w = 2 * (j0 + 16 * (x & 1) + px) + bb;
+        for (int x = 0; x < 8; ++x) {
+            const int h = 2 * (i0 + 4 * rq + (x >> 1)) + a, w = 2 * (j0 + 16 * (x & 1) + px) + bb;
             if (h < q.H && w < q.Wd)
                 first_sum_again<M, PRUNE ? RK : kFirstDense>(q, 7, 2, q.P, q.Q, q.C_out, q.dD + ((size_t)(b * q.H + h) * q.Wd + w) * q.C_in, b, h, w);
         }
