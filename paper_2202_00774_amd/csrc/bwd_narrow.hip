@@ -457,7 +457,7 @@ __global__ void __launch_bounds__(256, 2) bwd_narrow_mm(const NarrowParams p) {
 //     copies; pruning, when asked for, is done in place;
 //   * V's chunk (16 window positions x 16 columns, built once per call in the workspace) goes from the L2 straight to the 64
 //     registers that hold its sixteen fragments, beside the gradient's copies: without its 20 KB in LDS three workgroups
-//     fit a CU.  Bound by the ranker's instructions: batch 256 at 224 x 224, 2:4 random 212 us (217 with tiles in launch order,
+//     fit a CU.  Bound by the ranker's instructions: batch 256 at 224 x 224, 2:4 random 209 us (217 with tiles in launch order,
 //     whose halos the XCDs fetched one by one: 928 MB instead of 623; 258 with V in LDS and two workgroups per CU).  Through LDS, where one copy serves the four
 //     wavefronts, in some problems of few tiles (launch_first2);
 //   * a gradient fragment (16 pixels x 32 channels) is read once per (tile row, dq) and feeds up to four matrix
@@ -529,7 +529,7 @@ __device__ __forceinline__ const __attribute__((address_space(4))) Params& first
 // The stored channels of input pixel (b, h, w), some of them NaN: those are summed again over the pixel's own taps, term by term.
 // The window products above and below also multiply gradient pixels that no tap joins to the pixel, by a zero of V, and weights
 // whose gradient pixel does not exist, by a zero, which is a NaN where the other factor is infinite or NaN.  Rare, so it is short
-// rather than fast, but for a kept NaN under the pixel's own taps, a diverged step's gradient, after which nothing is summed; looking for NaN results costs up to 1 percent (3 -> 64 channels at 224 x 224, batch 256, 4:8 Rescaled 280.4 -> 284.2 us).
+// rather than fast, but for a kept NaN under the pixel's own taps, a diverged step's gradient, after which nothing is summed; looking for NaN results costs up to 1 percent (3 -> 64 channels at 224 x 224, batch 256, 4:8 Rescaled 278.0 -> 281.2 us).
 template <int M, int RK, typename Params>
 __device__ __forceinline__ void first_sum_again(const Params& p, int side, int stride, int P, int Q, int C_out, uint16_t* dst, int b, int h, int w) {
     const int hp = h + side / 2, wp = w + side / 2;   // (padding: half the filter)
