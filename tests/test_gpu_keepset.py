@@ -170,7 +170,7 @@ def test_padded_reduction_identity_equals_the_oracle():
 
 
 def test_ragged_reduction_identity_on_few_tiles_equals_the_oracle():
-    """The same channel counts on few rows: the small-problem kernel, whose last reduction step ends inside."""
+    """The same channel counts on few rows: 1000 on the small-problem kernel, whose last reduction step ends inside."""
     for rows, C in ((900, 40), (300, 1000)):
         check_exact(wl.ConvLayer("small_n%d" % C, rows, 1, 1, C, C, 1, 1, 1, 0), False,
                     [(2, 4, r) for r in RANKERS] + [(2, 8, oracle.RANDOM), (4, 4, oracle.GREEDY), (3, 8, oracle.GREEDY)], npix=rows)
