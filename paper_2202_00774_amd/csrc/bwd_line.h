@@ -1,0 +1,364 @@
+// Backward-data kernel for 3x3 stride-1 layers with one pixel of padding, fused with pruning (n <= 2 of m in {4, 8, 16}):
+// dL/dD = prune(dL/dO) (*) W as an implicit GEMM (Fig. 3 left; Sec. II-A), rows = input pixels, columns = input channels.
+//
+// The pixels of all images lie behind each other in one line, and a workgroup takes 256 consecutive ones wherever lines and images
+// begin: no tile is chosen for the image's shape and none is cut by its border.  The gradient pixels that their nine taps reach are
+// a run of 256 + 2 (width + 1) consecutive pixels.  In LDS they lie in a line of the padded image -- a zero in front of every image
+// line, a line of zeros between images -- where a tap is a constant distance: no tables, no tests in the loop.
+//   * The reduction runs in chunks of 32 channels; a stage = (chunk, filter row) = three taps between two barriers, as in bwd_row.h.
+//   * A lane ranks the same three pixels' halves (items of sixteen channels) in every chunk, one per stage, for the chunk after the
+//     current one; it asks for an item's 32 bytes one stage ahead, straight into registers.  Output: the operand of
+//     v_smfmac_f32_32x32x32_bf16, two values + two 2-bit positions per quad.
+//   * The ranker runs between the stage's matrix instructions, five or six of its instructions after each (NoGap in ranker.h), and
+//     so do the requests for the next fragments and the copies of W's next slabs.
+//   * Four wavefronts of 128 x 64 (128 columns) or 64 x 64 results (64 columns); LDS and registers of two or three workgroups fit a
+//     CU, so that one's first loads, ranking and stores run beside the other's matrix instructions.  bwd_row has one workgroup of
+//     512 pixels there, whose prologue and epilogue (7 us a round) nothing hides.
+//   * W through a two-set ring of direct-to-LDS copies, fragments by transposing reads, as in bwd_row.h.
+// What bounds it: the matrix and vector instructions share a SIMD's issue (a structured-sparse instruction takes 13 cycles of it and
+// 32 of the matrix pipe) and the clock, which falls from 2.4 to 1.6 - 1.9 GHz under them.  Measured against bwd_row, whole calls: 128 <- 256
+// channels at 16x16, batch 512, 2:4 Magnitude 51.9 -> 47.1 us, 64 <- 128 at 32x32 80.8 -> 64.5, 128 <- 128 at 28x28, batch 128,
+// 31 -> 24.8; 400 drawn layers 0.70 of the time, a hundred of one of m 0.76.
+#pragma once
+
+#include <type_traits>
+
+#include "fastdiv.h"
+#include "lds_copy.h"
+
+namespace sdgp {
+
+struct LineParams {
+    const uint16_t* dO;
+    const uint16_t* W;
+    uint16_t* dD;
+    int pixels;                  // B * H * Wd: as many gradient pixels as input pixels
+    int H, Wd, C_out, C_in;
+    FastDiv by_line, by_image;   // a pixel's line, a line's image
+    int w_row;                   // elements per W row: 9 * C_in
+    int n;
+    uint32_t mix;
+    int npos;                    // positions of the line that a tile's taps reach, at most
+    int ntiles_n, nblocks;
+};
+
+__device__ __align__(16) const uint32_t kLineZeros[4] = {0, 0, 0, 0};   // what a short last chunk lacks
+
+constexpr int kLineKC = 32;         // reduction channels per chunk
+constexpr int kLineThreads = 256;
+
+constexpr int kLineRows = 256;      // pixels of a workgroup tile
+// a lane ranks one item (sixteen channels of a gradient pixel) per stage; the three stages of a chunk cover the window
+constexpr int kLineMaxWindow = 3 * kLineThreads / 2;
+constexpr int kLineMaxWidth = (kLineMaxWindow - kLineRows) / 2 - 1;
+
+__host__ __device__ inline int line_window(int Wd) { return kLineRows + 2 * (Wd + 1); }
+
+// The longest run of the padded line, from the first to the last position that some tile's taps read.
+inline int line_positions(int H, int Wd) {
+    const int between = kLineRows - 1;
+    const int lines = (Wd - 1 + between) / Wd;                                                // line ends between a tile's first and last pixel
+    const int images = (int)(((int64_t)H * Wd - 1 + between) / ((int64_t)H * Wd));            // image ends
+    return between + lines + images * (Wd + 1) + 2 * (Wd + 2) + 1;
+}
+
+template <int BN>
+struct LineLayout {
+    static constexpr int kWRow = BN * 2;
+    static constexpr int kWSlab = kLineKC * kWRow;
+    static constexpr int kWSet = 3 * kWSlab;               // the slabs of one filter row
+    static constexpr int kOutPitch = BN * 2 + 16;
+    // value planes (16 bytes per position and half chunk) and planes of their 2-bit positions (2 bytes), with one position more, which
+    // takes what no tap reads; sizes are 128 modulo 256 bytes, so that the two halves of a wavefront read different halves of the banks
+    __host__ __device__ static int plane_a(int npos) { return (((npos + 1) * 16 + 127) & ~255) + 128; }
+    __host__ __device__ static int plane_m(int npos) { return (((npos + 1) * 2 + 127) & ~255) + 128; }
+    __host__ __device__ static int off_a() { return 2 * kWSet; }
+    __host__ __device__ static int buf_bytes(int npos) { return 2 * plane_a(npos) + 2 * plane_m(npos); }
+    __host__ __device__ static int total(int npos) {
+        const int loop = off_a() + 2 * buf_bytes(npos), out = kLineRows * kOutPitch;
+        return loop > out ? loop : out;
+    }
+};
+
+// keeps the computation of a value in front of what follows in the program
+template <class T>
+__device__ __forceinline__ void pin_value(T& x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(x));
+#endif
+}
+
+template <int BN, int M, int RK, bool TAIL, bool TWO>
+__global__ void __launch_bounds__(kLineThreads, BN == 64 ? 3 : 2) bwd_line(const LineParams p) {
+    using L = LineLayout<BN>;
+    constexpr int KC = kLineKC;
+    constexpr int BM = kLineRows;
+    constexpr int WAVES_N = BN / 64;
+    constexpr int WAVES_M = 4 / WAVES_N;
+    constexpr int WM = BM / WAVES_M;
+    constexpr int TM = WM / 32;
+    constexpr int TN = 2;
+    constexpr int CPR = BN / 8;                 // 16-byte columns per W row
+    constexpr int RPU = 1024 / L::kWRow;        // W rows per copy unit of 1 KB
+    constexpr int UPS = L::kWSlab / 1024;       // units per slab
+    constexpr int WSW = BN >= 128 ? 4 : 2;      // swizzle of the W slab, as in bwd_row.h
+
+    extern __shared__ __align__(16) unsigned char smem_generic[];
+    SDGP_LDS unsigned char* smem = (SDGP_LDS unsigned char*)smem_generic;
+    const uint32_t smem_base = (uint32_t)(uintptr_t)smem;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+
+    // consecutive logical ids stay on one XCD (workgroups are dealt round-robin over 8 XCDs)
+    int lid = blockIdx.x;
+    {
+        const int per = p.nblocks >> 3;
+        if (lid < (per << 3)) lid = (lid & 7) * per + (lid >> 3);
+    }
+    const int ntile = lid % p.ntiles_n;
+    const int mtile = lid / p.ntiles_n;
+    const int n0 = ntile * BN;
+    const int t0 = mtile * BM;
+    const int nchunks = TAIL ? (p.C_out + KC - 1) / KC : p.C_out / KC;
+    const int tail = p.C_out - (nchunks - 1) * KC;      // channels of the last chunk
+    // every workgroup walks the chunks in its own rotation: the sum does not care, and the workgroups of an XCD then ask its L2 for
+    // different W slabs at a given moment
+    const int c_rot = mtile % nchunks;
+
+    const int GW = p.Wd + 1;   // a line of the padded image: one zero in front
+    auto line_pos = [&](int px) {
+        const uint32_t row = divide((uint32_t)px, p.by_line);
+        return px + (int)row + ((int)divide(row, p.by_image) + 1) * GW + 1;
+    };
+    const int base = line_pos(t0) - GW - 1;    // line position of LDS position 0
+    const uint32_t plane_a = (uint32_t)L::plane_a(p.npos), plane_m = (uint32_t)L::plane_m(p.npos);
+    const uint32_t buf_bytes = (uint32_t)L::buf_bytes(p.npos);
+    const unsigned char* const gWb = reinterpret_cast<const unsigned char*>(p.W);
+
+    // ---- copies of W
+    const int w_lrow = (wave % UPS) * RPU + lane / CPR;
+    uint32_t w_voff;
+    {
+        int col = n0 + (((lane % CPR) ^ (WSW * (w_lrow & 3))) * 8);
+        if (col > p.C_in - 8) col = p.C_in - 8;  // columns past C_in feed accumulators that are never stored
+        w_voff = (uint32_t)(w_lrow * p.w_row + col) * 2u;
+    }
+    const uint32_t tapB = (uint32_t)p.C_in * 2u;
+    const uint32_t chunkB = (uint32_t)KC * (uint32_t)p.w_row * 2u;
+    const uint32_t unitB = (uint32_t)(4 * RPU) * (uint32_t)p.w_row * 2u;   // four units further down the slab
+    constexpr int WCOPIES = 3 * UPS / 4;        // copies of this wavefront per stage
+    auto copy_w = [&](int pc, int pr, uint32_t set_off, int i) {
+        const int j = i / (UPS / 4), k = i % (UPS / 4);
+        const unsigned char* const src = gWb + ((size_t)pc * chunkB + (size_t)(pr * 3 + j) * tapB + (size_t)k * unitB);
+        const uint32_t dst = smem_base + set_off + (uint32_t)j * L::kWSlab + (uint32_t)(wave + 4 * k) * 1024u;
+        if (TAIL && pc == nchunks - 1)
+            lds_copy16(w_lrow + 4 * RPU * k < tail ? src + w_voff : reinterpret_cast<const unsigned char*>(kLineZeros), dst);
+        else
+            lds_copy16(src, w_voff, dst);
+    };
+
+    // ---- this lane's items: the same pixels in every chunk
+    const int64_t g0 = (int64_t)t0 - GW;                       // first pixel of the window
+    const int half_i = tid & 1;
+    uint32_t it_voff[3];                                  // byte offset from the window's first pixel
+    uint32_t it_pos[3];                                   // LDS position; npos, which no tap reads: no pixel, or one that no tap reaches
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const int w = (k * kLineThreads + tid) >> 1;
+        const int64_t px = g0 + w;
+        uint32_t pos = (uint32_t)p.npos, at = (uint32_t)GW;
+        if (w < line_window(p.Wd) && px >= 0 && px < p.pixels) {
+            const uint32_t q = (uint32_t)(line_pos((int)px) - base);
+            at = (uint32_t)w;
+            if (q < (uint32_t)p.npos) pos = q;
+        }
+        it_pos[k] = pos;
+        it_voff[k] = at * (uint32_t)p.C_out * 2u + (uint32_t)half_i * 32u;
+    }
+    const unsigned char* const window = reinterpret_cast<const unsigned char*>(p.dO) + g0 * p.C_out * 2;
+    struct Raw {
+        u32x4_t v[2];
+    };
+    auto load_item = [&](int k, int pc) {
+        Raw r;
+        const unsigned char* const src = window + (size_t)pc * (KC * 2);
+        if (TAIL && pc == nchunks - 1) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const bool in = half_i * 16 + i * 8 < tail;
+                r.v[i] = *reinterpret_cast<const u32x4_t*>((in ? src : window) + it_voff[k] + (in ? i * 16 : -half_i * 32));
+                if (!in) r.v[i] = u32x4_t{0u, 0u, 0u, 0u};
+            }
+        } else {
+            r.v[0] = *reinterpret_cast<const u32x4_t*>(src + it_voff[k]);
+            r.v[1] = *reinterpret_cast<const u32x4_t*>(src + it_voff[k] + 16);
+        }
+        return r;
+    };
+    const uint64_t e_first = (uint64_t)(g0 * p.C_out);
+    auto rank_item = [&](const Raw& r, int k, int pc, uint32_t abuf, auto&& gap) __attribute__((always_inline)) {
+        const uint64_t e0 = e_first + (uint64_t)(it_voff[k] >> 1) + (uint64_t)(pc * KC);
+        uint32_t packed[4], meta;
+        prune16_compressed<M, RK>(r.v, TWO ? 2 : 1, p.mix, e0, packed, meta, gap);
+        *(SDGP_LDS u32x4_t*)(smem + abuf + (uint32_t)half_i * plane_a + it_pos[k] * 16u) = u32x4_t{packed[0], packed[1], packed[2], packed[3]};
+        *(SDGP_LDS uint16_t*)(smem + abuf + 2u * plane_a + (uint32_t)half_i * plane_m + it_pos[k] * 2u) = (uint16_t)meta;
+    };
+
+    // ---- prologue
+    int pc = c_rot;
+    int pc1 = pc + 1 == nchunks ? 0 : pc + 1;
+#pragma unroll
+    for (int i = 0; i < WCOPIES; ++i) copy_w(pc, 0, 0u, i);
+    Raw raw;
+    {
+        Raw first[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) first[k] = load_item(k, pc);
+        const u32x4_t z = {0u, 0u, 0u, 0u};
+        for (uint32_t o = (uint32_t)tid * 16u; o < 2u * buf_bytes; o += kLineThreads * 16u) *(SDGP_LDS u32x4_t*)(smem + L::off_a() + o) = z;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 3; ++k) rank_item(first[k], k, pc, (uint32_t)L::off_a(), NoGap{});
+        if (nchunks > 1) raw = load_item(0, pc1);
+    }
+
+    f32x16_t acc[TM][TN];
+#pragma unroll
+    for (int t = 0; t < TM; ++t)
+#pragma unroll
+        for (int u = 0; u < TN; ++u)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[t][u][r] = 0.0f;
+
+    // ---- fragments
+    uint32_t b_lane[TN];
+#pragma unroll
+    for (int u = 0; u < TN; ++u) {
+        const int L16 = lane & 15;
+        const int chunk = 8 * wn + 4 * u + 2 * ((lane >> 4) & 1) + ((L16 & 3) >> 1);
+        b_lane[u] = (uint32_t)((8 * (lane >> 5) + (L16 >> 2)) * L::kWRow + ((chunk ^ (WSW * (L16 >> 2))) * 16) + (L16 & 1) * 8);
+    }
+    const uint32_t half = (uint32_t)(lane >> 5);
+    // where this lane's rows lie in the buffer and at the filter row of the current stage; tap s is 2 - s positions further
+    uint32_t a_stage[TM], m_stage[TM];
+#pragma unroll
+    for (int t = 0; t < TM; ++t) {
+        const int px = t0 + wm * WM + t * 32 + (lane & 31);
+        const uint32_t pos = (uint32_t)((px < p.pixels ? line_pos(px) - base - GW - 1 : 0) + 2 * GW);
+        a_stage[t] = (uint32_t)L::off_a() + half * plane_a + pos * 16u;
+        m_stage[t] = (uint32_t)L::off_a() + 2u * plane_a + half * plane_m + pos * 2u;
+    }
+    struct Frags {
+        u32x4_t a[TM];
+        int meta[TM];
+        bf16x16_t b[TN];
+    };
+    auto load_a = [&](Frags& f, int t, int s) {
+        f.a[t] = *(SDGP_LDS u32x4_t*)(smem + a_stage[t] + (2 - s) * 16);
+        f.meta[t] = *(SDGP_LDS uint16_t*)(smem + m_stage[t] + (2 - s) * 2);
+    };
+    auto load_b = [&](Frags& f, int u, uint32_t slab_off) {
+        SDGP_LDS unsigned char* wb = smem + b_lane[u] + slab_off;
+        s16x4_t q[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            q[i] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SDGP_LDS s16x4_t*)(wb + ((i >> 1) * 16 + (i & 1) * 4) * L::kWRow));
+        typedef short s16x16_t __attribute__((ext_vector_type(16)));
+        const s16x16_t all = {q[0][0], q[0][1], q[0][2], q[0][3], q[1][0], q[1][1], q[1][2], q[1][3],
+                              q[2][0], q[2][1], q[2][2], q[2][3], q[3][0], q[3][1], q[3][2], q[3][3]};
+        f.b[u] = __builtin_bit_cast(bf16x16_t, all);
+    };
+
+    wait_lds_copies<0>();
+    __syncthreads();
+
+    // ---- main loop
+    uint32_t set_off = 0u, abuf = (uint32_t)L::off_a(), abuf_other = (uint32_t)L::off_a() + buf_bytes;
+    Frags fr[2];
+    auto chunk = [&](auto more, int pc2) __attribute__((always_inline)) {
+        constexpr bool has1 = decltype(more)::value;
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const uint32_t other_set = (uint32_t)L::kWSet - set_off;
+#pragma unroll
+            for (int t = 0; t < TM; ++t) load_a(fr[0], t, 0);
+#pragma unroll
+            for (int u = 0; u < TN; ++u) load_b(fr[0], u, set_off);
+            Raw raw_next;
+            int g = 0;   // the next matrix instruction
+            auto gap = [&](auto&... values) __attribute__((always_inline)) {
+                (pin_value(values), ...);
+                constexpr int G = TM * TN;
+                if (g >= 3 * G) return;
+                const int q = g / G, i = g % G;
+                Frags& cur = fr[q & 1];
+                Frags& nxt = fr[(q & 1) ^ 1];
+                const int t = i / TN, u = i % TN;
+                __builtin_amdgcn_sched_barrier(0);
+                acc[t][u] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(__builtin_bit_cast(bf16x8_t, cur.a[t]), cur.b[u], acc[t][u], cur.meta[t], 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (q < 2) {
+                    if (i < TN) load_b(nxt, i, set_off + (uint32_t)(q + 1) * L::kWSlab);
+                    else if (i - TN < TM) load_a(nxt, i - TN, q + 1);
+                }
+                if (has1 && g == 0) raw_next = load_item(r < 2 ? r + 1 : 0, r < 2 ? pc1 : pc2);
+                if (g < WCOPIES) {
+                    if (r < 2) copy_w(pc, r + 1, other_set, g);
+                    else if (has1) copy_w(pc1, 0, other_set, g);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                ++g;
+            };
+            if (has1) rank_item(raw, r, pc1, abuf_other, gap);
+#pragma unroll
+            for (int i = 0; i < 3 * TM * TN; ++i) gap();
+            __builtin_amdgcn_sched_barrier(0);
+            wait_lds_copies<0>();
+            __syncthreads();
+            raw = raw_next;
+            set_off = other_set;
+            const uint32_t da = r < 2 ? 0u - (uint32_t)GW * 16u : (uint32_t)GW * 32u + (abuf_other - abuf);
+            const uint32_t dm = r < 2 ? 0u - (uint32_t)GW * 2u : (uint32_t)GW * 4u + (abuf_other - abuf);
+#pragma unroll
+            for (int t = 0; t < TM; ++t) a_stage[t] += da, m_stage[t] += dm;
+        }
+    };
+    for (int c = 0; c + 1 < nchunks; ++c) {
+        const int pc2 = pc1 + 1 == nchunks ? 0 : pc1 + 1;   // (in front of the last chunk nobody reads what is asked for)
+        chunk(std::true_type{}, pc2);
+        pc = pc1, pc1 = pc2;
+        const uint32_t x = abuf; abuf = abuf_other; abuf_other = x;
+    }
+    chunk(std::false_type{}, 0);
+
+    // ---- epilogue: fp32 -> bf16 (RNE) into LDS, then whole pixel rows with 16-byte stores
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int tt = 0; tt < TM; ++tt)
+#pragma unroll
+        for (int u = 0; u < TN; ++u)
+#pragma unroll
+            for (int rr = 0; rr < 16; rr += 2) {
+                const int m = wm * WM + tt * 32 + 8 * (rr >> 2) + 4 * (lane >> 5) + (rr & 3);
+                const int col = wn * 64 + u * 32 + (lane & 31);
+                const f32x2_t v = {acc[tt][u][rr], acc[tt][u][rr + 1]};
+                const uint32_t pk = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+                *(SDGP_LDS uint16_t*)(smem + m * L::kOutPitch + col * 2) = (uint16_t)pk;
+                *(SDGP_LDS uint16_t*)(smem + (m + 1) * L::kOutPitch + col * 2) = (uint16_t)(pk >> 16);
+            }
+    __syncthreads();
+#pragma unroll 4
+    for (int idx = tid; idx < BM * CPR; idx += kLineThreads) {
+        const int m = idx / CPR, cc = idx % CPR;
+        const int px = t0 + m;
+        if (px < p.pixels && n0 + cc * 8 < p.C_in) {
+            const u32x4_t v = *(SDGP_LDS u32x4_t*)(smem + m * L::kOutPitch + cc * 16);
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(p.dD + (size_t)px * p.C_in + n0 + cc * 8));
+        }
+    }
+}
+
+}  // namespace sdgp

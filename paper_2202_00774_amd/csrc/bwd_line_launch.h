@@ -1,0 +1,34 @@
+// Launch helpers of the line kernel; included by the files that instantiate it.
+#pragma once
+
+#include "bwd_line.h"
+
+namespace sdgp {
+
+template <int BN, int M, int RK, bool TAIL, bool TWO>
+int launch_line_as(const LineParams& p, hipStream_t stream) {
+    auto kern = bwd_line<BN, M, RK, TAIL, TWO>;
+    static const hipError_t attr =
+        hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (attr != hipSuccess) return SDGP_ERR_HIP;
+    hipLaunchKernelGGL(kern, dim3(p.nblocks), dim3(kLineThreads), LineLayout<BN>::total(p.npos), stream, p);
+    return launch_status();
+}
+
+// (one of m is rarer than two: one instantiation for all channel counts)
+template <int BN, int M, int RK>
+int launch_line_one(const LineParams& p, hipStream_t stream) {
+    if (p.n == 1) return launch_line_as<BN, M, RK, true, false>(p, stream);
+    return p.C_out % kLineKC != 0 ? launch_line_as<BN, M, RK, true, true>(p, stream) : launch_line_as<BN, M, RK, false, true>(p, stream);
+}
+
+template <int M>
+int launch_line_rk(const LineParams& p, int bn, int rk, hipStream_t stream) {
+    switch (rk) {
+        case kRandom: return bn == 128 ? launch_line_one<128, M, kRandom>(p, stream) : launch_line_one<64, M, kRandom>(p, stream);
+        case kGreedy: return bn == 128 ? launch_line_one<128, M, kGreedy>(p, stream) : launch_line_one<64, M, kGreedy>(p, stream);
+        default: return bn == 128 ? launch_line_one<128, M, kAdjusted>(p, stream) : launch_line_one<64, M, kAdjusted>(p, stream);
+    }
+}
+
+}  // namespace sdgp

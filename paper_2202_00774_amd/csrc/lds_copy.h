@@ -36,11 +36,11 @@ __device__ __forceinline__ void wait_lds_copies() {
 }
 
 // Sixteen consecutive channels of one gradient pixel -> the compressed operand (Sec. III-B).
-template <int M, int RK>
+template <int M, int RK, class Gap = NoGap>
 __device__ __forceinline__ void prune16_compressed(const u32x4_t (&v)[2], int n, uint32_t mix, uint64_t e0, uint32_t (&packed)[4],
-                                             uint32_t& meta) {
+                                             uint32_t& meta, Gap&& gap = Gap{}) {
     const uint32_t w[8] = {v[0][0], v[0][1], v[0][2], v[0][3], v[1][0], v[1][1], v[1][2], v[1][3]};
-    prune_compress16<M, RK>(w, n, mix, e0, packed, meta);
+    prune_compress16<M, RK>(w, n, mix, e0, packed, meta, gap);
 }
 
 // Sixteen consecutive channels of one gradient pixel, pruned (Sec. III-B) and written back dense with zeros.

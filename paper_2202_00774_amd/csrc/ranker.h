@@ -522,36 +522,51 @@ __host__ __device__ __forceinline__ void prune_of4_magnitude(uint32_t d01, uint3
     }
 }
 
+// The rankers of sixteen channels call gap every five or six instructions, with the values just computed: a kernel puts a matrix
+// instruction there, which runs beside the ranking instead of after it (bwd_line.h), and pins the values to the place.
+struct NoGap {
+    template <class... T>
+    __host__ __device__ __forceinline__ void operator()(T&...) const {}
+};
+
 // The survivors of a quad by their positions p < q: p in bits 0..1, q - 1 in bits 16..17.
-__host__ __device__ __forceinline__ uint32_t rank_2of4_magnitude(uint32_t d01, uint32_t d23) {
+template <class Gap = NoGap>
+__host__ __device__ __forceinline__ uint32_t rank_2of4_magnitude(uint32_t d01, uint32_t d23, Gap&& gap = Gap{}) {
     // the outer channels (0, 3) against the inner ones (1, 2): one order of the halves serves both survivors
-    const uint32_t outer = sdgp_perm(d23, d01, 0x07060100u) & 0x7FFF7FFFu;
-    const uint32_t inner = sdgp_perm(d23, d01, 0x05040302u) & 0x7FFF7FFFu;
-    const uint32_t turned = sdgp_rotl(inner, 16);
-    const uint32_t o = outer + kLowWinsTies;
-    const uint32_t near = o - inner;                             // 0 beats 1, 3 beats 2
-    const uint32_t far = o - turned;                             // 0 beats 2, 3 beats 1
-    const uint32_t ends = o - sdgp_rotl(outer, 16);              // 0 beats 3, 3 beats 0
-    const uint32_t mid = (inner + kLowWinsTies) - turned;        // 1 beats 2, 2 beats 1
+    uint32_t outer = sdgp_perm(d23, d01, 0x07060100u) & 0x7FFF7FFFu;
+    uint32_t inner = sdgp_perm(d23, d01, 0x05040302u) & 0x7FFF7FFFu;
+    uint32_t turned = sdgp_rotl(inner, 16);
+    uint32_t o = outer + kLowWinsTies;
+    gap(outer, inner, turned, o);
+    uint32_t near = o - inner;                                   // 0 beats 1, 3 beats 2
+    uint32_t far = o - turned;                                   // 0 beats 2, 3 beats 1
+    uint32_t ends = o - sdgp_rotl(outer, 16);                    // 0 beats 3, 3 beats 0
+    uint32_t mid = (inner + kLowWinsTies) - turned;              // 1 beats 2, 2 beats 1
+    gap(near, far, ends, mid);
     const uint32_t keep_o = bitop3<kMaj>(near, far, ends);
     const uint32_t keep_i = bitop3<kMajNotAC>(near, mid, sdgp_rotl(far, 16));
-    const uint32_t u = keep_o ^ 0xFFFFu;                         // 0 dropped, 3 kept
-    const uint32_t v = bitop3<0xA6>(keep_o, keep_i, u);          // 0 and 1 dropped, 2 or 3 kept
+    uint32_t u = keep_o ^ 0xFFFFu;                               // 0 dropped, 3 kept
+    uint32_t v = bitop3<0xA6>(keep_o, keep_i, u);                // 0 and 1 dropped, 2 or 3 kept
+    gap(u, v);
     return ((u >> 15) & 0x00010001u) + ((v >> 15) & 0x00010001u);
 }
 
 // The two values of every quad and the sixteen channels' positions, from the quads' codes.
+template <class Gap = NoGap>
 __host__ __device__ __forceinline__ void take_2of4(const uint32_t (&w)[8], const uint32_t (&code)[4], uint32_t (&packed)[4],
-                                                   uint32_t& meta) {
+                                                   uint32_t& meta, Gap&& gap = Gap{}) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) packed[q] = sdgp_perm(w[2 * q + 1], w[2 * q], code[q] * 0x0202u + 0x03020100u);
+    for (int q = 0; q < 4; ++q) {
+        packed[q] = sdgp_perm(w[2 * q + 1], w[2 * q], code[q] * 0x0202u + 0x03020100u);
+        if (q & 1) gap(packed[q - 1], packed[q]);
+    }
     const uint32_t all = code[0] | (code[1] << 4) | (code[2] << 8) | (code[3] << 12);
     meta = ((all & 0xFFFFu) | (all >> 14)) + 0x4444u;
 }
 
-template <int M, int RK>
+template <int M, int RK, class Gap = NoGap>
 __host__ __device__ __forceinline__ void prune_compress16_bf16(const uint32_t (&w)[8], int n, uint32_t (&packed)[4],
-                                                               uint32_t& meta) {
+                                                               uint32_t& meta, Gap&& gap = Gap{}) {
     static_assert(M == 4 || M == 8 || M == 16, "group sizes that tile sixteen channels");
     static_assert(RK == kGreedy || RK == kAdjusted, "magnitude rankers only");
     constexpr uint32_t kKeyMask = 0xFFFE0001u;  // magnitude and sign
@@ -565,8 +580,11 @@ __host__ __device__ __forceinline__ void prune_compress16_bf16(const uint32_t (&
     if (M == 4 && (RK == kAdjusted || two)) {   // (n is uniform over the wavefront)
         uint32_t code[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) code[q] = rank_2of4_magnitude(w[2 * q], w[2 * q + 1]);
-        take_2of4(w, code, packed, meta);
+        for (int q = 0; q < 4; ++q) {
+            code[q] = rank_2of4_magnitude(w[2 * q], w[2 * q + 1], gap);
+            gap(code[q]);
+        }
+        take_2of4(w, code, packed, meta, gap);
         uint32_t mask[4] = {~0u, ~0u, ~0u, ~0u};
         if (RK == kAdjusted && !two) {   // the larger of a quad's two stays
 #pragma unroll
@@ -583,9 +601,11 @@ __host__ __device__ __forceinline__ void prune_compress16_bf16(const uint32_t (&
                 total = __fadd_rn(total, bits_to_float(w[2 * q] & 0x7FFF0000u));
                 total = __fadd_rn(total, bits_to_float((w[2 * q + 1] << 16) & 0x7FFF0000u));
                 total = __fadd_rn(total, bits_to_float(w[2 * q + 1] & 0x7FFF0000u));
+                gap(total);
                 const uint32_t d = packed[q];
                 const float kept = __fadd_rn(bits_to_float((d << 16) & 0x7FFF0000u), bits_to_float(d & 0x7FFF0000u));
-                const float scale = (kept == 0.0f) ? 1.0f : __fdiv_rn(total, kept);
+                float scale = (kept == 0.0f) ? 1.0f : __fdiv_rn(total, kept);
+                gap(scale);
                 packed[q] = mask[q] & float2_to_bf16x2(__fmul_rn(bits_to_float(d << 16), scale), __fmul_rn(bits_to_float(d & 0xFFFF0000u), scale));
             }
         }
@@ -596,14 +616,16 @@ __host__ __device__ __forceinline__ void prune_compress16_bf16(const uint32_t (&
     for (int q = 0; q < 4; ++q) {
         const uint32_t d01 = w[2 * q], d23 = w[2 * q + 1];
         const uint32_t c0 = ((uint32_t)(M - 1 - (4 * q) % M) << 1) | kMark;  // code of the quad's first element
-        const uint32_t k0 = (sdgp_rotl(d01, 17) & kKeyMask) | c0;
-        const uint32_t k1 = (sdgp_rotl(d01, 1) & kKeyMask) | (c0 - 2u);
-        const uint32_t k2 = (sdgp_rotl(d23, 17) & kKeyMask) | (c0 - 4u);
-        const uint32_t k3 = (sdgp_rotl(d23, 1) & kKeyMask) | (c0 - 6u);
+        uint32_t k0 = (sdgp_rotl(d01, 17) & kKeyMask) | c0;
+        uint32_t k1 = (sdgp_rotl(d01, 1) & kKeyMask) | (c0 - 2u);
+        uint32_t k2 = (sdgp_rotl(d23, 17) & kKeyMask) | (c0 - 4u);
+        uint32_t k3 = (sdgp_rotl(d23, 1) & kKeyMask) | (c0 - 6u);
+        gap(k0, k1, k2, k3);
         const uint32_t hi = sdgp_umax(k0, k1), lo = sdgp_umin(k0, k1);
         const uint32_t hi2 = sdgp_umax(k2, k3), lo2 = sdgp_umin(k2, k3);
         f[q] = sdgp_umax(hi, hi2);
         s[q] = sdgp_umax(sdgp_umax(sdgp_umin(hi, hi2), lo), lo2);
+        gap(f[q], s[q]);
     }
     // drop what is below the group's threshold
     if constexpr (M == 4) {
@@ -626,6 +648,7 @@ __host__ __device__ __forceinline__ void prune_compress16_bf16(const uint32_t (&
             const int q = g * QG + i;
             f[q] = f[q] >= thr ? f[q] : (f[q] & kCodeMask);
             s[q] = s[q] >= thr ? s[q] : (s[q] & kCodeMask);
+            gap(f[q], s[q]);
         }
     }
     float total[16 / M];
@@ -638,6 +661,7 @@ __host__ __device__ __forceinline__ void prune_compress16_bf16(const uint32_t (&
                 const uint32_t d = w[g * (M / 2) + i];
                 t = __fadd_rn(t, bits_to_float((d << 16) & 0x7FFF0000u));
                 t = __fadd_rn(t, bits_to_float(d & 0x7FFF0000u));
+                if (i & 1) gap(t);
             }
             total[g] = t;
         }
@@ -654,7 +678,9 @@ __host__ __device__ __forceinline__ void prune_compress16_bf16(const uint32_t (&
 #else
         packed[q] = ((x >> 8) & 0xFFFFu) | ((y << 8) & 0xFFFF0000u);
 #endif
+        gap(packed[q], lo_key[q], hi_key[q]);
         inv |= (((x >> 24) & 3u) | (((y >> 24) & 3u) << 2)) << (4 * q);
+        if (q & 1) gap(inv);
     }
     meta = inv ^ 0xFFFFu;  // position = 3 - code
     if constexpr (RK == kAdjusted) {
@@ -678,6 +704,7 @@ __host__ __device__ __forceinline__ void prune_compress16_bf16(const uint32_t (&
                 // a dropped slot stays +0 whatever the scale is (the mark went away with the value)
                 const uint32_t mlo = (0u - (lo_key[q] & 1u)) & 0xFFFFu, mhi = (0u - (hi_key[q] & 1u)) << 16;
                 packed[q] = y & (mlo | mhi);
+                gap(packed[q]);
             }
         }
     }
@@ -688,9 +715,9 @@ __host__ __device__ __forceinline__ void prune_compress16_bf16(const uint32_t (&
 // distinct and ordered exactly like (key, lower position first): the kept set is {word >= n-th largest of the group}.
 // The two largest words of a quad contain every survivor of that quad.  The values are fetched by position afterwards
 // (they are not part of the key).
-template <int M>
+template <int M, class Gap = NoGap>
 __host__ __device__ __forceinline__ void prune_compress16_random(const uint32_t (&w)[8], int n, uint32_t mix, uint64_t e0,
-                                                                 uint32_t (&packed)[4], uint32_t& meta) {
+                                                                 uint32_t (&packed)[4], uint32_t& meta, Gap&& gap = Gap{}) {
     static_assert(M == 4 || M == 8 || M == 16, "group sizes that tile sixteen channels");
     const bool two = n >= 2;
     uint32_t f[4], s[4];  // largest and second largest word of each quad
@@ -701,15 +728,18 @@ __host__ __device__ __forceinline__ void prune_compress16_random(const uint32_t 
     for (int q = 0; q < 4; ++q) {
         const uint32_t e_lo = (uint32_t)e0 + (uint32_t)(4 * q);            // the quad's first element
         const uint32_t c0 = (uint32_t)(15 - (4 * q) % M);
-        const uint32_t hq = hash_quad(hrow, e_lo);                         // e_lo is a multiple of 4: one word per quad
-        const uint32_t k0 = hash_lane(hq, 0u) | c0;
-        const uint32_t k1 = hash_lane(hq, 1u) | (c0 - 1u);
-        const uint32_t k2 = hash_lane(hq, 2u) | (c0 - 2u);
-        const uint32_t k3 = hash_lane(hq, 3u) | (c0 - 3u);
+        uint32_t hq = hash_quad(hrow, e_lo);                               // e_lo is a multiple of 4: one word per quad
+        gap(hq);
+        uint32_t k0 = hash_lane(hq, 0u) | c0;
+        uint32_t k1 = hash_lane(hq, 1u) | (c0 - 1u);
+        uint32_t k2 = hash_lane(hq, 2u) | (c0 - 2u);
+        uint32_t k3 = hash_lane(hq, 3u) | (c0 - 3u);
+        gap(k0, k1, k2, k3);
         const uint32_t hi = sdgp_umax(k0, k1), lo = sdgp_umin(k0, k1);
         const uint32_t hi2 = sdgp_umax(k2, k3), lo2 = sdgp_umin(k2, k3);
         f[q] = sdgp_umax(hi, hi2);
         s[q] = sdgp_umax(sdgp_umin(hi, hi2), sdgp_umax(lo, lo2));
+        gap(f[q], s[q]);
     }
     uint32_t thr[4];  // the group's threshold, per quad
 #pragma unroll
@@ -722,6 +752,7 @@ __host__ __device__ __forceinline__ void prune_compress16_random(const uint32_t 
             const uint32_t cf = f[g * QG + i], cs = s[g * QG + i];   // cf > cs
             v2 = sdgp_umax(sdgp_umax(sdgp_umin(v1, cf), v2), sdgp_umin(sdgp_umax(v1, cf), cs));
             v1 = sdgp_umax(v1, cf);
+            gap(v1, v2);
         }
         const uint32_t th = two ? v2 : v1;
 #pragma unroll
@@ -735,7 +766,9 @@ __host__ __device__ __forceinline__ void prune_compress16_random(const uint32_t 
             const uint32_t pf = ~f[q] & 3u, ps = ~s[q] & 3u;
             const uint32_t p_lo = sdgp_umin(pf, ps), p_hi = sdgp_umax(pf, ps);
             packed[q] = sdgp_perm(w[2 * q + 1], w[2 * q], (p_lo | (p_hi << 16)) * 0x0202u + 0x01000100u);
+            gap(packed[q]);
             meta |= (p_lo | (p_hi << 2)) << (4 * q);
+            gap(meta);
         }
         return;
     }
@@ -753,8 +786,10 @@ __host__ __device__ __forceinline__ void prune_compress16_random(const uint32_t 
         const bool keep_lo = f_first ? keep_f : keep_s, keep_hi = f_first ? keep_s : keep_f;
         sel = keep_lo ? sel : ((sel & 0xFFFF0000u) | 0x00000C0Cu);   // selector 12 yields a zero byte
         sel = keep_hi ? sel : ((sel & 0x0000FFFFu) | 0x0C0C0000u);
+        gap(sel);
         packed[q] = sdgp_perm(w[2 * q + 1], w[2 * q], sel);
         meta |= (p_lo | (p_hi << 2)) << (4 * q);
+        gap(packed[q], meta);
     }
 }
 
@@ -777,13 +812,13 @@ __device__ __forceinline__ void compress_quad(const bool (&k)[4], const uint32_t
 
 // Sixteen consecutive bf16 channels (eight dwords), n <= 2 of m in {4, 8, 16}, any ranker -> the operand format of the
 // structured-sparse matrix instructions.  e0 = flat index of the first channel (Random only).
-template <int M, int RK>
+template <int M, int RK, class Gap = NoGap>
 __device__ __forceinline__ void prune_compress16(const uint32_t (&w)[8], int n, uint32_t mix, uint64_t e0, uint32_t (&packed)[4],
-                                                 uint32_t& meta) {
+                                                 uint32_t& meta, Gap&& gap = Gap{}) {
     if constexpr (RK != kRandom) {
-        prune_compress16_bf16<M, RK>(w, n, packed, meta);
+        prune_compress16_bf16<M, RK>(w, n, packed, meta, gap);
     } else {
-        prune_compress16_random<M>(w, n, mix, e0, packed, meta);
+        prune_compress16_random<M>(w, n, mix, e0, packed, meta, gap);
     }
 }
 
