@@ -1,0 +1,5 @@
+// Instantiates the stride-2 kernel for n <= 2 of m = 8.
+#include "bwd_stride2_launch.h"
+namespace sdgp {
+int launch_stride2_m8(const Stride2Params& p, int shape, int rk, hipStream_t stream) { return launch_stride2_rk<8>(p, shape, rk, stream); }
+}  // namespace sdgp
