@@ -1,4 +1,4 @@
-// Backward-data kernel for 3x3 stride-1 layers with one pixel of padding, fused with pruning (n <= 2 of m in {4, 8, 16}):
+// Backward-data kernel for 3x3 stride-1 layers with one pixel of padding, fused with pruning or unpruned (then also the forward pass):
 // dL/dD = prune(dL/dO) (*) W as an implicit GEMM (Fig. 3 left; Sec. II-A), rows = input pixels, columns = input channels.
 //
 // The pixels of all images lie behind each other in one line, and a workgroup takes 256 consecutive ones wherever lines and images
@@ -15,10 +15,13 @@
 //     CU, so that one's first loads, ranking and stores run beside the other's matrix instructions.  bwd_row has one workgroup of
 //     512 pixels there, whose prologue and epilogue (7 us a round) nothing hides.
 //   * W through a two-set ring of direct-to-LDS copies, fragments by transposing reads, as in bwd_row.h.
+//   * Patterns with more than two of a quad, groups of 32 and the unpruned gradient lie in LDS whole, eight channels a plane, and use
+//     the dense instruction; their rankers (none, or a sorting network) run in front of the stage's matrix instructions.
 // What bounds it: the matrix and vector instructions share a SIMD's issue (a structured-sparse instruction takes 13 cycles of it and
 // 32 of the matrix pipe) and the clock, which falls from 2.4 to 1.6 - 1.9 GHz under them.  Measured against bwd_row, whole calls: 128 <- 256
 // channels at 16x16, batch 512, 2:4 Magnitude 51.9 -> 47.1 us, 64 <- 128 at 32x32 80.8 -> 64.5, 128 <- 128 at 28x28, batch 128,
-// 31 -> 24.8; 400 drawn layers 0.70 of the time, a hundred of one of m 0.76.
+// 31 -> 24.8; 400 drawn layers 0.70 of the time, a hundred of one of m 0.76;
+// of general n:m 0.76 (80 layers), unpruned 0.79 (70; 128 <- 320 at 28x28, batch 112, 88.7 -> 60.5 us).
 #pragma once
 
 #include <type_traits>
@@ -62,7 +65,7 @@ inline int line_positions(int H, int Wd) {
     return between + lines + images * (Wd + 1) + 2 * (Wd + 2) + 1;
 }
 
-template <int BN>
+template <int BN, int MODE>
 struct LineLayout {
     static constexpr int kWRow = BN * 2;
     static constexpr int kWSlab = kLineKC * kWRow;
@@ -73,7 +76,8 @@ struct LineLayout {
     __host__ __device__ static int plane_a(int npos) { return (((npos + 1) * 16 + 127) & ~255) + 128; }
     __host__ __device__ static int plane_m(int npos) { return (((npos + 1) * 2 + 127) & ~255) + 128; }
     __host__ __device__ static int off_a() { return 2 * kWSet; }
-    __host__ __device__ static int buf_bytes(int npos) { return 2 * plane_a(npos) + 2 * plane_m(npos); }
+    // (the whole gradient, MODE 0 and 1: four planes, eight channels each)
+    __host__ __device__ static int buf_bytes(int npos) { return MODE == 2 ? 2 * plane_a(npos) + 2 * plane_m(npos) : 4 * plane_a(npos); }
     __host__ __device__ static int total(int npos) {
         const int loop = off_a() + 2 * buf_bytes(npos), out = kLineRows * kOutPitch;
         return loop > out ? loop : out;
@@ -88,9 +92,15 @@ __device__ __forceinline__ void pin_value(T& x) {
 #endif
 }
 
-template <int BN, int M, int RK, bool TAIL, bool TWO>
-__global__ void __launch_bounds__(kLineThreads, BN == 64 ? 3 : 2) bwd_line(const LineParams p) {
-    using L = LineLayout<BN>;
+// MODE 2: at most two of a quad stay (TWO: two of m, else one), the structured-sparse instruction; 1: any n of m up to 32, stored with
+// zeros, the dense one; 0: unpruned.
+template <int BN, int MODE, int M, int RK, bool TAIL, bool TWO>
+__global__ void __launch_bounds__(kLineThreads, MODE == 2 && BN == 64 ? 3 : 2) bwd_line(const LineParams p) {
+    using L = LineLayout<BN, MODE>;
+    constexpr bool SPARSE = MODE == 2;
+    constexpr int KSTEPS = SPARSE ? 3 : 6;      // of a stage
+    constexpr bool WHOLE = MODE == 1 && M == 32;   // an item is a pixel's 32 channels, and two of them cover the window
+    constexpr int ITEMS = WHOLE ? 2 : 3;
     constexpr int KC = kLineKC;
     constexpr int BM = kLineRows;
     constexpr int WAVES_N = BN / 64;
@@ -161,12 +171,12 @@ __global__ void __launch_bounds__(kLineThreads, BN == 64 ? 3 : 2) bwd_line(const
 
     // ---- this lane's items: the same pixels in every chunk
     const int64_t g0 = (int64_t)t0 - GW;                       // first pixel of the window
-    const int half_i = tid & 1;
-    uint32_t it_voff[3];                                  // byte offset from the window's first pixel
-    uint32_t it_pos[3];                                   // LDS position; npos, which no tap reads: no pixel, or one that no tap reaches
+    const int half_i = WHOLE ? 0 : tid & 1;
+    uint32_t it_voff[ITEMS];                                  // byte offset from the window's first pixel
+    uint32_t it_pos[ITEMS];                                   // LDS position; npos, which no tap reads: no pixel, or one that no tap reaches
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const int w = (k * kLineThreads + tid) >> 1;
+    for (int k = 0; k < ITEMS; ++k) {
+        const int w = WHOLE ? k * kLineThreads + tid : (k * kLineThreads + tid) >> 1;
         const int64_t px = g0 + w;
         uint32_t pos = (uint32_t)p.npos, at = (uint32_t)GW;
         if (w < line_window(p.Wd) && px >= 0 && px < p.pixels) {
@@ -179,7 +189,7 @@ __global__ void __launch_bounds__(kLineThreads, BN == 64 ? 3 : 2) bwd_line(const
     }
     const unsigned char* const window = reinterpret_cast<const unsigned char*>(p.dO) + g0 * p.C_out * 2;
     struct Raw {
-        u32x4_t v[2];
+        u32x4_t v[WHOLE ? 4 : 2];
     };
     auto load_item = [&](int k, int pc) {
         Raw r;
@@ -192,18 +202,27 @@ __global__ void __launch_bounds__(kLineThreads, BN == 64 ? 3 : 2) bwd_line(const
                 if (!in) r.v[i] = u32x4_t{0u, 0u, 0u, 0u};
             }
         } else {
-            r.v[0] = *reinterpret_cast<const u32x4_t*>(src + it_voff[k]);
-            r.v[1] = *reinterpret_cast<const u32x4_t*>(src + it_voff[k] + 16);
+#pragma unroll
+            for (int i = 0; i < (WHOLE ? 4 : 2); ++i) r.v[i] = *reinterpret_cast<const u32x4_t*>(src + it_voff[k] + 16 * i);
         }
         return r;
     };
     const uint64_t e_first = (uint64_t)(g0 * p.C_out);
     auto rank_item = [&](const Raw& r, int k, int pc, uint32_t abuf, auto&& gap) __attribute__((always_inline)) {
         const uint64_t e0 = e_first + (uint64_t)(it_voff[k] >> 1) + (uint64_t)(pc * KC);
-        uint32_t packed[4], meta;
-        prune16_compressed<M, RK>(r.v, TWO ? 2 : 1, p.mix, e0, packed, meta, gap);
-        *(SDGP_LDS u32x4_t*)(smem + abuf + (uint32_t)half_i * plane_a + it_pos[k] * 16u) = u32x4_t{packed[0], packed[1], packed[2], packed[3]};
-        *(SDGP_LDS uint16_t*)(smem + abuf + 2u * plane_a + (uint32_t)half_i * plane_m + it_pos[k] * 2u) = (uint16_t)meta;
+        if constexpr (SPARSE) {
+            uint32_t packed[4], meta;
+            prune16_compressed<M, RK>(r.v, TWO ? 2 : 1, p.mix, e0, packed, meta, gap);
+            *(SDGP_LDS u32x4_t*)(smem + abuf + (uint32_t)half_i * plane_a + it_pos[k] * 16u) = u32x4_t{packed[0], packed[1], packed[2], packed[3]};
+            *(SDGP_LDS uint16_t*)(smem + abuf + 2u * plane_a + (uint32_t)half_i * plane_m + it_pos[k] * 2u) = (uint16_t)meta;
+        } else {
+            Raw o = r;
+            if constexpr (WHOLE) prune32_dense<RK, false>(o.v, p.n, p.mix, e0);
+            else if constexpr (MODE == 1) prune16_dense<M, RK, false>(o.v, p.n, p.mix, e0);
+#pragma unroll
+            for (int i = 0; i < (WHOLE ? 4 : 2); ++i)
+                *(SDGP_LDS u32x4_t*)(smem + abuf + (uint32_t)(2 * half_i + i) * plane_a + it_pos[k] * 16u) = o.v[i];
+        }
     };
 
     // ---- prologue
@@ -213,14 +232,14 @@ __global__ void __launch_bounds__(kLineThreads, BN == 64 ? 3 : 2) bwd_line(const
     for (int i = 0; i < WCOPIES; ++i) copy_w(pc, 0, 0u, i);
     Raw raw;
     {
-        Raw first[3];
+        Raw first[ITEMS];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) first[k] = load_item(k, pc);
+        for (int k = 0; k < ITEMS; ++k) first[k] = load_item(k, pc);
         const u32x4_t z = {0u, 0u, 0u, 0u};
         for (uint32_t o = (uint32_t)tid * 16u; o < 2u * buf_bytes; o += kLineThreads * 16u) *(SDGP_LDS u32x4_t*)(smem + L::off_a() + o) = z;
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 3; ++k) rank_item(first[k], k, pc, (uint32_t)L::off_a(), NoGap{});
+        for (int k = 0; k < ITEMS; ++k) rank_item(first[k], k, pc, (uint32_t)L::off_a(), NoGap{});
         if (nchunks > 1) raw = load_item(0, pc1);
     }
 
@@ -253,22 +272,37 @@ __global__ void __launch_bounds__(kLineThreads, BN == 64 ? 3 : 2) bwd_line(const
     struct Frags {
         u32x4_t a[TM];
         int meta[TM];
-        bf16x16_t b[TN];
+        typename std::conditional<SPARSE, bf16x16_t, bf16x8_t>::type b[TN];
     };
-    auto load_a = [&](Frags& f, int t, int s) {
-        f.a[t] = *(SDGP_LDS u32x4_t*)(smem + a_stage[t] + (2 - s) * 16);
-        f.meta[t] = *(SDGP_LDS uint16_t*)(smem + m_stage[t] + (2 - s) * 2);
+    // of k-step q: tap q, or tap q / 2 and its sixteen channels q % 2
+    auto load_a = [&](Frags& f, int t, int q) {
+        if constexpr (SPARSE) {
+            f.a[t] = *(SDGP_LDS u32x4_t*)(smem + a_stage[t] + (2 - q) * 16);
+            f.meta[t] = *(SDGP_LDS uint16_t*)(smem + m_stage[t] + (2 - q) * 2);
+        } else {
+            f.a[t] = *(SDGP_LDS u32x4_t*)(smem + a_stage[t] + (2 - q / 2) * 16 + (q & 1 ? 2u * plane_a : 0u));
+        }
     };
-    auto load_b = [&](Frags& f, int u, uint32_t slab_off) {
-        SDGP_LDS unsigned char* wb = smem + b_lane[u] + slab_off;
-        s16x4_t q[4];
+    auto load_b = [&](Frags& f, int u, uint32_t set, int q) {
+        SDGP_LDS unsigned char* wb = smem + b_lane[u] + set;
+        if constexpr (SPARSE) {
+            s16x4_t x[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            q[i] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SDGP_LDS s16x4_t*)(wb + ((i >> 1) * 16 + (i & 1) * 4) * L::kWRow));
-        typedef short s16x16_t __attribute__((ext_vector_type(16)));
-        const s16x16_t all = {q[0][0], q[0][1], q[0][2], q[0][3], q[1][0], q[1][1], q[1][2], q[1][3],
-                              q[2][0], q[2][1], q[2][2], q[2][3], q[3][0], q[3][1], q[3][2], q[3][3]};
-        f.b[u] = __builtin_bit_cast(bf16x16_t, all);
+            for (int i = 0; i < 4; ++i)
+                x[i] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SDGP_LDS s16x4_t*)(wb + q * L::kWSlab + ((i >> 1) * 16 + (i & 1) * 4) * L::kWRow));
+            typedef short s16x16_t __attribute__((ext_vector_type(16)));
+            const s16x16_t all = {x[0][0], x[0][1], x[0][2], x[0][3], x[1][0], x[1][1], x[1][2], x[1][3],
+                                  x[2][0], x[2][1], x[2][2], x[2][3], x[3][0], x[3][1], x[3][2], x[3][3]};
+            f.b[u] = __builtin_bit_cast(bf16x16_t, all);
+        } else {
+            s16x4_t x[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                x[i] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SDGP_LDS s16x4_t*)(wb + (q / 2) * L::kWSlab + ((q & 1) * 16 + i * 4) * L::kWRow));
+            typedef short s16x8_t __attribute__((ext_vector_type(8)));
+            const s16x8_t all = {x[0][0], x[0][1], x[0][2], x[0][3], x[1][0], x[1][1], x[1][2], x[1][3]};
+            f.b[u] = __builtin_bit_cast(bf16x8_t, all);
+        }
     };
 
     wait_lds_copies<0>();
@@ -285,25 +319,28 @@ __global__ void __launch_bounds__(kLineThreads, BN == 64 ? 3 : 2) bwd_line(const
 #pragma unroll
             for (int t = 0; t < TM; ++t) load_a(fr[0], t, 0);
 #pragma unroll
-            for (int u = 0; u < TN; ++u) load_b(fr[0], u, set_off);
+            for (int u = 0; u < TN; ++u) load_b(fr[0], u, set_off, 0);
             Raw raw_next;
             int g = 0;   // the next matrix instruction
             auto gap = [&](auto&... values) __attribute__((always_inline)) {
                 (pin_value(values), ...);
                 constexpr int G = TM * TN;
-                if (g >= 3 * G) return;
+                if (g >= KSTEPS * G) return;
                 const int q = g / G, i = g % G;
                 Frags& cur = fr[q & 1];
                 Frags& nxt = fr[(q & 1) ^ 1];
                 const int t = i / TN, u = i % TN;
                 __builtin_amdgcn_sched_barrier(0);
-                acc[t][u] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(__builtin_bit_cast(bf16x8_t, cur.a[t]), cur.b[u], acc[t][u], cur.meta[t], 0, 0);
+                if constexpr (SPARSE)
+                    acc[t][u] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(__builtin_bit_cast(bf16x8_t, cur.a[t]), cur.b[u], acc[t][u], cur.meta[t], 0, 0);
+                else
+                    acc[t][u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, cur.a[t]), cur.b[u], acc[t][u], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
-                if (q < 2) {
-                    if (i < TN) load_b(nxt, i, set_off + (uint32_t)(q + 1) * L::kWSlab);
+                if (q + 1 < KSTEPS) {
+                    if (i < TN) load_b(nxt, i, set_off, q + 1);
                     else if (i - TN < TM) load_a(nxt, i - TN, q + 1);
                 }
-                if (has1 && g == 0) raw_next = load_item(r < 2 ? r + 1 : 0, r < 2 ? pc1 : pc2);
+                if (has1 && g == 0 && (r == 2 || r + 1 < ITEMS)) raw_next = load_item(r < 2 ? r + 1 : 0, r < 2 ? pc1 : pc2);
                 if (g < WCOPIES) {
                     if (r < 2) copy_w(pc, r + 1, other_set, g);
                     else if (has1) copy_w(pc1, 0, other_set, g);
@@ -311,9 +348,9 @@ __global__ void __launch_bounds__(kLineThreads, BN == 64 ? 3 : 2) bwd_line(const
                 __builtin_amdgcn_sched_barrier(0);
                 ++g;
             };
-            if (has1) rank_item(raw, r, pc1, abuf_other, gap);
+            if (has1 && r < ITEMS) rank_item(raw, r, pc1, abuf_other, gap);
 #pragma unroll
-            for (int i = 0; i < 3 * TM * TN; ++i) gap();
+            for (int i = 0; i < KSTEPS * TM * TN; ++i) gap();
             __builtin_amdgcn_sched_barrier(0);
             wait_lds_copies<0>();
             __syncthreads();

@@ -1,5 +1,5 @@
-// Host side of the line kernel: 3x3 stride-1 layers with one pixel of padding and n <= 2 of m in {4, 8, 16}, on images up to 63
-// pixels wide.
+// Host side of the line kernel: 3x3 stride-1 layers with one pixel of padding, pruned by n of m in {4, 8, 16, 32} or not at all, on
+// images up to 63 pixels wide.
 #include <climits>
 
 #include "bwd_line.h"
@@ -9,10 +9,15 @@ namespace sdgp {
 int launch_line_m4(const LineParams& p, int bn, int rk, hipStream_t stream);
 int launch_line_m8(const LineParams& p, int bn, int rk, hipStream_t stream);
 int launch_line_m16(const LineParams& p, int bn, int rk, hipStream_t stream);
+int launch_line_masked_m4(const LineParams& p, int rk, hipStream_t stream);
+int launch_line_masked_m8(const LineParams& p, int rk, hipStream_t stream);
+int launch_line_masked_m16(const LineParams& p, int rk, hipStream_t stream);
+int launch_line_masked_m32(const LineParams& p, int rk, hipStream_t stream);
+int launch_line_dense(const LineParams& p, hipStream_t stream);
 
 namespace {
 
-// Columns of a tile.  What decides is how many workgroups the fullest CU gets: one of 128 columns takes about 1.7 times as long as
+// Columns of a tile for n <= 2.  What decides is how many workgroups the fullest CU gets: one of 128 columns takes about 1.7 times as long as
 // one of 64, which ranks the same pixels (94 layers of more than 64 input channels: 1.2 percent above the better of the two, at most
 // 15; always 64 columns 4.8 and 33 percent, always 128 10 and 59).  3x3 224 <- 192 at 34x34, batch 82, 2:8 Rescaled 64 us on 128
 // columns and 86 on 64; 128 <- 96 at 9x9, batch 301, 2:4 Rescaled 14.6 and 11.9.  The magnitude rankers that
@@ -30,13 +35,15 @@ int tile_columns(int64_t row_tiles, int64_t C_in, int64_t C_out, int n, int m, i
 // SDGP_OK after launching, a positive value when the problem does not fit, or a negative sdgp_status.
 int bwd_line_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S,
                     int stride, int pad, int n, int m, int rk, uint64_t seed, hipStream_t stream) {
-    if (R != 3 || S != 3 || stride != 1 || pad != 1 || n == m || n > 2 || (m != 4 && m != 8 && m != 16)) return 1;
-    if (C_out < 8 || (C_out % 8) != 0 || (C_out % m) != 0 || (C_in % 8) != 0) return 1;
+    if (R != 3 || S != 3 || stride != 1 || pad != 1) return 1;
+    const int mode = n == m ? 0 : n <= 2 && (m == 4 || m == 8 || m == 16) ? 2 : 1;
+    if (mode != 0 && m != 4 && m != 8 && m != 16 && m != 32) return 1;
+    if (C_out < 8 || (C_out % 8) != 0 || (mode != 0 && (C_out % m) != 0) || (C_in % 8) != 0) return 1;
     if (!is_aligned16(dO) || !is_aligned16(W) || !is_aligned16(dD)) return 1;
     if (Wd > kLineMaxWidth) return 1;   // wider: the three items a lane has do not cover a tile's window (bwd_row takes them)
     const int64_t pixels = B * H * Wd;
     // (the random ranker's sixteen channels of a short chunk must not straddle a carry into the index's high word)
-    if (rk == kRandom && C_out % 16 != 0 && pixels > (int64_t)0xFFFFFFFFu / C_out) return 1;
+    if (rk == kRandom && mode != 0 && C_out % 16 != 0 && pixels > (int64_t)0xFFFFFFFFu / C_out) return 1;
     // a position of the padded line is below four times the pixel's number; offsets into W are counted in 32 bits
     if (pixels >= (1 << 28) || 9 * C_in >= (1 << 24) || C_out * 9 * C_in >= (1 << 30) || C_out > (1 << 20)) return 1;
     LineParams p{};
@@ -49,12 +56,21 @@ int bwd_line_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t 
     p.n = n;
     p.mix = seed_mix(seed);
     const int64_t row_tiles = (pixels + kLineRows - 1) / kLineRows;
-    const int bn = tile_columns(row_tiles, C_in, C_out, n, m, rk);
+    // (the whole gradient takes twice the LDS of the compressed one: 128 columns leave one workgroup on a CU, 1.3 times the time over 60
+    // unpruned layers)
+    const int bn = mode == 2 ? tile_columns(row_tiles, C_in, C_out, n, m, rk) : 64;
     p.npos = line_positions((int)H, (int)Wd);
     p.ntiles_n = (int)((C_in + bn - 1) / bn);
     const int64_t blocks = row_tiles * p.ntiles_n;
     if (blocks >= INT_MAX / kLineThreads) return 1;
     p.nblocks = (int)blocks;
+    if (mode == 0) return launch_line_dense(p, stream);
+    if (mode == 1) {
+        if (m == 4) return launch_line_masked_m4(p, rk, stream);
+        if (m == 8) return launch_line_masked_m8(p, rk, stream);
+        if (m == 16) return launch_line_masked_m16(p, rk, stream);
+        return launch_line_masked_m32(p, rk, stream);
+    }
     if (m == 4) return launch_line_m4(p, bn, rk, stream);
     if (m == 8) return launch_line_m8(p, bn, rk, stream);
     return launch_line_m16(p, bn, rk, stream);

@@ -1,6 +1,6 @@
 """The kernel for 3x3 stride-1 layers that takes 256 consecutive pixels of all images at a time (csrc/bwd_line.h): image sizes at
 which lines, images and tiles begin in every position to each other, the widest image it takes and the next, column counts around
-its tiles, short last chunks, one and two of m, every ranker.  Against the oracle on sampled pixels, image borders included.
+its tiles, short last chunks, one and two of m, any n of m up to 32 and none pruned, every ranker.  Against the oracle on sampled pixels, image borders included.
 
 Tolerance: the tests of the other bf16 kernels, 1e-2 of sum |a||w| (one rounding to bf16 shows 2^-9)."""
 import numpy as np
@@ -48,6 +48,21 @@ def test_channels(C_in, C_out, n, m, ranker):
 def test_groups_of_eight_cut_by_the_last_chunk(C_out):
     check(150, 16, 17, 72, C_out, 2, 8, oracle.GREEDY_ADJUSTED)
     check(150, 16, 17, 72, C_out, 1, 4, oracle.RANDOM)
+
+
+@pytest.mark.parametrize("n,m,ranker", [(3, 4, oracle.GREEDY_ADJUSTED), (4, 8, oracle.RANDOM), (5, 8, oracle.GREEDY), (4, 16, oracle.GREEDY),
+                                        (9, 16, oracle.RANDOM), (2, 32, oracle.GREEDY), (4, 32, oracle.RANDOM), (16, 32, oracle.GREEDY_ADJUSTED),
+                                        (4, 4, oracle.GREEDY), (8, 8, oracle.RANDOM)])
+@pytest.mark.parametrize("B,H,Wd,C_in,C_out", [(150, 16, 17, 8, 32), (150, 16, 17, 72, 96), (50, 16, 17, 264, 160), (9000, 2, 2, 64, 64),
+                                               (9, 63, 63, 64, 32), (11, 50, 62, 40, 64)])
+def test_whole_gradient(B, H, Wd, C_in, C_out, n, m, ranker):
+    check(B, H, Wd, C_in, C_out, n, m, ranker)
+
+
+@pytest.mark.parametrize("C_out,n,m", [(8, 4, 8), (40, 3, 4), (56, 5, 8), (72, 8, 8), (80, 5, 16), (48, 16, 16)])
+def test_whole_gradient_cut_by_the_last_chunk(C_out, n, m):
+    check(150, 16, 17, 72, C_out, n, m, oracle.GREEDY_ADJUSTED)
+    check(150, 16, 17, 72, C_out, n, m, oracle.RANDOM)
 
 
 def test_infinite_gradient_stays_with_its_pixels():
