@@ -28,6 +28,7 @@
 
 #include "fastdiv.h"
 #include "lds_copy.h"
+#include "quad_rows.h"
 
 namespace sdgp {
 
@@ -70,7 +71,6 @@ struct LineLayout {
     static constexpr int kWRow = BN * 2;
     static constexpr int kWSlab = kLineKC * kWRow;
     static constexpr int kWSet = 3 * kWSlab;               // the slabs of one filter row
-    static constexpr int kOutPitch = BN * 2 + 16;
     // value planes (16 bytes per position and half chunk) and planes of their 2-bit positions (2 bytes), with one position more, which
     // takes what no tap reads; sizes are 128 modulo 256 bytes, so that the two halves of a wavefront read different halves of the banks
     __host__ __device__ static int plane_a(int npos) { return (((npos + 1) * 16 + 127) & ~255) + 128; }
@@ -78,10 +78,7 @@ struct LineLayout {
     __host__ __device__ static int off_a() { return 2 * kWSet; }
     // (the whole gradient, MODE 0 and 1: four planes, eight channels each)
     __host__ __device__ static int buf_bytes(int npos) { return MODE == 2 ? 2 * plane_a(npos) + 2 * plane_m(npos) : 4 * plane_a(npos); }
-    __host__ __device__ static int total(int npos) {
-        const int loop = off_a() + 2 * buf_bytes(npos), out = kLineRows * kOutPitch;
-        return loop > out ? loop : out;
-    }
+    __host__ __device__ static int total(int npos) { return off_a() + 2 * buf_bytes(npos); }
 };
 
 // keeps the computation of a value in front of what follows in the program
@@ -252,12 +249,15 @@ __global__ void __launch_bounds__(kLineThreads, MODE == 2 && BN == 64 ? 3 : 2) b
             for (int r = 0; r < 16; ++r) acc[t][u][r] = 0.0f;
 
     // ---- fragments
+    // Column n of tile u is 8 (n / 4) + 4 (u ^ (n / 16)) + n % 4 of the wavefront's 64: the lanes of a quad then hold eight consecutive
+    // columns in their two tiles, sixteen bytes of a row.  (The halves of a transposing read's lanes take different halves of the
+    // sixteen bytes, or they would meet in the same banks.)
     uint32_t b_lane[TN];
 #pragma unroll
     for (int u = 0; u < TN; ++u) {
-        const int L16 = lane & 15;
-        const int chunk = 8 * wn + 4 * u + 2 * ((lane >> 4) & 1) + ((L16 & 3) >> 1);
-        b_lane[u] = (uint32_t)((8 * (lane >> 5) + (L16 >> 2)) * L::kWRow + ((chunk ^ (WSW * (L16 >> 2))) * 16) + (L16 & 1) * 8);
+        const int L16 = lane & 15, upper = (lane >> 4) & 1;
+        const int chunk = 8 * wn + 4 * upper + (L16 & 3);
+        b_lane[u] = (uint32_t)((8 * (lane >> 5) + (L16 >> 2)) * L::kWRow + ((chunk ^ (WSW * (L16 >> 2))) * 16) + (u ^ upper) * 8);
     }
     const uint32_t half = (uint32_t)(lane >> 5);
     // where this lane's rows lie in the buffer and at the filter row of the current stage; tap s is 2 - s positions further
@@ -370,32 +370,16 @@ __global__ void __launch_bounds__(kLineThreads, MODE == 2 && BN == 64 ? 3 : 2) b
     }
     chunk(std::false_type{}, 0);
 
-    // ---- epilogue: fp32 -> bf16 (RNE) into LDS, then whole pixel rows with 16-byte stores
-    typedef float f32x2_t __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    // ---- epilogue: whole 128-byte rows straight from the registers (through LDS, with a barrier: 1.01 to 1.03 of the time of a call)
+    const int col = n0 + wn * 64 + 2 * (lane & 28);
 #pragma unroll
-    for (int tt = 0; tt < TM; ++tt)
+    for (int t = 0; t < TM; ++t)
 #pragma unroll
-        for (int u = 0; u < TN; ++u)
-#pragma unroll
-            for (int rr = 0; rr < 16; rr += 2) {
-                const int m = wm * WM + tt * 32 + 8 * (rr >> 2) + 4 * (lane >> 5) + (rr & 3);
-                const int col = wn * 64 + u * 32 + (lane & 31);
-                const f32x2_t v = {acc[tt][u][rr], acc[tt][u][rr + 1]};
-                const uint32_t pk = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
-                *(SDGP_LDS uint16_t*)(smem + m * L::kOutPitch + col * 2) = (uint16_t)pk;
-                *(SDGP_LDS uint16_t*)(smem + (m + 1) * L::kOutPitch + col * 2) = (uint16_t)(pk >> 16);
-            }
-    __syncthreads();
-#pragma unroll 4
-    for (int idx = tid; idx < BM * CPR; idx += kLineThreads) {
-        const int m = idx / CPR, cc = idx % CPR;
-        const int px = t0 + m;
-        if (px < p.pixels && n0 + cc * 8 < p.C_in) {
-            const u32x4_t v = *(SDGP_LDS u32x4_t*)(smem + m * L::kOutPitch + cc * 16);
-            __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(p.dD + (size_t)px * p.C_in + n0 + cc * 8));
+        for (int g = 0; g < 4; ++g) {
+            const u32x4_t out = quad_rows(acc[t][0], acc[t][1], g, lane);
+            const int px = t0 + wm * WM + t * 32 + 8 * g + 4 * (lane >> 5) + (lane & 3);
+            if (px < p.pixels && col < p.C_in) __builtin_nontemporal_store(out, reinterpret_cast<u32x4_t*>(p.dD + (size_t)px * p.C_in + col));
         }
-    }
 }
 
 }  // namespace sdgp

@@ -21,6 +21,7 @@
 
 #include "fastdiv.h"
 #include "lds_copy.h"
+#include "quad_rows.h"
 
 namespace sdgp {
 
@@ -257,14 +258,10 @@ __global__ void __launch_bounds__(kStride2Threads, 2) bwd_stride2(const Stride2P
     };
     clear();
 
-    // ---- a finished class: fp32 -> bf16 (RNE) and out.  Four registers of a lane are four rows of one column; the four lanes of a
-    // quad exchange them, so that each has one row's four columns of either tile, and a store is eight whole 128-byte rows.
-    // (Through LDS, sixteen rows of a wavefront at a time, a class took 8000 cycles of waiting for its own reads and writes; stores of
-    // half a line each cost the memory a quarter of the whole call's time.)
-    const uint32_t row_sel = lane & 1 ? 0x03020706u : 0x05040100u;
+    // ---- a finished class: out of the registers, a store is eight whole 128-byte rows.  (Through LDS, sixteen rows of a wavefront at a
+    // time, a class took 8000 cycles of waiting for its own reads and writes; stores of half a line each cost the memory a quarter of
+    // the whole call's time.)
     auto store_class = [&](int a, int b) __attribute__((always_inline)) {
-        typedef float f32x2_t __attribute__((ext_vector_type(2)));
-        typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
         const uint32_t outside = (a ? 1u << 31 : 0u) | (b ? 1u << 30 : 0u);
         const int col = n0 + wn * 64 + 2 * (lane & 28);
         const bool in = col < p.C_in;
@@ -277,23 +274,7 @@ __global__ void __launch_bounds__(kStride2Threads, 2) bwd_stride2(const Stride2P
         for (int t = 0; t < TM; ++t)
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                u32x2_t quad[TN];
-#pragma unroll
-                for (int u = 0; u < TN; ++u) {
-                    const f32x2_t v01 = {acc[t][u][4 * g], acc[t][u][4 * g + 1]}, v23 = {acc[t][u][4 * g + 2], acc[t][u][4 * g + 3]};
-                    const uint32_t p01 = __builtin_bit_cast(uint32_t, __builtin_convertvector(v01, bf16x2_t));
-                    const uint32_t p23 = __builtin_bit_cast(uint32_t, __builtin_convertvector(v23, bf16x2_t));
-                    const uint32_t n01 = (uint32_t)__builtin_amdgcn_mov_dpp((int)p01, 0xB1, 0xF, 0xF, true);   // the neighbour's: lane ^ 1
-                    const uint32_t n23 = (uint32_t)__builtin_amdgcn_mov_dpp((int)p23, 0xB1, 0xF, 0xF, true);
-                    const uint32_t q01 = __builtin_amdgcn_perm(n01, p01, row_sel);   // even lanes: row 0 of two columns, odd ones: row 1
-                    const uint32_t q23 = __builtin_amdgcn_perm(n23, p23, row_sel);   // rows 2 and 3
-                    const uint32_t give = lane & 2 ? q01 : q23;
-                    const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)give, 0x4E, 0xF, 0xF, true);  // lane ^ 2
-                    quad[u] = u32x2_t{lane & 2 ? got : q01, lane & 2 ? q23 : got};
-                }
-                const bool swap = (lane & 16) != 0;
-                const u32x4_t out = {swap ? quad[1][0] : quad[0][0], swap ? quad[1][1] : quad[0][1],
-                                     swap ? quad[0][0] : quad[1][0], swap ? quad[0][1] : quad[1][1]};
+                const u32x4_t out = quad_rows(acc[t][0], acc[t][1], g, lane);
                 const uint32_t e = place[t][g];
                 if (in && e != 3u << 30 && (e & outside) == 0u) {
                     const size_t pix = (size_t)((e & 0x1FFFFFFFu) + (uint32_t)(a * p.Wd + b));
