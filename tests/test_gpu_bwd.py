@@ -241,7 +241,7 @@ PRE_COMPRESSED = [
     wl.ConvLayer("pre_1x1_wide", 4, 13, 13, 2048, 128, 1, 1, 1, 0),      # ragged last row tile, 16 column tiles
     wl.ConvLayer("small_1x1_wide", 3, 13, 13, 2048, 128, 1, 1, 1, 0),    # a quarter fewer pixels: the small-problem kernel
     wl.ConvLayer("pre_1x1_s2", 5, 27, 27, 1024, 192, 1, 1, 2, 0),        # stride 2: three chunks of 64 channels
-    wl.ConvLayer("pre_3x3s2", 44, 40, 40, 64, 128, 3, 3, 2, 1),          # four parity classes, one to four taps
+    wl.ConvLayer("pre_3x3s2", 44, 40, 40, 64, 128, 3, 3, 2, 1),          # four parity classes, one to four taps (the stride-2 kernel)
     wl.ConvLayer("pre_4x4s2", 44, 40, 40, 72, 64, 4, 4, 2, 1),           # four taps in every class, ragged column tile
 ]
 

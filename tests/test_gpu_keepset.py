@@ -96,7 +96,10 @@ def nm_settings(ms=(4, 8, 16)):
 
 # (layer, spread): which kernel the dispatcher picks for it is noted per case
 CASES = [
-    # row-per-stage kernel: 512-row tiles with 64 and with 128 columns, 256-row tiles
+    # line kernel: 64 and 128 columns, few and many lines and images a tile (the names are those of the row kernel's tiles, which took
+    # these layers before; the wide images are its own)
+    (wl.ConvLayer("row512_n64_wide", 30, 20, 70, 64, 64, 3, 3, 1, 1), False),
+    (wl.ConvLayer("row512_n128_wide_spread", 30, 20, 70, 128, 128, 3, 3, 1, 1), True),
     (wl.ConvLayer("row512_n64", 400, 16, 16, 64, 64, 3, 3, 1, 1), False),
     (wl.ConvLayer("row512_n128", 400, 16, 16, 128, 128, 3, 3, 1, 1), False),
     (wl.ConvLayer("row512_n128_spread", 400, 16, 16, 128, 128, 3, 3, 1, 1), True),
@@ -106,14 +109,16 @@ CASES = [
     (wl.ConvLayer("pw_n64", 64, 23, 23, 64, 64, 1, 1, 1, 0), False),
     (wl.ConvLayer("pw_n160", 64, 23, 23, 160, 160, 1, 1, 1, 0), False),
     (wl.ConvLayer("pw_s2_n64", 64, 31, 29, 64, 64, 1, 1, 2, 0), False),
-    # pointwise kernel gathering rows per tap: stride-2 3x3 (classes of 1, 2, 2, 4 taps) and 4x4
+    # pointwise kernel gathering rows per tap, stride-2 3x3 (classes of 1, 2, 2, 4 taps) and 4x4; stride-2 kernel
+    (wl.ConvLayer("stride2_n128_spread", 64, 56, 54, 128, 128, 3, 3, 2, 1), True),
     (wl.ConvLayer("gather_s2_3x3", 64, 30, 28, 64, 64, 3, 3, 2, 1), True),
     (wl.ConvLayer("gather_s2_4x4", 64, 32, 32, 64, 64, 4, 4, 2, 1), True),
-    # between the small-problem kernel's 256 tiles of 32 rows and the row kernel's 128 of 256: the producer/consumer kernel
+    # between the small-problem kernel's 256 tiles of 32 rows and the row kernel's 128 of 256: the line kernel, 5x5 the producer/consumer
+    # kernel
     (wl.ConvLayer("conv3_n64", 40, 16, 16, 64, 64, 3, 3, 1, 1), False),
     (wl.ConvLayer("conv3_n64_spread", 40, 16, 16, 64, 64, 3, 3, 1, 1), True),
     (wl.ConvLayer("conv3_5x5", 72, 12, 12, 64, 64, 5, 5, 1, 2), True),
-    # channel count not a multiple of 32: the parity-class kernel; stride 2 below the pointwise classes' 64 tiles of 128 rows
+    # channel count not a multiple of 32: the line kernel; stride 2 below the pointwise classes' 64 tiles of 128 rows: the stride-2 kernel
     (wl.ConvLayer("tiled_n48", 66, 16, 16, 48, 48, 3, 3, 1, 1), False),
     (wl.ConvLayer("tiled_n48_spread", 66, 16, 16, 48, 48, 3, 3, 1, 1), True),
     (wl.ConvLayer("tiled_s2", 90, 14, 14, 32, 32, 3, 3, 2, 1), True),
@@ -133,6 +138,9 @@ CASES = [
 # The same on patterns that no structured-sparse instruction takes: the ranked rows are multiplied dense.  32 channels a
 # group, and more than two survivors.
 DENSE_ROWS = [
+    (wl.ConvLayer("line_n128", 200, 16, 16, 128, 128, 3, 3, 1, 1), False),
+    (wl.ConvLayer("line_n96_spread", 200, 16, 16, 96, 96, 3, 3, 1, 1), True),
+    (wl.ConvLayer("row_n96_wide", 30, 20, 70, 96, 96, 3, 3, 1, 1), False),
     (wl.ConvLayer("tiled_n64", 70, 16, 16, 64, 64, 3, 3, 1, 1), False),        # between 512 tiles of 32 rows and 128 of 256
     (wl.ConvLayer("tiled_s2_n96", 400, 9, 9, 96, 96, 3, 3, 2, 1), False),      # classes of 25 to 16 pixels: the last has 50 tiles of 128 rows
     (wl.ConvLayer("small_n96", 4, 16, 16, 96, 96, 3, 3, 1, 1), False),

@@ -65,6 +65,14 @@ def test_whole_gradient_cut_by_the_last_chunk(C_out, n, m):
     check(150, 16, 17, 72, C_out, n, m, oracle.RANDOM)
 
 
+@pytest.mark.parametrize("n,m,ranker", [(2, 4, oracle.GREEDY), (2, 4, oracle.RANDOM), (1, 4, oracle.GREEDY_ADJUSTED), (2, 8, oracle.GREEDY),
+                                        (2, 16, oracle.RANDOM), (3, 4, oracle.GREEDY), (4, 8, oracle.RANDOM), (5, 16, oracle.GREEDY_ADJUSTED),
+                                        (4, 32, oracle.GREEDY), (4, 4, oracle.GREEDY)])
+@pytest.mark.parametrize("B,C_in,C_out", [(40, 64, 64), (20, 136, 96)])
+def test_wider_images_stay_on_the_row_kernel(B, C_in, C_out, n, m, ranker):
+    check(B, 20, 70, C_in, C_out, n, m, ranker)
+
+
 def test_infinite_gradient_stays_with_its_pixels():
     """The pixels next to it in the line, but across an image's or a line's end, are not its neighbours."""
     layer = wl.ConvLayer("t", 150, 16, 17, 64, 64, 3, 3, 1, 1)

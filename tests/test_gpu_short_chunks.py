@@ -13,7 +13,7 @@ from util import rel_error, to_gpu, to_host
 
 pytestmark = pytest.mark.gpu
 
-KINDS = {  # B, H, Wd, C_in and R, S, stride, pad: enough tiles for the kernel named
+KINDS = {  # B, H, Wd, C_in and R, S, stride, pad: enough tiles for the kernel named ("row": the line kernel)
     "row_256": ((150, 16, 16, 72), (3, 3, 1, 1)),
     "row_64": ((300, 9, 9, 40), (3, 3, 1, 1)),
     "pointwise": ((1100, 13, 13, 136), (1, 1, 1, 0)),       # (past the limit of the small ones)

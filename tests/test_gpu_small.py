@@ -55,11 +55,11 @@ def test_filters(H, Wd, R, S, stride, pad):
 @pytest.mark.parametrize("n,m", [(2, 4), (4, 4), (5, 8)])
 @pytest.mark.parametrize("shape", [
     (2100, 4, 4, 264, 40, 1, 1, 1, 0),      # 1x1, ragged C_out: the pointwise kernel's short last chunk
-    (270, 8, 8, 16, 40, 3, 3, 1, 1),        # ragged C_out, more than 512 tiles: bwd_tiled
+    (270, 8, 8, 16, 40, 3, 3, 1, 1),        # ragged C_out, more than 512 tiles: the line kernel
     (300, 9, 11, 24, 40, 3, 3, 2, 1),       # the same, strided
     (70, 16, 16, 72, 64, 5, 5, 1, 2),       # a filter neither three wide nor 1x1, more than 512 tiles: bwd_conv3
     (65, 16, 16, 72, 64, 2, 2, 1, 1),
-    (130, 16, 16, 64, 64, 3, 3, 1, 1),      # the row kernel
+    (130, 16, 16, 64, 64, 3, 3, 1, 1),      # the line kernel
     (350, 7, 7, 136, 64, 1, 1, 1, 0),       # the pointwise kernel
     (170, 14, 14, 72, 64, 3, 3, 2, 1),      # its parity classes
 ])
