@@ -2,40 +2,13 @@
 // gradient fits into LDS.
 #include <climits>
 
-#include "bwd_stride2.h"
+#include "bwd_stride2_shapes.h"
 
 namespace sdgp {
 
 int launch_stride2_m4(const Stride2Params& p, int shape, int rk, hipStream_t stream);
 int launch_stride2_m8(const Stride2Params& p, int shape, int rk, hipStream_t stream);
 int launch_stride2_m16(const Stride2Params& p, int shape, int rk, hipStream_t stream);
-
-namespace {
-
-struct Shape {
-    int bn, rows, npos, lds;
-    int64_t blocks;
-    double time;
-};
-
-template <int BN, int TM>
-Shape shape_of(int64_t pixels, int P, int Q, int64_t C_in, int parts) {
-    using L = Stride2Layout<BN, TM>;
-    Shape s;
-    s.bn = BN, s.rows = L::kRows, s.npos = L::positions(P, Q), s.lds = L::total(s.npos, parts);
-    s.blocks = (pixels + s.rows - 1) / s.rows * ((C_in + BN - 1) / BN);
-    // Time in units of a workgroup of 256 positions and 128 columns beside another one; one of half the size takes 0.7 of that, one
-    // alone on its CU loses a third of the CU, a third one gains 15 percent.  (131 layers: 1.03 times the best shape's time; always
-    // the first shape 1.27, the second 1.07, the third 1.10.)
-    const int most = (int)(160 * 1024 / s.lds), per_cu = most < (TM == 4 ? 2 : 3) ? most : (TM == 4 ? 2 : 3);
-    constexpr double kBeside[4] = {0.0, 1.5, 1.0, 0.85};
-    const int64_t round = 256 * per_cu, rest = s.blocks % round;
-    const int left = (int)((rest + 255) / 256);
-    s.time = per_cu < 1 ? 0.0 : (TM == 4 ? 1.0 : 0.7) * ((double)(s.blocks / round) * per_cu * kBeside[per_cu] + left * kBeside[left]);
-    return s;
-}
-
-}  // namespace
 
 // SDGP_OK after launching, a positive value when the problem does not fit, or a negative sdgp_status.
 // classes: the parity-class kernel would take the problem.  It is the faster one where this kernel has less than a workgroup for every
@@ -56,13 +29,10 @@ int bwd_stride2_launch(bool classes, const void* dO, const void* W, void* dD, in
     if (rk == kRandom && C_out % 16 != 0 && pixels > (int64_t)0xFFFFFFFFu / C_out) return 1;
     Stride2Params p{};
     p.parts = 2 * (int)((C_out + 31) / 32);
-    const Shape shapes[3] = {shape_of<128, 4>(pixels, (int)P, (int)Q, C_in, p.parts), shape_of<128, 2>(pixels, (int)P, (int)Q, C_in, p.parts),
-                             shape_of<64, 2>(pixels, (int)P, (int)Q, C_in, p.parts)};
-    int best = -1;
-    for (int i = 0; i < 3; ++i)
-        if (shapes[i].lds <= (classes ? 80 : 132) * 1024 && (best < 0 || shapes[i].time < shapes[best].time)) best = i;
+    Stride2Shape shape;
+    const int best = stride2_choose(pixels, (int)P, (int)Q, C_in, p.parts, (classes ? 80 : 132) * 1024, shape);
     if (best < 0) return 1;
-    if (classes && (C_out > 224 || (C_out >= 192 && C_in <= 64) || shapes[best].blocks < (C_out >= 192 ? 320 : 256))) return 1;
+    if (classes && (C_out > 224 || (C_out >= 192 && C_in <= 64) || shape.blocks < (C_out >= 192 ? 320 : 256))) return 1;
     p.dO = static_cast<const uint16_t*>(dO);
     p.W = static_cast<const uint16_t*>(W);
     p.dD = static_cast<uint16_t*>(dD);
@@ -71,10 +41,10 @@ int bwd_stride2_launch(bool classes, const void* dO, const void* W, void* dD, in
     p.w_row = 9 * (int)C_in;
     p.n = n;
     p.mix = seed_mix(seed);
-    p.npos = shapes[best].npos;
-    p.ntiles_n = (int)((C_in + shapes[best].bn - 1) / shapes[best].bn);
-    if (shapes[best].blocks >= INT_MAX / kStride2Threads) return 1;
-    p.nblocks = (int)shapes[best].blocks;
+    p.npos = shape.npos;
+    p.ntiles_n = (int)((C_in + shape.bn - 1) / shape.bn);
+    if (shape.blocks >= INT_MAX / kStride2Threads) return 1;
+    p.nblocks = (int)shape.blocks;
     if (m == 4) return launch_stride2_m4(p, best, rk, stream);
     if (m == 8) return launch_stride2_m8(p, best, rk, stream);
     return launch_stride2_m16(p, best, rk, stream);

@@ -1,0 +1,26 @@
+// Host build of the rules by which the line and the stride-2 kernel and their neighbours share the 3x3 layers
+// (csrc/bwd_stride2_shapes.h).  Test infrastructure, not product code; built without optimisation, so that what the rules compute
+// for shapes that do not fit is computed.
+//   stride2 B H Wd C_in C_out LDS    the shape chosen within LDS bytes: "bn rows lds blocks", or "none"
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+
+#include "bwd_stride2_shapes.h"
+
+using namespace sdgp;
+
+int main(int argc, char** argv) {
+    int64_t v[16] = {};
+    for (int i = 2; i < argc && i < 16; ++i) v[i - 2] = atoll(argv[i]);
+    if (argc == 8 && !strcmp(argv[1], "stride2")) {
+        const int64_t P = (v[1] + 1) / 2, Q = (v[2] + 1) / 2;
+        Stride2Shape s;
+        if (stride2_choose(v[0] * P * Q, (int)P, (int)Q, v[3], 2 * (int)((v[4] + 31) / 32), (int)v[5], s) < 0) return puts("none"), 0;
+        printf("%d %d %d %lld\n", s.bn, s.rows, s.lds, (long long)s.blocks);
+        return 0;
+    }
+    return 2;
+}

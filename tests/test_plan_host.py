@@ -1,0 +1,40 @@
+"""The rules by which 3x3 layers find their kernel, compiled for the host without optimisation (tests/native/plan_host_check.hip)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+
+pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc to compile the host check")
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("native") / "plan_host_check")
+    src = os.path.join(ROOT, "tests", "native", "plan_host_check.hip")
+    subprocess.run([HIPCC, "-O0", "-std=c++17", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                    "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(ROOT, "paper_2202_00774_amd", "csrc"), "-o", exe, src],
+                   check=True, capture_output=True, timeout=300)
+
+    def run(*args):
+        done = subprocess.run([exe, *map(str, args)], capture_output=True, text=True, timeout=60)
+        assert done.returncode == 0, (args, done.returncode)
+        return done.stdout.split()
+    return run
+
+
+@pytest.mark.parametrize("C_out", [256, 512, 1000, 1024])
+@pytest.mark.parametrize("H,Wd", [(1, 1), (14, 14), (56, 56), (3, 1023)])
+def test_stride2_shapes_beyond_the_lds(ask, C_out, H, Wd):
+    """Layers of which no shape, or not every one, fits a CU's LDS: 512 <- 512 at 14x14 wants 240640 bytes for one of them."""
+    for lds in (80 * 1024, 132 * 1024):
+        got = ask("stride2", 256, H, Wd, 512, C_out, lds)
+        assert got == ["none"] or int(got[2]) <= lds
+    assert ask("stride2", 256, 14, 14, 512, 1024, 132 * 1024) == ["none"]
+
+
+def test_stride2_shapes_within_the_lds(ask):
+    assert ask("stride2", 256, 56, 56, 128, 128, 80 * 1024) == ["128", "256", "81408", "784"]
