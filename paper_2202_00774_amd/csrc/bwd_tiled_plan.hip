@@ -154,8 +154,11 @@ int bwd_tiled_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t
         const int64_t t = (int64_t)((B + p.TB - 1) / p.TB) * cl.tiles_h * cl.tiles_w;
         if (tiles + t >= INT_MAX / 8) return 1;
         tiles += (int)t;
+        if (cl.tiles_h == 0 || cl.tiles_w == 0) {
+            cl.tiles_h = cl.tiles_w = 1;  // empty class: owns no tile and needs no halo (the tile was not chosen for one), avoid /0
+            continue;
+        }
         p.halo_max = std::max(p.halo_max, p.TB * cl.HTH * cl.HTW);
-        if (cl.tiles_h == 0 || cl.tiles_w == 0) cl.tiles_h = cl.tiles_w = 1;  // empty class: owns no tile, avoid /0
     }
     // Classes that own no tile must not capture tile ids: give them an unreachable base.
     for (int c = 0; c < p.nclass; ++c)
