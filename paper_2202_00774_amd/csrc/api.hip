@@ -32,7 +32,7 @@ int bwd_gather_launch(const void* dO, const void* W, void* dD, int64_t B, int64_
 bool bwd_pw_workspace_unread(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n, int m);
 size_t bwd_pw_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S, int stride, int pad, int n,
                         int m);
-int bwd_stride2_launch(bool classes, const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
+int bwd_stride2_launch(int classes, const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
                        int R, int S, int stride, int pad, int n, int m, int rk, uint64_t seed, hipStream_t stream);
 int bwd_line_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S,
                     int stride, int pad, int n, int m, int rk, uint64_t seed, hipStream_t stream);
@@ -173,7 +173,7 @@ int bwd_dispatch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, 
         if (rc <= 0) return rc;
         rc = sdgp::bwd_line_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, stream);
         if (rc <= 0) return rc;
-        rc = sdgp::bwd_stride2_launch(false, dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, stream);
+        rc = sdgp::bwd_stride2_launch(0, dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, stream);
         if (rc <= 0) return rc;
         rc = sdgp::bwd_conv3_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, stream);
         if (rc <= 0) return rc;

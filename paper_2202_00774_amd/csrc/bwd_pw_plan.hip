@@ -24,7 +24,7 @@ int launch_pw_classes_masked_m16(const PwClasses& all, int ncls, int shape, int 
 int launch_pw_classes_masked_m32(const PwClasses& all, int ncls, int shape, int rk, hipStream_t stream);
 int launch_pw_pre(const PwParams& p, int shape, hipStream_t stream);
 int launch_pw_classes_pre(const PwClasses& all, int ncls, int shape, hipStream_t stream);
-int bwd_stride2_launch(bool classes, const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
+int bwd_stride2_launch(int classes, const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
                        int R, int S, int stride, int pad, int n, int m, int rk, uint64_t seed, hipStream_t stream);
 size_t compress_meta_offset(int64_t rows, int64_t C_out);
 size_t compress_bytes(int64_t rows, int64_t C_out);
@@ -338,7 +338,7 @@ int bwd_gather_launch(const void* dO, const void* W, void* dD, int64_t B, int64_
     }
     if (!planned && gather_plan(B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, false, plan) != 0) return 1;
     // 3x3 of stride 2: the kernel that ranks a gradient element once for all four classes, where it is the faster one
-    const int rc2 = bwd_stride2_launch(true, dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, stream);
+    const int rc2 = bwd_stride2_launch(plan.pre ? 2 : 1, dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, stream);
     if (rc2 <= 0) return rc2;
     const int64_t rows_dO = plan.all.c[0].rows_dO;
     const void* grad = dO;

@@ -11,13 +11,11 @@ int launch_stride2_m8(const Stride2Params& p, int shape, int rk, hipStream_t str
 int launch_stride2_m16(const Stride2Params& p, int shape, int rk, hipStream_t stream);
 
 // SDGP_OK after launching, a positive value when the problem does not fit, or a negative sdgp_status.
-// classes: the parity-class kernel would take the problem.  It is the faster one where this kernel has less than a workgroup for every
-// CU (its classes are four workgroups: 32 <- 64 at 10x10, batch 452, 10.3 us against 12.9), where the ranked gradient leaves one
-// workgroup on a CU (384 <- 256 at 40x40, batch 61, 61 against 85), and for 192 channels and more, ranked ahead there, on little more
-// than a workgroup a CU (256 <- 192 at 17x17, batch 233, 28 against 31) or with half of the columns empty (64 <- 192 at 25x25,
-// batch 484, 45 against 50).  Above these lines 150 layers took 0.78 of its time, the
-// slowest 1.04.  Against what takes the others (bwd_tiled) one workgroup on a CU is still the faster way: 0.53 to 0.96.
-int bwd_stride2_launch(bool classes, const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
+// classes: 1 if the parity-class kernel would take the problem, ranking per tap, 2 if it would with the gradient ranked ahead, 0 if not.
+// That kernel is also the faster one where the ranked gradient leaves one workgroup on a CU here (384 <- 256 at 40x40, batch 61, 61 us
+// against 85).  Above these lines 150 layers took 0.78 of its time, the slowest 1.04.  Against what takes the others (bwd_tiled) one
+// workgroup on a CU is still the faster way: 0.53 to 0.96.
+int bwd_stride2_launch(int classes, const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
                        int R, int S, int stride, int pad, int n, int m, int rk, uint64_t seed, hipStream_t stream) {
     if (R != 3 || S != 3 || stride != 2 || pad != 1 || n == m || n > 2 || (m != 4 && m != 8 && m != 16)) return 1;
     if (C_out < 8 || (C_out % 8) != 0 || (C_out % m) != 0 || (C_in % 8) != 0) return 1;
@@ -30,9 +28,9 @@ int bwd_stride2_launch(bool classes, const void* dO, const void* W, void* dD, in
     Stride2Params p{};
     p.parts = 2 * (int)((C_out + 31) / 32);
     Stride2Shape shape;
-    const int best = stride2_choose(pixels, (int)P, (int)Q, C_in, p.parts, (classes ? 80 : 132) * 1024, shape);
+    const int best = stride2_choose(pixels, (int)P, (int)Q, C_in, p.parts, (classes != 0 ? 80 : 132) * 1024, shape);
     if (best < 0) return 1;
-    if (classes && (C_out > 224 || (C_out >= 192 && C_in <= 64) || shape.blocks < (C_out >= 192 ? 320 : 256))) return 1;
+    if (classes != 0 && stride2_classes_faster(classes == 2, H, Wd, C_in, C_out, shape.blocks)) return 1;
     p.dO = static_cast<const uint16_t*>(dO);
     p.W = static_cast<const uint16_t*>(W);
     p.dD = static_cast<uint16_t*>(dD);

@@ -45,4 +45,20 @@ inline int stride2_choose(int64_t pixels, int P, int Q, int64_t C_in, int parts,
     return best;
 }
 
+// Whether the parity-class kernel is the faster one for a layer that it would take, ranking the gradient ahead (`ahead`, in a pass of its
+// own) or once per tap.
+//   * Less than a workgroup for every CU here (its classes are four workgroups: 32 <- 64 at 10x10, batch 452, 10.3 us against 12.9).
+//   * 192 channels and more, ranked ahead there, on little more than a workgroup a CU (256 <- 192 at 17x17, batch 233, 28 against 31) or
+//     with half of the columns empty (64 <- 192 at 25x25, batch 484, 45 against 50).  More than 224 never fit two workgroups on a CU.
+//   * Small images of odd sides: all four classes are computed for every position, and at 3x3 nine of the sixteen pixels exist, 0.44 of
+//     the products; the classes have what exists.  128 channels and more, ranked ahead there, and less than 5/8 of the products needed
+//     (3x3, 3x5, 3x7, 5x5): 0.87 of this kernel's time over 186 layers (448 <- 128 at 3x3, batch 11004, 44 against 66).  With 64
+//     channels, or from 5x7 on, this one is faster: 0.89 over 319 layers, 0.94 over 48.
+inline bool stride2_classes_faster(bool ahead, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int64_t blocks) {
+    if (C_out > 224 || (C_out >= 192 && C_in <= 64) || blocks < (C_out >= 192 ? 320 : 256)) return true;
+    const int64_t P = (H + 1) / 2, Q = (Wd + 1) / 2;
+    const int64_t needed = (2 * (H / 2) + P) * (2 * (Wd / 2) + Q), computed = 9 * P * Q;   // taps times pixels of an image
+    return ahead && C_out >= 128 && 8 * needed < 5 * computed;
+}
+
 }  // namespace sdgp

@@ -2,6 +2,7 @@
 // (csrc/bwd_stride2_shapes.h).  Test infrastructure, not product code; built without optimisation, so that what the rules compute
 // for shapes that do not fit is computed.
 //   stride2 B H Wd C_in C_out LDS    the shape chosen within LDS bytes: "bn rows lds blocks", or "none"
+//   classes AHEAD B H Wd C_in C_out  who takes a layer that the parity-class kernel could take: "classes" or "stride2"
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -20,6 +21,13 @@ int main(int argc, char** argv) {
         Stride2Shape s;
         if (stride2_choose(v[0] * P * Q, (int)P, (int)Q, v[3], 2 * (int)((v[4] + 31) / 32), (int)v[5], s) < 0) return puts("none"), 0;
         printf("%d %d %d %lld\n", s.bn, s.rows, s.lds, (long long)s.blocks);
+        return 0;
+    }
+    if (argc == 8 && !strcmp(argv[1], "classes")) {
+        const int64_t P = (v[2] + 1) / 2, Q = (v[3] + 1) / 2;
+        Stride2Shape s;
+        const bool fits = stride2_choose(v[1] * P * Q, (int)P, (int)Q, v[4], 2 * (int)((v[5] + 31) / 32), 80 * 1024, s) >= 0;
+        puts(!fits || stride2_classes_faster(v[0] != 0, v[2], v[3], v[4], v[5], s.blocks) ? "classes" : "stride2");
         return 0;
     }
     return 2;

@@ -63,3 +63,10 @@ def test_infinite_gradient_stays_with_its_pixels():
     W = wl.normal(layer.W_shape, 0.1, 4, wl.BF16)
     out = sdgp.sdgp_conv_bwd_data(to_gpu(dO), to_gpu(W), 24, 25, 2, 1, 2, 4, oracle.GREEDY, 1)
     assert np.array_equal(~np.isfinite(wl.to_f64(to_host(out))).all(axis=3), hit)
+
+
+@pytest.mark.parametrize("n,m,ranker", [(2, 4, oracle.RANDOM), (1, 8, oracle.GREEDY), (2, 16, oracle.GREEDY_ADJUSTED)])
+@pytest.mark.parametrize("B,H,Wd", [(20000, 3, 3), (9000, 3, 5), (9000, 5, 3), (6000, 5, 5)])
+def test_small_images_of_odd_sides(B, H, Wd, n, m, ranker):
+    """128 channels: the parity-class kernel with the gradient ranked ahead, which computes only the pixels there are."""
+    check(B, H, Wd, 72, 128, n, m, ranker)

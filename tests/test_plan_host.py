@@ -38,3 +38,15 @@ def test_stride2_shapes_beyond_the_lds(ask, C_out, H, Wd):
 
 def test_stride2_shapes_within_the_lds(ask):
     assert ask("stride2", 256, 56, 56, 128, 128, 80 * 1024) == ["128", "256", "81408", "784"]
+
+
+@pytest.mark.parametrize("ahead,B,H,Wd,C_in,C_out,taker", [
+    (1, 11004, 3, 3, 448, 128, "classes"), (1, 51098, 3, 3, 64, 128, "classes"), (1, 6156, 3, 5, 512, 128, "classes"),
+    (1, 20310, 5, 5, 64, 128, "classes"),
+    (0, 11004, 3, 3, 448, 128, "stride2"),      # nothing ranked ahead there
+    (1, 11004, 3, 3, 448, 64, "stride2"),       # 64 channels
+    (1, 6000, 5, 7, 256, 128, "stride2"), (1, 6000, 4, 4, 256, 128, "stride2"), (1, 256, 56, 56, 128, 128, "stride2")])
+def test_small_images_of_odd_sides(ask, ahead, B, H, Wd, C_in, C_out, taker):
+    """3x3 stride 2, n <= 2: the kernel that computes all four parity classes of every position, and the one that computes what exists
+    of them, measured on either side of the line."""
+    assert ask("classes", ahead, B, H, Wd, C_in, C_out) == [taker]
