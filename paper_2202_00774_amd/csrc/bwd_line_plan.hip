@@ -2,7 +2,7 @@
 // images up to 63 pixels wide.
 #include <climits>
 
-#include "bwd_line.h"
+#include "bwd_line_choice.h"
 
 namespace sdgp {
 
@@ -14,23 +14,6 @@ int launch_line_masked_m8(const LineParams& p, int rk, hipStream_t stream);
 int launch_line_masked_m16(const LineParams& p, int rk, hipStream_t stream);
 int launch_line_masked_m32(const LineParams& p, int rk, hipStream_t stream);
 int launch_line_dense(const LineParams& p, hipStream_t stream);
-
-namespace {
-
-// Columns of a tile for n <= 2.  What decides is how many workgroups the fullest CU gets: one of 128 columns takes about 1.7 times as long as
-// one of 64, which ranks the same pixels (94 layers of more than 64 input channels: 1.2 percent above the better of the two, at most
-// 15; always 64 columns 4.8 and 33 percent, always 128 10 and 59).  3x3 224 <- 192 at 34x34, batch 82, 2:8 Rescaled 64 us on 128
-// columns and 86 on 64; 128 <- 96 at 9x9, batch 301, 2:4 Rescaled 14.6 and 11.9.  The magnitude rankers that
-// sort keys have no registers left for 128 columns where the instantiation also cuts the last chunk (448 <- 128 at 27x27, batch 60,
-// 1:4 Magnitude 56 us, 41 on 64 columns; 368 <- 272 at 22x22, batch 62, 2:16 79 and 54).
-int tile_columns(int64_t row_tiles, int64_t C_in, int64_t C_out, int n, int m, int rk) {
-    const bool cuts = n == 1 || C_out % kLineKC != 0, keys = rk != kRandom && (m > 4 || (n == 1 && rk == kGreedy));
-    if (C_in <= 64 || (cuts && keys)) return 64;
-    const int64_t per_cu_64 = (row_tiles * ((C_in + 63) / 64) + 255) / 256, per_cu_128 = (row_tiles * ((C_in + 127) / 128) + 255) / 256;
-    return per_cu_128 * 17 < per_cu_64 * 10 ? 128 : 64;
-}
-
-}  // namespace
 
 // SDGP_OK after launching, a positive value when the problem does not fit, or a negative sdgp_status.
 int bwd_line_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out, int R, int S,
@@ -58,7 +41,7 @@ int bwd_line_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t 
     const int64_t row_tiles = (pixels + kLineRows - 1) / kLineRows;
     // (the whole gradient takes twice the LDS of the compressed one: 128 columns leave one workgroup on a CU, 1.3 times the time over 60
     // unpruned layers)
-    const int bn = mode == 2 ? tile_columns(row_tiles, C_in, C_out, n, m, rk) : 64;
+    const int bn = mode == 2 ? tile_columns(row_tiles, (int)H, (int)Wd, C_in, C_out, n, m, rk) : 64;
     p.npos = line_positions((int)H, (int)Wd);
     p.ntiles_n = (int)((C_in + bn - 1) / bn);
     const int64_t blocks = row_tiles * p.ntiles_n;

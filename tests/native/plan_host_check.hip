@@ -1,6 +1,7 @@
 // Host build of the rules by which the line and the stride-2 kernel and their neighbours share the 3x3 layers
-// (csrc/bwd_stride2_shapes.h).  Test infrastructure, not product code; built without optimisation, so that what the rules compute
+// (csrc/bwd_line_choice.h, csrc/bwd_stride2_shapes.h).  Test infrastructure, not product code; built without optimisation, so that what the rules compute
 // for shapes that do not fit is computed.
+//   columns B H Wd C_in C_out n m ranker   columns of the line kernel's tile for n <= 2
 //   stride2 B H Wd C_in C_out LDS    the shape chosen within LDS bytes: "bn rows lds blocks", or "none"
 //   classes AHEAD B H Wd C_in C_out  who takes a layer that the parity-class kernel could take: "classes" or "stride2"
 #include <hip/hip_runtime.h>
@@ -9,6 +10,7 @@
 #include <cstdlib>
 #include <cstring>
 
+#include "bwd_line_choice.h"
 #include "bwd_stride2_shapes.h"
 
 using namespace sdgp;
@@ -16,6 +18,11 @@ using namespace sdgp;
 int main(int argc, char** argv) {
     int64_t v[16] = {};
     for (int i = 2; i < argc && i < 16; ++i) v[i - 2] = atoll(argv[i]);
+    if (argc == 10 && !strcmp(argv[1], "columns")) {
+        const int64_t row_tiles = (v[0] * v[1] * v[2] + kLineRows - 1) / kLineRows;
+        printf("%d\n", tile_columns(row_tiles, (int)v[1], (int)v[2], v[3], v[4], (int)v[5], (int)v[6], (int)v[7]));
+        return 0;
+    }
     if (argc == 8 && !strcmp(argv[1], "stride2")) {
         const int64_t P = (v[1] + 1) / 2, Q = (v[2] + 1) / 2;
         Stride2Shape s;

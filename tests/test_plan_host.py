@@ -50,3 +50,16 @@ def test_small_images_of_odd_sides(ask, ahead, B, H, Wd, C_in, C_out, taker):
     """3x3 stride 2, n <= 2: the kernel that computes all four parity classes of every position, and the one that computes what exists
     of them, measured on either side of the line."""
     assert ask("classes", ahead, B, H, Wd, C_in, C_out) == [taker]
+
+
+RANDOM, GREEDY, RESCALED = 0, 1, 2
+
+
+@pytest.mark.parametrize("B,H,Wd,C_in,C_out,n,m,ranker,columns", [
+    (15, 62, 62, 432, 240, 2, 8, RANDOM, 64), (17, 63, 63, 384, 256, 1, 4, RANDOM, 64),     # one workgroup of 128 columns a CU
+    (1038, 2, 33, 352, 256, 2, 16, RANDOM, 64),
+    (33, 60, 60, 128, 64, 2, 16, RANDOM, 128),                                              # two
+    (512, 16, 16, 128, 256, 2, 4, GREEDY, 128), (82, 34, 34, 224, 192, 2, 8, RESCALED, 128), (301, 9, 9, 128, 96, 2, 4, RESCALED, 64),
+    (60, 27, 27, 448, 128, 1, 4, GREEDY, 64)])
+def test_line_columns(ask, B, H, Wd, C_in, C_out, n, m, ranker, columns):
+    assert ask("columns", B, H, Wd, C_in, C_out, n, m, ranker) == [str(columns)]
