@@ -33,4 +33,34 @@ inline int tile_columns(int64_t row_tiles, int H, int Wd, int64_t C_in, int64_t 
     return per_cu_128 * (alone ? 19 : 17) < per_cu_64 * 10 ? 128 : 64;
 }
 
+// The whole gradient of an image of few lines (zeros between the lines and images: 1x1 to 3x3, one or two lines, one column) leaves one
+// workgroup of the line kernel on a CU; so do images 58 to 63 pixels wide.
+inline bool line_alone(int H, int Wd) { return line_lds(0, 64, H, Wd) > kLineLdsPair; }
+
+// A round of 256 workgroups of rows x bn of the row kernel, in rounds of a line kernel that has the CUs to itself (mode 0 or 1).
+inline double row_round(int mode, int m, int rows, int bn) {
+    if (mode == 0) return rows == 256 ? (bn == 64 ? 1.1 : 1.8) : (bn == 64 ? 1.85 : 3.0);
+    if (rows == 256) return bn == 64 ? 1.2 : 1.75;
+    return bn == 64 && m != 32 ? 1.75 : 2.1;
+}
+
+// Whether the row kernel, planned with `blocks` tiles of rows x bn, is faster than a line kernel alone on its CUs with `line_blocks`
+// workgroups.  With row_worth_planning, over images of few lines: 600 unpruned layers 1.4 percent above the better of the two (line kernel
+// only 3.8; 512 <- 64 at 1x1, batch 95360, 85 us, 57 on the row kernel), 600 of general n:m 0.4 (0.6; 56 <- 152 at 2x2, batch 63185, 4:8, 80
+// and 66).  On wide images it gained nothing over the line kernel, which is 0.4 and 0.5 percent above the better one there (643 layers).
+inline bool row_faster_than_lone_line(int mode, int m, int64_t blocks, int rows, int bn, int64_t line_blocks) {
+    return (double)((blocks + 255) / 256) * row_round(mode, m, rows, bn) < (double)((line_blocks + 255) / 256);
+}
+
+// Whether a layer is worth planning for the row kernel to find that out: an image of few lines, no fewer tiles than without any waste
+// faster, and a search (7 us for 1x56, 25 for 600x1, 2 for 3x3) that the call hides: a round is 7 us and more.
+inline bool row_worth_planning(int mode, int m, int64_t pixels, int64_t H, int64_t Wd, int64_t C_in, int64_t line_blocks) {
+    if (mode == 2 || H < 1 || Wd < 1 || Wd > 56 || !line_alone((int)H, (int)Wd)) return false;
+    if (H * Wd > 16 && line_blocks <= 5 * 256) return false;
+    for (int rows = 256; rows <= 512; rows *= 2)
+        for (int bn = 64; bn <= 128; bn *= 2)
+            if (row_faster_than_lone_line(mode, m, (pixels + rows - 1) / rows * ((C_in + bn - 1) / bn), rows, bn, line_blocks)) return true;
+    return false;
+}
+
 }  // namespace sdgp

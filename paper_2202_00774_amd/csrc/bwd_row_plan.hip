@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <climits>
 
+#include "bwd_line_choice.h"
 #include "bwd_row.h"
 
 namespace sdgp {
@@ -79,9 +80,11 @@ int bwd_row_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H
         return 1;
 
     // As many tiles as this file asks for, whatever their shape: the line kernel, where it fits (0.70 of this one's time over 400 drawn
-    // layers), needs no search for one.
-    const bool many = (B * H * Wd + 255) / 256 * ((C_in + 63) / 64) >= 128;
-    if (many) {
+    // layers), needs no search for one.  Not so on images of few lines where it would be alone on its CUs and this one may be faster.
+    const int64_t line_blocks = (B * H * Wd + 255) / 256 * ((C_in + 63) / 64);
+    const bool many = line_blocks >= 128;
+    const bool compare = many && R == 3 && pad == 1 && row_worth_planning(mode, m, B * H * Wd, H, Wd, C_in, line_blocks);
+    if (many && !compare) {
         const int rc = bwd_line_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, stream);
         if (rc <= 0) return rc;
     }
@@ -119,12 +122,14 @@ int bwd_row_launch(const void* dO, const void* W, void* dD, int64_t B, int64_t H
     }
     p = chosen;
     if (blocks == 0 && (B == 0 || H == 0 || Wd == 0)) return SDGP_OK;
-    if (blocks < 128 || blocks >= INT_MAX) return 1;  // too few tiles to keep half the chip busy: another kernel takes it
-    p.nblocks = (int)blocks;
-    if (!many) {
+    const bool enough = blocks >= 128 && blocks < INT_MAX;
+    if (!enough && !compare) return 1;  // too few tiles to keep half the chip busy: another kernel takes it
+    if (compare ? !enough || !row_faster_than_lone_line(mode, m, blocks, rows, bn, line_blocks) : !many) {
         const int rc = bwd_line_launch(dO, W, dD, B, H, Wd, C_in, C_out, R, S, stride, pad, n, m, rk, seed, stream);
         if (rc <= 0) return rc;
     }
+    if (!enough) return 1;
+    p.nblocks = (int)blocks;
 
     if (mode == 0) return launch_row_dense(p, bn, rows, stream);
     if (mode == 1) {

@@ -85,3 +85,11 @@ def test_infinite_gradient_stays_with_its_pixels():
     for b, y, x in ((0, 5, 16), (7, 15, 16), (8, 0, 0), (149, 15, 16), (20, 8, 0)):
         hit[b, max(0, y - 1):y + 2, max(0, x - 1):x + 2] = True
     assert np.array_equal(~np.isfinite(wl.to_f64(to_host(out))).all(axis=3), hit)
+
+
+@pytest.mark.parametrize("n,m,ranker", [(4, 4, oracle.GREEDY), (4, 8, oracle.RANDOM), (5, 16, oracle.GREEDY), (16, 32, oracle.GREEDY_ADJUSTED)])
+@pytest.mark.parametrize("B,H,Wd,C_in,C_out", [(95000, 1, 1, 136, 32), (40000, 2, 2, 72, 64), (30000, 1, 3, 136, 32), (13000, 3, 3, 72, 32),
+                                               (13000, 1, 56, 40, 32), (600, 300, 1, 72, 64)])
+def test_whole_gradient_of_images_of_few_lines(B, H, Wd, C_in, C_out, n, m, ranker):
+    """One workgroup of the line kernel on a CU, or the row kernel where its rounds are the shorter ones."""
+    check(B, H, Wd, C_in, C_out, n, m, ranker)

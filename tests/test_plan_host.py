@@ -63,3 +63,27 @@ RANDOM, GREEDY, RESCALED = 0, 1, 2
     (60, 27, 27, 448, 128, 1, 4, GREEDY, 64)])
 def test_line_columns(ask, B, H, Wd, C_in, C_out, n, m, ranker, columns):
     assert ask("columns", B, H, Wd, C_in, C_out, n, m, ranker) == [str(columns)]
+
+
+def test_line_alone_on_a_cu(ask):
+    alone = {(H, Wd) for H in (1, 2, 3, 4, 7, 56, 300) for Wd in (1, 2, 3, 4, 7, 56, 57, 58, 63) if ask("alone", H, Wd) == ["1"]}
+    assert {(1, 1), (2, 2), (3, 3), (1, 56), (300, 1), (300, 58), (300, 63)} <= alone
+    assert not alone & {(4, 4), (7, 7), (56, 56), (300, 2), (300, 56)}
+
+
+@pytest.mark.parametrize("mode,m,blocks,rows,bn,line,taker", [
+    (0, 4, 746, 512, 128, 2984, "row"),      # 512 <- 64 at 1x1, batch 95360: 57 us against 85
+    (0, 4, 202, 256, 64, 202, "line"),       # a round of either
+    (1, 8, 494, 512, 128, 988, "line"), (1, 32, 1897, 512, 64, 4332, "row")])
+def test_row_kernel_beside_a_lone_line_kernel(ask, mode, m, blocks, rows, bn, line, taker):
+    assert ask("row", mode, m, blocks, rows, bn, line) == [taker]
+
+
+@pytest.mark.parametrize("mode,m,B,H,Wd,C_in,way", [
+    (0, 4, 95360, 1, 1, 512, "search"), (1, 8, 63185, 2, 2, 56, "search"),
+    (2, 4, 95360, 1, 1, 512, "line"),          # n <= 2: faster there in every layer seen
+    (0, 4, 87, 178, 1, 192, "line"),           # one round: a search of 8 us for a call of 7
+    (0, 4, 3000, 1, 56, 64, "line"), (0, 4, 13000, 1, 56, 64, "search"),
+    (0, 4, 64, 60, 60, 512, "line"), (0, 4, 95360, 4, 4, 512, "line")])     # wide; two workgroups on a CU
+def test_what_is_planned_for_the_row_kernel(ask, mode, m, B, H, Wd, C_in, way):
+    assert ask("plan", mode, m, B, H, Wd, C_in) == [way]
