@@ -58,6 +58,12 @@ constexpr int kLineMaxWidth = (kLineMaxWindow - kLineRows) / 2 - 1;
 
 __host__ __device__ inline int line_window(int Wd) { return kLineRows + 2 * (Wd + 1); }
 
+// Whether bwd_line is built with 128 columns for n <= 2 (one: one of m; cut: the last chunk is short; one of m is built for all channel
+// counts).  The magnitude rankers that sort keys leave no registers for them where the last chunk is cut.
+constexpr bool line_has_128(int m, int rk, bool one, bool cut) {
+    return !((one || cut) && rk != kRandom && (m > 4 || (one && rk == kGreedy)));
+}
+
 // The longest run of the padded line, from the first to the last position that some tile's taps read.
 inline int line_positions(int H, int Wd) {
     const int between = kLineRows - 1;

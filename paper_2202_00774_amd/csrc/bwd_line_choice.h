@@ -21,13 +21,12 @@ inline int line_lds(int mode, int bn, int H, int Wd) {
 //   * 1.9 times where the LDS leaves one workgroup of 128 columns on a CU but two of 64 -- images 61 to 63 pixels wide, and of few lines:
 //     1124 layers 0.3 percent above the better of the two, at most 15 (by 1.7 times 1.1 and 29: 432 <- 240 at 62x62, batch 15, 2:8 Random
 //     145 us on 128 columns, 118 on 64; 2.0 times 1.9 and 25).
-//   * The magnitude rankers that sort keys have no registers left for 128 columns where the instantiation also cuts the last chunk
+//   * Always 64 where the magnitude rankers that sort keys would have no registers left: line_has_128
 //     (448 <- 128 at 27x27, batch 60, 1:4 Magnitude 56 us, 41 on 64 columns; 368 <- 272 at 22x22, batch 62, 2:16 79 and 54).
 //   * The random ranker spills there too (5 to 16 registers), but where this rule picks 128 columns they are still the faster ones: 0.91
 //     of the time of 64 over 78 layers, 0.95 over 33 whose last chunk is cut.
 inline int tile_columns(int64_t row_tiles, int H, int Wd, int64_t C_in, int64_t C_out, int n, int m, int rk) {
-    const bool cuts = n == 1 || C_out % kLineKC != 0, keys = rk != kRandom && (m > 4 || (n == 1 && rk == kGreedy));
-    if (C_in <= 64 || (cuts && keys)) return 64;
+    if (C_in <= 64 || !line_has_128(m, rk, n == 1, C_out % kLineKC != 0)) return 64;
     const bool alone = line_lds(2, 128, H, Wd) > kLineLdsPair && line_lds(2, 64, H, Wd) <= kLineLdsPair;
     const int64_t per_cu_64 = (row_tiles * ((C_in + 63) / 64) + 255) / 256, per_cu_128 = (row_tiles * ((C_in + 127) / 128) + 255) / 256;
     return per_cu_128 * (alone ? 19 : 17) < per_cu_64 * 10 ? 128 : 64;

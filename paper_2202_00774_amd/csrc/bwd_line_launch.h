@@ -7,12 +7,16 @@ namespace sdgp {
 
 template <int BN, int MODE, int M, int RK, bool TAIL, bool TWO>
 int launch_line_as(const LineParams& p, hipStream_t stream) {
-    auto kern = bwd_line<BN, MODE, M, RK, TAIL, TWO>;
-    static const hipError_t attr =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (attr != hipSuccess) return SDGP_ERR_HIP;
-    hipLaunchKernelGGL(kern, dim3(p.nblocks), dim3(kLineThreads), (LineLayout<BN, MODE>::total(p.npos)), stream, p);
-    return launch_status();
+    if constexpr (MODE == 2 && BN == 128 && !line_has_128(M, RK, !TWO, TAIL)) {
+        return 1;   // not built, and not asked for
+    } else {
+        auto kern = bwd_line<BN, MODE, M, RK, TAIL, TWO>;
+        static const hipError_t attr =
+            hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (attr != hipSuccess) return SDGP_ERR_HIP;
+        hipLaunchKernelGGL(kern, dim3(p.nblocks), dim3(kLineThreads), (LineLayout<BN, MODE>::total(p.npos)), stream, p);
+        return launch_status();
+    }
 }
 
 // (one of m is rarer than two: one instantiation for all channel counts)

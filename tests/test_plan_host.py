@@ -1,5 +1,6 @@
 """The rules by which 3x3 layers find their kernel, compiled for the host without optimisation (tests/native/plan_host_check.hip)."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -87,3 +88,18 @@ def test_row_kernel_beside_a_lone_line_kernel(ask, mode, m, blocks, rows, bn, li
     (0, 4, 64, 60, 60, 512, "line"), (0, 4, 95360, 4, 4, 512, "line")])     # wide; two workgroups on a CU
 def test_what_is_planned_for_the_row_kernel(ask, mode, m, B, H, Wd, C_in, way):
     assert ask("plan", mode, m, B, H, Wd, C_in) == [way]
+
+
+def test_no_line_kernel_is_built_that_no_layer_gets(ask):
+    """The kernels of 128 columns in the library are those that the rule of the columns picks for some layer."""
+    lib = os.path.join(ROOT, "paper_2202_00774_amd", "libsdgp.so")
+    names = subprocess.run(["nm", "-C", lib], capture_output=True, text=True, check=True).stdout
+    built = set(re.findall(r"bwd_line<128, 2, (\d+), (\d+), (true|false), (true|false)>", names))
+    picked = set()
+    for m in (4, 8, 16):
+        for ranker in (RANDOM, GREEDY, RESCALED):
+            for n in (1, 2):
+                for C_out in (96, 80):
+                    if ask("columns", 256, 16, 16, 128, C_out, n, m, ranker) == ["128"]:
+                        picked.add((str(m), str(ranker), "true" if n == 1 or C_out % 32 else "false", "true" if n == 2 else "false"))
+    assert len(picked) == 18 and built == picked
