@@ -122,6 +122,13 @@ CASES = [
     (wl.ConvLayer("tiled_n48", 66, 16, 16, 48, 48, 3, 3, 1, 1), False),
     (wl.ConvLayer("tiled_n48_spread", 66, 16, 16, 48, 48, 3, 3, 1, 1), True),
     (wl.ConvLayer("tiled_s2", 90, 14, 14, 32, 32, 3, 3, 2, 1), True),
+    # images wider than the line kernel takes, fewer than 128 tiles of 256: the producer/consumer kernel, and the tiled one where C_out is
+    # no multiple of 64; a strided filter wider than twice its stride: the tiled one too
+    (wl.ConvLayer("conv3_n64_wide", 12, 20, 70, 64, 64, 3, 3, 1, 1), False),
+    (wl.ConvLayer("conv3_n64_wide_spread", 12, 20, 70, 64, 64, 3, 3, 1, 1), True),
+    (wl.ConvLayer("tiled_n48_wide", 12, 20, 70, 48, 48, 3, 3, 1, 1), False),
+    (wl.ConvLayer("tiled_n48_wide_spread", 12, 20, 70, 48, 48, 3, 3, 1, 1), True),
+    (wl.ConvLayer("tiled_5x5s2", 140, 17, 19, 64, 64, 5, 5, 2, 2), True),
     # the small-problem kernel: 3x3, 5x5, stride 2, a channel count that ends inside a reduction step, and 1x1
     (wl.ConvLayer("small_n64", 4, 16, 16, 64, 64, 3, 3, 1, 1), False),
     (wl.ConvLayer("small_n64_spread", 4, 16, 16, 64, 64, 3, 3, 1, 1), True),
@@ -141,7 +148,9 @@ DENSE_ROWS = [
     (wl.ConvLayer("line_n128", 200, 16, 16, 128, 128, 3, 3, 1, 1), False),
     (wl.ConvLayer("line_n96_spread", 200, 16, 16, 96, 96, 3, 3, 1, 1), True),
     (wl.ConvLayer("row_n96_wide", 30, 20, 70, 96, 96, 3, 3, 1, 1), False),
-    (wl.ConvLayer("tiled_n64", 70, 16, 16, 64, 64, 3, 3, 1, 1), False),        # between 512 tiles of 32 rows and 128 of 256
+    (wl.ConvLayer("tiled_n64", 70, 16, 16, 64, 64, 3, 3, 1, 1), False),        # between 512 tiles of 32 rows and 128 of 256: the line kernel
+    (wl.ConvLayer("tiled_n64_wide", 12, 20, 70, 64, 64, 3, 3, 1, 1), False),   # the same, wider than the line kernel takes
+    (wl.ConvLayer("tiled_n64_wide_spread", 12, 20, 70, 64, 64, 3, 3, 1, 1), True),
     (wl.ConvLayer("tiled_s2_n96", 400, 9, 9, 96, 96, 3, 3, 2, 1), False),      # classes of 25 to 16 pixels: the last has 50 tiles of 128 rows
     (wl.ConvLayer("small_n96", 4, 16, 16, 96, 96, 3, 3, 1, 1), False),
     (wl.ConvLayer("small_s2_n96", 3, 14, 14, 96, 96, 3, 3, 2, 1), False),

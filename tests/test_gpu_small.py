@@ -56,8 +56,8 @@ def test_filters(H, Wd, R, S, stride, pad):
 @pytest.mark.parametrize("shape", [
     (2100, 4, 4, 264, 40, 1, 1, 1, 0),      # 1x1, ragged C_out: the pointwise kernel's short last chunk
     (270, 8, 8, 16, 40, 3, 3, 1, 1),        # ragged C_out, more than 512 tiles: the line kernel
-    (300, 9, 11, 24, 40, 3, 3, 2, 1),       # the same, strided
-    (70, 16, 16, 72, 64, 5, 5, 1, 2),       # a filter neither three wide nor 1x1, more than 512 tiles: bwd_conv3
+    (300, 9, 11, 24, 40, 3, 3, 2, 1),       # the same, strided: bwd_tiled, at 2:4 the stride-2 kernel
+    (70, 16, 16, 72, 64, 5, 5, 1, 2),       # a filter neither three wide nor 1x1, more than 512 tiles: bwd_conv3, at 5:8 bwd_tiled
     (65, 16, 16, 72, 64, 2, 2, 1, 1),
     (130, 16, 16, 64, 64, 3, 3, 1, 1),      # the line kernel
     (350, 7, 7, 136, 64, 1, 1, 1, 0),       # the pointwise kernel
@@ -71,8 +71,17 @@ def test_neighbours(shape, n, m):
 @pytest.mark.parametrize("n,m", [(1, 4), (2, 16), (7, 16), (4, 32), (16, 32)])
 @pytest.mark.parametrize("shape", [(70, 16, 16, 64, 96, 3, 3, 1, 1), (300, 9, 11, 24, 96, 3, 3, 2, 1)])
 def test_tiled_patterns(shape, n, m, ranker):
-    """bwd_tiled on every ranker: more than 512 tiles of 32 rows and fewer than 128 of 256; a strided layer of which a parity
-    class has fewer than 64 tiles of 128."""
+    """More than 512 tiles of 32 rows and fewer than 128 of 256: the line kernel.  A strided layer of which a parity class has fewer than
+    64 tiles of 128: the stride-2 kernel, for general n:m bwd_tiled."""
+    check(shape, n, m, ranker)
+
+
+@pytest.mark.parametrize("ranker", RANKERS)
+@pytest.mark.parametrize("n,m", [(2, 4), (1, 4), (2, 8), (2, 16), (7, 16), (4, 32), (16, 32), (4, 4)])
+@pytest.mark.parametrize("shape", [(12, 20, 70, 64, 96, 3, 3, 1, 1), (140, 17, 19, 64, 96, 5, 5, 2, 2)])
+def test_tiled_on_every_ranker(shape, n, m, ranker):
+    """bwd_tiled: an image wider than the line kernel takes, with fewer than 128 tiles of 256 and C_out no multiple of 64; a strided filter
+    that is wider than twice its stride."""
     check(shape, n, m, ranker)
 
 

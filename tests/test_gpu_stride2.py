@@ -32,7 +32,8 @@ def check(B, H, Wd, C_in, C_out, n, m, ranker, seed=5):
 
 @pytest.mark.parametrize("ranker", (oracle.RANDOM, oracle.GREEDY, oracle.GREEDY_ADJUSTED))
 @pytest.mark.parametrize("B,H,Wd", [(70000, 2, 2), (40000, 3, 2), (20000, 2, 5), (2100, 2, 31), (1100, 63, 2), (1500, 13, 11),
-                                    (300, 28, 28), (300, 27, 29), (30, 100, 112)])
+                                    (300, 28, 28), (300, 27, 29), (30, 100, 112), (70000, 1, 1), (30000, 1, 2), (9000, 1, 16), (2100, 1, 31),
+                                    (1100, 60, 1), (12000, 5, 1)])
 def test_image_sizes(B, H, Wd, ranker):
     check(B, H, Wd, 64, 64, 2, 4, ranker)
 
