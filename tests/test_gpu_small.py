@@ -87,7 +87,8 @@ def test_tiled_on_every_ranker(shape, n, m, ranker):
 
 @pytest.mark.parametrize("n,m,ranker", [(2, 4, oracle.RANDOM), (2, 16, oracle.GREEDY_ADJUSTED), (5, 8, oracle.GREEDY), (16, 32, oracle.RANDOM),
                                         (4, 4, oracle.GREEDY)])
-@pytest.mark.parametrize("shape", [(4500, 1, 1, 64, 448, 3, 3, 2, 1), (3000, 1, 4, 72, 416, 3, 3, 2, 1), (2000, 5, 1, 64, 448, 3, 3, 2, 1)])
+@pytest.mark.parametrize("shape", [(4500, 1, 1, 64, 448, 3, 3, 2, 1), (3000, 1, 4, 72, 416, 3, 3, 2, 1), (2000, 5, 1, 64, 448, 3, 3, 2, 1),
+                                   (1528, 26, 1, 40, 64, 7, 7, 2, 3)])
 def test_strided_images_one_pixel_wide_or_high(shape, n, m, ranker):
     """bwd_tiled where some parity classes have no pixel.  The halo such a class would have is larger than what the tile was chosen
     for, and once counted it sent these layers back as not supported."""
