@@ -164,7 +164,8 @@ int sdgp_conv_bwd_data(const void* dO, const void* W, void* dD, int64_t B, int64
  *     workspace every product is exact, with it within 2^-24 of itself, over the whole range
  *     of fp32; the sums are rounded less often then, and the error against 64 bits is smaller.
  * The sizes hold for every ranker and alignment, so a call may leave its workspace
- * unread: problems of few tiles run a kernel that needs none. */
+ * unread: problems of few tiles run a kernel that needs none, and so do most 3x3 layers of
+ * stride 2 and padding 1, which are refused without it all the same. */
 size_t sdgp_conv_bwd_data_workspace(int64_t B, int64_t H, int64_t Wd, int64_t C_in, int64_t C_out,
                                     int R, int S, int stride, int pad, int dt, int n, int m);
 

@@ -11,17 +11,19 @@
 //     v_smfmac_f32_32x32x32_bf16, two values + two 2-bit positions per quad.
 //   * The ranker runs between the stage's matrix instructions, five or six of its instructions after each (NoGap in ranker.h), and
 //     so do the requests for the next fragments and the copies of W's next slabs.
-//   * Four wavefronts of 128 x 64 (128 columns) or 64 x 64 results (64 columns); LDS and registers of two or three workgroups fit a
-//     CU, so that one's first loads, ranking and stores run beside the other's matrix instructions.  bwd_row has one workgroup of
-//     512 pixels there, whose prologue and epilogue (7 us a round) nothing hides.
+//   * Four wavefronts of 128 x 64 (128 columns) or 64 x 64 results (64 columns).  More than one workgroup on a CU lets one's first loads,
+//     ranking and stores run beside the other's matrix instructions; bwd_row has one workgroup of 512 pixels there, whose prologue and
+//     epilogue (7 us a round) nothing hides.  The LDS leaves two of 128 columns on images 4 to 60 pixels wide, three of 64 on 5 to 46 and two
+//     to 63, of the whole gradient two on 4 to 57; a single one beyond that and on images of few lines (bwd_line_choice.h).
 //   * W through a two-set ring of direct-to-LDS copies, fragments by transposing reads, as in bwd_row.h.
 //   * Patterns with more than two of a quad, groups of 32 and the unpruned gradient lie in LDS whole, eight channels a plane, and use
 //     the dense instruction; their rankers (none, or a sorting network) run in front of the stage's matrix instructions.
 // What bounds it: the matrix and vector instructions share a SIMD's issue (a structured-sparse instruction takes 13 cycles of it and
 // 32 of the matrix pipe) and the clock, which falls from 2.4 to 1.6 - 1.9 GHz under them.  Measured against bwd_row, whole calls: 128 <- 256
-// channels at 16x16, batch 512, 2:4 Magnitude 51.9 -> 47.1 us, 64 <- 128 at 32x32 80.8 -> 64.5, 128 <- 128 at 28x28, batch 128,
+// channels at 16x16, batch 512, 2:4 Magnitude 51.9 -> 46.5 to 48.3 us, 64 <- 128 at 32x32 80.8 -> 64.5, 128 <- 128 at 28x28, batch 128,
 // 31 -> 24.8; 400 drawn layers 0.70 of the time, a hundred of one of m 0.76;
-// of general n:m 0.76 (80 layers), unpruned 0.79 (70; 128 <- 320 at 28x28, batch 112, 88.7 -> 60.5 us).
+// of general n:m 0.76 (80 layers), unpruned 0.79 (70; 128 <- 320 at 28x28, batch 112, 88.7 -> 60.5 us; the slowest
+// of 700 more 1.04: 128 <- 384 at 14x14, batch 567, one round of bwd_row).
 #pragma once
 
 #include <type_traits>
