@@ -13,7 +13,7 @@
 //   * A class leaves as soon as its taps are done, straight from the registers (store_class), while the next class's slabs arrive.
 // The parity-class kernel (bwd_pw.h) needs a pass that ranks ahead, or ranks an element once per tap, and its workgroups are too short
 // to hide their first loads and their stores: four and a half steps each.  128 <- 128 channels at 56x56, batch 256, 2:4 random
-// 97.2 -> 76 to 78 us (94.8 -> 72.1 on another card; 16 of the old time the pass), Magnitude 101 -> 75; 192 <- 96 at 51x51, batch 60, 39 -> 21; 150 layers that kernel took
+// 97.2 -> 76 to 79 us (94.8 -> 72.1 on another card; 16 of the old time the pass), Magnitude 101 -> 75; 192 <- 96 at 51x51, batch 60, 39 -> 21; 150 layers that kernel took
 // before 0.78 of the time.  Per workgroup of 256 x 128, in cycles: 36 stages of 800 (256 of them matrix instructions, two wavefronts a
 // SIMD), ranking 10 000, four stores of a class; 128 KB a workgroup go to memory.  Tried: eight wavefronts of 32 x 64 results, half
 // the instructions each, and 64 channels a stage: 83 us, bound by the fragments' LDS reads.
